@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "common.h"
+#include "scan.h"
 
 // Workspace of mgrit_gru_forward_static: one array per GPU, held from the moment the library's
 // code object is loaded on that GPU until the process ends.  In host code this name is only a
@@ -268,6 +269,7 @@ struct FwdCtx {
   float* emit_kapl[MAX_LEVELS];  // [l]: coefficient array of level l >= 1 that the closing
                                  // relaxation of level l - 1 fills along with it (or null)
   float dt;         // step size of level 0 (1 for the GRU propagators, Sec. 3.3)
+  int* ctl;         // control words of the one-launch serial solves
   hipStream_t s;
 };
 
@@ -379,7 +381,30 @@ static int vcycle_fwd(const FwdCtx& x, int l, bool f_points_current = false, boo
   const long long cf = x.c->cf, S = x.lay->S[l], N = x.lay->N[l];
   const int L = x.lay->L;
   if (l == L - 1) {
-    // coarsest level: serial propagation (Appendix A.1)
+    // coarsest level: serial propagation (Appendix A.1), as one launch where that form covers it
+    const bool keep = l == 0 && x.emit_kap;
+    const int kind = x.c->propagator == PROP_ODE_DEMO ? SCAN_ODE
+                     : prop_is_lstm(x.c->propagator) ? SCAN_LSTM : SCAN_GRU;
+    const int hidden = kind == SCAN_LSTM ? x.c->H / 2 : x.c->H;
+    if (!keep && scan_covers(kind, N, x.c->B, hidden)) {
+      ScanArgs a;
+      std::memset(&a, 0, sizeof(a));
+      a.Wt = x.U;
+      a.b_h = x.b_h;
+      a.P = x.P;
+      a.u = x.ul[l];
+      a.g = x.gl[l];
+      a.ctl = x.ctl;
+      a.N = (int)N;
+      a.B = x.c->B;
+      a.H = hidden;
+      a.pstep = S;
+      a.gamma = (float)S * x.dt;
+      a.implicit_ = x.c->propagator == MGRIT_PROP_IMPLICIT || x.c->propagator == PROP_LSTM_IMPLICIT;
+      a.bf16 = kform(x.c->dtype);
+      CHECK_HIP(launch_scan(kind, a, x.s));
+      return MGRIT_OK;
+    }
     for (long long k = 1; k <= N; ++k) {
       PhiArgs a = phi_base(x, l);
       a.mode = STEP_RELAX;
@@ -531,6 +556,7 @@ static int forward_impl(const mgrit_gru_cfg* cin, bool serial, const void* W, co
   ctx.b_h = b_h;
   ctx.P = (const float*)(base + lay.P);
   ctx.dt = ode ? ode_dt : 1.f;
+  ctx.ctl = (int*)(base + lay.part);     // (the gradient partials, formed after every solve)
   ctx.s = s;
   ctx.tmp = (float*)(base + lay.tmp);
   ctx.ul[0] = h;
@@ -574,6 +600,7 @@ struct BwdCtx {
   float* gl[MAX_LEVELS];
   float* tmp;
   double* norm;
+  int* ctl;         // as in FwdCtx
   hipStream_t s;
 };
 
@@ -646,6 +673,22 @@ static int vcycle_bwd(const BwdCtx& x, int l, bool f_points_current = false,
   const long long cf = x.c->cf, N = x.lay->N[l];
   const int L = x.lay->L;
   if (l == L - 1) {
+    if (scan_covers(SCAN_ADJOINT, N, x.c->B, x.c->H)) {
+      ScanArgs a;
+      std::memset(&a, 0, sizeof(a));
+      a.Wt = x.UT;
+      a.kap = x.kap[l];
+      a.kw = (l == 0 ? 5 : 4) * x.c->H;
+      a.u = x.wl[l];
+      a.g = x.gl[l];
+      a.ctl = x.ctl;
+      a.N = (int)N;
+      a.B = x.c->B;
+      a.H = x.c->H;
+      a.bf16 = kform(x.c->dtype);
+      CHECK_HIP(launch_scan(SCAN_ADJOINT, a, x.s));
+      return MGRIT_OK;
+    }
     for (long long k = N; k >= 1; --k) {
       AdjArgs a = adj_base(x, l);
       a.mode = STEP_RELAX;
@@ -765,6 +808,7 @@ static int backward_impl(const mgrit_gru_cfg* cin, bool serial, const void* W, c
   ctx.lay = &lay;
   ctx.UT = base + lay.UT;
   ctx.UT3 = base + lay.UT3;
+  ctx.ctl = (int*)(base + lay.part);
   ctx.s = s;
   ctx.tmp = (float*)(base + lay.tmp);
   ctx.wl[0] = w;

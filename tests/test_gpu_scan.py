@@ -1,0 +1,132 @@
+"""Serial propagation as one launch (kernels_scan.hip) against the oracles, at the edges of its
+shapes: partly filled row quads, column groups and K chunks, several row groups per workgroup, one
+and two chunks per wave.  Bar: 1e-5 of the largest value (fp32 arithmetic throughout, also on bf16
+weights, which the oracle reads as they are)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2203_04738_amd as mg
+from oracle import demo_ode_oracle as oo
+from oracle import lstm_oracle as lo
+from oracle import mgrit_gru_oracle as orc
+from paper_2203_04738_amd.binding import MGRIT_BF16_STATE2, MGRIT_F32, MgritGruCfg
+from synthetic_inputs import random_lstm, random_ode, random_small, round_to_bf16
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+T = 9
+# B, H: quads 1..16, column groups 1..64; (33, 512) and (64, 500) two row groups per workgroup,
+# (64, 1024) four, (3, 1000) and (8, 516) two chunks per wave with a ragged tail
+SHAPES = [(1, 16), (3, 20), (4, 64), (5, 68), (33, 128), (32, 512), (33, 512), (64, 500), (3, 1000),
+          (8, 516), (9, 1024), (64, 1024)]
+
+
+def _rel(a, b):
+    a = a.cpu().numpy().astype(np.float64)
+    assert np.all(np.isfinite(a))
+    return float(np.max(np.abs(a - b)) / np.max(np.abs(b)))
+
+
+def _dev(d, half=False):
+    t = {k: torch.from_numpy(v).to(DEV) for k, v in d.items()}
+    if half:
+        for k in ("x", "W", "U"):
+            t[k] = t[k].to(torch.bfloat16)
+    return t
+
+
+def _gru(B, H, half=False, steps=T):
+    d = random_small(B * 1000 + H, steps, B, 8, H, scale=0.7 / np.sqrt(H))
+    if half:
+        for k in ("x", "W", "U"):
+            d[k] = round_to_bf16(d[k])
+    t = _dev(d, half)
+    cfg = MgritGruCfg(steps, B, 8, H, dtype=MGRIT_BF16_STATE2 if half else MGRIT_F32)
+    ws = torch.empty(mg.mgrit_gru_workspace_bytes(cfg), dtype=torch.uint8, device=DEV)
+    return d, t, cfg, ws, (t["W"], t["U"], t["b_i"], t["b_h"], t["x"])
+
+
+def _check_gru(B, H, half=False):
+    d, t, cfg, ws, p = _gru(B, H, half)
+    P = (d["W"], d["U"], d["b_i"], d["b_h"])
+    h = torch.full((T + 1, B, H), 7.0, device=DEV)
+    mg.gru_serial_scan(cfg, *p, t["h0"], h, ws)
+    want = orc.serial_scan(*P, d["x"], d["h0"])
+    assert _rel(h, want) <= 1e-5
+    w = torch.full((T + 1, B, H), 7.0, device=DEV)
+    g = [torch.empty(3 * H, 8, device=DEV), torch.empty(3 * H, H, device=DEV),
+         torch.empty(3 * H, device=DEV), torch.empty(3 * H, device=DEV)]
+    mg.gru_serial_scan_backward(cfg, *p, h, t["dL_dhT"], w, *g, ws)
+    out = orc.serial_bptt(*P, d["x"], want, d["dL_dhT"])
+    # bf16 weights: more than 64 rows of coefficient vectors come from the tile kernels, which
+    # carry the state as two bf16 terms there (2^-17 per product: the 1e-4 bar of that form)
+    assert _rel(w, out[0]) <= (1e-4 if half else 1e-5)
+
+
+@pytest.mark.parametrize("B,H", SHAPES)
+def test_gru_and_adjoint(B, H):
+    print("scan case", B, H, flush=True)
+    _check_gru(B, H)
+
+
+@pytest.mark.parametrize("B,H", [(5, 24), (8, 1024)])
+def test_gru_and_adjoint_bf16_weights(B, H):
+    print("scan case bf16", B, H, flush=True)
+    _check_gru(B, H, half=True)
+
+
+@pytest.mark.parametrize("B,H", [(3, 20), (32, 512), (64, 500), (5, 1000), (64, 1024)])
+def test_lstm_and_ode(B, H):
+    print("scan case lstm, ode", B, H, flush=True)
+    d = random_lstm(1, T, B, 8, H, scale=0.7 / np.sqrt(H))
+    t = _dev(d)
+    cfg = MgritGruCfg(T, B, 8, H)
+    ws = torch.empty(mg.mgrit_lstm_workspace_bytes(cfg), dtype=torch.uint8, device=DEV)
+    u = torch.full((T + 1, B, 2 * H), 7.0, device=DEV)
+    mg.lstm_serial_scan(cfg, t["W"], t["U"], t["b_i"], t["b_h"], t["x"], t["u0"], u, ws)
+    assert _rel(u, lo.lstm_serial_scan(d["W"], d["U"], d["b_i"], d["b_h"], d["x"], d["u0"])) <= 1e-5
+    d = random_ode(2, T, B, 8, H)
+    t = _dev(d)
+    h = torch.full((T + 1, B, H), 7.0, device=DEV)
+    mg.ode_serial_scan(cfg, 0.25, t["A"], t["Bw"], t["b"], t["d"], t["h0"], h, ws)
+    assert _rel(h, oo.ode_serial_scan(d["A"], d["Bw"], d["b"], d["d"], d["h0"], 0.25)) <= 1e-5
+
+
+@pytest.mark.parametrize("B,H", [(5, 68), (32, 512)])
+def test_a_solve_that_is_given_up_is_repaired(B, H, monkeypatch):
+    # a wait limit of zero: the workgroups leave before all have arrived, the second kernel solves
+    monkeypatch.setenv("MGRIT_SCAN_WAIT_TICKS", "0")
+    print("scan case without waiting", B, H, flush=True)
+    _check_gru(B, H)
+    test_lstm_and_ode(B, H)
+
+
+def test_a_nan_with_every_bit_set_passes_through():
+    d, t, cfg, ws, p = _gru(6, 72)
+    h = torch.empty(T + 1, 6, 72, device=DEV)
+    mg.gru_serial_scan(cfg, *p, t["h0"], h, ws)
+    clean = h.clone()
+    t["h0"].view(torch.int32)[2, :] = -1
+    t["x"].view(torch.int32)[4, 1, :] = -1
+    mg.gru_serial_scan(cfg, *p, t["h0"], h, ws)
+    keep = [0, 3, 4, 5]
+    assert torch.equal(h[:, keep], clean[:, keep])
+    assert torch.isnan(h[:, 2]).all() and torch.isnan(h[5:, 1]).all()
+    assert torch.equal(h[:5, 1], clean[:5, 1])
+
+
+def test_solves_on_several_streams_at_once():
+    runs = [_gru(32, 512, steps=64) for _ in range(3)]
+    outs = [torch.empty(65, 32, 512, device=DEV) for _ in runs]
+    streams = [torch.cuda.Stream() for _ in runs]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for (d, t, cfg, ws, p), h, s in zip(runs, outs, streams):
+            with torch.cuda.stream(s):
+                mg.gru_serial_scan(cfg, *p, t["h0"], h, ws)
+    torch.cuda.synchronize()
+    d = runs[0][0]
+    want = orc.serial_scan(d["W"], d["U"], d["b_i"], d["b_h"], d["x"], d["h0"])
+    for h in outs:
+        assert _rel(h, want) <= 1e-5
