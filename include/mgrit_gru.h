@@ -34,7 +34,12 @@
  *   exponent range of fp32) and keep six of the nine term products, accumulated
  *   in fp32 on the bf16 matrix pipe, which is faster than the fp32 one.  The
  *   weights' term arrays live in the workspace (it is larger for this dtype)
- *   and are rebuilt by every call; H and D must be multiples of 8.
+ *   and are rebuilt by every call; H and D must be multiples of 8.  A tile with
+ *   a sum that is not finite (an operand the terms cannot carry, like an
+ *   infinity) is contracted again on the fp32 matrix pipe.
+ *   MGRIT_F32 takes the same form by itself for GRU problems where it is faster
+ *   and no less accurate (widths that are multiples of 8, at least 128, and 1024
+ *   rows or more per level-0 launch), in a workspace that is no larger.
  * - Level l of the hierarchy has N_l = T / cf^l steps and step size cf^l
  *   (Sec. 3.3); `levels` counts the fine level (three levels over 128 steps
  *   with cf = 4 are grids of 128, 32 and 8 steps).  cf^(levels-1) must divide T.

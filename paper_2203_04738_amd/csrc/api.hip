@@ -95,6 +95,7 @@ struct Layout {
   size_t norm;
   size_t kap[MAX_LEVELS];
   size_t UT, WT, part;
+  size_t total_part;              // bytes of the partials
   size_t U3, UT3, W3;             // MGRIT_F32_BF16X3: three-term bf16 copies of U, U^T and
                                   // W (or W^T, once the projection is done)
   size_t total;
@@ -168,6 +169,7 @@ static int make_layout(const mgrit_gru_cfg* c, Layout* lay) {
   off = align_up(off + (size_t)3 * c->H * c->D * sizeof(float));
   lay->part = off;
   off = align_up(off + grad_partial_floats(c->T, c->B, c->D, c->H, kform(c->dtype)) * sizeof(float));
+  lay->total_part = off - lay->part;
   if (c->dtype == MGRIT_F32_BF16X3) {
     lay->U3 = off;
     off = align_up(off + (size_t)3 * 3 * c->H * c->H * 2);
@@ -191,6 +193,53 @@ static bool misaligned(const void* p) { return ((uintptr_t)p & 15) != 0; }
   do {                                           \
     if ((expr) != hipSuccess) return MGRIT_E_LAUNCH; \
   } while (0)
+
+// ---------------------------------------------------------------------------
+// operand form of a call
+// ---------------------------------------------------------------------------
+// MGRIT_F32 runs the tile kernels on the bf16 matrix pipe, each fp32 operand as three bf16 terms
+// (exact; see gemm_core_bf16.h), where that is faster and no less accurate than the fp32 MFMAs.
+// (MGRIT_F32_BF16X3 asks for the terms on every shape.)  The line:
+//  - widths are multiples of 8 (16-byte rows of terms), of at least 128 (64 for the projection).
+//    Error of a contraction against 64 bits: 1.35e-7 against 1.44e-7 of the fp32 MFMAs over 64
+//    columns, 2.5 : 2.9 over 256, 5.0 : 5.8 over 1024 (fewer additions into the sum), but 0.83 :
+//    0.73 over 16.  Below 128 columns nothing is gained in time;
+//  - the GRU (the LSTM and ODE kernels have no such form);
+//  - 1024 rows or more in a level-0 launch.  Training step of two levels, fp32 MFMAs : terms:
+//    256 rows x 1000 1.44 : 1.52 ms, 512 x 512 0.88 : 0.88, 1024 x 512 1.66 : 1.52, 4096 x 1000
+//    12.8 : 10.7;
+//  - the terms fit the space of the gradient partials, which nothing else uses until the last
+//    solve of a call is done: the workspace is no larger than without them.
+struct Forms {
+  int rec, proj;            // operand form of the recurrent contractions and gradients / of W x
+  char *U3, *UT3, *W3;      // three-term arrays (null: not needed)
+};
+constexpr long long TERMS_MIN_ROWS = 1024;
+constexpr int TERMS_MIN_H = 128, TERMS_MIN_D = 64;
+constexpr size_t CTL_BYTES = 256;         // head of the partials: control words of the serial solves
+
+static Forms make_forms(const mgrit_gru_cfg& c, const Layout& lay, char* base) {
+  Forms f{kform(c.dtype), kform(c.dtype), nullptr, nullptr, nullptr};
+  if (c.dtype == MGRIT_F32_BF16X3) {
+    f.U3 = base + lay.U3;
+    f.UT3 = base + lay.UT3;
+    f.W3 = base + lay.W3;
+    return f;
+  }
+  const bool gru = c.propagator == MGRIT_PROP_IMPLICIT || c.propagator == MGRIT_PROP_CLASSIC;
+  const long long rows = (long long)c.T * c.B / (c.levels > 1 ? c.cf : 1);
+  if (c.dtype != MGRIT_F32 || !gru || c.H % 8 != 0 || c.H < TERMS_MIN_H || rows < TERMS_MIN_ROWS) return f;
+  const size_t u3 = align_up((size_t)18 * c.H * c.H);
+  const size_t w3 = align_up((size_t)18 * c.H * c.D);
+  const size_t room = lay.total_part - CTL_BYTES;
+  if (u3 + (u3 > w3 ? u3 : w3) > room) return f;
+  f.rec = 2;
+  f.U3 = base + lay.part + CTL_BYTES;
+  f.UT3 = f.U3 + u3;                      // W3 and UT3 take turns: the projection comes first, the
+  f.W3 = f.UT3;                           // input gradients after the last adjoint step
+  if (c.D % 8 == 0 && c.D >= TERMS_MIN_D) f.proj = 2;
+  return f;
+}
 
 // ---------------------------------------------------------------------------
 // what a workspace holds (host-side record; no device read, no synchronisation)
@@ -259,6 +308,7 @@ static bool coeffs_match(const WsRecord& r, const mgrit_gru_cfg& c, bool serial,
 struct FwdCtx {
   const mgrit_gru_cfg* c;
   const Layout* lay;
+  int form;         // operand form of the step kernels
   const void *U, *U3;
   const float *b_h, *P;
   float* ul[MAX_LEVELS];
@@ -287,7 +337,7 @@ static PhiArgs phi_base(const FwdCtx& x, int l) {
   a.H = x.c->H;
   a.gamma = (float)x.lay->S[l] * x.dt;
   a.propagator = x.c->propagator;
-  a.bf16 = kform(x.c->dtype);
+  a.bf16 = x.form;
   a.one_term = one_term(x.c->dtype);
   return a;
 }
@@ -476,18 +526,15 @@ static int vcycle_fwd(const FwdCtx& x, int l, bool f_points_current = false, boo
   return relax_fwd(x, l, false, false, last);
 }
 
-static int run_projection(const mgrit_gru_cfg* c, const Layout& lay, char* base, const void* W,
-                          const float* b_i, const void* x, hipStream_t s) {
+static int run_projection(const mgrit_gru_cfg* c, const Layout& lay, const Forms& f, char* base,
+                          const void* W, const float* b_i, const void* x, hipStream_t s) {
   if (c->flags & MGRIT_REUSE_PROJECTION) return MGRIT_OK;
-  if (c->dtype == MGRIT_F32_BF16X3) {
-    CHECK_HIP(launch_split3((const float*)W, base + lay.W3, 3LL * c->H * c->D, s));
-    W = base + lay.W3;
-  }
+  if (f.proj == 2) CHECK_HIP(launch_split3((const float*)W, f.W3, 3LL * c->H * c->D, s));
   // GRU: three gates; demonstration ODE: one block; LSTM: four gates of the hidden width c->H / 2
   const int width = c->propagator == PROP_ODE_DEMO ? c->H
                     : prop_is_lstm(c->propagator) ? 2 * c->H : 3 * c->H;
-  CHECK_HIP(launch_projection(x, W, b_i, (float*)(base + lay.P), (long long)c->T * c->B, width,
-                              c->D, kform(c->dtype), s));
+  CHECK_HIP(launch_projection(x, W, f.W3, b_i, (float*)(base + lay.P), (long long)c->T * c->B,
+                              width, c->D, f.proj, s));
   return MGRIT_OK;
 }
 
@@ -547,12 +594,11 @@ static int forward_impl(const mgrit_gru_cfg* cin, bool serial, const void* W, co
   FwdCtx ctx;
   ctx.c = &c;
   ctx.lay = &lay;
+  const Forms forms = make_forms(c, lay, base);
+  ctx.form = forms.rec;
   ctx.U = U;
-  ctx.U3 = nullptr;
-  if (c.dtype == MGRIT_F32_BF16X3) {
-    ctx.U3 = base + lay.U3;
-    CHECK_HIP(launch_split3((const float*)U, base + lay.U3, 3LL * c.H * c.H, s));
-  }
+  ctx.U3 = forms.U3;
+  if (forms.rec == 2) CHECK_HIP(launch_split3((const float*)U, forms.U3, 3LL * c.H * c.H, s));
   ctx.b_h = b_h;
   ctx.P = (const float*)(base + lay.P);
   ctx.dt = ode ? ode_dt : 1.f;
@@ -574,7 +620,7 @@ static int forward_impl(const mgrit_gru_cfg* cin, bool serial, const void* W, co
     ctx.emit_kapl[l] = (ctx.emit_kap && forward_leaves_coeffs(l, lay.L))
                            ? (float*)(base + lay.kap[l]) : nullptr;
 
-  if ((rc = run_projection(&c, lay, base, W, b_i, x, s))) return rc;
+  if ((rc = run_projection(&c, lay, forms, base, W, b_i, x, s))) return rc;
   const long long BH = (long long)c.B * c.H;
   for (int l = 0; l < lay.L; ++l)   // point 0 of every level is the initial condition
     CHECK_HIP(launch_copy_points(ctx.ul[l], h0, Idx{0, 0}, Idx{0, 0}, 1, BH, s));
@@ -594,6 +640,7 @@ static int forward_impl(const mgrit_gru_cfg* cin, bool serial, const void* W, co
 struct BwdCtx {
   const mgrit_gru_cfg* c;
   const Layout* lay;
+  int form;         // operand form of the step kernels
   const void *UT, *UT3;
   const float* kap[MAX_LEVELS];
   float* wl[MAX_LEVELS];
@@ -616,7 +663,7 @@ static AdjArgs adj_base(const BwdCtx& x, int l) {
   a.g = x.gl[l];
   a.B = x.c->B;
   a.H = x.c->H;
-  a.bf16 = kform(x.c->dtype);
+  a.bf16 = x.form;
   a.one_term = one_term(x.c->dtype);
   return a;
 }
@@ -795,19 +842,21 @@ static int backward_impl(const mgrit_gru_cfg* cin, bool serial, const void* W, c
   ws_record_put(ws, rec);
   (void)hipGetLastError();   // an error left by earlier, unrelated work is not this call's
 
-  if ((rc = run_projection(&c, lay, base, W, b_i, x, s))) return rc;
+  const Forms forms = make_forms(c, lay, base);
+  if ((rc = run_projection(&c, lay, forms, base, W, b_i, x, s))) return rc;
   const int bf16 = kform(c.dtype) == 1;
   CHECK_HIP(launch_transpose(U, base + lay.UT, 3 * c.H, c.H, bf16, s));
-  if (c.dtype == MGRIT_F32_BF16X3) {
-    CHECK_HIP(launch_split3((const float*)U, base + lay.U3, 3LL * c.H * c.H, s));
-    CHECK_HIP(launch_split3((const float*)(base + lay.UT), base + lay.UT3, 3LL * c.H * c.H, s));
+  if (forms.rec == 2) {
+    CHECK_HIP(launch_split3((const float*)U, forms.U3, 3LL * c.H * c.H, s));
+    CHECK_HIP(launch_split3((const float*)(base + lay.UT), forms.UT3, 3LL * c.H * c.H, s));
   }
 
   BwdCtx ctx;
   ctx.c = &c;
   ctx.lay = &lay;
   ctx.UT = base + lay.UT;
-  ctx.UT3 = base + lay.UT3;
+  ctx.UT3 = forms.UT3;
+  ctx.form = forms.rec;
   ctx.ctl = (int*)(base + lay.part);
   ctx.s = s;
   ctx.tmp = (float*)(base + lay.tmp);
@@ -824,8 +873,8 @@ static int backward_impl(const mgrit_gru_cfg* cin, bool serial, const void* W, c
     PhiArgs a;
     std::memset(&a, 0, sizeof(a));
     a.U = U;
-    a.U3 = base + lay.U3;
-    a.bf16 = kform(c.dtype);
+    a.U3 = forms.U3;
+    a.bf16 = forms.rec;
     a.one_term = one_term(c.dtype);
     a.b_h = b_h;
     a.P = P;
@@ -877,16 +926,13 @@ static int backward_impl(const mgrit_gru_cfg* cin, bool serial, const void* W, c
   if (resnorm && !serial) CHECK_HIP(launch_sqrt_to_float(norm, resnorm, c.iters, s));
   if (ngrad == 4)
     CHECK_HIP(launch_param_grads(ctx.kap[0], w, h, x, dW, dU, db_i, db_h,
-                                 (float*)(base + lay.part), c.T, c.B, c.D, c.H, kform(c.dtype),
-                                 one_term(c.dtype), s));
+                                 (float*)(base + lay.part), lay.total_part / sizeof(float), c.T,
+                                 c.B, c.D, c.H, forms.rec, one_term(c.dtype), s));
   if (dx) {
     CHECK_HIP(launch_transpose(W, base + lay.WT, 3 * c.H, c.D, bf16, s));
     const void* WT = base + lay.WT;
-    if (c.dtype == MGRIT_F32_BF16X3) {
-      CHECK_HIP(launch_split3((const float*)WT, base + lay.W3, 3LL * c.H * c.D, s));
-      WT = base + lay.W3;
-    }
-    CHECK_HIP(launch_input_grads(ctx.kap[0], w, WT, dx, c.T, c.B, c.D, c.H, kform(c.dtype),
+    if (forms.rec == 2) CHECK_HIP(launch_split3((const float*)WT, forms.W3, 3LL * c.H * c.D, s));
+    CHECK_HIP(launch_input_grads(ctx.kap[0], w, WT, forms.W3, dx, c.T, c.B, c.D, c.H, forms.rec,
                                  one_term(c.dtype), s));
   }
   return MGRIT_OK;

@@ -125,28 +125,31 @@ hipError_t launch_lstm_step(const PhiArgs& a, hipStream_t s);
 hipError_t launch_adj_step(const AdjArgs& a, hipStream_t s);
 
 // P[M,N] = X[M,K] W[N,K]^T + bias[N]
-// X, W: float (bf16 = 0) or bf16 (bf16 = 1); bf16 = 2: X float, W the three bf16 terms
-// [3][N,K] of the float weights
-hipError_t launch_projection(const void* X, const void* W, const float* bias, float* P,
-                             long long M, int N, int K, int bf16, hipStream_t s);
+// X, W: float (bf16 = 0) or bf16 (bf16 = 1); bf16 = 2: X, W float, W3 the three bf16 terms
+// [3][N,K] of the weights (otherwise not read)
+hipError_t launch_projection(const void* X, const void* W, const void* W3, const float* bias,
+                             float* P, long long M, int N, int K, int bf16, hipStream_t s);
 // UT[H,3H] = U[3H,H]^T; elements are 4 bytes (bf16 = 0) or 2 bytes
 hipError_t launch_transpose(const void* U, void* UT, int rows, int cols, int bf16, hipStream_t s);
 
 // Weight gradients (Alg. 3 gradient line) from the level-0 coefficients kap0[(T+1),B,5H]
 // (row t = step t), the adjoint w[(T+1),B,H], the states h[(T+1),B,H] and x[T,B,D].
-// part: scratch of grad_partial_floats(...) floats.
+// part: scratch of part_floats >= grad_partial_floats(...) floats, the operand form of the caller's
+// dtype (the kernels may run another form than that: fewer row splits then, if need be).
 size_t grad_partial_floats(int T, int B, int D, int H, int bf16);
 // x: float (bf16 = 0) or bf16 (bf16 = 1); one_term: as in PhiArgs (the wide bf16 kernel only;
 // the narrow one keeps two terms)
 hipError_t launch_param_grads(const float* kap0, const float* w, const float* h, const void* x,
                               float* dW, float* dU, float* db_i, float* db_h, float* part,
-                              int T, int B, int D, int H, int bf16, int one_term, hipStream_t s);
+                              size_t part_floats, int T, int B, int D, int H, int bf16,
+                              int one_term, hipStream_t s);
 
 // Input gradients dx[T,B,D] from the level-0 coefficients, the adjoint w and the
-// transposed input weights WT[D,3H] (float, or bf16 with bf16 = 1, or its three bf16 terms
-// [3][D,3H] with bf16 = 2).
-hipError_t launch_input_grads(const float* kap0, const float* w, const void* WT, float* dx, int T,
-                              int B, int D, int H, int bf16, int one_term, hipStream_t s);
+// transposed input weights WT[D,3H] (float, or bf16 with bf16 = 1; with bf16 = 2 WT3 holds its three
+// bf16 terms [3][D,3H]).
+hipError_t launch_input_grads(const float* kap0, const float* w, const void* WT, const void* WT3,
+                              float* dx, int T, int B, int D, int H, int bf16, int one_term,
+                              hipStream_t s);
 
 // dst[t][i] (t = 0..2, bf16) = t-th term of src[i]: src = dst[0] + dst[1] + dst[2] exactly
 // unless a term underflows; n a multiple of 4

@@ -76,16 +76,19 @@ __device__ inline void split_bf16(const F32x8& v, bf16x8& hi, bf16x8& lo) {
 // is planned for.
 // NP: 1 = operands as stored (A optionally in two terms), 3 = three terms per operand.
 // TKB: elements per K-slice and K-split group.
+// LOSUM (NP = 3): the five products of lower-order terms are summed apart from a0 * b0 and added once
+// at the end, which leaves a sixth of the additions into the large sum (twice the accumulators).
 // A2: an fp32 operand A goes to the MFMAs as two bf16 terms (hi + lo); false: as one, rounded
 // to nearest (what mixed-precision training feeds its matrix pipe).
 template <int WM_, int WN_, int BM_, int BN_, int NG_, bool SPLIT_A_, int KS_ = 1, int DEPTH_ = 1,
-          int MINWG_ = 2, int NP_ = 1, int TKB_ = 64, bool A2_ = true>
+          int MINWG_ = 2, int NP_ = 1, int TKB_ = 64, bool A2_ = true, bool LOSUM_ = false>
 struct TileCfgB {
   static constexpr int WM = WM_, WN = WN_, BM = BM_, BN = BN_, NG = NG_;
   static constexpr bool SPLIT_A = SPLIT_A_;
   static constexpr int DEPTH = DEPTH_, MINWG = MINWG_;
   static constexpr int KS = KS_;                // K-split groups of waves (see TileCfg)
   static constexpr int NP = NP_;
+  static constexpr bool LOSUM = LOSUM_;
   static constexpr int TK = TKB_ * KS;          // bf16 elements per K-slice
   static constexpr int NA = NP == 3 ? 3 : (SPLIT_A && A2_) ? 2 : 1;   // A tiles in LDS
   static constexpr int NBP = NP == 3 ? 3 : 1;                // B tiles in LDS
@@ -171,7 +174,15 @@ __device__ inline void gemm_nt_tile_bf16(Acc<C>& acc, int K, LoadA loadA, LoadB 
       const bool dead = KTAIL && k0 + (q % C::CPR) * 8 >= K;
       if constexpr (C::NA == 3) {
         bf16x8 t0, t1, t2;
-        split_bf16_3(finA(ra[d][s]), t0, t1, t2);
+        // odd tile rows enter with the opposite sign (see the end)
+        F32x8 v = finA(ra[d][s]);
+        const unsigned sgn = (unsigned)((q / C::CPR) & 1) << 31;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          v.lo4[i] = __uint_as_float(__float_as_uint(v.lo4[i]) ^ sgn);
+          v.hi4[i] = __uint_as_float(__float_as_uint(v.hi4[i]) ^ sgn);
+        }
+        split_bf16_3(v, t0, t1, t2);
         *reinterpret_cast<bf16x8*>(&As[off]) = dead ? z : t0;
         *reinterpret_cast<bf16x8*>(&As[C::TM * C::LD + off]) = dead ? z : t1;
         *reinterpret_cast<bf16x8*>(&As[2 * C::TM * C::LD + off]) = dead ? z : t2;
@@ -231,6 +242,8 @@ __device__ inline void gemm_nt_tile_bf16(Acc<C>& acc, int K, LoadA loadA, LoadB 
       }
   };
 
+  Acc<C> lo;                                      // LOSUM: products of lower-order terms
+  if constexpr (C::LOSUM) lo.zero();
   const int nkt = (K + C::TK - 1) / C::TK;
 #pragma unroll
   for (int d = 0; d < DP; ++d)
@@ -274,15 +287,21 @@ __device__ inline void gemm_nt_tile_bf16(Acc<C>& acc, int K, LoadA loadA, LoadB 
                 f[g * C::BN + b] = *reinterpret_cast<const bf16x8*>(
                     &Bs[u * C::BROWS * C::LD + b_row + (g * C::TN + b * 32) * C::LD + kpos(c)]);
           };
-          auto mm = [&](const bf16x8 (&f)[C::BM], const bf16x8 (&h)[NB]) {
+          auto mm_into = [&](Acc<C>& sum, const bf16x8 (&f)[C::BM], const bf16x8 (&h)[NB]) {
 #pragma unroll
             for (int g = 0; g < C::NG; ++g)
 #pragma unroll
               for (int b = 0; b < C::BN; ++b)
 #pragma unroll
                 for (int a = 0; a < C::BM; ++a)
-                  acc.v[g][a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                      f[a], h[g * C::BN + b], acc.v[g][a][b], 0, 0, 0);
+                  sum.v[g][a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                      f[a], h[g * C::BN + b], sum.v[g][a][b], 0, 0, 0);
+          };
+          auto mm = [&](const bf16x8 (&f)[C::BM], const bf16x8 (&h)[NB]) {
+            if constexpr (C::LOSUM)
+              mm_into(lo, f, h);
+            else
+              mm_into(acc, f, h);
           };
           constexpr int UM = C::BM * NB;            // MFMAs of one (A term, B term) pair
           rdA(0, 0, a0[0]);
@@ -294,7 +313,7 @@ __device__ inline void gemm_nt_tile_bf16(Acc<C>& acc, int K, LoadA loadA, LoadB 
             const int s0 = (3 * c) & 1;            // register set of B term 0 of this group
             // unit 0
             rdB(c, 1, bt[s0 ^ 1]);
-            mm(a0[c & 1], bt[s0]);
+            mm_into(acc, a0[c & 1], bt[s0]);
             mm(a2, bt[s0]);
             mm(a1, bt[s0]);
 #pragma unroll
@@ -375,6 +394,78 @@ __device__ inline void gemm_nt_tile_bf16(Acc<C>& acc, int K, LoadA loadA, LoadB 
         }
       }
     }
+  }
+  if constexpr (C::LOSUM) {
+#pragma unroll
+    for (int g = 0; g < C::NG; ++g)
+#pragma unroll
+      for (int a = 0; a < C::BM; ++a)
+#pragma unroll
+        for (int b = 0; b < C::BN; ++b) acc.v[g][a][b] += lo.v[g][a][b];
+  }
+  if constexpr (C::NP == 3) {
+    // The bf16 MFMA rounds its sum down (towards minus infinity) below the last bit: 4e-8 of the sum
+    // per 1024 columns, the same way in every row.  Sums over rows (bias gradients, residual norms)
+    // would collect it; with the sign of the odd rows turned it alternates instead (bias gradients
+    // at 12800 rows x 1000: 4.3e-7 off with the signs as they are, 2.9e-7 with fp32 MFMAs).
+#pragma unroll
+    for (int g = 0; g < C::NG; ++g)
+#pragma unroll
+      for (int a = 0; a < C::BM; ++a)
+#pragma unroll
+        for (int b = 0; b < C::BN; ++b)
+#pragma unroll
+          for (int e = 1; e < 16; e += 2) acc.v[g][a][b][e] = -acc.v[g][a][b][e];
+  }
+}
+
+// Whether any sum of the workgroup's tile is not finite (the same answer in every thread).  The
+// terms of an infinity, and of the values bf16 rounds to one, are NaNs, so a three-term sum shows
+// any operand it cannot carry; such a tile is contracted again by contract_f32, which gives what
+// the fp32 MFMAs of gemm_core.h give.
+template <class C>
+__device__ inline bool tile_not_finite(const Acc<C>& acc) {
+  float t = 0.f;
+#pragma unroll
+  for (int g = 0; g < C::NG; ++g)
+#pragma unroll
+    for (int a = 0; a < C::BM; ++a)
+#pragma unroll
+      for (int b = 0; b < C::BN; ++b)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) t = fmaf(acc.v[g][a][b][e], 0.f, t);
+  return __syncthreads_or(t != t) != 0;
+}
+// acc = A * B^T in fp32, operands straight from memory (small rather than fast: only tiles with
+// sums that are not finite come here).  load_a(r, k): columns k..k+3 of tile row r of A; b_row(r):
+// tile row r of B.  K a multiple of 4.
+template <class C, class LoadA4, class BRow>
+__device__ inline void contract_f32(Acc<C>& acc, int K, LoadA4 load_a, BRow b_row) {
+  const int lane = threadIdx.x & 63;
+  const int wave = (threadIdx.x >> 6) % (C::WM * C::WN);
+  const int ks = (threadIdx.x >> 6) / (C::WM * C::WN);
+  const int ra = (wave / C::WN) * C::BM * 32 + (lane & 31);
+  const int rb = (wave % C::WN) * C::BN * 32 + (lane & 31);
+  const int lh = lane >> 5;
+  acc.zero();
+#pragma unroll 1
+  for (int k0 = 8 * ks; k0 < K; k0 += 8 * C::KS) {
+    const int k = k0 + 4 * lh, kc = k < K ? k : K - 4;
+    floatx4 fa[C::BM];
+#pragma unroll
+    for (int a = 0; a < C::BM; ++a) fa[a] = k < K ? load_a(ra + a * 32, kc) : zero4();
+#pragma unroll
+    for (int g = 0; g < C::NG; ++g)
+#pragma unroll
+      for (int b = 0; b < C::BN; ++b) {
+        const floatx4 fb = k < K ? ldg4(b_row(g * C::TN + rb + b * 32) + kc) : zero4();
+#pragma unroll
+        for (int a = 0; a < C::BM; ++a)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            acc.v[g][a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[a][e], fb[e],
+                                                                  acc.v[g][a][b], 0, 0, 0);
+      }
   }
 }
 

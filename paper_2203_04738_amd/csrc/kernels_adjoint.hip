@@ -275,6 +275,16 @@ __global__ __launch_bounds__(C::NT, C::MINWG) void adj_step_kernel_bf16(AdjArgs 
       gemm_nt_tile_bf16<C, false>(acc, K, la, lb, fa, lds);
     else
       gemm_nt_tile_bf16<C, true>(acc, K, la, lb, fa, lds);
+    if (tile_not_finite<C>(acc))
+      contract_f32<C>(
+          acc, K,
+          [&](int tr, int k) {
+            const int kk = k >= 2 * H ? k - 2 * H : (k >= H ? k - H : k);
+            return ldg4(a.kap + rowtab[tr].k + k) * ldg4(a.w_in + rowtab[tr].in + kk);
+          },
+          [&](int tr) {
+            return (const float*)a.UT + (long long)(n0 + tr < H ? n0 + tr : H - 1) * K;
+          });
   } else {
     auto lb = [&](int s, int k) { return ldg8h(brow[s] + k); };
     if (K % C::TK == 0)
@@ -370,7 +380,7 @@ __global__ __launch_bounds__(DxCfg::NT) void input_grad_kernel(
 template <class C>
 __global__ __launch_bounds__(C::NT, C::NT > 256 ? 2 : 1) void input_grad_kernel_bf16(
     const float* __restrict__ kap0, const float* __restrict__ w, const bf16_t* __restrict__ WT,
-    float* __restrict__ dx, long long R, int B, int H, int D) {
+    const float* __restrict__ WTf, float* __restrict__ dx, long long R, int B, int H, int D) {
   __shared__ __attribute__((aligned(16))) bf16_t lds[C::LDS_ELEMS];
   const int K = 3 * H;
   long long rt;
@@ -413,6 +423,16 @@ __global__ __launch_bounds__(C::NT, C::NT > 256 ? 2 : 1) void input_grad_kernel_
       gemm_nt_tile_bf16<C, false>(acc, K, la, lb, fa, lds);
     else
       gemm_nt_tile_bf16<C, true>(acc, K, la, lb, fa, lds);
+    if (tile_not_finite<C>(acc))
+      contract_f32<C>(
+          acc, K,
+          [&](int tr, int k) {
+            const long long r = m0 + tr < R ? m0 + tr : R - 1;
+            const int kk = k >= 2 * H ? k - 2 * H : (k >= H ? k - H : k);
+            const int ks = k >= 2 * H ? k + 2 * H : k;
+            return ldg4(kap0 + (r + B) * (5LL * H) + ks) * ldg4(w + (r + B) * H + kk);
+          },
+          [&](int tr) { return WTf + (long long)(n0 + tr < D ? n0 + tr : D - 1) * K; });
   } else {
     auto lb = [&](int s, int k) { return ldg8h(brow[s] + k); };
     if (K % C::TK == 0)
@@ -423,25 +443,26 @@ __global__ __launch_bounds__(C::NT, C::NT > 256 ? 2 : 1) void input_grad_kernel_
   store_tile<C>(acc, dx, m0, n0, R, D);
 }
 
-hipError_t launch_input_grads(const float* kap0, const float* w, const void* WT, float* dx, int T,
-                              int B, int D, int H, int bf16, int one_term, hipStream_t s) {
+hipError_t launch_input_grads(const float* kap0, const float* w, const void* WT, const void* WT3,
+                              float* dx, int T, int B, int D, int H, int bf16, int one_term,
+                              hipStream_t s) {
   const long long R = (long long)T * B;
   prof_begin(6, s);
   if (bf16 == 2) {
     typedef DxCfgS C;
     dim3 grid((unsigned)xcd_grid((R + C::TM - 1) / C::TM, (D + C::TN - 1) / C::TN));
     hipLaunchKernelGGL(input_grad_kernel_bf16<C>, grid, dim3(C::NT), 0, s, kap0, w,
-                       (const bf16_t*)WT, dx, R, B, H, D);
+                       (const bf16_t*)WT3, (const float*)WT, dx, R, B, H, D);
   } else if (bf16 && one_term) {
     typedef DxCfgF C;
     dim3 grid((unsigned)xcd_grid((R + C::TM - 1) / C::TM, (D + C::TN - 1) / C::TN));
     hipLaunchKernelGGL(input_grad_kernel_bf16<C>, grid, dim3(C::NT), 0, s, kap0, w,
-                       (const bf16_t*)WT, dx, R, B, H, D);
+                       (const bf16_t*)WT, (const float*)nullptr, dx, R, B, H, D);
   } else if (bf16) {
     typedef DxCfgB C;
     dim3 grid((unsigned)xcd_grid((R + C::TM - 1) / C::TM, (D + C::TN - 1) / C::TN));
     hipLaunchKernelGGL(input_grad_kernel_bf16<C>, grid, dim3(C::NT), 0, s, kap0, w,
-                       (const bf16_t*)WT, dx, R, B, H, D);
+                       (const bf16_t*)WT, (const float*)nullptr, dx, R, B, H, D);
   } else {
     typedef DxCfg C;
     dim3 grid((unsigned)xcd_grid((R + C::TM - 1) / C::TM, (D + C::TN - 1) / C::TN));
@@ -694,43 +715,18 @@ struct GradArgs {
   int splits;          // row splits (a multiple of 8, or fewer than 8)
 };
 
-// C[m, n] = sum_k S[k, m] Bm[k, n] over this split's rows k.  Both operands are
-// read with the contracted index k slowest, so an LDS slice is stored [k][m] and
-// a lane reads its MFMA operand as one float per k-pair.
-// 1-D grid: workgroups go round-robin over the 8 XCDs, so split z is given to XCD
-// z % 8 and all output tiles of a split run on that XCD: its rows of S and Bm are
-// fetched into one L2 only.
+// acc += sum over the rows k in [kbeg, kend) of S[k, m] Bm[k, n], m = m0.., n = n0..; colsum: this
+// thread's share of the column sums of S.  Both operands are read with the contracted index k
+// slowest, so an LDS slice is stored [k][m] and a lane reads its MFMA operand as one float per
+// k-pair.  As, Bs: GTK * GLD floats each.
 template <class BT>
-__global__ __launch_bounds__(256, 3) void grad_gemm_kernel(GradArgs a) {
-  __shared__ __attribute__((aligned(16))) float As[1][GTK * GLD];
-  __shared__ __attribute__((aligned(16))) float Bs[1][GTK * GLD];
+__device__ inline void grad_contract_f32(const GradArgs& a, int m0, int n0, long long kbeg,
+                                         long long kend, float* As, float* Bs,
+                                         floatx16 (&acc)[2][2], floatx4& colsum) {
   const int H = a.H, N = a.N, M = 3 * a.H;
-  const int tiles = a.mtiles * a.ntiles;
-  int tile, z;
-  if (a.splits % NXCD == 0) {
-    const int j = blockIdx.x / NXCD;
-    tile = j % tiles;
-    z = (j / tiles) * NXCD + blockIdx.x % NXCD;
-  } else {
-    tile = blockIdx.x % tiles;
-    z = blockIdx.x / tiles;
-  }
-  const int m0 = (tile % a.mtiles) * GT, n0 = (tile / a.mtiles) * GT;
-  const long long kbeg = (long long)z * a.Kper;
-  long long kend = kbeg + a.Kper;
-  if (kend > a.Ktot) kend = a.Ktot;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1, li = lane & 31, lh = lane >> 5;
   const long long rowoff = a.B;   // kap0 / w rows are one time point ahead
-
-  floatx16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
   // each thread stages NCH float4 of A and of B per slice: slice row = q/32, col4 = q%32.
   // The column part is fixed per thread; out-of-range columns and rows are clamped
   // for the load and zeroed when the slice is written to LDS.
@@ -742,9 +738,6 @@ __global__ __launch_bounds__(256, 3) void grad_gemm_kernel(GradArgs a) {
   const int gate = mc / H, jcol = mc - gate * H;
   const int src = gate == 2 ? a.third_off + jcol : mc;
   floatx4 rk[NCH], rw[NCH], rb[NCH];
-  // Bias gradients are the column sums of S: every thread adds up the products it stages
-  // (its four columns, its rows of every slice); the eight row groups meet in LDS at the end.
-  floatx4 colsum = zero4();
   auto fetch = [&](long long k0) {
 #pragma unroll
     for (int s = 0; s < NCH; ++s) {
@@ -756,42 +749,40 @@ __global__ __launch_bounds__(256, 3) void grad_gemm_kernel(GradArgs a) {
     }
   };
   const int wcol = (c4 * 4) ^ (((tid >> 5) & 1) << 5);     // slice rows kr and tid >> 5: same parity
-  auto stash = [&](long long k0, int buf) {
+  auto stash = [&](long long k0) {
 #pragma unroll
     for (int s = 0; s < NCH; ++s) {
       const int kr = (tid >> 5) + s * 8;
       const bool k_ok = k0 + kr < kend;
       const floatx4 p = (k_ok && m_ok) ? rk[s] * rw[s] : zero4();
       colsum += p;
-      *reinterpret_cast<floatx4*>(&As[buf][kr * GLD + wcol]) = p;
-      *reinterpret_cast<floatx4*>(&Bs[buf][kr * GLD + wcol]) = (k_ok && n_ok) ? rb[s] : zero4();
+      *reinterpret_cast<floatx4*>(&As[kr * GLD + wcol]) = p;
+      *reinterpret_cast<floatx4*>(&Bs[kr * GLD + wcol]) = (k_ok && n_ok) ? rb[s] : zero4();
     }
   };
-  auto frags = [&](int buf, int p, float (&av)[2], float (&bv)[2]) {
+  auto frags = [&](int p, float (&av)[2], float (&bv)[2]) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
-      av[i] = As[buf][(2 * p + lh) * GLD + wm * 64 + ((i ^ lh) << 5) + li];
+      av[i] = As[(2 * p + lh) * GLD + wm * 64 + ((i ^ lh) << 5) + li];
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      bv[j] = Bs[buf][(2 * p + lh) * GLD + wn * 64 + ((j ^ lh) << 5) + li];
+      bv[j] = Bs[(2 * p + lh) * GLD + wn * 64 + ((j ^ lh) << 5) + li];
   };
 
-  const int nt = tile / a.mtiles;
   if (kbeg < kend) {
     fetch(kbeg);
-    stash(kbeg, 0);
+    stash(kbeg);
     __syncthreads();
-    constexpr int buf = 0;
     for (long long k0 = kbeg; k0 < kend; k0 += GTK) {
       const bool more = k0 + GTK < kend;
       if (more) fetch(k0 + GTK);
       __builtin_amdgcn_sched_barrier(0);
       float av[2][2], bv[2][2];
       __builtin_amdgcn_s_setprio(2);      // MFMA phase first at issue (see gemm_core.h)
-      frags(buf, 0, av[0], bv[0]);
+      frags(0, av[0], bv[0]);
 #pragma unroll
       for (int p = 0; p < GTK / 2; ++p) {
-        if (p + 1 < GTK / 2) frags(buf, p + 1, av[(p + 1) & 1], bv[(p + 1) & 1]);
+        if (p + 1 < GTK / 2) frags(p + 1, av[(p + 1) & 1], bv[(p + 1) & 1]);
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -812,13 +803,54 @@ __global__ __launch_bounds__(256, 3) void grad_gemm_kernel(GradArgs a) {
       __builtin_amdgcn_s_setprio(0);
       __syncthreads();
       if (more) {
-        stash(k0 + GTK, buf);
+        stash(k0 + GTK);
         __syncthreads();
       }
     }
   }
+}
+
+// C[m, n] = sum_k S[k, m] Bm[k, n] over this split's rows k.
+// 1-D grid: workgroups go round-robin over the 8 XCDs, so split z is given to XCD
+// z % 8 and all output tiles of a split run on that XCD: its rows of S and Bm are
+// fetched into one L2 only.
+template <class BT>
+__global__ __launch_bounds__(256, 3) void grad_gemm_kernel(GradArgs a) {
+  __shared__ __attribute__((aligned(16))) float As[GTK * GLD];
+  __shared__ __attribute__((aligned(16))) float Bs[GTK * GLD];
+  const int N = a.N, M = 3 * a.H;
+  const int tiles = a.mtiles * a.ntiles;
+  int tile, z;
+  if (a.splits % NXCD == 0) {
+    const int j = blockIdx.x / NXCD;
+    tile = j % tiles;
+    z = (j / tiles) * NXCD + blockIdx.x % NXCD;
+  } else {
+    tile = blockIdx.x % tiles;
+    z = blockIdx.x / tiles;
+  }
+  const int m0 = (tile % a.mtiles) * GT, n0 = (tile / a.mtiles) * GT;
+  const long long kbeg = (long long)z * a.Kper;
+  long long kend = kbeg + a.Kper;
+  if (kend > a.Ktot) kend = a.Ktot;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1, li = lane & 31, lh = lane >> 5;
+  const int c4 = tid & 31;
+
+  floatx16 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  // Bias gradients are the column sums of S: every thread adds up the products it stages
+  // (its four columns, its rows of every slice); the eight row groups meet in LDS at the end.
+  floatx4 colsum = zero4();
+  grad_contract_f32<BT>(a, m0, n0, kbeg, kend, As, Bs, acc, colsum);
+  const int nt = tile / a.mtiles;
   {
-    float* red = As[0];                    // [8][GT] floats (the slices are no longer read)
+    float* red = As;                    // [8][GT] floats (the slices are no longer read)
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < 4; ++e) red[(tid >> 5) * GT + c4 * 4 + e] = colsum[e];
@@ -1345,8 +1377,10 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
       for (int r = 0; r < 4; ++r) {
         v.lo4[r] = p[r][e];
         v.hi4[r] = p[4 + r][e];
-        colsum[e] += p[r][e] + p[4 + r][e];
       }
+      // (a tree: one addition per slice into the long sum)
+      colsum[e] += ((p[0][e] + p[1][e]) + (p[2][e] + p[3][e])) +
+                   ((p[4][e] + p[5][e]) + (p[6][e] + p[7][e]));
       bf16x8 t0, t1, t2;
       split_bf16_3(v, t0, t1, t2);
       *reinterpret_cast<bf16x8*>(dst + e * HS_LD) = t0;
@@ -1397,6 +1431,28 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
         stash(k0 + HS_TK);
         __syncthreads();
       }
+    }
+  }
+  {
+    // sums that are not finite: with fp32 operands (see gemm_core_bf16.h)
+    float t = 0.f;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) t = fmaf(acc[i][j][e], 0.f, t);
+    if (__syncthreads_or(t != t)) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+      static_assert(sizeof(As) >= GTK * GLD * sizeof(float), "fp32 slice must fit");
+      floatx4 unused = zero4();
+      grad_contract_f32<float>(a, m0, n0, kbeg, kend, (float*)&As[0][0], (float*)&Bs[0][0], acc,
+                               unused);
     }
   }
   // column sums of S: the four row groups of a column meet in LDS (the A tiles are free now)
@@ -1513,12 +1569,15 @@ size_t grad_partial_floats(int T, int B, int D, int H, int bf16) {
 
 hipError_t launch_param_grads(const float* kap0, const float* w, const float* h, const void* x,
                               float* dW, float* dU, float* db_i, float* db_h, float* part,
-                              int T, int B, int D, int H, int bf16, int one_term, hipStream_t s) {
+                              size_t part_floats, int T, int B, int D, int H, int bf16,
+                              int one_term, hipStream_t s) {
   const long long Ktot = (long long)T * B;
   const int M = 3 * H;
   prof_begin(3, s);
-  const size_t su = (size_t)grad_splits(Ktot, M, H, bf16) * M * H;
-  const size_t sw = (size_t)grad_splits(Ktot, M, D, bf16) * M * D;
+  // splits of the form that runs, if the caller's scratch has room for them, else of the fp32 form
+  const int sform = grad_partial_floats(T, B, D, H, bf16) <= part_floats ? bf16 : 0;
+  const size_t su = (size_t)grad_splits(Ktot, M, H, sform) * M * H;
+  const size_t sw = (size_t)grad_splits(Ktot, M, D, sform) * M * D;
   float* bpart[2];
   int nbpart[2];
   bpart[0] = part + (su > sw ? su : sw);
@@ -1533,7 +1592,7 @@ hipError_t launch_param_grads(const float* kap0, const float* w, const float* h,
     a.Ktot = Ktot;
     a.B = B;
     a.H = H;
-    const int splits = grad_splits(Ktot, M, a.N, bf16);
+    const int splits = grad_splits(Ktot, M, a.N, sform);
     long long per = (Ktot + splits - 1) / splits;
     const int slice = bf16 == 1 ? HB_TK : GTK;      // (both multiples of the 32 of bf16 = 2)
     a.Kper = (per + slice - 1) / slice * slice;

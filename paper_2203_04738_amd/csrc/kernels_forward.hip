@@ -75,12 +75,12 @@ __global__ __launch_bounds__(ProjCfg::NT) void projection_kernel(
 // bf16 inputs and weights (ProjCfgB), or fp32 inputs with the weights given as their three
 // bf16 terms W3[3][N,K] (ProjCfgS); fp32 accumulation and output
 typedef TileCfgB<2, 2, 2, 2, 1, false> ProjCfgB;
-typedef TileCfgB<4, 2, 1, 2, 1, true, 1, 1, 2, 3, 32> ProjCfgS;   // 8 waves of 32 x 64
+typedef TileCfgB<2, 2, 2, 2, 1, true, 1, 1, 2, 3, 32, true, true> ProjCfgS;
 
 template <class C>
-__global__ __launch_bounds__(C::NT, C::NT > 256 ? 2 : 1) void projection_kernel_bf16(
-    const void* __restrict__ Xv, const bf16_t* __restrict__ W, const float* __restrict__ bias,
-    float* __restrict__ P, long long M, int N, int K) {
+__global__ __launch_bounds__(C::NT, C::NP == 3 ? 2 : 1) void projection_kernel_bf16(
+    const void* __restrict__ Xv, const bf16_t* __restrict__ W, const float* __restrict__ Wf,
+    const float* __restrict__ bias, float* __restrict__ P, long long M, int N, int K) {
   typedef typename std::conditional<C::SPLIT_A, float, bf16_t>::type AT;
   const AT* X = (const AT*)Xv;
   __shared__ __attribute__((aligned(16))) bf16_t lds[C::LDS_ELEMS];
@@ -115,6 +115,10 @@ __global__ __launch_bounds__(C::NT, C::NT > 256 ? 2 : 1) void projection_kernel_
       gemm_nt_tile_bf16<C, false>(acc, K, la, lb, fa, lds);
     else
       gemm_nt_tile_bf16<C, true>(acc, K, la, lb, fa, lds);
+    if (tile_not_finite<C>(acc))
+      contract_f32<C>(acc, K,
+                      [&](int r, int k) { return ldg4(X + (m0 + r < M ? m0 + r : M - 1) * K + k); },
+                      [&](int r) { return Wf + (long long)(n0 + r < N ? n0 + r : N - 1) * K; });
   } else {
     auto la = [&](int s, int k) { return ldg8h(arow[s] + k); };
     auto lb = [&](int s, int k) { return ldg8h(brow[s] + k); };
@@ -142,19 +146,19 @@ __global__ __launch_bounds__(C::NT, C::NT > 256 ? 2 : 1) void projection_kernel_
     }
 }
 
-hipError_t launch_projection(const void* X, const void* W, const float* bias, float* P,
-                             long long M, int N, int K, int bf16, hipStream_t s) {
+hipError_t launch_projection(const void* X, const void* W, const void* W3, const float* bias,
+                             float* P, long long M, int N, int K, int bf16, hipStream_t s) {
   prof_begin(2, s);
   if (bf16 == 2) {
     typedef ProjCfgS C;
     dim3 grid((unsigned)xcd_grid((M + C::TM - 1) / C::TM, (N + C::TN - 1) / C::TN));
-    hipLaunchKernelGGL(projection_kernel_bf16<C>, grid, dim3(C::NT), 0, s, X, (const bf16_t*)W,
-                       bias, P, M, N, K);
+    hipLaunchKernelGGL(projection_kernel_bf16<C>, grid, dim3(C::NT), 0, s, X, (const bf16_t*)W3,
+                       (const float*)W, bias, P, M, N, K);
   } else if (bf16) {
     typedef ProjCfgB C;
     dim3 grid((unsigned)xcd_grid((M + C::TM - 1) / C::TM, (N + C::TN - 1) / C::TN));
     hipLaunchKernelGGL(projection_kernel_bf16<C>, grid, dim3(C::NT), 0, s, X, (const bf16_t*)W,
-                       bias, P, M, N, K);
+                       (const float*)nullptr, bias, P, M, N, K);
   } else {
     typedef ProjCfg C;
     dim3 grid((unsigned)xcd_grid((M + C::TM - 1) / C::TM, (N + C::TN - 1) / C::TN));
@@ -642,6 +646,13 @@ __global__ __launch_bounds__(C::NT, C::MINWG) void phi_step_kernel_bf16(PhiArgs 
       gemm_nt_tile_bf16<C, false>(acc, H, la, lb, fa, lds);
     else
       gemm_nt_tile_bf16<C, true>(acc, H, la, lb, fa, lds);
+    if (tile_not_finite<C>(acc))
+      contract_f32<C>(
+          acc, H, [&](int tr, int k) { return ldg4(a.u_in + rowtab[tr].in + k); },
+          [&](int tr) {
+            const int j = n0 + tr % C::TN;
+            return (const float*)a.U + ((long long)(tr / C::TN) * H + (j < H ? j : H - 1)) * H;
+          });
   } else {
     auto lb = [&](int s, int k) { return ldg8h(brow[s] + k); };
     if (H % C::TK == 0)

@@ -1,0 +1,92 @@
+"""MGRIT_F32 on the bf16 matrix pipe (three terms per fp32 operand): the shapes its rule sends there,
+at the edges of the tiles, and operands that the terms cannot carry."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2203_04738_amd as mg
+from oracle import mgrit_gru_oracle as orc
+from paper_2203_04738_amd.binding import MgritGruCfg
+from synthetic_inputs import random_small
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gh():
+    import gpu_harness
+    return gpu_harness
+
+
+# T, B, D, H: 1024 rows per level-0 launch and a few more; K tails (136, 72), a projection that stays
+# in fp32 (20, 132), row and column tails of the tiles
+@pytest.mark.parametrize("T,B,D,H", [(64, 64, 64, 128), (64, 67, 72, 136), (128, 33, 20, 128),
+                                     (64, 65, 132, 200), (32, 129, 96, 264)])
+def test_training_step_against_the_oracle(gh, T, B, D, H):
+    print("terms case", T, B, D, H, flush=True)
+    d = random_small(T + B + H, T, B, D, H, scale=0.5 / np.sqrt(H))
+    run = gh.GpuRun(d, cf=4, levels=2)
+    P = (d["W"], d["U"], d["b_i"], d["b_h"])
+    z = np.zeros((T + 1, B, H))
+    h_ref, _ = orc.mgrit_forward(*P, d["x"], d["h0"], z, 4, 2, 2)
+    its, _ = run.forward_iterates(2, per_call=2)
+    assert gh.rel_err(its[-1], h_ref) <= 1e-5
+    out = orc.mgrit_backward(*P, d["x"], h_ref, d["dL_dhT"], z, 4, 2, 1)
+    wits, _, grads = run.backward_iterates(h_ref, 1, per_call=1)
+    assert gh.rel_err(wits[-1], out[0]) <= 1e-5
+    for got, want in zip(grads, out[2:6]):
+        assert gh.rel_err(got, want) <= 1e-5
+
+
+@pytest.mark.parametrize("value", [float("inf"), 3.4e38, float("nan")])
+def test_operands_the_terms_cannot_carry(value):
+    # one element of x: its row of the projection, and with it one batch element from that step on,
+    # take what fp32 arithmetic gives; the other rows keep their values
+    T, B, D, H, dev = 64, 64, 64, 128, "cuda:0"
+    d = random_small(3, T, B, D, H, scale=0.3)
+    t = {k: torch.from_numpy(v).to(dev) for k, v in d.items()}
+    cfg = MgritGruCfg(T, B, D, H, cf=4, levels=2, iters=8)
+    ws = torch.empty(mg.mgrit_gru_workspace_bytes(cfg), dtype=torch.uint8, device=dev)
+
+    def solve():
+        h = torch.zeros(T + 1, B, H, device=dev)
+        mg.mgrit_gru_forward(cfg, t["W"], t["U"], t["b_i"], t["b_h"], t["x"], t["h0"], h, None, ws)
+        P = ws[:T * B * 3 * H * 4].view(torch.float32).view(T, B, 3 * H)
+        return h, P.clone()
+
+    _, P0 = solve()
+    t["x"][10, 5, 7] = value
+    t["W"][3, 7] = 0.5
+    t["W"][4, 7] = -0.5
+    t["W"][5, 7] = 2.0
+    _, P1 = solve()
+    want = t["x"][10, 5] @ t["W"].T + t["b_i"]
+    got = P1[10, 5]
+    assert torch.equal(torch.isnan(got), torch.isnan(want))
+    assert torch.equal(torch.isinf(got), torch.isinf(want))
+    ok = torch.isfinite(want)
+    assert torch.allclose(got[ok], want[ok], rtol=1e-5)
+    others = [b for b in range(B) if b != 5]
+    cols = [j for j in range(3 * H) if j not in (3, 4, 5)]
+    # (rows of the same tile are contracted with fp32 operands then: other rounding)
+    assert torch.allclose(P1[:, others][..., cols], P0[:, others][..., cols], rtol=1e-5, atol=1e-5)
+
+
+def test_infinite_adjoints_reach_the_gradients():
+    T, B, D, H, dev = 64, 64, 64, 128, "cuda:0"
+    d = random_small(4, T, B, D, H, scale=0.3)
+    t = {k: torch.from_numpy(v).to(dev) for k, v in d.items()}
+    cfg = MgritGruCfg(T, B, D, H, cf=4, levels=2, iters=1)
+    ws = torch.empty(mg.mgrit_gru_workspace_bytes(cfg), dtype=torch.uint8, device=dev)
+    h = torch.from_numpy(orc.serial_scan(d["W"], d["U"], d["b_i"], d["b_h"], d["x"],
+                                         d["h0"]).astype(np.float32)).to(dev)
+    t["dL_dhT"][2, 9] = float("inf")
+    w = torch.zeros(T + 1, B, H, device=dev)
+    g = [torch.zeros(3 * H, D, device=dev), torch.zeros(3 * H, H, device=dev),
+         torch.zeros(3 * H, device=dev), torch.zeros(3 * H, device=dev)]
+    mg.mgrit_gru_backward(cfg, t["W"], t["U"], t["b_i"], t["b_h"], t["x"], h, t["dL_dhT"], w, None, *g,
+                          ws)
+    assert torch.isinf(w[T, 2, 9]) and not torch.isfinite(w[T - 1, 2]).any()
+    others = [b for b in range(B) if b != 2]
+    assert torch.isfinite(w[:, others]).all()
+    assert all((~torch.isfinite(q)).any() for q in g)
