@@ -44,7 +44,8 @@ struct ProfRec {
   int kind, mode;
   long long rows;
   hipEvent_t e0, e1;
-  double flops, bytes;
+  double flops, bytes, share;
+  int count;
   bool open;           // begun, end not yet recorded
 };
 static bool g_prof = false;
@@ -66,20 +67,27 @@ void prof_begin(int kind, hipStream_t s, long long rows, int mode) {
   r.rows = rows;
   r.mode = mode;
   r.flops = r.bytes = 0;
+  r.count = 1;
+  r.share = 1.0;
   r.open = true;
   if (hipEventCreate(&r.e0) != hipSuccess || hipEventCreate(&r.e1) != hipSuccess) return;
   (void)hipEventRecord(r.e0, s);
   g_recs.push_back(r);
 }
 
-void prof_end(int kind, double flops, double bytes, hipStream_t s) {
+void prof_end(int kind, double flops, double bytes, hipStream_t s, int count, double share) {
   if (!g_prof || t_no_prof) return;
   std::lock_guard<std::mutex> lk(g_prof_mu);
-  if (g_recs.empty() || g_recs.back().kind != kind || !g_recs.back().open) return;
-  g_recs.back().open = false;
-  g_recs.back().flops = flops;
-  g_recs.back().bytes = bytes;
-  (void)hipEventRecord(g_recs.back().e1, s);
+  size_t i = g_recs.size();
+  while (i > 0 && !g_recs[i - 1].open) --i;
+  if (i == 0 || g_recs[i - 1].kind != kind) return;
+  ProfRec& r = g_recs[i - 1];
+  r.open = false;
+  r.flops = flops;
+  r.bytes = bytes;
+  r.count = count;
+  r.share = share;
+  (void)hipEventRecord(r.e1, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -342,6 +350,20 @@ static PhiArgs phi_base(const FwdCtx& x, int l) {
   return a;
 }
 
+// Whether the sub-steps of a sweep run as one launch (kernels_sweep.hip): GRU layers of up to 128
+// columns with fp32 weights.
+static bool sweeps_fused(const mgrit_gru_cfg& c) {
+  return (c.propagator == MGRIT_PROP_IMPLICIT || c.propagator == MGRIT_PROP_CLASSIC) &&
+         kform(c.dtype) != 1 && c.H <= SWEEP_MAX_H && (c.levels == 1 || c.cf > 1);
+}
+
+// A launch of one sub-step loads the weights for a single use: the sweep kernel takes it where they
+// are few (training step of 64 steps x 4: 245 against 262 us with the step kernels at 32 columns,
+// 430 : 405 at 128) and the rows do not fill the chip several times (1024 x 64 x 32: 854 : 818).
+static bool single_fused(const mgrit_gru_cfg& c, int nk) {
+  return sweeps_fused(c) && c.H <= 64 && (long long)nk * c.B <= 4096;
+}
+
 // F-relaxation (Alg. 1) or, with include_c, FC-relaxation on level l: sub-step j
 // advances every interval from point i*cf+j-1 to i*cf+j.  All intervals move in one
 // launch, so the C-sweep reads only values written by earlier launches (Jacobi in
@@ -366,12 +388,17 @@ static bool forward_leaves_coeffs(int l, int L) { return l >= 1 && l < L && (l =
 // evaluates the coarse step and leaves  R u' - Phi_c(R u')  in the coarse right-hand side
 // array (mode STEP_RELAX_RHS).  *rhs_fused tells the caller whether such a launch ran.
 // first_done: the first sub-step of the sweep is in place already (see vcycle_fwd).
+// Fused sweeps (sweeps_fused) take the F-part in one launch; the C-sub-step, whose results are the
+// starting points of the neighbouring intervals, stays a launch of its own.  resid (then only; may be
+// null): the residual launch that follows the F-sweep is its last sub-step, with the coarse arrays
+// given here.
 static int relax_fwd(const FwdCtx& x, int l, bool include_c, bool f_points_current = false,
                      bool emit = false, bool zero_c = false, bool* rhs_fused = nullptr,
-                     bool first_done = false) {
+                     bool first_done = false, const PhiArgs* resid = nullptr) {
   const long long cf = x.c->cf, S = x.lay->S[l];
   const int nint = (int)(x.lay->N[l] / cf);
   if (rhs_fused) *rhs_fused = false;
+  const bool fused = sweeps_fused(*x.c);
   // f_points_current: the F-points already equal the propagation of their coarse
   // points (they were written by the closing F-relaxation of the previous cycle of
   // this call and nothing changed since), so recomputing them would reproduce the
@@ -416,6 +443,27 @@ static int relax_fwd(const FwdCtx& x, int l, bool include_c, bool f_points_curre
       *rhs_fused = true;
     }
     const bool overlap = (cf == 1);   // reads and writes would share points
+    int n = j < cf ? (int)(cf - j) : 1;                 // the F-sub-steps that are left, or the C one
+    if (fused && !overlap && (n + (resid && j < cf) > 1 || single_fused(*x.c, a.nk))) {
+      a.zero_from = 0;
+      const int rest = a.mode == STEP_RELAX_KAPPA2 ? STEP_RELAX_KAPPA
+                       : a.mode == STEP_RELAX_KAPPA ? STEP_RELAX_KAPPA : STEP_RELAX;
+      int last = rest;
+      if (resid && j < cf) {
+        a.uc = resid->uc;
+        a.gc = resid->gc;
+        a.a = resid->a;
+        a.norm = resid->norm;
+        a.resid_adds = rhs_fused && *rhs_fused;
+        a.ff_cf = a.resid_adds ? resid->ff_cf : 0;
+        a.ff_rem = resid->ff_rem;
+        last = STEP_RESID;
+        ++n;
+      }
+      CHECK_HIP(launch_phi_sweep(a, n, rest, last, S, x.s));
+      if (j < cf) j = cf - 1;
+      continue;
+    }
     if (overlap) a.u = x.tmp;
     CHECK_HIP(launch_phi_step(a, x.s));
     if (overlap)
@@ -436,6 +484,20 @@ static int vcycle_fwd(const FwdCtx& x, int l, bool f_points_current = false, boo
     const int kind = x.c->propagator == PROP_ODE_DEMO ? SCAN_ODE
                      : prop_is_lstm(x.c->propagator) ? SCAN_LSTM : SCAN_GRU;
     const int hidden = kind == SCAN_LSTM ? x.c->H / 2 : x.c->H;
+    if (sweeps_fused(*x.c)) {
+      PhiArgs a = phi_base(x, l);
+      a.mode = keep ? STEP_RELAX_KAPPA : STEP_RELAX;
+      if (keep) {
+        a.uc = x.emit_kap;
+        a.kappa_width = 5 * x.c->H;
+      }
+      a.nk = 1;
+      a.in = Idx{0, 0};
+      a.o = Idx{1, 0};
+      a.p = Idx{S - 1, 0};
+      CHECK_HIP(launch_phi_sweep(a, (int)N, a.mode, a.mode, S, x.s));
+      return MGRIT_OK;
+    }
     if (!keep && scan_covers(kind, N, x.c->B, hidden)) {
       ScanArgs a;
       std::memset(&a, 0, sizeof(a));
@@ -476,37 +538,45 @@ static int vcycle_fwd(const FwdCtx& x, int l, bool f_points_current = false, boo
   const bool cur = l == 0 && f_points_current;
   const bool zc = l == 0 && zero_guess && !cur;
   bool rhs_fused = false;
-  if (l == 0 && x.c->fine_relax == 0) {
-    if ((rc = relax_fwd(x, l, false, cur, false, zc, &rhs_fused))) return rc;
-  } else {
-    if ((rc = relax_fwd(x, l, true, cur, false, zc, nullptr, first_f_done))) return rc;
-    if ((rc = relax_fwd(x, l, false, false, false, false, &rhs_fused))) return rc;
-  }
   const int Nc = (int)(N / cf);
   const long long Sc = x.lay->S[l + 1];
-  bool child_first_done = false;
-  {  // lines 2-3: residual at the coarse points, restricted state
-    PhiArgs a = phi_base(x, l);
-    a.mode = STEP_RESID;
-    a.nk = Nc;
-    a.in = Idx{cf - 1, cf};
-    a.o = Idx{cf, cf};
-    a.p = Idx{cf * S - 1, cf * S};
-    a.a = Idx{1, 1};
-    a.uc = x.ul[l + 1];
-    a.gc = x.gl[l + 1];
-    a.norm = l == 0 ? x.norm : nullptr;
-    a.resid_adds = rhs_fused ? 1 : 0;     // completes g_c = (R u' - Phi_c(R u')) - R r
-    // A coarse level that relaxes starts with an F-sweep from the restricted iterate; its first
-    // sub-step gives Phi_c(R u')_k + g_k = (R u')_k - (R r)_k at the points k = 1 (mod cf): this
-    // launch writes them.  (Only with the fused right-hand side: a separate right-hand-side
-    // launch reads the restricted iterate from the coarse array.)
-    child_first_done = rhs_fused && cf > 1 && l + 1 < L - 1;
-    if (child_first_done) {
-      a.ff_cf = (int)cf;
-      a.ff_rem = 1;
-    }
-    CHECK_HIP(launch_phi_step(a, x.s));
+  // lines 2-3: residual at the coarse points, restricted state
+  PhiArgs ra = phi_base(x, l);
+  ra.mode = STEP_RESID;
+  ra.nk = Nc;
+  ra.in = Idx{cf - 1, cf};
+  ra.o = Idx{cf, cf};
+  ra.p = Idx{cf * S - 1, cf * S};
+  ra.a = Idx{1, 1};
+  ra.uc = x.ul[l + 1];
+  ra.gc = x.gl[l + 1];
+  ra.norm = l == 0 ? x.norm : nullptr;
+  // A coarse level that relaxes starts with an F-sweep from the restricted iterate; its first
+  // sub-step gives Phi_c(R u')_k + g_k = (R u')_k - (R r)_k at the points k = 1 (mod cf): this
+  // launch writes them.  (Only with the fused right-hand side: a separate right-hand-side
+  // launch reads the restricted iterate from the coarse array.)
+  if (cf > 1 && l + 1 < L - 1) {
+    ra.ff_cf = (int)cf;
+    ra.ff_rem = 1;
+  }
+  const bool f_only = l == 0 && x.c->fine_relax == 0;
+  // the residual is the last sub-step of the F-sweep before it, where one runs and is fused
+  const bool in_sweep = sweeps_fused(*x.c) && !(f_only && cur);
+  const PhiArgs* tail = in_sweep ? &ra : nullptr;
+  if (f_only) {
+    if ((rc = relax_fwd(x, l, false, cur, false, zc, &rhs_fused, false, tail))) return rc;
+  } else {
+    if ((rc = relax_fwd(x, l, true, cur, false, zc, nullptr, first_f_done))) return rc;
+    if ((rc = relax_fwd(x, l, false, false, false, false, &rhs_fused, false, tail))) return rc;
+  }
+  const bool child_first_done = rhs_fused && ra.ff_cf > 0;
+  if (!in_sweep) {
+    ra.resid_adds = rhs_fused ? 1 : 0;    // completes g_c = (R u' - Phi_c(R u')) - R r
+    if (!child_first_done) ra.ff_cf = 0;
+    if (single_fused(*x.c, ra.nk))
+      CHECK_HIP(launch_phi_sweep(ra, 1, STEP_RESID, STEP_RESID, S, x.s));
+    else
+      CHECK_HIP(launch_phi_step(ra, x.s));
   }
   if (!rhs_fused) {  // line 4, right-hand side of Eq. 11: g_c = A_c(R u') - R r
     PhiArgs a = phi_base(x, l + 1);
@@ -678,8 +748,10 @@ static AdjArgs adj_base(const BwdCtx& x, int l) {
 // left out of the launches; on return *lo is the bound that holds after the sweep (one
 // interval lower).
 // first_done: the first sub-step of the sweep is in place already (see vcycle_bwd).
+// resid: as in relax_fwd.
 static int relax_bwd(const BwdCtx& x, int l, bool include_c, bool f_points_current = false,
-                     long long* lo = nullptr, bool first_done = false) {
+                     long long* lo = nullptr, bool first_done = false,
+                     const AdjArgs* resid = nullptr) {
   const long long cf = x.c->cf;
   const int nint = (int)(x.lay->N[l] / cf);
   long long i0 = 0;                        // first interval that can hold non-zero values
@@ -697,6 +769,24 @@ static int relax_bwd(const BwdCtx& x, int l, bool include_c, bool f_points_curre
     a.k = a.in;
     a.o = Idx{cf - j + i0 * cf, cf};
     const bool overlap = (cf == 1);
+    int n = j < cf ? (int)(cf - j) : 1;
+    if (sweeps_fused(*x.c) && !overlap &&
+        (n + (resid && j < cf) > 1 || single_fused(*x.c, a.nk))) {
+      int last = STEP_RELAX;
+      if (resid && j < cf) {
+        a.wc = resid->wc;
+        a.gc = resid->gc;
+        a.a = Idx{i0, 1};
+        a.norm = resid->norm;
+        a.ff_cf = i0 == 0 ? resid->ff_cf : 0;
+        a.ff_rem = resid->ff_rem;
+        last = STEP_RESID;
+        ++n;
+      }
+      CHECK_HIP(launch_adj_sweep(a, n, STEP_RELAX, last, x.s));
+      if (j < cf) j = cf - 1;
+      continue;
+    }
     if (overlap) a.w = x.tmp;
     CHECK_HIP(launch_adj_step(a, x.s));
     if (overlap)
@@ -720,6 +810,15 @@ static int vcycle_bwd(const BwdCtx& x, int l, bool f_points_current = false,
   const long long cf = x.c->cf, N = x.lay->N[l];
   const int L = x.lay->L;
   if (l == L - 1) {
+    if (sweeps_fused(*x.c)) {
+      AdjArgs a = adj_base(x, l);
+      a.mode = STEP_RELAX;
+      a.nk = 1;
+      a.in = a.k = Idx{N, 0};
+      a.o = Idx{N - 1, 0};
+      CHECK_HIP(launch_adj_sweep(a, (int)N, STEP_RELAX, STEP_RELAX, x.s));
+      return MGRIT_OK;
+    }
     if (scan_covers(SCAN_ADJOINT, N, x.c->B, x.c->H)) {
       ScanArgs a;
       std::memset(&a, 0, sizeof(a));
@@ -752,41 +851,49 @@ static int vcycle_bwd(const BwdCtx& x, int l, bool f_points_current = false,
   long long lo = lo_in;
   long long* plo = lo > 0 && cf > 1 ? &lo : nullptr;
   if (!plo) lo = 0;
-  if (l == 0 && x.c->fine_relax == 0) {
-    if ((rc = relax_bwd(x, l, false, cur, plo))) return rc;
-  } else {
-    if ((rc = relax_bwd(x, l, true, cur, plo, first_f_done))) return rc;
-    if ((rc = relax_bwd(x, l, false, false, plo))) return rc;
-  }
   const int Nc = (int)(N / cf);
-  // coarse points below lo have a zero iterate, a zero successor and a zero right-hand
-  // side: their residual is zero and is written as such
-  const long long iR = lo / cf;            // first coarse point with a non-zero residual
+  const long long BH = (long long)x.c->B * x.c->H;
+  // residual at the coarse points; coarse right-hand side -R r, zero guess
+  AdjArgs ra = adj_base(x, l);
+  ra.mode = STEP_RESID;
+  ra.wc = x.wl[l + 1];
+  ra.gc = x.gl[l + 1];
+  ra.norm = l == 0 ? x.norm : nullptr;
   // A coarse level that relaxes starts with an F-sweep from its zero guess; the first sub-step
   // gives g_k = -(R r)_k at the points k = cf - 1 (mod cf): the residual launch writes them
   // (not in a cycle that skips zero intervals).
-  const bool child_first_done = cf > 1 && l + 1 < L - 1 && iR == 0;
-  const long long BH = (long long)x.c->B * x.c->H;
+  if (cf > 1 && l + 1 < L - 1) {
+    ra.ff_cf = (int)cf;
+    ra.ff_rem = (int)cf - 1;
+  }
+  const bool f_only = l == 0 && x.c->fine_relax == 0;
+  const bool in_sweep = sweeps_fused(*x.c) && !(f_only && cur);     // as in vcycle_fwd
+  const AdjArgs* tail = in_sweep ? &ra : nullptr;
+  if (f_only) {
+    if ((rc = relax_bwd(x, l, false, cur, plo, false, tail))) return rc;
+  } else {
+    if ((rc = relax_bwd(x, l, true, cur, plo, first_f_done))) return rc;
+    if ((rc = relax_bwd(x, l, false, false, plo, false, tail))) return rc;
+  }
+  // coarse points below lo have a zero iterate, a zero successor and a zero right-hand
+  // side: their residual is zero and is written as such
+  const long long iR = lo / cf;            // first coarse point with a non-zero residual
+  const bool child_first_done = ra.ff_cf > 0 && iR == 0;
   if (iR > 0) {
     CHECK_HIP(launch_zero_f32(x.wl[l + 1], iR * BH, x.s));
     CHECK_HIP(launch_zero_f32(x.gl[l + 1], iR * BH, x.s));
   }
-  {  // residual at coarse points i*cf, i = iR..Nc-1; coarse right-hand side -R r, zero guess
-    AdjArgs a = adj_base(x, l);
-    a.mode = STEP_RESID;
-    a.nk = Nc - (int)iR;
-    a.in = Idx{1 + iR * cf, cf};
-    a.k = a.in;
-    a.o = Idx{iR * cf, cf};
-    a.a = Idx{iR, 1};
-    a.wc = x.wl[l + 1];
-    a.gc = x.gl[l + 1];
-    a.norm = l == 0 ? x.norm : nullptr;
-    if (child_first_done) {
-      a.ff_cf = (int)cf;
-      a.ff_rem = (int)cf - 1;
-    }
-    CHECK_HIP(launch_adj_step(a, x.s));
+  if (!in_sweep) {  // residual at coarse points i*cf, i = iR..Nc-1
+    ra.nk = Nc - (int)iR;
+    ra.in = Idx{1 + iR * cf, cf};
+    ra.k = ra.in;
+    ra.o = Idx{iR * cf, cf};
+    ra.a = Idx{iR, 1};
+    if (!child_first_done) ra.ff_cf = 0;
+    if (single_fused(*x.c, ra.nk))
+      CHECK_HIP(launch_adj_sweep(ra, 1, STEP_RESID, STEP_RESID, x.s));
+    else
+      CHECK_HIP(launch_adj_step(ra, x.s));
   }
   // on the coarse level iterate and right-hand side are zero below iR
   if ((rc = vcycle_bwd(x, l + 1, false, iR / cf * cf, child_first_done))) return rc;
@@ -1122,8 +1229,8 @@ int mgrit_gru_profile_read_shape(int kind, int64_t rows, int mode, int64_t* laun
     }
     float t = 0.f;
     if (hipEventSynchronize(r.e1) == hipSuccess && hipEventElapsedTime(&t, r.e0, r.e1) == hipSuccess) {
-      *launches += 1;
-      *ms += t;
+      *launches += r.count;
+      *ms += t * r.share;
       *flops += r.flops;
       *bytes += r.bytes;
     }

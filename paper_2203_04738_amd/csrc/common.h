@@ -124,6 +124,16 @@ hipError_t launch_ode_step(const PhiArgs& a, hipStream_t s);
 hipError_t launch_lstm_step(const PhiArgs& a, hipStream_t s);
 hipError_t launch_adj_step(const AdjArgs& a, hipStream_t s);
 
+// Several consecutive sub-steps of the same intervals in one launch (kernels_sweep.hip): sub-step
+// j = 0..n-1 is `first` with every level point one further on per sub-step (in, o: + j; p: + j * pstep;
+// the adjoint's in, k, o: - j).  Its epilogue mode is first.mode (j = 0), last (j = n - 1 > 0) or
+// `mid`.  The coarse arrays (uc, gc, wc, norm, index a) serve whichever sub-step's mode uses them; in a
+// sweep that keeps coefficients uc is the coefficient array.  GRU, fp32 weights, H <= 128.
+constexpr int SWEEP_MAX_H = 128;
+hipError_t launch_phi_sweep(const PhiArgs& first, int n, int mid, int last, long long pstep,
+                            hipStream_t s);
+hipError_t launch_adj_sweep(const AdjArgs& first, int n, int mid, int last, hipStream_t s);
+
 // P[M,N] = X[M,K] W[N,K]^T + bias[N]
 // X, W: float (bf16 = 0) or bf16 (bf16 = 1); bf16 = 2: X, W float, W3 the three bf16 terms
 // [3][N,K] of the weights (otherwise not read)
@@ -169,6 +179,9 @@ hipError_t launch_sqrt_to_float(const double* acc, float* out, int n, hipStream_
 // profiling brackets (see mgrit_gru_profile_enable)
 // rows / mode describe the launch shape of a step kernel (0 / -1 where they do not apply)
 void prof_begin(int kind, hipStream_t s, long long rows = 0, int mode = -1);
-void prof_end(int kind, double flops, double bytes, hipStream_t s);
+// closes the last open record of the kind; count: launches it stands for, share: their part of the
+// time between the events (sweeps run several sub-steps in one launch)
+void prof_end(int kind, double flops, double bytes, hipStream_t s, int count = 1,
+              double share = 1.0);
 
 }  // namespace mg

@@ -1483,13 +1483,37 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
       }
 }
 
-__global__ void reduce_partials_kernel(const float* __restrict__ part, float* __restrict__ out,
-                                       long long n, int splits) {
-  long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float s = 0.f;
-  for (int z = 0; z < splits; ++z) s += part[(long long)z * n + i];
-  out[i] = s;
+// out[i] = sum over the row splits of part[z][i], four elements per thread.  Few outputs leave most
+// of the chip idle and a thread's additions wait for one load after the other, so G thread rows of a
+// workgroup share the splits (eight loads in flight each) and meet in LDS, in a fixed order.
+template <int G>
+__global__ __launch_bounds__(256) void reduce_partials_kernel(const floatx4* __restrict__ part,
+                                                              floatx4* __restrict__ out,
+                                                              long long n4, int splits) {
+  constexpr int CW = 256 / G;
+  __shared__ floatx4 red[G > 1 ? G : 1][CW];
+  const int c = threadIdx.x % CW, grp = threadIdx.x / CW;
+  const long long i = (long long)blockIdx.x * CW + c;
+  floatx4 s = zero4();
+  if (i < n4) {
+    int z = grp;
+    for (; z + 7 * G < splits; z += 8 * G) {
+      floatx4 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = part[(z + u * G) * n4 + i];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; z < splits; z += G) s += part[z * n4 + i];
+  }
+  if (G > 1) {
+    red[grp][c] = s;
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int q = 1; q < G; ++q) s += red[q][c];
+  }
+  if (i < n4) out[i] = s;
 }
 
 // Bias gradients from the column sums the two gradient GEMMs leave behind, one row per
@@ -1621,8 +1645,15 @@ hipError_t launch_param_grads(const float* kap0, const float* w, const float* h,
     else
       hipLaunchKernelGGL(grad_gemm_kernel<float>, grid, dim3(256), 0, s, a);
     const long long n = (long long)M * a.N;
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                       part, which == 0 ? dU : dW, n, splits);
+    // (3 H N is a multiple of four: so are H and N)
+    const long long n4 = n / 4;
+    floatx4* dst = (floatx4*)(which == 0 ? dU : dW);
+    if (n4 < 65536 && splits >= 16)
+      hipLaunchKernelGGL(reduce_partials_kernel<8>, dim3((unsigned)((n4 + 31) / 32)), dim3(256), 0,
+                         s, (const floatx4*)part, dst, n4, splits);
+    else
+      hipLaunchKernelGGL(reduce_partials_kernel<1>, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0,
+                         s, (const floatx4*)part, dst, n4, splits);
   }
   hipLaunchKernelGGL(bias_reduce_kernel, dim3((3 * H + 31) / 32), dim3(256), 0, s, bpart[0],
                      nbpart[0], bpart[1], nbpart[1], db_i, db_h, H);

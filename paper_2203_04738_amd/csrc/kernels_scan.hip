@@ -16,13 +16,8 @@
 // 1024, 3-4 us among 256 (many small column groups): hence 16 columns per workgroup and as many
 // row blocks as the rows give.
 //
-// Contraction on v_mfma_f32_4x4x1_16b_f32 (16 blocks of 4 rows x 4 columns, one k each): four rows
-// fill the instruction, where a 16-row MFMA idles on three quarters of its rows.  With CBSZ = 2 the
-// A block `abid` of each group of four is broadcast to the group, so a group (16 lanes) contracts
-// 4 rows x 16 columns over its own k and the four groups split K:
-//   A: lane l holds rows l % 4 at k = 4 (l / 4) + e (one 16-byte load per 64 k);
-//   B: lane l holds column l % 16 at k = 16 (l / 16) + 4 abid + e;
-//   D: register v of lane l is row v, column l % 16, summed over the k of group l / 16.
+// Contraction in quads of rows (see quad.h): each workgroup needs few rows, where a 16-row MFMA would
+// idle on three quarters of its rows.
 // Waves split K as well; the groups are added by lane swaps, the waves through LDS (one barrier
 // per step, two buffers).
 //
@@ -43,6 +38,7 @@
 
 #include "gates.h"
 #include "gemm_core_bf16.h"
+#include "quad.h"
 #include "scan.h"
 
 namespace mg {
@@ -120,33 +116,6 @@ __device__ inline void scan_store(float* p, float val, bool ok) {
     asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
 
-// Sum of the four k-groups of a 4-row x 16-column block: in, register v of lane l is row v, column
-// l % 16 of group l / 16; out, lane l holds row scan_row(l), column l % 16 of the sum.
-__device__ inline float scan_fold(const floatx4& a) {
-  typedef unsigned u2 __attribute__((ext_vector_type(2)));
-  auto add = [](u2 s) { return __uint_as_float(s[0]) + __uint_as_float(s[1]); };
-  auto u = [](float f) { return __float_as_uint(f); };
-  const float x01 = add(__builtin_amdgcn_permlane32_swap(u(a[0]), u(a[1]), false, false));
-  const float x23 = add(__builtin_amdgcn_permlane32_swap(u(a[2]), u(a[3]), false, false));
-  return add(__builtin_amdgcn_permlane16_swap(u(x01), u(x23), false, false));
-}
-__device__ inline int scan_row(int lane) { return ((lane >> 5) & 1) + 2 * ((lane >> 4) & 1); }
-
-// acc[r][g] += A_rg (64 k of four rows, see above) * the sixteen weights of gate g at those k; the
-// sums of the gates and row groups alternate, so that consecutive MFMAs do not wait for each other
-// (a lone sum is kept as two).
-template <int RB, int NG, int NP, class GetA, class GetW>
-__device__ inline void scan_mma(floatx4 (&acc)[RB][NG][NP], GetA getA, GetW getW) {
-#define MG_SCAN_STEP(E, A)                                                                       \
-  _Pragma("unroll") for (int r = 0; r < RB; ++r) _Pragma("unroll") for (int g = 0; g < NG; ++g)  \
-      acc[r][g][A % NP] = __builtin_amdgcn_mfma_f32_4x4x1f32(                                    \
-          getA(r, g)[E], getW(g)[4 * A + E], acc[r][g][A % NP], 2, A, 0);
-#define MG_SCAN_E(E) MG_SCAN_STEP(E, 0) MG_SCAN_STEP(E, 1) MG_SCAN_STEP(E, 2) MG_SCAN_STEP(E, 3)
-  MG_SCAN_E(0) MG_SCAN_E(1) MG_SCAN_E(2) MG_SCAN_E(3)
-#undef MG_SCAN_E
-#undef MG_SCAN_STEP
-}
-
 // NCH: chunks of 64 k per wave; RB: groups of four rows per workgroup.  Registers: NG 16 NCH
 // weights; one workgroup per CU is planned for (two waves per SIMD at eight waves).
 template <int KIND, int NCH, int RB, class WT>
@@ -206,7 +175,7 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
   }
   // output element of this lane: wave r finishes row group r
   const bool epi = wv < RB;
-  const int orow = r0 + 4 * wv + scan_row(lane), oj = j0 + (lane & 15);
+  const int orow = r0 + 4 * wv + quad_row(lane), oj = j0 + (lane & 15);
   const bool ok = epi && orow < B && oj < H;
   const int er = min(orow, B - 1), ej = min(oj, H - 1);
   const long long eo = (long long)er * W + ej;
@@ -323,7 +292,7 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
         for (int q = 0; q < NP; ++q) acc[r][g][q] = zero4();
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
-      scan_mma<RB, NG, NP>(acc, [&](int r, int g) { return op[c][r][ADJ ? g : 0]; },
+      quad_mma<RB, NG, NP>(acc, [&](int r, int g) { return op[c][r][ADJ ? g : 0]; },
                            [&](int g) -> const float (&)[16] { return w[g][c]; });
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
@@ -331,10 +300,10 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
 #pragma unroll
       for (int g = 0; g < NG; ++g) sum[g] = NP > 1 ? acc[r][g][0] + acc[r][g][NP - 1] : acc[r][g][0];
       if (ADJ) {
-        part[buf][wv][r][0][lane] = scan_fold(sum[0] + sum[NG > 1 ? 1 : 0] + sum[NG - 1]);
+        part[buf][wv][r][0][lane] = quad_fold(sum[0] + sum[NG > 1 ? 1 : 0] + sum[NG - 1]);
       } else {
 #pragma unroll
-        for (int g = 0; g < NG; ++g) part[buf][wv][r][ADJ ? 0 : g][lane] = scan_fold(sum[g]);
+        for (int g = 0; g < NG; ++g) part[buf][wv][r][ADJ ? 0 : g][lane] = quad_fold(sum[g]);
       }
     }
     __syncthreads();

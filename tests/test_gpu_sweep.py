@@ -1,0 +1,57 @@
+"""Sweeps of narrow layers in one launch (kernels_sweep.hip) against the oracle: partly filled quads,
+waves and K chunks, one to many quads per workgroup, cf 2 (sweeps of one sub-step and a residual) to
+8, levels that keep coefficients, and serial solves of more than 64 rows.  Bar 1e-5 (fp32)."""
+import numpy as np
+import pytest
+
+from oracle import mgrit_gru_oracle as orc
+from paper_2203_04738_amd.binding import MGRIT_ZERO_ADJOINT_GUESS
+from synthetic_inputs import random_small
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gh():
+    import gpu_harness
+    return gpu_harness
+
+
+@pytest.mark.parametrize("T,B,H,cf,levels,fine,prop",
+                         [(16, 1, 4, 2, 3, 1, 0), (32, 3, 20, 2, 2, 0, 0), (64, 2, 64, 4, 3, 1, 0),
+                          (64, 3, 68, 4, 3, 1, 0), (64, 71, 100, 8, 2, 1, 0), (48, 5, 128, 3, 2, 0, 0),
+                          (128, 70, 128, 4, 2, 1, 0), (64, 2, 32, 4, 2, 1, 1)])
+def test_cycles_of_narrow_layers(gh, T, B, H, cf, levels, fine, prop):
+    print("sweep case", T, B, H, cf, levels, fine, prop, flush=True)
+    d = random_small(T + B + H, T, B, 8, H, scale=0.3 / np.sqrt(H))
+    run = gh.GpuRun(d, cf=cf, levels=levels, fine_relax=fine, propagator=prop)
+    P, z = (d["W"], d["U"], d["b_i"], d["b_h"]), np.zeros((T + 1, B, H))
+    kw = dict(fine_relax_fcf=bool(fine), propagator=orc.IMPLICIT if prop == 0 else orc.CLASSIC)
+    h_ref, res = orc.mgrit_forward(*P, d["x"], d["h0"], z, cf, levels, 2, **kw)
+    its, norms = run.forward_iterates(2, per_call=2)
+    assert gh.rel_err(its[-1], h_ref) <= 1e-5
+    floor = 2e-6 * np.sqrt(T * B * H / cf)
+    assert np.allclose(norms, res, rtol=1e-4, atol=floor)
+    out = orc.mgrit_backward(*P, d["x"], h_ref, d["dL_dhT"], z, cf, levels, 2, **kw)
+    for flags in (0, MGRIT_ZERO_ADJOINT_GUESS):
+        wits, _, grads = run.backward_iterates(h_ref, 2, per_call=2, first_call_flags=flags)
+        assert gh.rel_err(wits[-1], out[0]) <= 1e-5
+        for got, want in zip(grads, out[2:6]):
+            assert gh.rel_err(got, want) <= 1e-5
+
+
+def test_kept_coefficients_and_a_serial_scan_of_many_rows(gh):
+    d = random_small(7, 64, 66, 8, 48, scale=0.1)
+    for serial in (False, True):
+        run = gh.GpuRun(d, cf=4, levels=3)
+        got = run.forward_then_backward_reusing_coeffs(2, 2, serial=serial)
+        P, z = (d["W"], d["U"], d["b_i"], d["b_h"]), np.zeros((65, 66, 48))
+        if serial:
+            h = orc.serial_scan(*P, d["x"], d["h0"])
+            out = orc.serial_bptt(*P, d["x"], h, d["dL_dhT"])
+            want = (h, out[0])
+        else:
+            h, _ = orc.mgrit_forward(*P, d["x"], d["h0"], z, 4, 3, 2)
+            out = orc.mgrit_backward(*P, d["x"], h, d["dL_dhT"], z, 4, 3, 2)
+            want = (h, out[0])
+        assert gh.rel_err(got[0], want[0]) <= 1e-5 and gh.rel_err(got[1], want[1]) <= 1e-5
