@@ -37,7 +37,7 @@
  *   and are rebuilt by every call; H and D must be multiples of 8.  A tile with
  *   a sum that is not finite (an operand the terms cannot carry, like an
  *   infinity) is contracted again on the fp32 matrix pipe.
- *   MGRIT_F32 takes the same form by itself for GRU problems where it is faster
+ *   MGRIT_F32 takes the same form by itself for GRU and LSTM problems where it is faster
  *   and no less accurate (widths that are multiples of 8, at least 128, and 1024
  *   rows or more per level-0 launch), in a workspace that is no larger.
  * - Level l of the hierarchy has N_l = T / cf^l steps and step size cf^l

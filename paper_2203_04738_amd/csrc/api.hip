@@ -212,7 +212,7 @@ static bool misaligned(const void* p) { return ((uintptr_t)p & 15) != 0; }
 //    Error of a contraction against 64 bits: 1.35e-7 against 1.44e-7 of the fp32 MFMAs over 64
 //    columns, 2.5 : 2.9 over 256, 5.0 : 5.8 over 1024 (fewer additions into the sum), but 0.83 :
 //    0.73 over 16.  Below 128 columns nothing is gained in time;
-//  - the GRU (the LSTM and ODE kernels have no such form);
+//  - GRU and LSTM (the ODE kernels have no such form);
 //  - 1024 rows or more in a level-0 launch.  Training step of two levels, fp32 MFMAs : terms:
 //    256 rows x 1000 1.44 : 1.52 ms, 512 x 512 0.88 : 0.88, 1024 x 512 1.66 : 1.52, 4096 x 1000
 //    12.8 : 10.7;
@@ -235,10 +235,14 @@ static Forms make_forms(const mgrit_gru_cfg& c, const Layout& lay, char* base) {
     return f;
   }
   const bool gru = c.propagator == MGRIT_PROP_IMPLICIT || c.propagator == MGRIT_PROP_CLASSIC;
+  const bool lstm = prop_is_lstm(c.propagator);        // (c.H is the state width 2 H then)
+  const int H = lstm ? c.H / 2 : c.H, gates = lstm ? 4 : 3;
   const long long rows = (long long)c.T * c.B / (c.levels > 1 ? c.cf : 1);
-  if (c.dtype != MGRIT_F32 || !gru || c.H % 8 != 0 || c.H < TERMS_MIN_H || rows < TERMS_MIN_ROWS) return f;
-  const size_t u3 = align_up((size_t)18 * c.H * c.H);
-  const size_t w3 = align_up((size_t)18 * c.H * c.D);
+  if (c.dtype != MGRIT_F32 || (!gru && !lstm) || H % 8 != 0 || H < TERMS_MIN_H ||
+      rows < TERMS_MIN_ROWS)
+    return f;
+  const size_t u3 = align_up((size_t)6 * gates * H * H);
+  const size_t w3 = align_up((size_t)6 * gates * H * c.D);
   const size_t room = lay.total_part - CTL_BYTES;
   if (u3 + (u3 > w3 ? u3 : w3) > room) return f;
   f.rec = 2;
@@ -599,10 +603,10 @@ static int vcycle_fwd(const FwdCtx& x, int l, bool f_points_current = false, boo
 static int run_projection(const mgrit_gru_cfg* c, const Layout& lay, const Forms& f, char* base,
                           const void* W, const float* b_i, const void* x, hipStream_t s) {
   if (c->flags & MGRIT_REUSE_PROJECTION) return MGRIT_OK;
-  if (f.proj == 2) CHECK_HIP(launch_split3((const float*)W, f.W3, 3LL * c->H * c->D, s));
   // GRU: three gates; demonstration ODE: one block; LSTM: four gates of the hidden width c->H / 2
   const int width = c->propagator == PROP_ODE_DEMO ? c->H
                     : prop_is_lstm(c->propagator) ? 2 * c->H : 3 * c->H;
+  if (f.proj == 2) CHECK_HIP(launch_split3((const float*)W, f.W3, (long long)width * c->D, s));
   CHECK_HIP(launch_projection(x, W, f.W3, b_i, (float*)(base + lay.P), (long long)c->T * c->B,
                               width, c->D, f.proj, s));
   return MGRIT_OK;
@@ -668,7 +672,8 @@ static int forward_impl(const mgrit_gru_cfg* cin, bool serial, const void* W, co
   ctx.form = forms.rec;
   ctx.U = U;
   ctx.U3 = forms.U3;
-  if (forms.rec == 2) CHECK_HIP(launch_split3((const float*)U, forms.U3, 3LL * c.H * c.H, s));
+  const long long nU = lstm ? (long long)c.H * c.H : 3LL * c.H * c.H;    // (LSTM: 4 (H / 2)^2)
+  if (forms.rec == 2) CHECK_HIP(launch_split3((const float*)U, forms.U3, nU, s));
   ctx.b_h = b_h;
   ctx.P = (const float*)(base + lay.P);
   ctx.dt = ode ? ode_dt : 1.f;

@@ -13,7 +13,7 @@
 // STEP_RESID, STEP_RHS; forward propagation only.
 #include "common.h"
 #include "gates.h"
-#include "gemm_core.h"
+#include "gemm_core_bf16.h"
 #include "skinny.h"
 
 namespace mg {
@@ -195,6 +195,73 @@ __global__ __launch_bounds__(C::NT, C::NT > 256 ? 1 : C::MINWG) void lstm_step_k
 
   double nrm = 0.0;
   lstm_tile_epilogue<C, MODE>(a, acc, rowtab, lds, m0, n0, R, nrm);
+  if (MODE == STEP_RESID && a.norm) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) nrm += __shfl_down(nrm, off, 64);
+    if ((tid & 63) == 0) atomicAdd(a.norm, nrm);
+  }
+}
+
+// The same step with each fp32 operand as three bf16 terms (see gemm_core_bf16.h): the weights come
+// as their terms a.U3[3][4H, H], the states are split on their way to LDS.
+template <class C, int MODE>
+__global__ __launch_bounds__(C::NT, 2) void lstm_step_kernel_x3(PhiArgs a) {
+  constexpr int LDSF =
+      C::LDS_ELEMS / 2 + 1 > EpiStage<C>::FLOATS ? C::LDS_ELEMS / 2 + 1 : EpiStage<C>::FLOATS;
+  __shared__ __attribute__((aligned(16))) float ldsf[LDSF];
+  const int S = a.H, H = S / 2, B = a.B;
+  const long long R = (long long)a.nk * B;
+  long long rt;
+  int ct;
+  if (!xcd_tile(blockIdx.x, (R + C::TM - 1) / C::TM, (H + C::TN - 1) / C::TN, rt, ct)) return;
+  const long long m0 = rt * C::TM;
+  const int n0 = ct * C::TN;
+  const int tid = threadIdx.x;
+  __shared__ LstmRow rowtab[C::TM];
+  if (tid < C::TM) {
+    long long r = m0 + tid;
+    if (r >= R) r = R - 1;
+    rowtab[tid] = lstm_row(a, r);
+  }
+  // (visible to all waves after the barriers inside the contraction)
+
+  const float* arow[C::A_CHUNKS];
+  const bf16_t* brow[C::B_CHUNKS];
+#pragma unroll
+  for (int s = 0; s < C::A_CHUNKS; ++s) {
+    long long r = m0 + chunk_row_b<C>(s);
+    if (r >= R) r = R - 1;     // clamped rows are never stored
+    const long long pt = (unsigned)r / (unsigned)B;
+    const int b = (int)(r - pt * B);
+    arow[s] = a.u_in + (a.in.at(pt) * B + b) * S;       // h half of the state row
+  }
+#pragma unroll
+  for (int s = 0; s < C::B_CHUNKS; ++s) {
+    const int tr = chunk_row_b<C>(s);
+    const int j = min(n0 + tr % C::TN, H - 1);
+    brow[s] = (const bf16_t*)a.U3 + ((long long)(tr / C::TN) * H + j) * H;
+  }
+  Acc<C> acc;
+  acc.zero();
+  const long long term = 4LL * H * H;
+  auto la = [&](int s, int k) { return F32x8{ldg4(arow[s] + k), ldg4(arow[s] + k + 4)}; };
+  auto lb = [&](int s, int k) {
+    return Bf16x8x3{{ldg8h(brow[s] + k), ldg8h(brow[s] + term + k), ldg8h(brow[s] + 2 * term + k)}};
+  };
+  auto fa = [](const F32x8& v) { return v; };
+  if (H % C::TK == 0)
+    gemm_nt_tile_bf16<C, false>(acc, H, la, lb, fa, (bf16_t*)ldsf);
+  else
+    gemm_nt_tile_bf16<C, true>(acc, H, la, lb, fa, (bf16_t*)ldsf);
+  if (tile_not_finite<C>(acc))
+    contract_f32<C>(
+        acc, H, [&](int tr, int k) { return ldg4(a.u_in + rowtab[tr].in + k); },
+        [&](int tr) {
+          return (const float*)a.U + ((long long)(tr / C::TN) * H + min(n0 + tr % C::TN, H - 1)) * H;
+        });
+
+  double nrm = 0.0;
+  lstm_tile_epilogue<C, MODE>(a, acc, rowtab, ldsf, m0, n0, R, nrm);
   if (MODE == STEP_RESID && a.norm) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) nrm += __shfl_down(nrm, off, 64);
@@ -439,6 +506,25 @@ typedef TileCfg<4, 2, 1, 1, 4> LstmBig;
 typedef TileCfg<2, 2, 1, 1, 4> LstmMid;                  //  64 x 64
 typedef TileCfg<1, 1, 1, 1, 4, 128, 1, 4> LstmSmall;     //  32 x 32, 4 waves splitting K
 
+// Three-term operands: 64 x 64 tiles at every size (16384 rows x 512: 239 us against 247 for 128 x 64
+// as eight waves, whose staged sums leave one workgroup per CU, and 332 on the fp32 MFMAs; 4096 rows:
+// 65 against 81).  Smaller launches stay on the K-split fp32 tile.
+typedef TileCfgB<2, 2, 1, 1, 4, true, 1, 1, 2, 3, 32> LstmMidS;
+
+static void launch_lstm_x3(const PhiArgs& a, hipStream_t s) {
+  typedef LstmMidS C;
+  const long long R = (long long)a.nk * a.B;
+  const int H = a.H / 2;
+  dim3 grid((unsigned)xcd_grid((R + C::TM - 1) / C::TM, (H + C::TN - 1) / C::TN));
+  dim3 block(C::NT);
+  if (a.mode == STEP_RELAX)
+    hipLaunchKernelGGL((lstm_step_kernel_x3<C, STEP_RELAX>), grid, block, 0, s, a);
+  else if (a.mode == STEP_RESID)
+    hipLaunchKernelGGL((lstm_step_kernel_x3<C, STEP_RESID>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((lstm_step_kernel_x3<C, STEP_RHS>), grid, block, 0, s, a);
+}
+
 template <class C>
 static void launch_lstm_cfg(const PhiArgs& a, hipStream_t s) {
   const long long R = (long long)a.nk * a.B;
@@ -473,6 +559,8 @@ hipError_t launch_lstm_step(const PhiArgs& a, hipStream_t s) {
       launch_lstm_skinny<2>(a, grid, rb, s);
     else
       launch_lstm_skinny<1>(a, grid, rb, s);
+  } else if (a.bf16 == 2 && R > 32 && tiles(LstmMid::TM, LstmMid::TN) >= 128) {
+    launch_lstm_x3(a, s);
   } else if (tiles(LstmBig::TM, LstmBig::TN) >= 384)
     launch_lstm_cfg<LstmBig>(a, s);
   else if (R > 32 && tiles(LstmMid::TM, LstmMid::TN) >= 128)

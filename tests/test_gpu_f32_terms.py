@@ -5,9 +5,10 @@ import pytest
 import torch
 
 import paper_2203_04738_amd as mg
+from oracle import lstm_oracle as lo
 from oracle import mgrit_gru_oracle as orc
 from paper_2203_04738_amd.binding import MgritGruCfg
-from synthetic_inputs import random_small
+from synthetic_inputs import random_lstm, random_small
 
 pytestmark = pytest.mark.gpu
 
@@ -36,6 +37,21 @@ def test_training_step_against_the_oracle(gh, T, B, D, H):
     assert gh.rel_err(wits[-1], out[0]) <= 1e-5
     for got, want in zip(grads, out[2:6]):
         assert gh.rel_err(got, want) <= 1e-5
+
+
+@pytest.mark.parametrize("T,B,D,H", [(64, 64, 64, 128), (64, 67, 20, 136), (128, 129, 72, 200)])
+def test_lstm_solve_against_the_oracle(T, B, D, H):
+    print("terms case lstm", T, B, D, H, flush=True)
+    d = random_lstm(T + B + H, T, B, D, H, scale=0.5 / np.sqrt(H))
+    t = {k: torch.from_numpy(v).to("cuda:0") for k, v in d.items()}
+    cfg = MgritGruCfg(T, B, D, H, cf=4, levels=2, iters=2)
+    ws = torch.empty(mg.mgrit_lstm_workspace_bytes(cfg), dtype=torch.uint8, device="cuda:0")
+    u = torch.zeros(T + 1, B, 2 * H, device="cuda:0")
+    mg.mgrit_lstm_forward(cfg, t["W"], t["U"], t["b_i"], t["b_h"], t["x"], t["u0"], u, None, ws)
+    want, _ = lo.mgrit_lstm_forward(d["W"], d["U"], d["b_i"], d["b_h"], d["x"], d["u0"],
+                                    np.zeros((T + 1, B, 2 * H)), 4, 2, 2)
+    got = u.cpu().numpy().astype(np.float64)
+    assert np.max(np.abs(got - want)) <= 1e-5 * np.max(np.abs(want))
 
 
 @pytest.mark.parametrize("value", [float("inf"), 3.4e38, float("nan")])
