@@ -563,7 +563,10 @@ typedef TileCfgB<2, 2, 2, 2, 1, true, 1, 1, 2, 3, 32> AdjBigS;
 // workgroups (16 waves, 128 registers per lane) share a CU and keep twice the loads in
 // flight; the relaxation mode fits that register budget, the others use the 4-wave form
 typedef TileCfgB<4, 2, 1, 2, 1, true, 1, 1, 2, 3, 32> AdjBigS8;
-typedef TileCfgB<2, 2, 1, 1, 1, true, 1, 1, 2, 3, 32> AdjMidS;
+// mid-size launches: 64 x 128 as four waves of 32 x 64, and 64 x 64 with two groups of four waves
+// splitting K (the adjoint's K is 3H: with one group the 64 x 64 tile waits on its slices)
+typedef TileCfgB<2, 2, 1, 2, 1, true, 1, 1, 2, 3, 32> AdjWideS;
+typedef TileCfgB<2, 2, 1, 1, 1, true, 2, 1, 2, 3, 32> AdjMidS;
 typedef TileCfgB<1, 1, 1, 1, 1, true, 4, 1, 2, 3, 32> AdjSmallS;
 
 template <class C, class CB, class CS, class CF>
@@ -599,6 +602,16 @@ static void launch_adj_cfg(const AdjArgs& a, hipStream_t s) {
     else
       hipLaunchKernelGGL((adj_step_kernel<C, STEP_RESID>), grid, block, 0, s, a);
   }
+}
+
+template <class C>
+static void launch_adj_x3(const AdjArgs& a, hipStream_t s) {
+  const long long R = (long long)a.nk * a.B;
+  dim3 grid((unsigned)xcd_grid((R + C::TM - 1) / C::TM, (a.H + C::TN - 1) / C::TN));
+  if (a.mode == STEP_RELAX)
+    hipLaunchKernelGGL((adj_step_kernel_bf16<C, STEP_RELAX>), grid, dim3(C::NT), 0, s, a);
+  else
+    hipLaunchKernelGGL((adj_step_kernel_bf16<C, STEP_RESID>), grid, dim3(C::NT), 0, s, a);
 }
 
 // Rows per workgroup of the few-row adjoint step: every workgroup streams the
@@ -650,6 +663,14 @@ hipError_t launch_adj_step(const AdjArgs& a, hipStream_t s) {
       launch_adj_skinny<1>(a, grid, s);
   } else if (tiles(AdjBig::TM, AdjBig::TN) >= (a.bf16 == 1 ? 256 : 384))
     launch_adj_cfg<AdjBig, AdjBigB, AdjBigS, AdjBigF>(a, s);
+  // three terms, by what fills the chip (us, 64 x 64 without the split : 64 x 128 : 64 x 64 split):
+  // 3200 rows x 1000 (400 wide tiles) 247 : 179 : 207, 4096 x 1024 (512) 215 : 169 : 193,
+  // 4096 x 512 (256) 65 : 69 : 56, 1024 x 1024 (256 tiles of 64 x 64) 101 : 121 : 75, 800 x 1000 (208)
+  // 99 with 32 x 32 tiles, 82 split
+  else if (a.bf16 == 2 && tiles(AdjWideS::TM, AdjWideS::TN) >= 384)
+    launch_adj_x3<AdjWideS>(a, s);
+  else if (a.bf16 == 2 && R > 32 && tiles(AdjMidS::TM, AdjMidS::TN) >= 192)
+    launch_adj_x3<AdjMidS>(a, s);
   else if (R > 32 && tiles(AdjMid::TM, AdjMid::TN) >= 256)
     launch_adj_cfg<AdjMid, AdjMidB, AdjMidS, AdjMidF>(a, s);
   else

@@ -731,6 +731,10 @@ typedef TileCfgB<2, 2, 1, 1, 3, true, 2, 1, 1, 1, 64, false> PhiMidFK;
 typedef TileCfgB<2, 2, 2, 1, 3, true, 1, 1, 2, 3, 32> PhiBigS;
 typedef TileCfgB<2, 2, 1, 1, 3, true, 1, 1, 2, 3, 32> PhiMidS;
 typedef TileCfgB<1, 1, 1, 1, 3, true, 4, 1, 2, 3, 32> PhiSmallS;
+// 64 x 32 with two groups of two waves splitting K, where 64 x 64 tiles leave CUs half empty (us, 64 x
+// 64 : this): 1024 rows x 1024 (256 tiles of 64 x 64) 64 : 50, 800 x 1000 (208) 66 : 53, 4096 x 256
+// (256) 19.6 : 16.7, but 4096 x 512 (512) 50 : 58
+typedef TileCfgB<2, 1, 1, 1, 3, true, 2, 1, 2, 3, 32> PhiNarrowS;
 
 #define MG_LAUNCH_BY_MODE(KERNEL, ...)                                                   \
   switch (a.mode) {                                                                      \
@@ -786,6 +790,14 @@ static void launch_phi_cfg(const PhiArgs& a, hipStream_t s) {
     dim3 block(C::NT);
     MG_LAUNCH_BY_MODE(phi_step_kernel, C)
   }
+}
+
+template <class CS>
+static void launch_phi_x3(const PhiArgs& a, hipStream_t s) {
+  const long long R = (long long)a.nk * a.B;
+  dim3 grid((unsigned)xcd_grid((R + CS::TM - 1) / CS::TM, (a.H + CS::TN - 1) / CS::TN));
+  dim3 block(CS::NT);
+  MG_LAUNCH_BY_MODE(phi_step_kernel_bf16, CS)
 }
 
 constexpr int PHI_SK_ROWS = 32;   // rows per workgroup of the few-row forward step
@@ -886,7 +898,9 @@ hipError_t launch_phi_step(const PhiArgs& a, hipStream_t s) {
     launch_phi_cfg<PhiBig, PhiBigB, PhiBigS, PhiBigF>(a, s);
   } else if (R > 32 && tiles(PhiMid::TM, PhiMid::TN) >= 128) {
     contracted(PhiMid::TM);
-    if (a.bf16 == 1 && a.one_term && tiles(PhiMid::TM, PhiMid::TN) <= 256)
+    if (a.bf16 == 2 && tiles(PhiMid::TM, PhiMid::TN) < 512)
+      launch_phi_x3<PhiNarrowS>(a, s);
+    else if (a.bf16 == 1 && a.one_term && tiles(PhiMid::TM, PhiMid::TN) <= 256)
       launch_phi_cfg<PhiMid, PhiMidB, PhiMidS, PhiMidFK>(a, s);
     else
       launch_phi_cfg<PhiMid, PhiMidB, PhiMidS, PhiMidF>(a, s);

@@ -106,3 +106,21 @@ def test_infinite_adjoints_reach_the_gradients():
     others = [b for b in range(B) if b != 2]
     assert torch.isfinite(w[:, others]).all()
     assert all((~torch.isfinite(q)).any() for q in g)
+
+
+@pytest.mark.parametrize("B,H", [(33, 520), (65, 504)])
+def test_mid_size_tiles(gh, B, H):
+    """Level launches of 528 to 2080 rows of 504 and 520 columns: the adjoint's 64 x 128 and K-split
+    64 x 64 tiles, the forward 64 x 32 ones, each with row, column and K tails."""
+    T, D = 64, 8
+    print("terms case mid", B, H, flush=True)
+    d = random_small(B + H, T, B, D, H, scale=0.3 / np.sqrt(H))
+    for cf in (2, 4):
+        run = gh.GpuRun(d, cf=cf, levels=2)
+        P, z = (d["W"], d["U"], d["b_i"], d["b_h"]), np.zeros((T + 1, B, H))
+        h_ref, _ = orc.mgrit_forward(*P, d["x"], d["h0"], z, cf, 2, 1)
+        its, _ = run.forward_iterates(1)
+        assert gh.rel_err(its[-1], h_ref) <= 1e-5
+        out = orc.mgrit_backward(*P, d["x"], h_ref, d["dL_dhT"], z, cf, 2, 1)
+        wits, _, _ = run.backward_iterates(h_ref, 1)
+        assert gh.rel_err(wits[-1], out[0]) <= 1e-5
