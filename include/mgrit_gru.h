@@ -343,7 +343,8 @@ MGRIT_API const char* mgrit_gru_strerror(int code);
  *   kind: 0 = forward step (Phi) on MFMA tiles, 1 = adjoint step (Phi^T) on MFMA tiles,
  *         2 = projection GEMM, 3 = weight-gradient GEMMs, 4 / 5 = forward / adjoint step
  *         in the few-row form used by the serial scan and the coarsest-level solve (a solve of
- *         eight steps or more is one launch and one record with the work of all its steps),
+ *         eight steps or more is one launch and one record with the work of all its steps;
+ *         sweeps of layers of up to 128 columns count as their sub-steps, in kinds 0, 1, 4, 5),
  *         6 = input-gradient GEMM, 7 = point copies (coarse-grid correction, terminal and
  *         initial conditions), 8 = step of the demonstration ODE (tile and few-row forms),
  *         9 = LSTM step (tile and few-row forms).

@@ -567,31 +567,20 @@ typedef TileCfgB<4, 2, 1, 2, 1, true, 1, 1, 2, 3, 32> AdjBigS8;
 // splitting K (the adjoint's K is 3H: with one group the 64 x 64 tile waits on its slices)
 typedef TileCfgB<2, 2, 1, 2, 1, true, 1, 1, 2, 3, 32> AdjWideS;
 typedef TileCfgB<2, 2, 1, 1, 1, true, 2, 1, 2, 3, 32> AdjMidS;
-typedef TileCfgB<1, 1, 1, 1, 1, true, 4, 1, 2, 3, 32> AdjSmallS;
 
-template <class C, class CB, class CS, class CF>
+template <class C, class CB, class CF>
 static void launch_adj_cfg(const AdjArgs& a, hipStream_t s) {
   const long long R = (long long)a.nk * a.B;
   dim3 grid((unsigned)xcd_grid((R + C::TM - 1) / C::TM, (a.H + C::TN - 1) / C::TN));
-  dim3 block(a.bf16 == 2 ? CS::NT : a.bf16 ? CB::NT : C::NT);
+  dim3 block(a.bf16 == 1 ? CB::NT : C::NT);
   static_assert(CF::TM == CB::TM && CF::TN == CB::TN && CF::NT == CB::NT, "tile shapes must agree");
   static_assert(C::TM == CB::TM && C::TN == CB::TN, "tile shapes must agree");
-  static_assert(C::TM == CS::TM && C::TN == CS::TN, "tile shapes must agree");
-  static_assert(AdjBigS8::TM == AdjBigS::TM && AdjBigS8::TN == AdjBigS::TN, "tile shapes must agree");
-  if (a.bf16 == 2) {
-    if (a.mode == STEP_RELAX && std::is_same<CS, AdjBigS>::value)
-      hipLaunchKernelGGL((adj_step_kernel_bf16<AdjBigS8, STEP_RELAX>), grid, dim3(AdjBigS8::NT), 0,
-                         s, a);
-    else if (a.mode == STEP_RELAX)
-      hipLaunchKernelGGL((adj_step_kernel_bf16<CS, STEP_RELAX>), grid, block, 0, s, a);
-    else
-      hipLaunchKernelGGL((adj_step_kernel_bf16<CS, STEP_RESID>), grid, block, 0, s, a);
-  } else if (a.bf16 && a.one_term) {
+  if (a.bf16 == 1 && a.one_term) {
     if (a.mode == STEP_RELAX)
       hipLaunchKernelGGL((adj_step_kernel_bf16<CF, STEP_RELAX>), grid, block, 0, s, a);
     else
       hipLaunchKernelGGL((adj_step_kernel_bf16<CF, STEP_RESID>), grid, block, 0, s, a);
-  } else if (a.bf16) {
+  } else if (a.bf16 == 1) {
     if (a.mode == STEP_RELAX)
       hipLaunchKernelGGL((adj_step_kernel_bf16<CB, STEP_RELAX>), grid, block, 0, s, a);
     else
@@ -661,8 +650,14 @@ hipError_t launch_adj_step(const AdjArgs& a, hipStream_t s) {
       launch_adj_skinny<2>(a, grid, s);
     else
       launch_adj_skinny<1>(a, grid, s);
-  } else if (tiles(AdjBig::TM, AdjBig::TN) >= (a.bf16 == 1 ? 256 : 384))
-    launch_adj_cfg<AdjBig, AdjBigB, AdjBigS, AdjBigF>(a, s);
+  } else if (tiles(AdjBig::TM, AdjBig::TN) >= (a.bf16 == 1 ? 256 : 384)) {
+    if (a.bf16 == 2 && a.mode == STEP_RELAX)
+      launch_adj_x3<AdjBigS8>(a, s);
+    else if (a.bf16 == 2)
+      launch_adj_x3<AdjBigS>(a, s);
+    else
+      launch_adj_cfg<AdjBig, AdjBigB, AdjBigF>(a, s);
+  }
   // three terms, by what fills the chip (us, 64 x 64 without the split : 64 x 128 : 64 x 64 split):
   // 3200 rows x 1000 (400 wide tiles) 247 : 179 : 207, 4096 x 1024 (512) 215 : 169 : 193,
   // 4096 x 512 (256) 65 : 69 : 56, 1024 x 1024 (256 tiles of 64 x 64) 101 : 121 : 75, 800 x 1000 (208)
@@ -672,9 +667,9 @@ hipError_t launch_adj_step(const AdjArgs& a, hipStream_t s) {
   else if (a.bf16 == 2 && R > 32 && tiles(AdjMidS::TM, AdjMidS::TN) >= 192)
     launch_adj_x3<AdjMidS>(a, s);
   else if (R > 32 && tiles(AdjMid::TM, AdjMid::TN) >= 256)
-    launch_adj_cfg<AdjMid, AdjMidB, AdjMidS, AdjMidF>(a, s);
-  else
-    launch_adj_cfg<AdjSmall, AdjSmallB, AdjSmallS, AdjSmallF>(a, s);
+    launch_adj_cfg<AdjMid, AdjMidB, AdjMidF>(a, s);
+  else   // (three terms included: 32 x 32 tiles are faster in fp32, see launch_phi_cfg)
+    launch_adj_cfg<AdjSmall, AdjSmallB, AdjSmallF>(a, s);
   prof_end(kind, 6.0 * (double)R * a.H * a.H, 28.0 * (double)R * a.H, s);
   return hipGetLastError();
 }

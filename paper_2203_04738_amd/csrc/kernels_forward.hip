@@ -730,7 +730,6 @@ typedef TileCfgB<2, 2, 1, 1, 3, true, 2, 1, 1, 1, 64, false> PhiMidFK;
 // three-term operands: K-slices of 32 keep two workgroups' tiles in a CU's LDS
 typedef TileCfgB<2, 2, 2, 1, 3, true, 1, 1, 2, 3, 32> PhiBigS;
 typedef TileCfgB<2, 2, 1, 1, 3, true, 1, 1, 2, 3, 32> PhiMidS;
-typedef TileCfgB<1, 1, 1, 1, 3, true, 4, 1, 2, 3, 32> PhiSmallS;
 // 64 x 32 with two groups of two waves splitting K, where 64 x 64 tiles leave CUs half empty (us, 64 x
 // 64 : this): 1024 rows x 1024 (256 tiles of 64 x 64) 64 : 50, 800 x 1000 (208) 66 : 53, 4096 x 256
 // (256) 19.6 : 16.7, but 4096 x 512 (512) 50 : 58
@@ -769,19 +768,29 @@ typedef TileCfgB<2, 1, 1, 1, 3, true, 2, 1, 2, 3, 32> PhiNarrowS;
       hipLaunchKernelGGL((KERNEL<__VA_ARGS__, STEP_KAPPA>), grid, block, 0, s, a);       \
   }
 
+template <class CS>
+static void launch_phi_x3(const PhiArgs& a, hipStream_t s) {
+  const long long R = (long long)a.nk * a.B;
+  dim3 grid((unsigned)xcd_grid((R + CS::TM - 1) / CS::TM, (a.H + CS::TN - 1) / CS::TN));
+  dim3 block(CS::NT);
+  MG_LAUNCH_BY_MODE(phi_step_kernel_bf16, CS)
+}
+
+// CS: tile of the three-term form; void: such a launch runs on the fp32 tile (the 32 x 32 tiles of
+// the smallest launches: a training step of 128 x 100 x 1000, whose serial steps are such launches,
+// takes 7.27 ms with them in fp32 and 7.51 with terms, 256 x 65 x 184 2.45 and 2.67)
 template <class C, class CB, class CS, class CF>
 static void launch_phi_cfg(const PhiArgs& a, hipStream_t s) {
   const long long R = (long long)a.nk * a.B;
   static_assert(CF::TM == CB::TM && CF::TN == CB::TN, "tile shapes must agree");
-  if (a.bf16 == 2) {
-    dim3 grid((unsigned)xcd_grid((R + CS::TM - 1) / CS::TM, (a.H + CS::TN - 1) / CS::TN));
-    dim3 block(CS::NT);
-    MG_LAUNCH_BY_MODE(phi_step_kernel_bf16, CS)
-  } else if (a.bf16 && a.one_term) {
+  if constexpr (!std::is_void<CS>::value) {
+    if (a.bf16 == 2) return launch_phi_x3<CS>(a, s);
+  }
+  if (a.bf16 == 1 && a.one_term) {
     dim3 grid((unsigned)xcd_grid((R + CF::TM - 1) / CF::TM, (a.H + CF::TN - 1) / CF::TN));
     dim3 block(CF::NT);
     MG_LAUNCH_BY_MODE(phi_step_kernel_bf16, CF)
-  } else if (a.bf16) {
+  } else if (a.bf16 == 1) {
     dim3 grid((unsigned)xcd_grid((R + CB::TM - 1) / CB::TM, (a.H + CB::TN - 1) / CB::TN));
     dim3 block(CB::NT);
     MG_LAUNCH_BY_MODE(phi_step_kernel_bf16, CB)
@@ -790,14 +799,6 @@ static void launch_phi_cfg(const PhiArgs& a, hipStream_t s) {
     dim3 block(C::NT);
     MG_LAUNCH_BY_MODE(phi_step_kernel, C)
   }
-}
-
-template <class CS>
-static void launch_phi_x3(const PhiArgs& a, hipStream_t s) {
-  const long long R = (long long)a.nk * a.B;
-  dim3 grid((unsigned)xcd_grid((R + CS::TM - 1) / CS::TM, (a.H + CS::TN - 1) / CS::TN));
-  dim3 block(CS::NT);
-  MG_LAUNCH_BY_MODE(phi_step_kernel_bf16, CS)
 }
 
 constexpr int PHI_SK_ROWS = 32;   // rows per workgroup of the few-row forward step
@@ -906,7 +907,7 @@ hipError_t launch_phi_step(const PhiArgs& a, hipStream_t s) {
       launch_phi_cfg<PhiMid, PhiMidB, PhiMidS, PhiMidF>(a, s);
   } else {
     contracted(PhiSmall::TM);
-    launch_phi_cfg<PhiSmall, PhiSmallB, PhiSmallS, PhiSmallF>(a, s);
+    launch_phi_cfg<PhiSmall, PhiSmallB, void, PhiSmallF>(a, s);
   }
   prof_end(kind, 6.0 * (double)rows_done * a.H * a.H, 20.0 * (double)R * a.H, s);
   return hipGetLastError();
