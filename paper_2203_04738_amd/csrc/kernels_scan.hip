@@ -34,6 +34,7 @@
 // marked as given up, every workgroup leaves, and scan_repair_kernel, launched behind every solve,
 // does it row by row without any communication (slow, but it needs no residency); otherwise that
 // kernel returns at once.
+#include <atomic>
 #include <cstdlib>
 
 #include "gates.h"
@@ -46,7 +47,7 @@ namespace mg {
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 constexpr unsigned SENTINEL = 0xffffffffu;
 constexpr int SCAN_MAXW = 8;                 // waves per workgroup
-constexpr int SCAN_MAXWG = 256;              // workgroups of a solve: one per CU
+constexpr int SCAN_MAXWG = 256;              // workgroups of a solve at most (one per CU)
 constexpr int SCAN_CP = 16;                  // hidden columns per workgroup
 constexpr long long SCAN_ARRIVE_TICKS = 500000;      // 5 ms of the 100 MHz clock
 constexpr long long SCAN_STEP_TICKS = 200000000;     // 2 s: bound of a single wait
@@ -454,14 +455,29 @@ __global__ __launch_bounds__(1024) void scan_repair_kernel(ScanArgs a) {
 struct ScanShape {
   int nch, nw, rb, nrb, ncg;
 };
+// Workgroups that can be resident whatever the kernel's registers: one per CU of the current device
+// (a partition of the GPU has fewer than the whole).
+static int scan_max_wg() {
+  constexpr int MAX_DEV = 64;
+  static std::atomic<int> cus[MAX_DEV];                // 0: not asked yet
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEV) return 0;
+  int n = cus[dev].load(std::memory_order_relaxed);
+  if (n == 0) {
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    cus[dev].store(n, std::memory_order_relaxed);
+  }
+  return n < SCAN_MAXWG ? n : SCAN_MAXWG;
+}
 static ScanShape scan_shape(int B, int H) {
+  const int max_wg = scan_max_wg();
   ScanShape s;
   s.nch = H > 64 * SCAN_MAXW ? 2 : 1;
   s.nw = (H + 64 * s.nch - 1) / (64 * s.nch);
   s.ncg = (H + SCAN_CP - 1) / SCAN_CP;
   const int quads = (B + 3) / 4;
   s.rb = 1;
-  while (s.rb < 8 && (quads + s.rb - 1) / s.rb * s.ncg > SCAN_MAXWG) s.rb *= 2;
+  while (s.rb < 8 && (quads + s.rb - 1) / s.rb * s.ncg > max_wg) s.rb *= 2;
   s.nrb = (quads + s.rb - 1) / s.rb;
   if (s.nw < s.rb) s.nw = s.rb;                       // wave r finishes row group r
   return s;
@@ -475,7 +491,7 @@ bool scan_covers(int kind, long long N, int B, int H) {
   const ScanShape s = scan_shape(B, H);
   // registers: the adjoint holds three coefficient rows per state row, the LSTM four gates
   const int limit = kind == SCAN_ADJOINT && s.nch == 2 ? 2 : 4;
-  return s.rb <= limit && s.nrb * s.ncg <= SCAN_MAXWG;
+  return s.rb <= limit && s.nrb * s.ncg <= scan_max_wg();
 }
 
 template <int KIND, class WT>
