@@ -27,13 +27,19 @@
 // 1.3 us of exchange, 0.3 us of MFMAs, the rest LDS sums and gates).  A ninth wave that takes the
 // epilogue off the polling waves is slower (15.3 ms).
 //
-// Residency.  All workgroups have to be resident at once.  Each announces itself and waits, with
-// a time limit, until all have arrived before it takes the first step; the grid is limited to one
-// workgroup per CU, and after the arrival only data another resident workgroup is about to write is
-// waited for.  If the limit passes (the GPU is shared with other resident work), the solve is
-// marked as given up, every workgroup leaves, and scan_repair_kernel, launched behind every solve,
-// does it row by row without any communication (slow, but it needs no residency); otherwise that
-// kernel returns at once.
+// Residency.  Each workgroup keeps its columns for the whole solve, which needs all of them resident
+// at once: each announces itself and waits, with a time limit, until all have arrived before it takes
+// the first step (the grid is limited to one workgroup per CU).  If the limit passes (other work holds
+// CUs: two more solves on other streams, say), every workgroup leaves, and the launch behind takes the
+// solve over, which returns at once otherwise.  There a workgroup takes one (step, columns, rows) item
+// after the other from a counter.  An item waits only for items with smaller numbers, and those are
+// held by workgroups that run, so any number of resident workgroups gets through.  The weights are
+// loaded again for every item.  The arithmetic of an element is the same code on the same operands, so
+// the results do not depend on which launch computes them, bit for bit; an element both have computed
+// is written twice with one value.  Measured with the takeover forced (chain of step launches : this :
+// all resident, us per step): 8 x 1024 bf16 5.9 : 8.5 : 3.1, 64 x 1024 17.6 : 12.4 : 10.0, 3 x 500 4.1 :
+// 3.6 : 2.1, 16 x 256 4.0 : 3.8 : 1.6, LSTM 32 x 512 5.2 : 6.7 : 3.0; three streams at once, ms: bptt of
+// 256 x 32 x 1024 24.0 : 23.4, scans of 256 x 64 x 1024 9.8 : 11.5, LSTM 512 x 32 x 512 6.3 : 9.2.
 #include <atomic>
 #include <cstdlib>
 
@@ -49,8 +55,12 @@ constexpr unsigned SENTINEL = 0xffffffffu;
 constexpr int SCAN_MAXW = 8;                 // waves per workgroup
 constexpr int SCAN_MAXWG = 256;              // workgroups of a solve at most (one per CU)
 constexpr int SCAN_CP = 16;                  // hidden columns per workgroup
-constexpr long long SCAN_ARRIVE_TICKS = 500000;      // 5 ms of the 100 MHz clock
-constexpr long long SCAN_STEP_TICKS = 200000000;     // 2 s: bound of a single wait
+// Limit of the wait for all workgroups, in ticks of the 100 MHz clock: half a microsecond per step (a
+// quarter of the solve), 50 us (several times what an arrival on a free GPU takes) to 5 ms.
+constexpr long long SCAN_ARRIVE_PER_STEP = 50, SCAN_ARRIVE_MIN = 5000, SCAN_ARRIVE_MAX = 500000;
+constexpr long long SCAN_STEP_TICKS = 200000000;     // 2 s: bound of a single wait, all resident
+constexpr int SCAN_MAX_POLLS = 1 << 24;              // the same, items from the counter (counted in
+                                                     // polls: a GPU that is taken away counts none)
 
 template <int KIND>
 struct ScanGates {
@@ -100,14 +110,29 @@ __device__ inline const float* scan_uniform(const float* p) {
 __device__ inline int ctl_load(const int* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// next item of a solve whose workgroups are not all resident
+__device__ inline long long ctl_take(int* ctl) {
+  return (long long)__hip_atomic_fetch_add((unsigned long long*)(ctl + 2), 1ULL, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+}
+// One element of a state row that another workgroup may still be writing.
+__device__ inline float scan_own(const float* p) {
+  unsigned b = SENTINEL;
+  for (int polls = 0; b == SENTINEL && polls < SCAN_MAX_POLLS; ++polls)
+    b = __hip_atomic_load((const unsigned*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __uint_as_float(b);
+}
 __device__ inline long long ticks() { return (long long)__builtin_amdgcn_s_memrealtime(); }
 
+// A result that happens to be the sentinel (a NaN) is stored as another NaN.
+__device__ inline unsigned scan_bits(float val) {
+  const unsigned b = __float_as_uint(val);
+  return b == SENTINEL ? 0x7fc00000u : b;
+}
 // Column l % 16 of quad column 0 gathers its quad: lanes with l % 4 == 0 hold four consecutive
-// columns of a row and store them as one 16-byte access at agent scope.  A result that happens to
-// be the sentinel (a NaN) is stored as another NaN.
+// columns of a row and store them as one 16-byte access at agent scope.
 __device__ inline void scan_store(float* p, float val, bool ok) {
-  unsigned b = __float_as_uint(val);
-  b = b == SENTINEL ? 0x7fc00000u : b;
+  const unsigned b = scan_bits(val);
   uintx4 v;
   v[0] = b;
   v[1] = __builtin_amdgcn_mov_dpp(b, 0x55, 0xf, 0xf, true);   // quad_perm [1,1,1,1]
@@ -119,7 +144,10 @@ __device__ inline void scan_store(float* p, float val, bool ok) {
 
 // NCH: chunks of 64 k per wave; RB: groups of four rows per workgroup.  Registers: NG 16 NCH
 // weights; one workgroup per CU is planned for (two waves per SIMD at eight waves).
-template <int KIND, int NCH, int RB, class WT>
+// ITEMS: the workgroup takes (step, unit) items from the counter until none are left; otherwise it
+// takes every step of the unit it was launched as, once all workgroups of the solve are resident, and
+// leaves what remains to the launch with ITEMS behind it if they are not (see the top of the file).
+template <int KIND, int NCH, int RB, class WT, bool ITEMS>
 __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int nrb) {
   constexpr int NG = ScanGates<KIND>::value;
   constexpr bool ADJ = KIND == SCAN_ADJOINT;
@@ -128,325 +156,288 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
   constexpr int NP = RB * NG == 1 ? 2 : 1;            // sums per gate and row group
   __shared__ float part[2][SCAN_MAXW][RB][NS][64];
   __shared__ int stop[2];
+  __shared__ long long item;
   const int H = a.H, B = a.B, N = a.N;
   const int W = KIND == SCAN_LSTM ? 2 * H : H;        // state row
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6;
-  const int rb = blockIdx.x % nrb, cg = blockIdx.x / nrb;
-  const int r0 = rb * RB * 4, j0 = cg * SCAN_CP;
+  const int nwg = gridDim.x;
   const int kw0 = wv * 64 * NCH;                      // K slice of this wave
-
-  // weights: column j0 + lane % 16, k = kw0 + 64 c + 16 (lane / 16) + 0..15 (zero beyond H; columns
-  // beyond H repeat the last one and are never stored)
-  float w[NG][NCH][16];
-  {
-    const int j = min(j0 + (lane & 15), H - 1);
-#pragma unroll
-    for (int g = 0; g < NG; ++g)
-#pragma unroll
-      for (int c = 0; c < NCH; ++c)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int k = kw0 + 64 * c + 16 * (lane >> 4) + 4 * q;
-          const int kc = min(k, H - 4);               // H is a multiple of 4
-          const WT* p = (const WT*)a.Wt +
-                        (ADJ ? (long long)j * 3 * H + g * H + kc : ((long long)g * H + j) * H + kc);
-          const floatx4 v = k < H ? ldg4w(p) : zero4();
-#pragma unroll
-          for (int e = 0; e < 4; ++e) w[g][c][4 * q + e] = v[e];
-        }
-  }
-  // polled operand: rows r0 + 4 r + lane % 4, k = kw0 + 64 c + 4 (lane / 4) + 0..3; lanes beyond
-  // the rows or columns read a valid place and contribute nothing
-  unsigned off[NL];
-  bool live[NCH];
-  unsigned koff[ADJ ? RB : 1];
-  int kk[NCH];
-#pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int k = kw0 + 64 * c + 4 * (lane >> 2);
-    live[c] = k < H;
-    kk[c] = min(k, H - 4);
-  }
-#pragma unroll
-  for (int r = 0; r < RB; ++r) {
-    const int row = min(r0 + 4 * r + (lane & 3), B - 1);
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) off[r * NCH + c] = ((unsigned)row * W + kk[c]) * 4u;
-    if (ADJ) koff[r] = (unsigned)row * a.kw;
-  }
-  // output element of this lane: wave r finishes row group r
-  const bool epi = wv < RB;
-  const int orow = r0 + 4 * wv + quad_row(lane), oj = j0 + (lane & 15);
-  const bool ok = epi && orow < B && oj < H;
-  const int er = min(orow, B - 1), ej = min(oj, H - 1);
-  const long long eo = (long long)er * W + ej;
-  float bias[NG];
-#pragma unroll
-  for (int g = 0; g < NG; ++g)
-    bias[g] = (KIND == SCAN_GRU || KIND == SCAN_LSTM) ? a.b_h[g * H + ej] : 0.f;
-
-  // all workgroups of the solve are resident before the first step
-  if (tid < 2) stop[tid] = 0;
-  __syncthreads();
-  if (tid == 0) {
-    const int nwg = gridDim.x;
-    __hip_atomic_fetch_add(a.ctl, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const long long t0 = ticks();
-    while (ctl_load(a.ctl) < nwg) {
-      if (ctl_load(a.ctl + 1) != 0 || ticks() - t0 > a.wait_ticks) {
-        __hip_atomic_store(a.ctl + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        stop[0] = 1;
-        break;
-      }
-      __builtin_amdgcn_s_sleep(2);
-    }
-  }
-  __syncthreads();
-  if (stop[0]) return;
-  __syncthreads();
-
+  const bool epi = wv < RB;                           // wave r finishes row group r
   // points: forward step i = 0..N-1 goes from point i to i + 1, adjoint from N - i to N - i - 1
   const long long BW = (long long)B * W;
   auto in_pt = [&](int i) { return (long long)(ADJ ? N - i : i); };
   auto out_pt = [&](int i) { return (long long)(ADJ ? N - i - 1 : i + 1); };
 
-  float prev = 0.f, prevc = 0.f;                       // own state element of the input point
-  if (epi) {
-    prev = a.u[in_pt(0) * BW + eo];
-    if (KIND == SCAN_LSTM) prevc = a.u[in_pt(0) * BW + eo + H];
+  long long mine = 0;                                 // thread 0: the item after the current one
+  int unit = blockIdx.x, first = 0, last = N;
+  if (ITEMS) {
+    if (ctl_load(a.ctl + 1) == 0) return;             // all were resident: the solve is done
+    if (tid == 0) mine = ctl_take(a.ctl);
   }
-  // operands that do not depend on the state, requested one step ahead
-  float ep[NG], eg = 0.f, egc = 0.f, ekd = 0.f;
-  floatx4 kv[ADJ ? RB : 1][ADJ ? NG : 1][NCH];
-  auto request = [&](int i) {
-    if (ADJ) {
-      const float* kr = a.kap + in_pt(i) * B * a.kw;
+  if (tid < 2) stop[tid] = 0;
+
+  do {
+    if (ITEMS) {
+      // one barrier between the items, which also keeps part apart: its readers are through
+      if (tid == 0) item = mine;
+      __syncthreads();
+      const long long t = item;
+      if (t >= (long long)N * nwg) return;
+      if (tid == 0) mine = ctl_take(a.ctl);           // (arrives behind this item's work)
+      first = (int)(t / nwg);
+      unit = (int)(t % nwg);
+      last = first + 1;
+    }
+    const int rb = unit % nrb, cg = unit / nrb;
+    const int r0 = rb * RB * 4, j0 = cg * SCAN_CP;
+    // weights: column j0 + lane % 16, k = kw0 + 64 c + 16 (lane / 16) + 0..15 (zero beyond H; columns
+    // beyond H repeat the last one and are never stored)
+    float w[NG][NCH][16];
+    {
+      const int j = min(j0 + (lane & 15), H - 1);
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int k = kw0 + 64 * c + 16 * (lane >> 4) + 4 * q;
+            const int kc = min(k, H - 4);             // H is a multiple of 4
+            const WT* p = (const WT*)a.Wt +
+                          (ADJ ? (long long)j * 3 * H + g * H + kc : ((long long)g * H + j) * H + kc);
+            const floatx4 v = k < H ? ldg4w(p) : zero4();
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[g][c][4 * q + e] = v[e];
+          }
+    }
+    // polled operand: rows r0 + 4 r + lane % 4, k = kw0 + 64 c + 4 (lane / 4) + 0..3; lanes beyond
+    // the rows or columns read a valid place and contribute nothing
+    unsigned off[NL];
+    bool live[NCH];
+    unsigned koff[ADJ ? RB : 1];
+    int kk[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      const int k = kw0 + 64 * c + 4 * (lane >> 2);
+      live[c] = k < H;
+      kk[c] = min(k, H - 4);
+    }
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+      const int row = min(r0 + 4 * r + (lane & 3), B - 1);
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) off[r * NCH + c] = ((unsigned)row * W + kk[c]) * 4u;
+      if (ADJ) koff[r] = (unsigned)row * a.kw;
+    }
+    // output element of this lane
+    const int orow = r0 + 4 * wv + quad_row(lane), oj = j0 + (lane & 15);
+    const bool ok = epi && orow < B && oj < H;
+    const int er = min(orow, B - 1), ej = min(oj, H - 1);
+    const long long eo = (long long)er * W + ej;
+    float bias[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+      bias[g] = (KIND == SCAN_GRU || KIND == SCAN_LSTM) ? a.b_h[g * H + ej] : 0.f;
+
+    if (!ITEMS) {   // all workgroups of the solve are resident before the first step
+      __syncthreads();
+      if (tid == 0) {
+        __hip_atomic_fetch_add(a.ctl, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const long long t0 = ticks();
+        while (true) {
+          bool leave = ctl_load(a.ctl + 1) != 0;
+          if (!leave && ticks() - t0 >= a.wait_ticks) {
+            __hip_atomic_store(a.ctl + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            leave = true;
+          }
+          if (leave) {
+            stop[0] = 1;
+            break;
+          }
+          if (ctl_load(a.ctl) >= nwg) break;
+          __builtin_amdgcn_s_sleep(2);
+        }
+      }
+      __syncthreads();
+      if (stop[0]) return;
+      __syncthreads();
+    }
+
+    // operands that do not depend on the state, requested one step ahead
+    float ep[NG], eg = 0.f, egc = 0.f, ekd = 0.f;
+    floatx4 kv[ADJ ? RB : 1][ADJ ? NG : 1][NCH];
+    auto request = [&](int i) {
+      if (ADJ) {
+        const float* kr = a.kap + in_pt(i) * B * a.kw;
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+          for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int c = 0; c < NCH; ++c)
+              kv[ADJ ? r : 0][ADJ ? g : 0][c] = ldg4(kr + koff[ADJ ? r : 0] + g * H + kk[c]);
+        if (epi) ekd = kr[(long long)er * a.kw + 3 * H + ej];
+      } else if (epi) {
+        const float* pr =
+            a.P + (((long long)(i + 1) * a.pstep - 1) * B + er) * ((long long)NG * H) + ej;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) ep[g] = pr[g * H];
+      }
+      if (epi && a.g) {
+        eg = a.g[out_pt(i) * BW + eo];
+        if (KIND == SCAN_LSTM) egc = a.g[out_pt(i) * BW + eo + H];
+      }
+    };
+    request(first);
+    float prev = 0.f, prevc = 0.f;                     // own state element of the input point
+    if (epi) {
+      const float* p = a.u + in_pt(first) * BW + eo;
+      prev = first > 0 ? scan_own(p) : *p;
+      if (KIND == SCAN_LSTM) prevc = first > 0 ? scan_own(p + H) : p[H];
+    }
+
+    for (int i = first; i < last; ++i) {
+      const int buf = i & 1;
+      uintx4 v[NL];
+      const float* src = scan_uniform(a.u + in_pt(i) * BW);
+      scan_load(v, src, off);
+      if (i > 0) {
+        int polls = 0;
+        long long t0 = 0;
+        while (true) {
+          bool wait = false;
+#pragma unroll
+          for (int q = 0; q < NL; ++q)
+            wait |= v[q][0] == SENTINEL || v[q][1] == SENTINEL || v[q][2] == SENTINEL ||
+                    v[q][3] == SENTINEL;
+          if (!__any(wait)) break;
+          if ((++polls & 127) == 0) {
+            bool leave;
+            if (ITEMS) {
+              leave = polls >= SCAN_MAX_POLLS;
+            } else {
+              if (t0 == 0) t0 = ticks();
+              leave = ticks() - t0 > SCAN_STEP_TICKS;
+              if (leave)
+                __hip_atomic_store(a.ctl + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              leave |= ctl_load(a.ctl + 1) != 0;
+            }
+            if (leave) {
+              stop[buf] = 1;
+              break;
+            }
+          }
+          scan_load(v, src, off);
+        }
+      }
+      // operands of the contraction; those of the next step are requested as soon as these are
+      // formed, so that they arrive behind the contraction and the exchange
+      floatx4 op[NCH][RB][ADJ ? NG : 1];
+#pragma unroll
+      for (int c = 0; c < NCH; ++c)
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+          const floatx4 h = __builtin_bit_cast(floatx4, v[r * NCH + c]);
+#pragma unroll
+          for (int g = 0; g < (ADJ ? NG : 1); ++g)
+            op[c][r][g] = live[c] ? (ADJ ? kv[ADJ ? r : 0][g][c] * h : h) : zero4();
+        }
+      float cp[NG];
+#pragma unroll
+      for (int g = 0; g < NG; ++g) cp[g] = ep[g];
+      const float cgv = eg, cgc = egc, ckd = ekd;
+      if (i + 1 < last) request(i + 1);
+      floatx4 acc[RB][NG][NP];
 #pragma unroll
       for (int r = 0; r < RB; ++r)
 #pragma unroll
         for (int g = 0; g < NG; ++g)
 #pragma unroll
-          for (int c = 0; c < NCH; ++c) kv[ADJ ? r : 0][ADJ ? g : 0][c] = ldg4(kr + koff[ADJ ? r : 0] + g * H + kk[c]);
-      if (epi) ekd = kr[(long long)er * a.kw + 3 * H + ej];
-    } else if (epi) {
-      const float* pr = a.P + (((long long)(i + 1) * a.pstep - 1) * B + er) * ((long long)NG * H) + ej;
+          for (int q = 0; q < NP; ++q) acc[r][g][q] = zero4();
 #pragma unroll
-      for (int g = 0; g < NG; ++g) ep[g] = pr[g * H];
-    }
-    if (epi && a.g) {
-      eg = a.g[out_pt(i) * BW + eo];
-      if (KIND == SCAN_LSTM) egc = a.g[out_pt(i) * BW + eo + H];
-    }
-  };
-  request(0);
-
-  for (int i = 0; i < N; ++i) {
-    const int buf = i & 1;
-    uintx4 v[NL];
-    const float* src = scan_uniform(a.u + in_pt(i) * BW);
-    scan_load(v, src, off);
-    if (i > 0) {
-      int polls = 0;
-      long long t0 = 0;
-      while (true) {
-        bool wait = false;
-#pragma unroll
-        for (int q = 0; q < NL; ++q)
-          wait |= v[q][0] == SENTINEL || v[q][1] == SENTINEL || v[q][2] == SENTINEL ||
-                  v[q][3] == SENTINEL;
-        if (!__any(wait)) break;
-        if ((++polls & 127) == 0) {
-          if (t0 == 0) t0 = ticks();
-          const bool late = ticks() - t0 > SCAN_STEP_TICKS;
-          if (late) __hip_atomic_store(a.ctl + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if (late || ctl_load(a.ctl + 1) != 0) {
-            stop[buf] = 1;
-            break;
-          }
-        }
-        scan_load(v, src, off);
-      }
-    }
-    // operands of the contraction; those of the next step are requested as soon as these are
-    // formed, so that they arrive behind the contraction and the exchange
-    floatx4 op[NCH][RB][ADJ ? NG : 1];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c)
+      for (int c = 0; c < NCH; ++c)
+        quad_mma<RB, NG, NP>(acc, [&](int r, int g) { return op[c][r][ADJ ? g : 0]; },
+                             [&](int g) -> const float (&)[16] { return w[g][c]; });
 #pragma unroll
       for (int r = 0; r < RB; ++r) {
-        const floatx4 h = __builtin_bit_cast(floatx4, v[r * NCH + c]);
+        floatx4 sum[NG];
 #pragma unroll
-        for (int g = 0; g < (ADJ ? NG : 1); ++g)
-          op[c][r][g] = live[c] ? (ADJ ? kv[ADJ ? r : 0][g][c] * h : h) : zero4();
-      }
-    float cp[NG];
-#pragma unroll
-    for (int g = 0; g < NG; ++g) cp[g] = ep[g];
-    const float cgv = eg, cgc = egc, ckd = ekd;
-    if (i + 1 < N) request(i + 1);
-    floatx4 acc[RB][NG][NP];
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-#pragma unroll
-      for (int g = 0; g < NG; ++g)
-#pragma unroll
-        for (int q = 0; q < NP; ++q) acc[r][g][q] = zero4();
-#pragma unroll
-    for (int c = 0; c < NCH; ++c)
-      quad_mma<RB, NG, NP>(acc, [&](int r, int g) { return op[c][r][ADJ ? g : 0]; },
-                           [&](int g) -> const float (&)[16] { return w[g][c]; });
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      floatx4 sum[NG];
-#pragma unroll
-      for (int g = 0; g < NG; ++g) sum[g] = NP > 1 ? acc[r][g][0] + acc[r][g][NP - 1] : acc[r][g][0];
-      if (ADJ) {
-        part[buf][wv][r][0][lane] = quad_fold(sum[0] + sum[NG > 1 ? 1 : 0] + sum[NG - 1]);
-      } else {
-#pragma unroll
-        for (int g = 0; g < NG; ++g) part[buf][wv][r][ADJ ? 0 : g][lane] = quad_fold(sum[g]);
-      }
-    }
-    __syncthreads();
-    const int stopped = stop[buf];
-    if (epi) {
-      // partial sums of all waves (every read in flight before the first addition)
-      float s[NS], ps[NS][SCAN_MAXW];
-#pragma unroll
-      for (int g = 0; g < NS; ++g)
-#pragma unroll
-        for (int q = 0; q < SCAN_MAXW; ++q) ps[g][q] = part[buf][q < nw ? q : 0][wv][g][lane];
-      if (stopped) return;
-#pragma unroll
-      for (int g = 0; g < NS; ++g) {
-#pragma unroll
-        for (int q = 0; q < SCAN_MAXW; ++q) ps[g][q] = q < nw ? ps[g][q] : 0.f;
-        s[g] = ((ps[g][0] + ps[g][1]) + (ps[g][2] + ps[g][3])) +
-               ((ps[g][4] + ps[g][5]) + (ps[g][6] + ps[g][7]));
-      }
-      float out, outc = 0.f;
-      if constexpr (KIND == SCAN_GRU) {
-        const float rg = sigmoidf_(cp[0] + s[0] + bias[0]);
-        const float zg = sigmoidf_(cp[1] + s[1] + bias[1]);
-        const float n = tanhf_(cp[2] + rg * (s[2] + bias[2]));
-        const float c = a.gamma * (1.0f - zg);
-        out = a.implicit_ ? (prev + c * n) * fast_rcp(1.0f + c) : prev + c * (n - prev);
-      } else if constexpr (KIND == SCAN_LSTM) {
-        const float ig = sigmoidf_(s[0] + cp[0] + bias[0]);
-        const float fg = sigmoidf_(s[1] + cp[1] + bias[1]);
-        const float gg = tanhf_(s[2] + cp[2] + bias[2]);
-        const float og = sigmoidf_(s[3] + cp[3] + bias[3]);
-        if (a.implicit_) {
-          outc = (prevc + a.gamma * ig * gg) * fast_rcp(1.0f + a.gamma * (1.0f - fg));
-          out = (prev + a.gamma * og * tanhf_(outc)) * fast_rcp(1.0f + a.gamma);
+        for (int g = 0; g < NG; ++g)
+          sum[g] = NP > 1 ? acc[r][g][0] + acc[r][g][NP - 1] : acc[r][g][0];
+        if (ADJ) {
+          part[buf][wv][r][0][lane] = quad_fold(sum[0] + sum[NG > 1 ? 1 : 0] + sum[NG - 1]);
         } else {
-          outc = prevc + a.gamma * (ig * gg - (1.0f - fg) * prevc);
-          out = prev + a.gamma * (og * tanhf_(outc) - prev);
+#pragma unroll
+          for (int g = 0; g < NG; ++g) part[buf][wv][r][ADJ ? 0 : g][lane] = quad_fold(sum[g]);
         }
-        outc += cgc;
-      } else if constexpr (KIND == SCAN_ODE) {
-        out = prev + a.gamma * (sigmoidf_(s[0] + cp[0]) - 0.5f * prev);
-      } else {
-        out = ckd * prev + s[0];
       }
-      out += cgv;
-      float* dst = a.u + out_pt(i) * BW + eo;
-      scan_store(dst, out, ok);
-      if (KIND == SCAN_LSTM && ok) dst[H] = outc;
-      prev = out;
-      prevc = outc;
-    } else if (stopped) {
-      return;
+      __syncthreads();
+      const int stopped = stop[buf];
+      if (epi) {
+        // partial sums of all waves (every read in flight before the first addition)
+        float s[NS], ps[NS][SCAN_MAXW];
+#pragma unroll
+        for (int g = 0; g < NS; ++g)
+#pragma unroll
+          for (int q = 0; q < SCAN_MAXW; ++q) ps[g][q] = part[buf][q < nw ? q : 0][wv][g][lane];
+        if (stopped) return;
+#pragma unroll
+        for (int g = 0; g < NS; ++g) {
+#pragma unroll
+          for (int q = 0; q < SCAN_MAXW; ++q) ps[g][q] = q < nw ? ps[g][q] : 0.f;
+          s[g] = ((ps[g][0] + ps[g][1]) + (ps[g][2] + ps[g][3])) +
+                 ((ps[g][4] + ps[g][5]) + (ps[g][6] + ps[g][7]));
+        }
+        float out, outc = 0.f;
+        if constexpr (KIND == SCAN_GRU) {
+          const float rg = sigmoidf_(cp[0] + s[0] + bias[0]);
+          const float zg = sigmoidf_(cp[1] + s[1] + bias[1]);
+          const float n = tanhf_(cp[2] + rg * (s[2] + bias[2]));
+          const float c = a.gamma * (1.0f - zg);
+          out = a.implicit_ ? (prev + c * n) * fast_rcp(1.0f + c) : prev + c * (n - prev);
+        } else if constexpr (KIND == SCAN_LSTM) {
+          const float ig = sigmoidf_(s[0] + cp[0] + bias[0]);
+          const float fg = sigmoidf_(s[1] + cp[1] + bias[1]);
+          const float gg = tanhf_(s[2] + cp[2] + bias[2]);
+          const float og = sigmoidf_(s[3] + cp[3] + bias[3]);
+          if (a.implicit_) {
+            outc = (prevc + a.gamma * ig * gg) * fast_rcp(1.0f + a.gamma * (1.0f - fg));
+            out = (prev + a.gamma * og * tanhf_(outc)) * fast_rcp(1.0f + a.gamma);
+          } else {
+            outc = prevc + a.gamma * (ig * gg - (1.0f - fg) * prevc);
+            out = prev + a.gamma * (og * tanhf_(outc) - prev);
+          }
+          outc += cgc;
+        } else if constexpr (KIND == SCAN_ODE) {
+          out = prev + a.gamma * (sigmoidf_(s[0] + cp[0]) - 0.5f * prev);
+        } else {
+          out = ckd * prev + s[0];
+        }
+        out += cgv;
+        float* dst = a.u + out_pt(i) * BW + eo;
+        scan_store(dst, out, ok);
+        if (KIND == SCAN_LSTM && ok) {
+          if (ITEMS)                                   // (read by the workgroup of the next step)
+            __hip_atomic_store((unsigned*)dst + H, scan_bits(outc), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+          else
+            dst[H] = outc;
+        }
+        prev = out;
+        prevc = outc;
+      } else if (stopped) {
+        return;
+      }
     }
-  }
+  } while (ITEMS);
 }
 
 // Marks the points the solve will write and clears its control words.
 __global__ __launch_bounds__(256) void scan_mark_kernel(uintx4* p, long long n4, int* ctl) {
-  if (blockIdx.x == 0 && threadIdx.x < 2) ctl[threadIdx.x] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < 4) ctl[threadIdx.x] = 0;
   const uintx4 s = {SENTINEL, SENTINEL, SENTINEL, SENTINEL};
   for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n4; i += 256LL * gridDim.x)
     p[i] = s;
-}
-
-// The same solve for one row per workgroup, without communication between workgroups: runs only
-// if scan_kernel has given up (see above), from the first step on.
-template <int KIND, class WT>
-__global__ __launch_bounds__(1024) void scan_repair_kernel(ScanArgs a) {
-  constexpr int NG = ScanGates<KIND>::value;
-  constexpr bool ADJ = KIND == SCAN_ADJOINT;
-  extern __shared__ float sh[];                        // state row (adjoint: 3H products)
-  if (a.ctl[1] == 0) return;
-  const int H = a.H, B = a.B, N = a.N, b = blockIdx.x;
-  const int W = KIND == SCAN_LSTM ? 2 * H : H;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  for (int i = 0; i < N; ++i) {
-    const long long pin = ADJ ? N - i : i, pout = ADJ ? N - i - 1 : i + 1;
-    float* cur = a.u + (pin * B + b) * W;
-    float* nxt = a.u + (pout * B + b) * W;
-    const float* kr = ADJ ? a.kap + (pin * B + b) * (long long)a.kw : nullptr;
-    for (int k = threadIdx.x; k < H; k += blockDim.x) {
-      sh[k] = cur[k] * (ADJ ? kr[k] : 1.f);
-      if (ADJ) {
-        sh[H + k] = cur[k] * kr[H + k];
-        sh[2 * H + k] = cur[k] * kr[2 * H + k];
-      }
-    }
-    __syncthreads();
-    for (int j = wv; j < H; j += nw) {
-      float s[NG];
-#pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        const WT* row = (const WT*)a.Wt + (ADJ ? (long long)j * 3 * H + g * H : ((long long)g * H + j) * H);
-        const float* x = sh + (ADJ ? g * H : 0);
-        float t = 0.f;
-        for (int k = 4 * lane; k < H; k += 256) {
-          const floatx4 v = ldg4w(row + k);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) t = fmaf(v[e], x[k + e], t);
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
-        s[g] = t;
-      }
-      if (lane == 0) {
-        const float h = cur[j];
-        const float gv = a.g ? a.g[(pout * B + b) * W + j] : 0.f;
-        float out;
-        if constexpr (ADJ) {
-          out = kr[3 * H + j] * h + s[0] + s[NG > 1 ? 1 : 0] + s[NG - 1];
-        } else {
-          const float* pr = a.P + (((long long)(i + 1) * a.pstep - 1) * B + b) * ((long long)NG * H) + j;
-          if constexpr (KIND == SCAN_ODE) {
-            out = h + a.gamma * (sigmoidf_(s[0] + pr[0]) - 0.5f * h);
-          } else if constexpr (KIND == SCAN_GRU) {
-            const float rg = sigmoidf_(pr[0] + s[0] + a.b_h[j]);
-            const float zg = sigmoidf_(pr[H] + s[1] + a.b_h[H + j]);
-            const float n = tanhf_(pr[2 * H] + rg * (s[2] + a.b_h[2 * H + j]));
-            const float c = a.gamma * (1.0f - zg);
-            out = a.implicit_ ? (h + c * n) * fast_rcp(1.0f + c) : h + c * (n - h);
-          } else {
-            const float ig = sigmoidf_(s[0] + pr[0] + a.b_h[j]);
-            const float fg = sigmoidf_(s[1] + pr[H] + a.b_h[H + j]);
-            const float gg = tanhf_(s[2] + pr[2 * H] + a.b_h[2 * H + j]);
-            const float og = sigmoidf_(s[NG - 1] + pr[3 * H] + a.b_h[3 * H + j]);
-            const float c = cur[H + j];
-            float cn;
-            if (a.implicit_) {
-              cn = (c + a.gamma * ig * gg) * fast_rcp(1.0f + a.gamma * (1.0f - fg));
-              out = (h + a.gamma * og * tanhf_(cn)) * fast_rcp(1.0f + a.gamma);
-            } else {
-              cn = c + a.gamma * (ig * gg - (1.0f - fg) * c);
-              out = h + a.gamma * (og * tanhf_(cn) - h);
-            }
-            nxt[H + j] = cn + (a.g ? a.g[(pout * B + b) * W + H + j] : 0.f);
-          }
-        }
-        nxt[j] = out + gv;
-      }
-    }
-    __syncthreads();                                   // (orders the stores before the next step)
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -484,8 +475,8 @@ static ScanShape scan_shape(int B, int H) {
 }
 
 // Up to 64 rows (the few-row range of the step kernels) of 16 to 1024 columns.  A solve costs
-// three launches (mark, scan, repair) whatever its length: below eight steps the chain of step
-// launches is as fast.
+// three launches (mark, scan, items) whatever its length: below eight steps the chain of step launches
+// is as fast.
 bool scan_covers(int kind, long long N, int B, int H) {
   if (N < 8 || N > (1LL << 30) || B > 64 || H < 16 || H > 128 * SCAN_MAXW) return false;
   const ScanShape s = scan_shape(B, H);
@@ -494,13 +485,18 @@ bool scan_covers(int kind, long long N, int B, int H) {
   return s.rb <= limit && s.nrb * s.ncg <= scan_max_wg();
 }
 
+template <int KIND, int NCH, int RB, class WT>
+static void launch_scan_shape(const ScanArgs& a, dim3 grid, dim3 block, int nrb, hipStream_t st) {
+  hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT, false>), grid, block, 0, st, a, nrb);
+  hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT, true>), grid, block, 0, st, a, nrb);
+}
 template <int KIND, class WT>
 static void launch_scan_kind(const ScanArgs& a, hipStream_t st) {
   const ScanShape s = scan_shape(a.B, a.H);
   const dim3 grid((unsigned)(s.nrb * s.ncg)), block(64 * s.nw);
 #define MG_SCAN_CASE(NCH, RB)                                                                  \
   if (s.nch == NCH && s.rb == RB)                                                              \
-    hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT>), grid, block, 0, st, a, s.nrb);
+    launch_scan_shape<KIND, NCH, RB, WT>(a, grid, block, s.nrb, st);
   MG_SCAN_CASE(1, 1)
   MG_SCAN_CASE(1, 2)
   MG_SCAN_CASE(1, 4)
@@ -510,14 +506,14 @@ static void launch_scan_kind(const ScanArgs& a, hipStream_t st) {
     MG_SCAN_CASE(2, 4)
   }
 #undef MG_SCAN_CASE
-  const size_t lds = (size_t)(KIND == SCAN_ADJOINT ? 3 : 1) * a.H * sizeof(float);
-  hipLaunchKernelGGL((scan_repair_kernel<KIND, WT>), dim3(a.B), dim3(1024), lds, st, a);
 }
 
 hipError_t launch_scan(int kind, const ScanArgs& a0, hipStream_t st) {
   ScanArgs a = a0;
-  a.wait_ticks = SCAN_ARRIVE_TICKS;
-  // MGRIT_SCAN_WAIT_TICKS in the environment: another limit for the wait (tests use 0)
+  a.wait_ticks = a.N * SCAN_ARRIVE_PER_STEP;
+  if (a.wait_ticks < SCAN_ARRIVE_MIN) a.wait_ticks = SCAN_ARRIVE_MIN;
+  if (a.wait_ticks > SCAN_ARRIVE_MAX) a.wait_ticks = SCAN_ARRIVE_MAX;
+  // MGRIT_SCAN_WAIT_TICKS in the environment: another limit for the wait (tests use 0: no wait)
   if (const char* e = std::getenv("MGRIT_SCAN_WAIT_TICKS")) a.wait_ticks = std::atoll(e);
   const int W = kind == SCAN_LSTM ? 2 * a.H : a.H;
   const int prof = kind == SCAN_GRU ? 4 : kind == SCAN_ADJOINT ? 5 : kind == SCAN_LSTM ? 9 : 8;

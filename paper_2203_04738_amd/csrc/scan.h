@@ -16,7 +16,8 @@ struct ScanArgs {
   const float* kap;    // coefficient rows [N + 1, B, kw] (adjoint)
   float* u;            // state array [N + 1, B, H] (LSTM: [N + 1, B, 2H])
   const float* g;      // right-hand side, laid out like u (may be null)
-  int* ctl;            // device words: [0] workgroups that have arrived, [1] solve given up
+  int* ctl;            // four device words: [0] workgroups that have arrived, [1] not all came in time,
+                       // [2..3] (64 bits) next item
   int N, B, H, kw;
   long long pstep;     // forward: step k reads projection point k * pstep - 1
   float gamma;
