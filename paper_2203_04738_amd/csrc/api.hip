@@ -824,7 +824,11 @@ static int vcycle_bwd(const BwdCtx& x, int l, bool f_points_current = false,
       CHECK_HIP(launch_adj_sweep(a, (int)N, STEP_RELAX, STEP_RELAX, x.s));
       return MGRIT_OK;
     }
-    if (scan_covers(SCAN_ADJOINT, N, x.c->B, x.c->H)) {
+    // (the one-launch solve marks the rows it will write first, so a source term that shares memory
+    // with them, a caller's w formed in place of dL_dh, goes step by step)
+    const long long words = (N + 1) * x.c->B * x.c->H;
+    const bool in_place = x.gl[l] && x.gl[l] < x.wl[l] + words && x.wl[l] < x.gl[l] + words;
+    if (!in_place && scan_covers(SCAN_ADJOINT, N, x.c->B, x.c->H)) {
       ScanArgs a;
       std::memset(&a, 0, sizeof(a));
       a.Wt = x.UT;

@@ -147,6 +147,26 @@ def test_a_nan_with_every_bit_set_passes_through():
     assert torch.equal(h[:5, 1], clean[:5, 1])
 
 
+@pytest.mark.parametrize("B,H", [(3, 140), (70, 40)])
+def test_serial_adjoint_in_place_of_its_source_term(B, H):
+    # dL_dh and w_out may be one array: each source element is read before its row is written
+    d, t, cfg, ws, p = _gru(B, H, steps=24)
+    h = torch.empty(25, B, H, device=DEV)
+    mg.gru_serial_scan(cfg, *p, t["h0"], h, ws)
+    src = 0.1 * torch.randn(25, B, H, device=DEV, generator=torch.Generator(DEV).manual_seed(1))
+
+    def back(dL, w):
+        g = [torch.empty(3 * H, 8, device=DEV), torch.empty(3 * H, H, device=DEV),
+             torch.empty(3 * H, device=DEV), torch.empty(3 * H, device=DEV)]
+        dx = torch.empty(24, B, 8, device=DEV)
+        mg.gru_serial_scan_backward_steps(cfg, *p, h, dL, w, *g, dx, ws)
+        return w.cpu().numpy().astype(np.float64)
+
+    want = back(src, torch.full_like(src, 7.0))
+    both = src.clone()
+    assert _rel(torch.from_numpy(back(both, both)), want) <= 1e-5
+
+
 def test_solves_on_several_streams_at_once():
     runs = [_gru(32, 512, steps=64) for _ in range(3)]
     outs = [torch.empty(65, 32, 512, device=DEV) for _ in runs]
