@@ -161,8 +161,8 @@ hipError_t launch_input_grads(const float* kap0, const float* w, const void* WT,
                               float* dx, int T, int B, int D, int H, int bf16, int one_term,
                               hipStream_t s);
 
-// dst[t][i] (t = 0..2, bf16) = t-th term of src[i]: src = dst[0] + dst[1] + dst[2] exactly
-// unless a term underflows; n a multiple of 4
+// dst[t][i] (t = 0..2, bf16) = t-th term of 2^24 src[i] (exactly: see gemm_core_bf16.h); n a multiple
+// of 4
 hipError_t launch_split3(const float* src, void* dst, long long n, hipStream_t s);
 
 hipError_t launch_fill_f64(double* p, long long n, double v, hipStream_t s);

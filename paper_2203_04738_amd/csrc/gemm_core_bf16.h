@@ -15,7 +15,11 @@
 // products a_t * b_u with t + u <= 2 and drops the three of relative size 2^-24 and
 // below, so the fp32 accumulators receive what an fp32 product would have given them,
 // at the rate of the bf16 matrix pipe.  A is split on its way to LDS, B arrives already
-// split (three arrays, prepared once per call).
+// split (three arrays, prepared once per call).  Both are scaled by 2^24 before they are split and
+// the sums by 2^-48: bf16 has the exponents of fp32 and the last bit of a value lies 23 binary places
+// below its first, so without that the lower terms of values under 2^-102 would be subnormal and lost
+// (an adjoint of 1e-34 came out with 1e-5 instead of 1e-7).  Powers of two: nothing else changes.
+// Sums above 2^80 overflow that way and are contracted again in fp32 (see tile_not_finite).
 //
 // A lane supplies eight consecutive k of its row (one ds_read_b128) per MFMA, the
 // two half-waves taking k-offsets 0..7 and 8..15 of each group of sixteen; A and B
@@ -43,6 +47,8 @@ struct Bf16x8x3 {
 __device__ inline const bf16x8& operand_term(const bf16x8& v, int) { return v; }
 __device__ inline const bf16x8& operand_term(const Bf16x8x3& v, int u) { return v.p[u]; }
 
+constexpr float SPLIT3_SCALE = 0x1p24f, SPLIT3_UNSCALE = 0x1p-48f;
+// t0 + t1 + t2 = v: the caller has scaled v
 __device__ inline void split_bf16_3(const F32x8& v, bf16x8& t0, bf16x8& t1, bf16x8& t2) {
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
@@ -176,12 +182,9 @@ __device__ inline void gemm_nt_tile_bf16(Acc<C>& acc, int K, LoadA loadA, LoadB 
         bf16x8 t0, t1, t2;
         // odd tile rows enter with the opposite sign (see the end)
         F32x8 v = finA(ra[d][s]);
-        const unsigned sgn = (unsigned)((q / C::CPR) & 1) << 31;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          v.lo4[i] = __uint_as_float(__float_as_uint(v.lo4[i]) ^ sgn);
-          v.hi4[i] = __uint_as_float(__float_as_uint(v.hi4[i]) ^ sgn);
-        }
+        const float f = ((q / C::CPR) & 1) ? -SPLIT3_SCALE : SPLIT3_SCALE;
+        v.lo4 *= f;
+        v.hi4 *= f;
         split_bf16_3(v, t0, t1, t2);
         *reinterpret_cast<bf16x8*>(&As[off]) = dead ? z : t0;
         *reinterpret_cast<bf16x8*>(&As[C::TM * C::LD + off]) = dead ? z : t1;
@@ -415,7 +418,8 @@ __device__ inline void gemm_nt_tile_bf16(Acc<C>& acc, int K, LoadA loadA, LoadB 
 #pragma unroll
         for (int b = 0; b < C::BN; ++b)
 #pragma unroll
-          for (int e = 1; e < 16; e += 2) acc.v[g][a][b][e] = -acc.v[g][a][b][e];
+          for (int e = 0; e < 16; ++e)
+            acc.v[g][a][b][e] *= (e & 1) ? -SPLIT3_UNSCALE : SPLIT3_UNSCALE;
   }
 }
 

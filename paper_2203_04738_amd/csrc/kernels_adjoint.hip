@@ -1391,8 +1391,8 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
       F32x8 v;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        v.lo4[r] = p[r][e];
-        v.hi4[r] = p[4 + r][e];
+        v.lo4[r] = p[r][e] * SPLIT3_SCALE;
+        v.hi4[r] = p[4 + r][e] * SPLIT3_SCALE;
       }
       // (a tree: one addition per slice into the long sum)
       colsum[e] += ((p[0][e] + p[1][e]) + (p[2][e] + p[3][e])) +
@@ -1457,7 +1457,10 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) t = fmaf(acc[i][j][e], 0.f, t);
+        for (int e = 0; e < 16; ++e) {
+          acc[i][j][e] *= SPLIT3_UNSCALE;
+          t = fmaf(acc[i][j][e], 0.f, t);
+        }
     if (__syncthreads_or(t != t)) {
 #pragma unroll
       for (int i = 0; i < 2; ++i)

@@ -2,7 +2,7 @@
 // injection / correction transfers of Alg. 2 line 5 at coarse points) and the
 // final square root of the residual accumulators.
 #include "common.h"
-#include "gemm_core.h"
+#include "gemm_core_bf16.h"
 
 namespace mg {
 
@@ -75,7 +75,7 @@ hipError_t launch_add_points(float* dst, const float* src, Idx d, Idx s, int nk,
   return hipGetLastError();
 }
 
-// Three-term bf16 form of an fp32 array (weights of the MGRIT_F32_BF16X3 path).
+// Three-term bf16 form of an fp32 array, scaled as in gemm_core_bf16.h (weights of the three-term form).
 __global__ void split3_kernel(const float* __restrict__ src, unsigned short* __restrict__ dst,
                               long long n4) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -85,8 +85,9 @@ __global__ void split3_kernel(const float* __restrict__ src, unsigned short* __r
   unsigned short* tp = reinterpret_cast<unsigned short*>(t);
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const __bf16 h = (__bf16)v[e];
-    const float r1 = v[e] - (float)h;
+    const float a = v[e] * SPLIT3_SCALE;
+    const __bf16 h = (__bf16)a;
+    const float r1 = a - (float)h;
     const __bf16 m = (__bf16)r1;
     const __bf16 l = (__bf16)(r1 - (float)m);
     tp[e] = __builtin_bit_cast(unsigned short, h);

@@ -108,6 +108,34 @@ def test_infinite_adjoints_reach_the_gradients():
     assert all((~torch.isfinite(q)).any() for q in g)
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "fp32x3"])
+@pytest.mark.parametrize("what", ["dL_dhT", "x", "W"])
+def test_operands_far_below_one(gh, what, dtype):
+    """Operands around 3e-36, whose lower terms would be subnormal: the result is as accurate as at
+    any other scale (2048 rows per launch, so that relaxation, adjoint, projection and gradients
+    contract terms).  fp32 itself loses 2^-149 per sum element down there, 1176 x 2^-149 against
+    values of 2^-118: 2e-7."""
+    T, B, D, H = 64, 128, 64, 392
+    print("terms case tiny", what, dtype, flush=True)
+    d = dict(random_small(5, T, B, D, H, scale=0.3 / np.sqrt(H)))
+    d[what] = np.ldexp(d[what], -118).astype(np.float32)
+    if what != "dL_dhT":
+        d["b_i"] = np.zeros_like(d["b_i"])
+    run = gh.GpuRun(d, cf=4, levels=2, dtype=dtype)
+    P = (d["W"], d["U"], d["b_i"], d["b_h"])
+    z = np.zeros((T + 1, B, H))
+    h_ref, _ = orc.mgrit_forward(*P, d["x"], d["h0"], z, 4, 2, 1)
+    its, _ = run.forward_iterates(1)
+    assert gh.rel_err(its[-1], h_ref) <= 1e-5
+    proj = run.ws[:T * B * 3 * H * 4].view(torch.float32).view(T, B, 3 * H).cpu().numpy()
+    assert gh.rel_err(proj, d["x"].astype(np.float64) @ d["W"].T.astype(np.float64) + d["b_i"]) <= 1e-5
+    out = orc.mgrit_backward(*P, d["x"], h_ref, d["dL_dhT"], z, 4, 2, 1)
+    wits, _, grads = run.backward_iterates(h_ref, 1)
+    assert gh.rel_err(wits[-1], out[0]) <= 1e-5
+    for name, got, want in zip(("dW", "dU", "db_i", "db_h"), grads, out[2:6]):
+        assert gh.rel_err(got, want) <= 1e-5, name
+
+
 @pytest.mark.parametrize("B,H", [(33, 520), (65, 504)])
 def test_mid_size_tiles(gh, B, H):
     """Level launches of 528 to 2080 rows of 504 and 520 columns: the adjoint's 64 x 128 and K-split
