@@ -354,18 +354,30 @@ static PhiArgs phi_base(const FwdCtx& x, int l) {
   return a;
 }
 
-// Whether the sub-steps of a sweep run as one launch (kernels_sweep.hip): GRU layers of up to 128
-// columns with fp32 weights.
-static bool sweeps_fused(const mgrit_gru_cfg& c) {
+// Whether the sub-steps of a sweep over rows rows run as one launch (kernels_sweep.hip): GRU layers of
+// up to 128 columns with fp32 weights, while the workgroups have few quads of rows each.  A further
+// quad costs the sweep kernel about 1.3 us per sub-step, the tile kernels take large launches at a
+// higher rate.  All launches of a level, forward + adjoint, chain : sweep in us, cf 4: 4096 rows x 32
+// 276 : 238, 8192 301 : 328, 16384 345 : 538, 131072 1445 : 3717; 4096 x 64 309 : 265, 8192 396 : 386,
+// 16384 441 : 603; 4096 x 100 491 : 399, 8192 557 : 588, 16384 883 : 987; 4096 x 128 494 : 436, 8192 571 :
+// 641, 16384 873 : 1104; cf 8: 8192 x 32 573 : 511, 16384 642 : 884 (a chain also waits between its
+// launches, which these sums leave out).
+static bool sweeps_fused(const mgrit_gru_cfg& c, long long rows) {
   return (c.propagator == MGRIT_PROP_IMPLICIT || c.propagator == MGRIT_PROP_CLASSIC) &&
-         kform(c.dtype) != 1 && c.H <= SWEEP_MAX_H && (c.levels == 1 || c.cf > 1);
+         kform(c.dtype) != 1 && c.H <= SWEEP_MAX_H && (c.levels == 1 || c.cf > 1) && rows <= 8192;
+}
+// The same for a serial solve of B rows (scan + back-propagation of 32 steps, chain : sweep in us: 8192
+// rows x 32 846 : 720, 12288 1041 : 1092, 16384 1218 : 1460; 12288 x 64 1578 : 1583; 12288 x 100 2958 :
+// 2669, 16384 3502 : 3531; 12288 x 128 2934 : 2767, 16384 3490 : 3622).
+static bool serial_fused(const mgrit_gru_cfg& c) {
+  return sweeps_fused(c, 0) && c.B <= (c.H <= 64 ? 8192 : 12288);
 }
 
 // A launch of one sub-step loads the weights for a single use: the sweep kernel takes it where they
 // are few (training step of 64 steps x 4: 245 against 262 us with the step kernels at 32 columns,
 // 430 : 405 at 128) and the rows do not fill the chip several times (1024 x 64 x 32: 854 : 818).
 static bool single_fused(const mgrit_gru_cfg& c, int nk) {
-  return sweeps_fused(c) && c.H <= 64 && (long long)nk * c.B <= 4096;
+  return sweeps_fused(c, (long long)nk * c.B) && c.H <= 64 && (long long)nk * c.B <= 4096;
 }
 
 // F-relaxation (Alg. 1) or, with include_c, FC-relaxation on level l: sub-step j
@@ -393,16 +405,17 @@ static bool forward_leaves_coeffs(int l, int L) { return l >= 1 && l < L && (l =
 // array (mode STEP_RELAX_RHS).  *rhs_fused tells the caller whether such a launch ran.
 // first_done: the first sub-step of the sweep is in place already (see vcycle_fwd).
 // Fused sweeps (sweeps_fused) take the F-part in one launch; the C-sub-step, whose results are the
-// starting points of the neighbouring intervals, stays a launch of its own.  resid (then only; may be
-// null): the residual launch that follows the F-sweep is its last sub-step, with the coarse arrays
-// given here.
+// starting points of the neighbouring intervals, stays a launch of its own.  resid (F-sweeps; may be
+// null): the residual launch that follows the sweep, which a fused sweep takes as its last sub-step,
+// with the coarse arrays given here; *resid_done tells the caller whether it has.
 static int relax_fwd(const FwdCtx& x, int l, bool include_c, bool f_points_current = false,
                      bool emit = false, bool zero_c = false, bool* rhs_fused = nullptr,
-                     bool first_done = false, const PhiArgs* resid = nullptr) {
+                     bool first_done = false, const PhiArgs* resid = nullptr,
+                     bool* resid_done = nullptr) {
   const long long cf = x.c->cf, S = x.lay->S[l];
   const int nint = (int)(x.lay->N[l] / cf);
   if (rhs_fused) *rhs_fused = false;
-  const bool fused = sweeps_fused(*x.c);
+  const bool fused = sweeps_fused(*x.c, (long long)nint * x.c->B);
   // f_points_current: the F-points already equal the propagation of their coarse
   // points (they were written by the closing F-relaxation of the previous cycle of
   // this call and nothing changed since), so recomputing them would reproduce the
@@ -462,6 +475,7 @@ static int relax_fwd(const FwdCtx& x, int l, bool include_c, bool f_points_curre
         a.ff_cf = a.resid_adds ? resid->ff_cf : 0;
         a.ff_rem = resid->ff_rem;
         last = STEP_RESID;
+        *resid_done = true;
         ++n;
       }
       CHECK_HIP(launch_phi_sweep(a, n, rest, last, S, x.s));
@@ -488,7 +502,7 @@ static int vcycle_fwd(const FwdCtx& x, int l, bool f_points_current = false, boo
     const int kind = x.c->propagator == PROP_ODE_DEMO ? SCAN_ODE
                      : prop_is_lstm(x.c->propagator) ? SCAN_LSTM : SCAN_GRU;
     const int hidden = kind == SCAN_LSTM ? x.c->H / 2 : x.c->H;
-    if (sweeps_fused(*x.c)) {
+    if (serial_fused(*x.c)) {
       PhiArgs a = phi_base(x, l);
       a.mode = keep ? STEP_RELAX_KAPPA : STEP_RELAX;
       if (keep) {
@@ -564,14 +578,13 @@ static int vcycle_fwd(const FwdCtx& x, int l, bool f_points_current = false, boo
     ra.ff_rem = 1;
   }
   const bool f_only = l == 0 && x.c->fine_relax == 0;
-  // the residual is the last sub-step of the F-sweep before it, where one runs and is fused
-  const bool in_sweep = sweeps_fused(*x.c) && !(f_only && cur);
-  const PhiArgs* tail = in_sweep ? &ra : nullptr;
+  bool in_sweep = false;      // the residual was the last sub-step of the F-sweep before it
   if (f_only) {
-    if ((rc = relax_fwd(x, l, false, cur, false, zc, &rhs_fused, false, tail))) return rc;
+    if ((rc = relax_fwd(x, l, false, cur, false, zc, &rhs_fused, false, &ra, &in_sweep))) return rc;
   } else {
     if ((rc = relax_fwd(x, l, true, cur, false, zc, nullptr, first_f_done))) return rc;
-    if ((rc = relax_fwd(x, l, false, false, false, false, &rhs_fused, false, tail))) return rc;
+    if ((rc = relax_fwd(x, l, false, false, false, false, &rhs_fused, false, &ra, &in_sweep)))
+      return rc;
   }
   const bool child_first_done = rhs_fused && ra.ff_cf > 0;
   if (!in_sweep) {
@@ -753,10 +766,10 @@ static AdjArgs adj_base(const BwdCtx& x, int l) {
 // left out of the launches; on return *lo is the bound that holds after the sweep (one
 // interval lower).
 // first_done: the first sub-step of the sweep is in place already (see vcycle_bwd).
-// resid: as in relax_fwd.
+// resid, resid_done: as in relax_fwd.
 static int relax_bwd(const BwdCtx& x, int l, bool include_c, bool f_points_current = false,
                      long long* lo = nullptr, bool first_done = false,
-                     const AdjArgs* resid = nullptr) {
+                     const AdjArgs* resid = nullptr, bool* resid_done = nullptr) {
   const long long cf = x.c->cf;
   const int nint = (int)(x.lay->N[l] / cf);
   long long i0 = 0;                        // first interval that can hold non-zero values
@@ -775,7 +788,7 @@ static int relax_bwd(const BwdCtx& x, int l, bool include_c, bool f_points_curre
     a.o = Idx{cf - j + i0 * cf, cf};
     const bool overlap = (cf == 1);
     int n = j < cf ? (int)(cf - j) : 1;
-    if (sweeps_fused(*x.c) && !overlap &&
+    if (sweeps_fused(*x.c, (long long)a.nk * x.c->B) && !overlap &&
         (n + (resid && j < cf) > 1 || single_fused(*x.c, a.nk))) {
       int last = STEP_RELAX;
       if (resid && j < cf) {
@@ -786,6 +799,7 @@ static int relax_bwd(const BwdCtx& x, int l, bool include_c, bool f_points_curre
         a.ff_cf = i0 == 0 ? resid->ff_cf : 0;
         a.ff_rem = resid->ff_rem;
         last = STEP_RESID;
+        *resid_done = true;
         ++n;
       }
       CHECK_HIP(launch_adj_sweep(a, n, STEP_RELAX, last, x.s));
@@ -815,7 +829,7 @@ static int vcycle_bwd(const BwdCtx& x, int l, bool f_points_current = false,
   const long long cf = x.c->cf, N = x.lay->N[l];
   const int L = x.lay->L;
   if (l == L - 1) {
-    if (sweeps_fused(*x.c)) {
+    if (serial_fused(*x.c)) {
       AdjArgs a = adj_base(x, l);
       a.mode = STEP_RELAX;
       a.nk = 1;
@@ -876,13 +890,12 @@ static int vcycle_bwd(const BwdCtx& x, int l, bool f_points_current = false,
     ra.ff_rem = (int)cf - 1;
   }
   const bool f_only = l == 0 && x.c->fine_relax == 0;
-  const bool in_sweep = sweeps_fused(*x.c) && !(f_only && cur);     // as in vcycle_fwd
-  const AdjArgs* tail = in_sweep ? &ra : nullptr;
+  bool in_sweep = false;                                            // as in vcycle_fwd
   if (f_only) {
-    if ((rc = relax_bwd(x, l, false, cur, plo, false, tail))) return rc;
+    if ((rc = relax_bwd(x, l, false, cur, plo, false, &ra, &in_sweep))) return rc;
   } else {
     if ((rc = relax_bwd(x, l, true, cur, plo, first_f_done))) return rc;
-    if ((rc = relax_bwd(x, l, false, false, plo, false, tail))) return rc;
+    if ((rc = relax_bwd(x, l, false, false, plo, false, &ra, &in_sweep))) return rc;
   }
   // coarse points below lo have a zero iterate, a zero successor and a zero right-hand
   // side: their residual is zero and is written as such
