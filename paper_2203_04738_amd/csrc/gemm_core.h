@@ -105,6 +105,13 @@ __device__ inline void gemm_nt_tile(Acc<C>& acc, int K, LoadA loadA, LoadB loadB
   const int lh = lane >> 5;
   constexpr int NC = C::TK / 8 / C::KS;  // k-groups of eight per slice and K-split group
   constexpr int NB = C::NG * C::BN;      // B fragments per k-group
+  // A wave with one block sums every second k apart: half the additions into each sum.  Adjoint
+  // of 320 rows x 1024, error of w against 64 bits: 5.7e-8 with one sum, 5.2e-8 with two (three-term
+  // tiles: 5.4e-8), in the same time.
+  constexpr bool LONE = NB * C::BM == 1;
+  floatx16 odd;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) odd[e] = 0.f;
 
   decltype(loadA(0, 0)) ra[C::A_CHUNKS];
   decltype(loadB(0, 0)) rb[C::B_CHUNKS];
@@ -164,8 +171,11 @@ __device__ inline void gemm_nt_tile(Acc<C>& acc, int K, LoadA loadA, LoadB loadB
         for (int b = 0; b < C::BN; ++b)
 #pragma unroll
           for (int a = 0; a < C::BM; ++a)
-            acc.v[g][a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-                fa[a][e], fb[g * C::BN + b][e], acc.v[g][a][b], 0, 0, 0);
+            if (LONE && (e & 1))
+              odd = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[a][e], fb[g * C::BN + b][e], odd, 0, 0, 0);
+            else
+              acc.v[g][a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                  fa[a][e], fb[g * C::BN + b][e], acc.v[g][a][b], 0, 0, 0);
   };
 
   const int nkt = (K + C::TK - 1) / C::TK;
@@ -216,6 +226,7 @@ __device__ inline void gemm_nt_tile(Acc<C>& acc, int K, LoadA loadA, LoadB loadB
       }
     }
   }
+  if (LONE) acc.v[0][0][0] += odd;
 }
 
 // XCD-aware tile order.  Workgroups are dispatched round-robin over the 8 XCDs

@@ -668,7 +668,8 @@ hipError_t launch_adj_step(const AdjArgs& a, hipStream_t s) {
     launch_adj_x3<AdjMidS>(a, s);
   else if (R > 32 && tiles(AdjMid::TM, AdjMid::TN) >= 256)
     launch_adj_cfg<AdjMid, AdjMidB, AdjMidF>(a, s);
-  else   // (three terms included: 32 x 32 tiles are faster in fp32, see launch_phi_cfg)
+  else   // (three terms included: 32 x 32 tiles are faster in fp32, see launch_phi_cfg, and no less
+         // accurate, see gemm_nt_tile)
     launch_adj_cfg<AdjSmall, AdjSmallB, AdjSmallF>(a, s);
   prof_end(kind, 6.0 * (double)R * a.H * a.H, 28.0 * (double)R * a.H, s);
   return hipGetLastError();

@@ -90,3 +90,19 @@ def test_terms_of_small_and_large_magnitudes(gh):
     d["dL_dhT"] = (d["dL_dhT"] * 1e-20).astype(np.float32)
     d["x"] = (d["x"] * 50.0).astype(np.float32)
     _check_mgrit(gh, d, 4, 2, 2)
+
+
+def test_small_adjoint_launches_are_as_accurate_as_terms(gh):
+    """320 rows per launch run on 32 x 32 tiles of fp32 operands.  Their error must not exceed what
+    three-term tiles give there: 2-norm 5.45e-8 of w on these inputs (measured with such tiles; 1.3
+    million elements, so the figure repeats to about a per cent)."""
+    T, B, H = 64, 20, 1024
+    d = random_small(3, T, B, 64, H, scale=0.5 / np.sqrt(H))
+    run = gh.GpuRun(d, cf=4, levels=2, dtype=FORM)
+    h, _ = orc.mgrit_forward(*_P(d), d["x"], d["h0"], _zeros(d), 4, 2, 2)
+    h = h.astype(np.float32)
+    want = orc.mgrit_backward(*_P(d), d["x"], h, d["dL_dhT"], _zeros(d), 4, 2, 1)[0]
+    w = run.backward_iterates(h, 1)[0][-1].astype(np.float64)
+    err = np.linalg.norm(w - want) / np.linalg.norm(want)
+    print("error of w", err)
+    assert err <= 5.45e-8
