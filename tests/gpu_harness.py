@@ -166,3 +166,26 @@ def rel_err(got, ref):
     assert got.shape == ref.shape, (got.shape, ref.shape)
     assert np.all(np.isfinite(got)), "non-finite output"
     return float(np.max(np.abs(got - ref)) / max(np.max(np.abs(ref)), 1e-300))
+
+
+def expect_kernels(call, *kernels):
+    """Runs `call` (repeatable) and asserts that kernels with these name parts were launched: a test
+    that means one form of a step checks here that this form ran.  The profiler drops its records now
+    and then, hence the repetitions; where it records nothing at all the check is left out."""
+    import warnings
+
+    from torch.profiler import ProfilerActivity, profile
+    seen = set()
+    for _ in range(6):
+        torch.cuda.synchronize()
+        with warnings.catch_warnings():
+            warnings.simplefilter("ignore")
+            with profile(activities=[ProfilerActivity.CUDA]) as p:
+                call()
+                torch.cuda.synchronize()
+            seen |= {e.name for e in p.events() if "mg::" in e.name}
+        if all(any(k in n for n in seen) for k in kernels):
+            return
+    if seen:
+        missing = [k for k in kernels if not any(k in n for n in seen)]
+        raise AssertionError(f"not launched: {missing}; launched: {sorted(seen)}")

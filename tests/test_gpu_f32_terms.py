@@ -1,5 +1,6 @@
-"""MGRIT_F32 on the bf16 matrix pipe (three terms per fp32 operand): the shapes its rule sends there,
-at the edges of the tiles, and operands that the terms cannot carry."""
+"""MGRIT_F32 on the bf16 matrix pipe (three terms per fp32 operand): whole solves around the line of its
+rule, operands that the terms cannot carry, and operands far below one.  (The step kernels tile by
+tile: test_gpu_term_tiles.py.)"""
 import numpy as np
 import pytest
 import torch
@@ -19,8 +20,10 @@ def gh():
     return gpu_harness
 
 
-# T, B, D, H: 1024 rows per level-0 launch and a few more; K tails (136, 72), a projection that stays
-# in fp32 (20, 132), row and column tails of the tiles
+# T, B, D, H: 1024 rows per level-0 launch and a few more, the least that takes terms: projection,
+# coefficient pass and gradients run on them, with K tails (136, 72), a projection that stays in fp32
+# (20, 132) and row and column tails; the steps of so few rows run in fp32 (32 x 32 tiles, sweeps for
+# 128 columns)
 @pytest.mark.parametrize("T,B,D,H", [(64, 64, 64, 128), (64, 67, 72, 136), (128, 33, 20, 128),
                                      (64, 65, 132, 200), (32, 129, 96, 264)])
 def test_training_step_against_the_oracle(gh, T, B, D, H):
@@ -33,12 +36,18 @@ def test_training_step_against_the_oracle(gh, T, B, D, H):
     its, _ = run.forward_iterates(2, per_call=2)
     assert gh.rel_err(its[-1], h_ref) <= 1e-5
     out = orc.mgrit_backward(*P, d["x"], h_ref, d["dL_dhT"], z, 4, 2, 1)
-    wits, _, grads = run.backward_iterates(h_ref, 1, per_call=1)
+    box = []
+    gh.expect_kernels(lambda: box.append(run.backward_iterates(h_ref, 1, per_call=1)),
+                      "grad_gemm_x3_kernel", "phi_step_kernel_bf16",
+                      "projection_kernel_bf16" if D % 8 == 0 else "projection_kernel(")
+    wits, _, grads = box[0]
     assert gh.rel_err(wits[-1], out[0]) <= 1e-5
     for got, want in zip(grads, out[2:6]):
         assert gh.rel_err(got, want) <= 1e-5
 
 
+# (the last one has the 128 tiles of 64 x 64 that take the LSTM step to terms; the others run their
+# projection on terms and their steps in fp32)
 @pytest.mark.parametrize("T,B,D,H", [(64, 64, 64, 128), (64, 67, 20, 136), (128, 129, 72, 200)])
 def test_lstm_solve_against_the_oracle(T, B, D, H):
     print("terms case lstm", T, B, D, H, flush=True)
@@ -89,6 +98,7 @@ def test_operands_the_terms_cannot_carry(value):
 
 
 def test_infinite_adjoints_reach_the_gradients():
+    # 128 columns: the adjoint runs in the sweep kernel, the gradients on terms
     T, B, D, H, dev = 64, 64, 64, 128, "cuda:0"
     d = random_small(4, T, B, D, H, scale=0.3)
     t = {k: torch.from_numpy(v).to(dev) for k, v in d.items()}
@@ -106,6 +116,21 @@ def test_infinite_adjoints_reach_the_gradients():
     others = [b for b in range(B) if b != 2]
     assert torch.isfinite(w[:, others]).all()
     assert all((~torch.isfinite(q)).any() for q in g)
+
+
+def test_gradients_of_adjoints_beyond_the_terms(gh):
+    # sums that overflow in the scale of the terms but not in fp32: every tile is summed again in fp32
+    T, B, D, H = 64, 70, 72, 136
+    d = random_small(6, T, B, D, H, scale=0.3 / np.sqrt(H))
+    d["dL_dhT"][2, 9] = 1e35
+    run = gh.GpuRun(d, cf=4, levels=2)
+    P, z = (d["W"], d["U"], d["b_i"], d["b_h"]), np.zeros((T + 1, B, H))
+    h, _ = orc.mgrit_forward(*P, d["x"], d["h0"], z, 4, 2, 1)
+    out = orc.mgrit_backward(*P, d["x"], h, d["dL_dhT"], z, 4, 2, 1)
+    box = []
+    gh.expect_kernels(lambda: box.append(run.backward_iterates(h, 1)), "grad_gemm_x3_kernel")
+    for name, got, want in zip(("dW", "dU", "db_i", "db_h"), box[0][2], out[2:6]):
+        assert gh.rel_err(got, want) <= 1e-5, name
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "fp32x3"])
@@ -138,8 +163,8 @@ def test_operands_far_below_one(gh, what, dtype):
 
 @pytest.mark.parametrize("B,H", [(33, 520), (65, 504)])
 def test_mid_size_tiles(gh, B, H):
-    """Level launches of 528 to 2080 rows of 504 and 520 columns: the adjoint's 64 x 128 and K-split
-    64 x 64 tiles, the forward 64 x 32 ones, each with row, column and K tails."""
+    """Level launches of 528 to 2080 rows of 504 and 520 columns, K-split tiles with row, column and K
+    tails: (33, 520) the forward 64 x 32 tile at cf 2, (65, 504) that one and the adjoint's 64 x 64."""
     T, D = 64, 8
     print("terms case mid", B, H, flush=True)
     d = random_small(B + H, T, B, D, H, scale=0.3 / np.sqrt(H))
@@ -147,8 +172,12 @@ def test_mid_size_tiles(gh, B, H):
         run = gh.GpuRun(d, cf=cf, levels=2)
         P, z = (d["W"], d["U"], d["b_i"], d["b_h"]), np.zeros((T + 1, B, H))
         h_ref, _ = orc.mgrit_forward(*P, d["x"], d["h0"], z, cf, 2, 1)
-        its, _ = run.forward_iterates(1)
-        assert gh.rel_err(its[-1], h_ref) <= 1e-5
+        box = []
+        gh.expect_kernels(lambda: box.append(run.forward_iterates(1)),
+                          *(["TileCfgB<2, 1, 1, 1, 3, true, 2, 1, 2, 3"] if T * B // cf > 1030 else []))
+        assert gh.rel_err(box[0][0][-1], h_ref) <= 1e-5
         out = orc.mgrit_backward(*P, d["x"], h_ref, d["dL_dhT"], z, cf, 2, 1)
-        wits, _, _ = run.backward_iterates(h_ref, 1)
-        assert gh.rel_err(wits[-1], out[0]) <= 1e-5
+        box = []
+        gh.expect_kernels(lambda: box.append(run.backward_iterates(h_ref, 1)),
+                          *(["TileCfgB<2, 2, 1, 1, 1, true, 2, 1, 2, 3"] if T * B // cf > 2000 else []))
+        assert gh.rel_err(box[0][0][-1], out[0]) <= 1e-5

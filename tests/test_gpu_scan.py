@@ -1,7 +1,8 @@
 """Serial propagation as one launch (kernels_scan.hip) against the oracles, at the edges of its
 shapes: partly filled row quads, column groups and K chunks, several row groups per workgroup, one
-and two chunks per wave.  Bar: 1e-5 of the largest value (fp32 arithmetic throughout, also on bf16
-weights, which the oracle reads as they are)."""
+and two chunks per wave.  GRU layers of up to 128 columns with fp32 weights run their serial solves in
+the sweep kernels (kernels_sweep.hip); every case checks which of the two has run.  Bar: 1e-5 of the
+largest value (fp32 arithmetic throughout, also on bf16 weights, which the oracle reads as they are)."""
 import numpy as np
 import pytest
 import torch
@@ -16,10 +17,19 @@ from synthetic_inputs import random_lstm, random_ode, random_small, round_to_bf1
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 T = 9
-# B, H: quads 1..16, column groups 1..64; (33, 512) and (64, 500) two row groups per workgroup,
-# (64, 1024) four, (3, 1000) and (8, 516) two chunks per wave with a ragged tail
-SHAPES = [(1, 16), (3, 20), (4, 64), (5, 68), (33, 128), (32, 512), (33, 512), (64, 500), (3, 1000),
-          (8, 516), (9, 1024), (64, 1024)]
+# B, H: the sweep kernels up to 128 columns; above, quads 1..16, column groups 9..64: (1, 132), (3, 140)
+# and (33, 196) one row group per workgroup and a ragged last column group and K chunk, (33, 512) and
+# (64, 500) two row groups, (64, 1024) four, (3, 1000) and (8, 516) two chunks per wave with a ragged tail
+SHAPES = [(1, 16), (3, 20), (4, 64), (5, 68), (33, 128), (1, 132), (3, 140), (33, 196), (32, 512),
+          (33, 512), (64, 500), (3, 1000), (8, 516), (9, 1024), (64, 1024)]
+SCAN = {"gru": "scan_kernel<0,", "adjoint": "scan_kernel<1,", "lstm": "scan_kernel<2,",
+        "ode": "scan_kernel<3,"}
+
+
+@pytest.fixture(scope="module")
+def gh():
+    import gpu_harness
+    return gpu_harness
 
 
 def _rel(a, b):
@@ -36,8 +46,8 @@ def _dev(d, half=False):
     return t
 
 
-def _gru(B, H, half=False, steps=T):
-    d = random_small(B * 1000 + H, steps, B, 8, H, scale=0.7 / np.sqrt(H))
+def _gru(B, H, half=False, steps=T, seed=0):
+    d = random_small(B * 1000 + H + 7919 * seed, steps, B, 8, H, scale=0.7 / np.sqrt(H))
     if half:
         for k in ("x", "W", "U"):
             d[k] = round_to_bf16(d[k])
@@ -47,59 +57,68 @@ def _gru(B, H, half=False, steps=T):
     return d, t, cfg, ws, (t["W"], t["U"], t["b_i"], t["b_h"], t["x"])
 
 
-def _check_gru(B, H, half=False):
+def _check_gru(gh, B, H, half=False):
+    one_launch = half or H > 128
     d, t, cfg, ws, p = _gru(B, H, half)
     P = (d["W"], d["U"], d["b_i"], d["b_h"])
     h = torch.full((T + 1, B, H), 7.0, device=DEV)
-    mg.gru_serial_scan(cfg, *p, t["h0"], h, ws)
+    gh.expect_kernels(lambda: mg.gru_serial_scan(cfg, *p, t["h0"], h, ws),
+                      SCAN["gru"] if one_launch else "phi_sweep_kernel")
     want = orc.serial_scan(*P, d["x"], d["h0"])
     assert _rel(h, want) <= 1e-5
     w = torch.full((T + 1, B, H), 7.0, device=DEV)
     g = [torch.empty(3 * H, 8, device=DEV), torch.empty(3 * H, H, device=DEV),
          torch.empty(3 * H, device=DEV), torch.empty(3 * H, device=DEV)]
-    mg.gru_serial_scan_backward(cfg, *p, h, t["dL_dhT"], w, *g, ws)
+    # (the adjoint of more than 32 rows x 1024 would need more registers: step by step)
+    gh.expect_kernels(lambda: mg.gru_serial_scan_backward(cfg, *p, h, t["dL_dhT"], w, *g, ws),
+                      "adj_sweep_kernel" if not one_launch else
+                      "adj_" if B > 32 and H > 1000 else SCAN["adjoint"])
     out = orc.serial_bptt(*P, d["x"], want, d["dL_dhT"])
     # bf16 weights: more than 64 rows of coefficient vectors come from the tile kernels, which
     # carry the state as two bf16 terms there (2^-17 per product: the 1e-4 bar of that form)
-    assert _rel(w, out[0]) <= (1e-4 if half else 1e-5)
+    for got, ref in zip((w, *g), out):
+        assert _rel(got, ref) <= (1e-4 if half else 1e-5)
 
 
 @pytest.mark.parametrize("B,H", SHAPES)
-def test_gru_and_adjoint(B, H):
+def test_gru_and_adjoint(gh, B, H):
     print("scan case", B, H, flush=True)
-    _check_gru(B, H)
+    _check_gru(gh, B, H)
 
 
 @pytest.mark.parametrize("B,H", [(5, 24), (8, 1024)])
-def test_gru_and_adjoint_bf16_weights(B, H):
+def test_gru_and_adjoint_bf16_weights(gh, B, H):
     print("scan case bf16", B, H, flush=True)
-    _check_gru(B, H, half=True)
+    _check_gru(gh, B, H, half=True)
 
 
 @pytest.mark.parametrize("B,H", [(3, 20), (32, 512), (64, 500), (5, 1000), (64, 1024)])
-def test_lstm_and_ode(B, H):
+def test_lstm_and_ode(gh, B, H):
     print("scan case lstm, ode", B, H, flush=True)
     d = random_lstm(1, T, B, 8, H, scale=0.7 / np.sqrt(H))
     t = _dev(d)
     cfg = MgritGruCfg(T, B, 8, H)
     ws = torch.empty(mg.mgrit_lstm_workspace_bytes(cfg), dtype=torch.uint8, device=DEV)
     u = torch.full((T + 1, B, 2 * H), 7.0, device=DEV)
-    mg.lstm_serial_scan(cfg, t["W"], t["U"], t["b_i"], t["b_h"], t["x"], t["u0"], u, ws)
+    gh.expect_kernels(lambda: mg.lstm_serial_scan(cfg, t["W"], t["U"], t["b_i"], t["b_h"], t["x"],
+                                                  t["u0"], u, ws), SCAN["lstm"])
     assert _rel(u, lo.lstm_serial_scan(d["W"], d["U"], d["b_i"], d["b_h"], d["x"], d["u0"])) <= 1e-5
     d = random_ode(2, T, B, 8, H)
     t = _dev(d)
     h = torch.full((T + 1, B, H), 7.0, device=DEV)
-    mg.ode_serial_scan(cfg, 0.25, t["A"], t["Bw"], t["b"], t["d"], t["h0"], h, ws)
+    gh.expect_kernels(lambda: mg.ode_serial_scan(cfg, 0.25, t["A"], t["Bw"], t["b"], t["d"], t["h0"],
+                                                 h, ws), SCAN["ode"])
     assert _rel(h, oo.ode_serial_scan(d["A"], d["Bw"], d["b"], d["d"], d["h0"], 0.25)) <= 1e-5
 
 
-@pytest.mark.parametrize("B,H", [(5, 68), (32, 512)])
-def test_a_solve_that_is_given_up_is_repaired(B, H, monkeypatch):
-    # a wait limit of zero: the workgroups leave before all have arrived, the second kernel solves
+@pytest.mark.parametrize("B,H", [(5, 68), (5, 140), (32, 512)])
+def test_a_solve_that_is_given_up_is_repaired(gh, B, H, monkeypatch):
+    # a wait limit of zero: the workgroups leave at once, the launch behind solves (that it does is
+    # checked in test_results_do_not_depend_on_who_computes_them; 68 columns: LSTM and ODE only)
     monkeypatch.setenv("MGRIT_SCAN_WAIT_TICKS", "0")
     print("scan case without waiting", B, H, flush=True)
-    _check_gru(B, H)
-    test_lstm_and_ode(B, H)
+    _check_gru(gh, B, H)
+    test_lstm_and_ode(gh, B, H)
 
 
 @pytest.mark.parametrize("B,H", [(3, 136), (32, 512), (9, 1000), (64, 1024)])
@@ -133,16 +152,59 @@ def test_results_do_not_depend_on_who_computes_them(B, H, monkeypatch):
     assert 0 < int((left0 != left).sum()) <= 16
 
 
-def test_a_nan_with_every_bit_set_passes_through():
-    d, t, cfg, ws, p = _gru(6, 72)
-    h = torch.empty(T + 1, 6, 72, device=DEV)
+def _nan_case(gh, kind, B, H, call, x, state0, out, alone):
+    """Row 2 starts as the NaN with every bit set (the pattern that marks unwritten rows), row 1 meets
+    it in its data at step 4: both carry NaN from there on, the others keep their bits.  (If the
+    pattern were stored, every consumer would wait for it until the time limit.)"""
+    call()
+    clean = out.clone()
+    state0.view(torch.int32)[2, :] = -1
+    if x is not None:
+        x.view(torch.int32)[4, 1, :] = -1
+    gh.expect_kernels(call, SCAN[kind] if alone else "phi_sweep_kernel")
+    keep = [b for b in range(B) if b not in (1, 2)]
+    assert torch.equal(out[:, keep], clean[:, keep])
+    return clean
+
+
+@pytest.mark.parametrize("wait", [None, "0"])
+@pytest.mark.parametrize("H", [72, 136])
+def test_a_nan_with_every_bit_set_passes_through(gh, H, wait, monkeypatch):
+    if wait:
+        monkeypatch.setenv("MGRIT_SCAN_WAIT_TICKS", wait)
+    B, alone = 6, H > 128
+    print("scan case nan", H, wait, flush=True)
+    d, t, cfg, ws, p = _gru(B, H)
+    h = torch.empty(T + 1, B, H, device=DEV)
+    clean = _nan_case(gh, "gru", B, H, lambda: mg.gru_serial_scan(cfg, *p, t["h0"], h, ws), t["x"],
+                      t["h0"], h, alone)
+    assert torch.isnan(h[:, 2]).all() and torch.isnan(h[5:, 1]).all()
+    assert torch.equal(h[:5, 1], clean[:5, 1])
+    # adjoint: the terminal value of one row
+    g = [torch.empty(3 * H, 8, device=DEV), torch.empty(3 * H, H, device=DEV),
+         torch.empty(3 * H, device=DEV), torch.empty(3 * H, device=DEV)]
+    d, t, cfg, ws, p = _gru(B, H)
     mg.gru_serial_scan(cfg, *p, t["h0"], h, ws)
-    clean = h.clone()
-    t["h0"].view(torch.int32)[2, :] = -1
-    t["x"].view(torch.int32)[4, 1, :] = -1
-    mg.gru_serial_scan(cfg, *p, t["h0"], h, ws)
-    keep = [0, 3, 4, 5]
-    assert torch.equal(h[:, keep], clean[:, keep])
+    w = torch.empty(T + 1, B, H, device=DEV)
+
+    def back():
+        mg.gru_serial_scan_backward(cfg, *p, h, t["dL_dhT"], w, *g, ws)
+
+    back()
+    clean = w.clone()
+    t["dL_dhT"].view(torch.int32)[2, :] = -1
+    gh.expect_kernels(back, SCAN["adjoint"] if alone else "adj_sweep_kernel")
+    assert torch.isnan(w[:, 2]).all() and torch.equal(w[:, [0, 1, 3, 4, 5]], clean[:, [0, 1, 3, 4, 5]])
+    t = _dev(random_lstm(1, T, B, 8, H, scale=0.7 / np.sqrt(H)))
+    lws = torch.empty(mg.mgrit_lstm_workspace_bytes(cfg), dtype=torch.uint8, device=DEV)
+    u = torch.empty(T + 1, B, 2 * H, device=DEV)
+    clean = _nan_case(gh, "lstm", B, H, lambda: mg.lstm_serial_scan(
+        cfg, t["W"], t["U"], t["b_i"], t["b_h"], t["x"], t["u0"], u, lws), t["x"], t["u0"], u, True)
+    assert torch.isnan(u[:, 2]).all() and torch.isnan(u[5:, 1]).all()
+    assert torch.equal(u[:5, 1], clean[:5, 1])
+    t = _dev(random_ode(2, T, B, 8, H))
+    clean = _nan_case(gh, "ode", B, H, lambda: mg.ode_serial_scan(
+        cfg, 0.25, t["A"], t["Bw"], t["b"], t["d"], t["h0"], h, lws), t["d"], t["h0"], h, True)
     assert torch.isnan(h[:, 2]).all() and torch.isnan(h[5:, 1]).all()
     assert torch.equal(h[:5, 1], clean[:5, 1])
 
@@ -168,16 +230,23 @@ def test_serial_adjoint_in_place_of_its_source_term(B, H):
 
 
 def test_solves_on_several_streams_at_once():
-    runs = [_gru(32, 512, steps=64) for _ in range(3)]
+    # three problems of their own, 256 workgroups each: every pass overwrites a wrong value with the
+    # bits the problem gives alone
+    runs = [_gru(32, 512, steps=64, seed=s) for s in range(3)]
     outs = [torch.empty(65, 32, 512, device=DEV) for _ in runs]
     streams = [torch.cuda.Stream() for _ in runs]
-    torch.cuda.synchronize()
+    alone = []
+    for (d, t, cfg, ws, p), h in zip(runs, outs):
+        mg.gru_serial_scan(cfg, *p, t["h0"], h, ws)
+        alone.append(h.clone())
+        want = orc.serial_scan(d["W"], d["U"], d["b_i"], d["b_h"], d["x"], d["h0"])
+        assert _rel(h, want) <= 1e-5
     for _ in range(3):
+        for h in outs:
+            h.fill_(7.0)
+        torch.cuda.synchronize()
         for (d, t, cfg, ws, p), h, s in zip(runs, outs, streams):
             with torch.cuda.stream(s):
                 mg.gru_serial_scan(cfg, *p, t["h0"], h, ws)
-    torch.cuda.synchronize()
-    d = runs[0][0]
-    want = orc.serial_scan(d["W"], d["U"], d["b_i"], d["b_h"], d["x"], d["h0"])
-    for h in outs:
-        assert _rel(h, want) <= 1e-5
+        torch.cuda.synchronize()
+        assert all(torch.equal(h, a) for h, a in zip(outs, alone))

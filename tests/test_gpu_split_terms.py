@@ -1,9 +1,11 @@
 """Parity of the third operand form (MGRIT_F32_BF16X3: fp32 inputs and weights, the tile
 kernels contract them as three bf16 terms each on the bf16 matrix pipe) with the CPU oracle,
 element by element, through the C ABI.  It is an fp32 path: same inputs, same oracle and
-the same bar as the fp32 form, max|gpu - oracle| / max|oracle| <= 1e-5 per tensor.  The
-shapes below put more than 64 rows into every launch, so that the tile kernels (and not the
-few-row kernels, which are shared with the fp32 form) do the work."""
+the same bar as the fp32 form, max|gpu - oracle| / max|oracle| <= 1e-5 per tensor.  Projection,
+coefficient pass and gradients run on terms at every shape; the steps do in launches of 128 tiles
+of 64 x 64 (adjoint: 192) and more, and share the fp32 kernels below that (32 x 32 tiles, few-row
+kernels, one-launch solves, and the sweeps of layers of up to 128 columns).  The step kernels tile by
+tile, which this form shares with MGRIT_F32: test_gpu_term_tiles.py."""
 import numpy as np
 import pytest
 
@@ -34,9 +36,9 @@ def _zeros(d):
 @pytest.mark.parametrize("prop", [orc.IMPLICIT, orc.CLASSIC])
 @pytest.mark.parametrize("shape", [(6, 70, 16, 136), (9, 130, 8, 24), (5, 300, 40, 72), (6, 70, 8, 8)])
 def test_serial_scan_and_bptt(gh, prop, shape):
-    """Few tiles per launch: the K-split tile configuration, ragged rows, columns and K
-    (136 = 4 x 32 + 8, 3 x 24 = 72 = 2 x 32 + 8), down to the smallest widths the form takes
-    (H = D = 8: a quarter of one K-slice)."""
+    """Few rows per step: projection, coefficients and gradients on terms with ragged rows, columns and
+    K (136 = 4 x 32 + 8, 3 x 24 = 72 = 2 x 32 + 8), down to the smallest widths the form takes (H = D =
+    8: a quarter of one K-slice); the steps on 32 x 32 fp32 tiles (136) and in the sweep kernels."""
     T, B, D, H = shape
     d = random_small(900 + H, T, B, D, H, scale=0.3)
     ref = orc.serial_scan(*_P(d), d["x"], d["h0"], prop)
@@ -44,7 +46,9 @@ def test_serial_scan_and_bptt(gh, prop, shape):
     assert gh.rel_err(run.serial_scan(), ref) <= TOL
     h = ref.astype(np.float32)
     rb = orc.serial_bptt(*_P(d), d["x"], h, d["dL_dhT"], prop)
-    for name, g, r in zip(("w", "dW", "dU", "db_i", "db_h"), run.serial_backward(h), rb):
+    box = []
+    gh.expect_kernels(lambda: box.append(run.serial_backward(h)), "grad_gemm_x3_kernel")
+    for name, g, r in zip(("w", "dW", "dU", "db_i", "db_h"), box[0], rb):
         assert gh.rel_err(g, r) <= TOL, name
 
 
@@ -69,11 +73,24 @@ def _check_mgrit(gh, d, cf, levels, iters, fcf=True):
 
 @pytest.mark.parametrize("cf,levels,fcf", [(4, 3, True), (4, 2, False), (2, 4, True)])
 def test_mgrit_hierarchies_every_iterate(gh, cf, levels, fcf):
-    """96 intervals x 40 rows on level 0 down to 40 rows on the coarsest level: the three
-    tile configurations and the few-row kernels in one solve."""
+    """96 intervals x 40 rows on level 0 down to 40 rows on the coarsest level, 104 columns: sweeps and
+    serial solves in the sweep kernels, coefficients and gradients on terms."""
     T = 24 * cf ** (levels - 1) if cf == 4 else 192
     d = random_small(91, T, 40, 72, 104, scale=0.2)
     _check_mgrit(gh, d, cf, levels, 2, fcf)
+
+
+def test_mgrit_hierarchy_of_a_wide_layer(gh):
+    """4224 rows on level 0 (three-term tiles, forward and adjoint), 1056 on level 1 (fp32 tiles), 44 on
+    the coarsest level (one-launch solves): every form in one solve."""
+    d = random_small(92, 384, 44, 72, 136, scale=0.5 / np.sqrt(136))
+    run = gh.GpuRun(d, cf=4, levels=3, dtype=FORM)
+    gh.expect_kernels(lambda: run.forward_iterates(1), "phi_step_kernel_bf16<mg::TileCfgB<2, 1, 1, 1, 3",
+                      "phi_step_kernel<", "scan_kernel<0,")
+    h = run.h_dev.cpu().numpy()
+    gh.expect_kernels(lambda: run.backward_iterates(h, 1), "adj_step_kernel_bf16<mg::TileCfgB<2, 2, 1, 1, 1",
+                      "adj_step_kernel<", "scan_kernel<1,")
+    _check_mgrit(gh, d, 4, 3, 2)
 
 
 @pytest.mark.parametrize("name", ["C2", "C3", "C5"])
@@ -82,11 +99,12 @@ def test_mgrit_reduced_twins(gh, name):
     _check_mgrit(gh, make_inputs(wl), wl.cf, wl.levels, 2)
 
 
-def test_terms_of_small_and_large_magnitudes(gh):
+@pytest.mark.parametrize("T,B,D,H", [(32, 70, 16, 40), (16, 1030, 16, 136)])
+def test_terms_of_small_and_large_magnitudes(gh, T, B, D, H):
     """The three-term split keeps the exponent range of fp32: a tiny loss gradient (1e-20)
-    and large inputs change nothing about the relative error."""
-    T, B, D, H = 32, 70, 16, 40
-    d = dict(random_small(17, T, B, D, H, scale=0.3))
+    and large inputs change nothing about the relative error.  (40 columns: steps in the sweep
+    kernels; 4120 rows x 136: all steps of level 0 on terms.)"""
+    d = dict(random_small(17, T, B, D, H, scale=0.3 if H < 100 else 0.5 / np.sqrt(H)))
     d["dL_dhT"] = (d["dL_dhT"] * 1e-20).astype(np.float32)
     d["x"] = (d["x"] * 50.0).astype(np.float32)
     _check_mgrit(gh, d, 4, 2, 2)
