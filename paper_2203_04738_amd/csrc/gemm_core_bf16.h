@@ -48,18 +48,35 @@ __device__ inline const bf16x8& operand_term(const bf16x8& v, int) { return v; }
 __device__ inline const bf16x8& operand_term(const Bf16x8x3& v, int u) { return v.p[u]; }
 
 constexpr float SPLIT3_SCALE = 0x1p24f, SPLIT3_UNSCALE = 0x1p-48f;
-// t0 + t1 + t2 = v: the caller has scaled v
+// Two floats rounded to bf16 in one instruction (a in the low half); what their roundings leave.
+__device__ inline unsigned round2_bf16(float a, float b) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  typedef float floatx2 __attribute__((ext_vector_type(2)));
+  const floatx2 v = {a, b};
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+}
+__device__ inline void minus2_bf16(float& a, float& b, unsigned r) {
+  a -= __uint_as_float(r << 16);
+  b -= __uint_as_float(r & 0xffff0000u);
+}
+// t0 + t1 + t2 = v (the differences are exact): the caller has scaled v.  In pairs: element by element
+// the compiler converts everything twice, once for its value and once for the pair it is stored in.
 __device__ inline void split_bf16_3(const F32x8& v, bf16x8& t0, bf16x8& t1, bf16x8& t2) {
+  typedef unsigned uintx4_ __attribute__((ext_vector_type(4)));
+  uintx4_ w0, w1, w2;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const float a = i < 4 ? v.lo4[i] : v.hi4[i - 4];
-    const __bf16 h = (__bf16)a;
-    const float r1 = a - (float)h;           // exact
-    const __bf16 m = (__bf16)r1;
-    t0[i] = h;
-    t1[i] = m;
-    t2[i] = (__bf16)(r1 - (float)m);         // the difference is exact
+  for (int i = 0; i < 4; ++i) {
+    float a = i < 2 ? v.lo4[2 * i] : v.hi4[2 * i - 4];
+    float b = i < 2 ? v.lo4[2 * i + 1] : v.hi4[2 * i - 3];
+    w0[i] = round2_bf16(a, b);
+    minus2_bf16(a, b, w0[i]);
+    w1[i] = round2_bf16(a, b);
+    minus2_bf16(a, b, w1[i]);
+    w2[i] = round2_bf16(a, b);
   }
+  t0 = __builtin_bit_cast(bf16x8, w0);
+  t1 = __builtin_bit_cast(bf16x8, w1);
+  t2 = __builtin_bit_cast(bf16x8, w2);
 }
 
 __device__ inline void split_bf16(const F32x8& v, bf16x8& hi, bf16x8& lo) {

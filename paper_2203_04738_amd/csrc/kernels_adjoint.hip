@@ -1395,9 +1395,10 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
         v.lo4[r] = p[r][e] * SPLIT3_SCALE;
         v.hi4[r] = p[4 + r][e] * SPLIT3_SCALE;
       }
-      // (a tree: one addition per slice into the long sum)
-      colsum[e] += ((p[0][e] + p[1][e]) + (p[2][e] + p[3][e])) +
-                   ((p[4][e] + p[5][e]) + (p[6][e] + p[7][e]));
+      // (a tree: one addition per slice into the long sum; only the first column tile reports it)
+      if (is_a && nt == 0)
+        colsum[e] += ((p[0][e] + p[1][e]) + (p[2][e] + p[3][e])) +
+                     ((p[4][e] + p[5][e]) + (p[6][e] + p[7][e]));
       bf16x8 t0, t1, t2;
       split_bf16_3(v, t0, t1, t2);
       *reinterpret_cast<bf16x8*>(dst + e * HS_LD) = t0;
