@@ -28,9 +28,11 @@ def fp32_peak(T, B, H, D, cf, levels):
     """Matrix peak that bounds the algorithmic flops of an fp32 GRU / LSTM problem: problems that the
     library contracts as three bf16 terms (six bf16 products per multiply-add) are priced against a
     sixth of the bf16 peak, the others against the fp32 peak (the rule is MGRIT_F32's, see
-    include/mgrit_gru.h)."""
+    include/mgrit_gru.h; its last condition, that the terms fit the gradient partials, holds from a few
+    thousand steps x batch on; layers of 128 columns take their steps in the fp32 sweep kernel up to
+    8192 rows)."""
     rows = T * B // (cf if levels > 1 else 1)
-    terms = H % 8 == 0 and H >= 128 and rows >= 1024
+    terms = H % 8 == 0 and rows >= 1024 and (H > 128 or (H == 128 and rows > 8192))
     return MI355X_PEAK["bf16_TFLOPs"] / 6.0 if terms else MI355X_PEAK["fp32_TFLOPs"]
 
 
@@ -287,8 +289,8 @@ def stack_main(args):
     names = {0: "phi_step (fused forward level step, MFMA tiles)",
              1: "adj_step (fused adjoint level step, MFMA tiles)",
              2: "projection GEMM", 3: "weight-gradient GEMMs + bias sums",
-             4: "phi_skinny (few-row forward step, coarsest level)",
-             5: "adj_skinny (few-row adjoint step, coarsest level)",
+             4: "phi_fewrow (serial solves, one launch each, and few-row forward steps)",
+             5: "adj_fewrow (serial solves, one launch each, and few-row adjoint steps)",
              6: "input-gradient GEMM"}
     kernels = {}
     for kind, nm in names.items():
@@ -297,6 +299,8 @@ def stack_main(args):
             kernels[nm] = {"launches_per_step": n / args.steps, "ms_per_step": ms / args.steps,
                            "avg_launch_us": 1e3 * ms / n, "TFLOPs": fl / ms / 1e9,
                            "algorithmic_GBps": by / ms / 1e6}
+            if kind in (4, 5):      # a solve is one launch of many steps: time per step of B rows
+                kernels[nm]["us_per_step_of_batch"] = 1e3 * ms / (fl / (6.0 * B * H * H))
     peak = (MI355X_PEAK["bf16_TFLOPs"] if x3 else
             fp32_peak(wl.T, wl.B, wl.H, wl.D, wl.cf, wl.levels))
     step_flops = sum(v["TFLOPs"] * v["ms_per_step"] * 1e9 for v in kernels.values())
@@ -755,9 +759,9 @@ def main():
                                 "unit": rf.get("unit"), "frac": rf.get("frac"),
                                 "launches_per_step": rf.get("launches_per_step")},
                 "few_row_steps": {k.split(" ")[0]: {"launches_per_step": v["launches_per_step"],
-                                                    "avg_launch_us": v["avg_launch_us"],
+                                                    "us_per_step_of_batch": v["us_per_step_of_batch"],
                                                     "ms_per_step": v["ms_per_step"]}
-                                  for k, v in r["kernels"].items() if "skinny" in k},
+                                  for k, v in r["kernels"].items() if "fewrow" in k},
                 "whole_step_frac_of_mfma_peak": r["whole_step"]["frac_of_mfma_peak"]}
     print(json.dumps(out))
 
@@ -915,8 +919,8 @@ def run_workload(args, light=False):
     names = {0: "phi_step (fused forward level step, MFMA tiles)",
              1: "adj_step (fused adjoint level step, MFMA tiles)",
              2: "projection GEMM", 3: "weight-gradient GEMMs + bias sums",
-             4: "phi_skinny (few-row forward step, coarsest level)",
-             5: "adj_skinny (few-row adjoint step, coarsest level)",
+             4: "phi_fewrow (serial solves, one launch each, and few-row forward steps)",
+             5: "adj_fewrow (serial solves, one launch each, and few-row adjoint steps)",
              7: "copy_points (coarse-grid correction, end conditions; HBM-bound)"}
     # dominant launch shape: the level-0 relaxation sub-step (all intervals x batch rows, epilogue
     # mode 0), read first; its launches are put back into the class total below
@@ -931,6 +935,8 @@ def run_workload(args, light=False):
             kernels[nm] = {"launches_per_step": n / args.steps, "ms_per_step": ms / args.steps,
                            "avg_launch_us": 1e3 * ms / n, "TFLOPs": fl / ms / 1e9,
                            "algorithmic_GBps": by / ms / 1e6}
+            if kind in (4, 5):      # a solve is one launch of many steps: time per step of B rows
+                kernels[nm]["us_per_step_of_batch"] = 1e3 * ms / (fl / (6.0 * B * H * H))
             if kind in (0, 1, 2, 3):
                 kernels[nm]["frac_of_mfma_peak"] = fl / ms / 1e9 / (
                     fp32_peak(T, B, H, wl.D, wl.cf, wl.levels) if dtype_code == 0

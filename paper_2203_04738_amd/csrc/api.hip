@@ -207,13 +207,17 @@ static bool misaligned(const void* p) { return ((uintptr_t)p & 15) != 0; }
 // ---------------------------------------------------------------------------
 // MGRIT_F32 runs the tile kernels on the bf16 matrix pipe, each fp32 operand as three bf16 terms
 // (exact; see gemm_core_bf16.h), where that is faster and no less accurate than the fp32 MFMAs.
-// (MGRIT_F32_BF16X3 asks for the terms on every shape.)  The line:
+// (MGRIT_F32_BF16X3 asks for the terms on every shape; its smallest launches and its layers of up to
+// 128 columns share the fp32 kernels of MGRIT_F32 all the same, which are no less accurate: state and
+// adjoint errors at 72, 104 and 128 columns 1.2-1.7e-7 and 6.5e-8 against 1.5-2.0e-7 and 7.1e-8 with
+// terms, at 520 to 1024 columns 1.3-1.9e-7 and 7.0-7.9e-8 against 1.6-2.1e-7 and 7.7-8.9e-8.)  The line:
 //  - widths are multiples of 8 (16-byte rows of terms), of at least 128 (64 for the projection).
 //    Error of a contraction against 64 bits: 1.35e-7 against 1.44e-7 of the fp32 MFMAs over 64
 //    columns, 2.5 : 2.9 over 256, 5.0 : 5.8 over 1024 (fewer additions into the sum), but 0.83 :
 //    0.73 over 16.  Below 128 columns nothing is gained in time;
 //  - GRU and LSTM (the ODE kernels have no such form);
-//  - 1024 rows or more in a level-0 launch.  Training step of two levels, fp32 MFMAs : terms:
+//  - 1024 rows or more in a level-0 launch (serial propagation: steps x batch; projection,
+//    coefficients and gradients take all steps in one launch there).  Training step of two levels, fp32 MFMAs : terms:
 //    256 rows x 1000 1.44 : 1.52 ms, 512 x 512 0.88 : 0.88, 1024 x 512 1.66 : 1.52, 4096 x 1000
 //    12.8 : 10.7;
 //  - the terms fit the space of the gradient partials, which nothing else uses until the last
