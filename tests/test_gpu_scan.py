@@ -250,3 +250,34 @@ def test_solves_on_several_streams_at_once():
                 mg.gru_serial_scan(cfg, *p, t["h0"], h, ws)
         torch.cuda.synchronize()
         assert all(torch.equal(h, a) for h, a in zip(outs, alone))
+
+
+@pytest.mark.parametrize("wait", [None, "0"])
+def test_replays_of_a_captured_solve(wait, monkeypatch):
+    # control words and marks are set by kernels of the solve itself: every replay starts afresh
+    if wait:
+        monkeypatch.setenv("MGRIT_SCAN_WAIT_TICKS", wait)
+    d, t, cfg, ws, p = _gru(6, 136, steps=40)
+    h, w = (torch.empty(41, 6, 136, device=DEV) for _ in range(2))
+    g = [torch.empty(3 * 136, 8, device=DEV), torch.empty(3 * 136, 136, device=DEV),
+         torch.empty(3 * 136, device=DEV), torch.empty(3 * 136, device=DEV)]
+
+    def solve():
+        mg.gru_serial_scan(cfg, *p, t["h0"], h, ws)
+        mg.gru_serial_scan_backward(cfg, *p, h, t["dL_dhT"], w, *g, ws)
+
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        solve()
+    torch.cuda.synchronize()
+    want = [a.clone() for a in (h, w, *g)]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        solve()
+    for k in range(3):
+        for a in (h, w, *g):
+            a.fill_(float(k))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip((h, w, *g), want)), k
