@@ -10,11 +10,11 @@
 // and the latency of a tile's only K slice; here a further sub-step costs about 1.4 us (half of it
 // MFMAs of the CU's fp32 pipe, the rest LDS, gates and the barrier).  Forward + backward of two layers
 // of 128 steps x 100 x 100: 1.76 -> 1.19 ms, training step 64 x 2 x 32: 0.45 -> 0.27 ms, 16384 x 4 x
-// 64: 11.2 -> 3.4 ms (levels of up to 8192 rows here, the finest on tiles: api.hip has the line).  Two quads per workgroup at a time spill and gain nothing (level 0 there: 30
-// against 25 us per launch).  The same
-// kernel takes the serial solves of these layers (one interval, N sub-steps), whose state then
-// travels through LDS instead of memory.  Workgroups loop over quads of rows, so that the weights
-// are loaded once per workgroup.
+// 64: 11.2 -> 3.4 ms (its levels of up to 8192 rows; the finest is on tiles, see sweeps_fused in
+// api.hip).  Two quads per workgroup at a time spill and gain nothing (800 quads: 30 against 25 us per
+// launch).  The same kernel takes the serial solves of these layers (one interval, N sub-steps), whose
+// state then travels through LDS instead of memory.  Workgroups loop over quads of rows, so that the
+// weights are loaded once per workgroup.
 #include <algorithm>
 
 #include "phi_elem.h"

@@ -40,23 +40,30 @@ def test_cycles_of_narrow_layers(gh, T, B, H, cf, levels, fine, prop):
             assert gh.rel_err(got, want) <= 1e-5
 
 
-@pytest.mark.parametrize("T,B,H,cf,levels,fine",
-                         [(16, 2048, 20, 4, 2, 1), (16, 2049, 20, 4, 2, 1), (8, 2049, 128, 2, 3, 0)])
-def test_cycles_at_the_row_bound(gh, T, B, H, cf, levels, fine):
+@pytest.mark.parametrize("T,B,H,cf,levels,fine,dtype",
+                         [(16, 2048, 20, 4, 2, 1, "fp32"), (16, 2049, 20, 4, 2, 1, "fp32"),
+                          (8, 2049, 128, 2, 3, 0, "fp32"), (16, 2049, 24, 4, 2, 1, "fp32x3")])
+def test_cycles_at_the_row_bound(gh, T, B, H, cf, levels, fine, dtype):
     # up to 8192 rows per launch a sweep is one launch, above it a chain; (8, 2049, ..) has the fine
     # level above the bound and the next one below it.  A declared zero guess of the adjoint starts
     # with the last intervals only: fewer rows
-    print("sweep case bound", T, B, H, cf, flush=True)
+    print("sweep case bound", T, B, H, cf, dtype, flush=True)
     d = random_small(T + B + H, T, B, 8, H, scale=0.3 / np.sqrt(H))
-    run = gh.GpuRun(d, cf=cf, levels=levels, fine_relax=fine)
+    run = gh.GpuRun(d, cf=cf, levels=levels, fine_relax=fine, dtype=dtype)
     P, z = (d["W"], d["U"], d["b_i"], d["b_h"]), np.zeros((T + 1, B, H))
     kw = dict(fine_relax_fcf=bool(fine))
     h_ref, _ = orc.mgrit_forward(*P, d["x"], d["h0"], z, cf, levels, 2, **kw)
     out = orc.mgrit_backward(*P, d["x"], h_ref, d["dL_dhT"], z, cf, levels, 2, **kw)
-    its, _ = run.forward_iterates(2, per_call=2)
-    assert gh.rel_err(its[-1], h_ref) <= 1e-5
+    box = []
+    gh.expect_kernels(lambda: box.append(run.forward_iterates(2, per_call=2)), "phi_sweep_kernel",
+                      *(["phi_step_kernel"] if T * B // cf > 8192 else []))
+    assert gh.rel_err(box[0][0][-1], h_ref) <= 1e-5
     for flags in (0, MGRIT_ZERO_ADJOINT_GUESS):
-        wits, _, grads = run.backward_iterates(h_ref, 2, per_call=2, first_call_flags=flags)
+        box = []
+        gh.expect_kernels(lambda: box.append(run.backward_iterates(h_ref, 2, per_call=2,
+                                                                   first_call_flags=flags)),
+                          "adj_sweep_kernel", *(["adj_step_kernel"] if T * B // cf > 8192 else []))
+        wits, _, grads = box[0]
         for got, want in zip((wits[-1],) + grads, (out[0],) + tuple(out[2:6])):
             assert gh.rel_err(got, want) <= 1e-5
 
