@@ -225,13 +225,26 @@ static bool misaligned(const void* p) { return ((uintptr_t)p & 15) != 0; }
 struct Forms {
   int rec, proj;            // operand form of the recurrent contractions and gradients / of W x
   char *U3, *UT3, *W3;      // three-term arrays (null: not needed)
+  size_t part_bytes;        // of the partials that they take, behind the control words
 };
 constexpr long long TERMS_MIN_ROWS = 1024;
 constexpr int TERMS_MIN_H = 128, TERMS_MIN_D = 64;
 constexpr size_t CTL_BYTES = 256;         // head of the partials: control words of the serial solves
 
+// Scratch of the serial solves' exchange: the end of the space of the gradient partials, behind the
+// control words and the terms, or the space of W^T, which the input gradients fill after every solve.
+// Null if it has room in neither.
+static float* scan_ring(const mgrit_gru_cfg& c, const Layout& lay, const Forms& f, char* base,
+                        int kind, int hidden) {
+  const size_t need = align_up(scan_ring_floats(kind, c.B, hidden) * sizeof(float));
+  if (need == 0) return nullptr;
+  if (CTL_BYTES + f.part_bytes + need <= lay.total_part)
+    return (float*)(base + lay.part + lay.total_part - need);
+  return need <= lay.part - lay.WT ? (float*)(base + lay.WT) : nullptr;
+}
+
 static Forms make_forms(const mgrit_gru_cfg& c, const Layout& lay, char* base) {
-  Forms f{kform(c.dtype), kform(c.dtype), nullptr, nullptr, nullptr};
+  Forms f{kform(c.dtype), kform(c.dtype), nullptr, nullptr, nullptr, 0};
   if (c.dtype == MGRIT_F32_BF16X3) {
     f.U3 = base + lay.U3;
     f.UT3 = base + lay.UT3;
@@ -250,6 +263,7 @@ static Forms make_forms(const mgrit_gru_cfg& c, const Layout& lay, char* base) {
   const size_t room = lay.total_part - CTL_BYTES;
   if (u3 + (u3 > w3 ? u3 : w3) > room) return f;
   f.rec = 2;
+  f.part_bytes = u3 + (u3 > w3 ? u3 : w3);
   f.U3 = base + lay.part + CTL_BYTES;
   f.UT3 = f.U3 + u3;                      // W3 and UT3 take turns: the projection comes first, the
   f.W3 = f.UT3;                           // input gradients after the last adjoint step
@@ -336,6 +350,7 @@ struct FwdCtx {
                                  // relaxation of level l - 1 fills along with it (or null)
   float dt;         // step size of level 0 (1 for the GRU propagators, Sec. 3.3)
   int* ctl;         // control words of the one-launch serial solves
+  float* ring;      // and the scratch of their exchange (or null)
   hipStream_t s;
 };
 
@@ -529,6 +544,7 @@ static int vcycle_fwd(const FwdCtx& x, int l, bool f_points_current = false, boo
       a.u = x.ul[l];
       a.g = x.gl[l];
       a.ctl = x.ctl;
+      a.ring = x.ring;
       a.N = (int)N;
       a.B = x.c->B;
       a.H = hidden;
@@ -695,6 +711,8 @@ static int forward_impl(const mgrit_gru_cfg* cin, bool serial, const void* W, co
   ctx.P = (const float*)(base + lay.P);
   ctx.dt = ode ? ode_dt : 1.f;
   ctx.ctl = (int*)(base + lay.part);     // (the gradient partials, formed after every solve)
+  ctx.ring = scan_ring(c, lay, forms, base, ode ? SCAN_ODE : lstm ? SCAN_LSTM : SCAN_GRU,
+                       lstm ? c.H / 2 : c.H);
   ctx.s = s;
   ctx.tmp = (float*)(base + lay.tmp);
   ctx.ul[0] = h;
@@ -740,6 +758,7 @@ struct BwdCtx {
   float* tmp;
   double* norm;
   int* ctl;         // as in FwdCtx
+  float* ring;
   hipStream_t s;
 };
 
@@ -855,6 +874,7 @@ static int vcycle_bwd(const BwdCtx& x, int l, bool f_points_current = false,
       a.u = x.wl[l];
       a.g = x.gl[l];
       a.ctl = x.ctl;
+      a.ring = x.ring;
       a.N = (int)N;
       a.B = x.c->B;
       a.H = x.c->H;
@@ -991,6 +1011,7 @@ static int backward_impl(const mgrit_gru_cfg* cin, bool serial, const void* W, c
   ctx.UT3 = forms.UT3;
   ctx.form = forms.rec;
   ctx.ctl = (int*)(base + lay.part);
+  ctx.ring = scan_ring(c, lay, forms, base, SCAN_ADJOINT, c.H);
   ctx.s = s;
   ctx.tmp = (float*)(base + lay.tmp);
   ctx.wl[0] = w;

@@ -21,11 +21,13 @@
 // Waves split K as well; the groups are added by lane swaps, the waves through LDS (one barrier
 // per step, two buffers).
 //
-// Measured against the chain of step launches: serial scan + back-propagation of 2048 steps x 32 x
-// 512 fp32 31.4 -> 14.7 ms (of which 4.4 ms are the GEMMs both share), scan of 512 steps x 8 x 1024
-// on bf16 weights 3.20 -> 1.61 ms, of 777 steps x 3 x 500 3.09 -> 1.61 ms (2.0 us per step: about
-// 1.3 us of exchange, 0.3 us of MFMAs, the rest LDS sums and gates).  A ninth wave that takes the
-// epilogue off the polling waves is slower (15.3 ms).
+// Shapes whose row blocks each fit one XCD run there and exchange through its L2 (kernels_scan_xcd.hip;
+// the rule and what both measure are at scan_shape_xcd); this file has the form for the others, what both
+// share on the host, and the launch that takes over what neither could start.
+//
+// Measured against the chain of step launches: scan of 512 steps x 8 x 1024 on bf16 weights 3.20 -> 1.61
+// ms, of 777 steps x 3 x 500 3.09 -> 1.61 ms (2.0 us per step: about 1.3 us of exchange, 0.3 us of MFMAs,
+// the rest LDS sums and gates).
 //
 // Residency.  Each workgroup keeps its columns for the whole solve, which needs all of them resident
 // at once: each announces itself and waits, with a time limit, until all have arrived before it takes
@@ -43,73 +45,10 @@
 #include <atomic>
 #include <cstdlib>
 
-#include "gates.h"
-#include "gemm_core_bf16.h"
-#include "quad.h"
-#include "scan.h"
+#include "scan_exchange.h"
 
 namespace mg {
 
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-constexpr unsigned SENTINEL = 0xffffffffu;
-constexpr int SCAN_MAXW = 8;                 // waves per workgroup
-constexpr int SCAN_MAXWG = 256;              // workgroups of a solve at most (one per CU)
-constexpr int SCAN_CP = 16;                  // hidden columns per workgroup
-// Limit of the wait for all workgroups, in ticks of the 100 MHz clock: half a microsecond per step (a
-// quarter of the solve), 50 us (several times what an arrival on a free GPU takes) to 5 ms.
-constexpr long long SCAN_ARRIVE_PER_STEP = 50, SCAN_ARRIVE_MIN = 5000, SCAN_ARRIVE_MAX = 500000;
-constexpr long long SCAN_STEP_TICKS = 200000000;     // 2 s: bound of a single wait, all resident
-constexpr int SCAN_MAX_POLLS = 1 << 24;              // the same, items from the counter (counted in
-                                                     // polls: a GPU that is taken away counts none)
-
-template <int KIND>
-struct ScanGates {
-  static constexpr int value = KIND == SCAN_LSTM ? 4 : KIND == SCAN_ODE ? 1 : 3;
-};
-
-// N 16-byte loads at agent scope, all in flight together; base is uniform, off[] are byte offsets
-// of the lane.  The wait is part of the block: the results are valid when it ends.  So are the five
-// wait states between a vector instruction that writes the scalar base (v_readfirstlane) and the
-// first load that reads it: the compiler keeps that distance for its own instructions only.
-__device__ inline void scan_load(uintx4 (&v)[1], const float* base, const unsigned (&off)[1]) {
-  asm volatile("s_nop 4\n\tglobal_load_dwordx4 %0, %1, %2 sc1\n\ts_waitcnt vmcnt(0)"
-               : "=&v"(v[0]) : "v"(off[0]), "s"(base) : "memory");
-}
-__device__ inline void scan_load(uintx4 (&v)[2], const float* base, const unsigned (&off)[2]) {
-  asm volatile("s_nop 4\n\tglobal_load_dwordx4 %0, %2, %4 sc1\n\tglobal_load_dwordx4 %1, %3, %4 sc1\n\t"
-               "s_waitcnt vmcnt(0)"
-               : "=&v"(v[0]), "=&v"(v[1]) : "v"(off[0]), "v"(off[1]), "s"(base) : "memory");
-}
-__device__ inline void scan_load(uintx4 (&v)[4], const float* base, const unsigned (&off)[4]) {
-  asm volatile("s_nop 4\n\tglobal_load_dwordx4 %0, %4, %8 sc1\n\tglobal_load_dwordx4 %1, %5, %8 sc1\n\t"
-               "global_load_dwordx4 %2, %6, %8 sc1\n\tglobal_load_dwordx4 %3, %7, %8 sc1\n\t"
-               "s_waitcnt vmcnt(0)"
-               : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
-               : "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base) : "memory");
-}
-__device__ inline void scan_load(uintx4 (&v)[8], const float* base, const unsigned (&off)[8]) {
-  asm volatile("s_nop 4\n\tglobal_load_dwordx4 %0, %8, %16 sc1\n\tglobal_load_dwordx4 %1, %9, %16 sc1\n\t"
-               "global_load_dwordx4 %2, %10, %16 sc1\n\tglobal_load_dwordx4 %3, %11, %16 sc1\n\t"
-               "global_load_dwordx4 %4, %12, %16 sc1\n\tglobal_load_dwordx4 %5, %13, %16 sc1\n\t"
-               "global_load_dwordx4 %6, %14, %16 sc1\n\tglobal_load_dwordx4 %7, %15, %16 sc1\n\t"
-               "s_waitcnt vmcnt(0)"
-               : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]),
-                 "=&v"(v[6]), "=&v"(v[7])
-               : "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "v"(off[4]), "v"(off[5]),
-                 "v"(off[6]), "v"(off[7]), "s"(base) : "memory");
-}
-
-// The address is the same in every lane of the wave; this puts it into scalar registers.
-__device__ inline const float* scan_uniform(const float* p) {
-  const unsigned long long b = (unsigned long long)p;
-  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b);
-  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
-  return (const float*)(((unsigned long long)hi << 32) | lo);
-}
-
-__device__ inline int ctl_load(const int* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 // next item of a solve whose workgroups are not all resident
 __device__ inline long long ctl_take(int* ctl) {
   return (long long)__hip_atomic_fetch_add((unsigned long long*)(ctl + 2), 1ULL, __ATOMIC_RELAXED,
@@ -122,38 +61,18 @@ __device__ inline float scan_own(const float* p) {
     b = __hip_atomic_load((const unsigned*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return __uint_as_float(b);
 }
-__device__ inline long long ticks() { return (long long)__builtin_amdgcn_s_memrealtime(); }
-
-// A result that happens to be the sentinel (a NaN) is stored as another NaN.
-__device__ inline unsigned scan_bits(float val) {
-  const unsigned b = __float_as_uint(val);
-  return b == SENTINEL ? 0x7fc00000u : b;
-}
-// Column l % 16 of quad column 0 gathers its quad: lanes with l % 4 == 0 hold four consecutive
-// columns of a row and store them as one 16-byte access at agent scope.
-__device__ inline void scan_store(float* p, float val, bool ok) {
-  const unsigned b = scan_bits(val);
-  uintx4 v;
-  v[0] = b;
-  v[1] = __builtin_amdgcn_mov_dpp(b, 0x55, 0xf, 0xf, true);   // quad_perm [1,1,1,1]
-  v[2] = __builtin_amdgcn_mov_dpp(b, 0xaa, 0xf, 0xf, true);
-  v[3] = __builtin_amdgcn_mov_dpp(b, 0xff, 0xf, 0xf, true);
-  if (ok && (threadIdx.x & 3) == 0)
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
-}
-
 // NCH: chunks of 64 k per wave; RB: groups of four rows per workgroup.  Registers: NG 16 NCH
 // weights; one workgroup per CU is planned for (two waves per SIMD at eight waves).
 // ITEMS: the workgroup takes (step, unit) items from the counter until none are left; otherwise it
 // takes every step of the unit it was launched as, once all workgroups of the solve are resident, and
 // leaves what remains to the launch with ITEMS behind it if they are not (see the top of the file).
 template <int KIND, int NCH, int RB, class WT, bool ITEMS>
-__global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int nrb) {
+__global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int nrb, int xcd_quads) {
   constexpr int NG = ScanGates<KIND>::value;
   constexpr bool ADJ = KIND == SCAN_ADJOINT;
   constexpr int NS = ADJ ? 1 : NG;                    // sums an output needs
   constexpr int NL = RB * NCH;
-  constexpr int NP = RB * NG == 1 ? 2 : 1;            // sums per gate and row group
+  constexpr int NP = NG == 1 ? 2 : 1;                 // sums per gate and row group
   __shared__ float part[2][SCAN_MAXW][RB][NS][64];
   __shared__ int stop[2];
   __shared__ long long item;
@@ -170,8 +89,15 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
 
   long long mine = 0;                                 // thread 0: the item after the current one
   int unit = blockIdx.x, first = 0, last = N;
+  int done = 0;                                       // row quads before this one are solved
   if (ITEMS) {
+    for (long long q = (long long)blockIdx.x * blockDim.x + tid; q < a.ring4;
+         q += (long long)gridDim.x * blockDim.x)
+      ((uintx4*)a.ring)[q] = uintx4{0, 0, 0, 0};
     if (ctl_load(a.ctl + 1) == 0) return;             // all were resident: the solve is done
+    if (a.ring && ctl_load(a.ctl + CTL_ABORT) == 0)
+      done = xcd_groups((unsigned)ctl_load(a.ctl + CTL_WORD)) * xcd_quads;
+    if (done * 4 >= B) return;
     if (tid == 0) mine = ctl_take(a.ctl);
   }
   if (tid < 2) stop[tid] = 0;
@@ -189,6 +115,10 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
       last = first + 1;
     }
     const int rb = unit % nrb, cg = unit / nrb;
+    if (ITEMS && (rb + 1) * RB <= done) {
+      __syncthreads();                                 // (every thread has read item)
+      continue;
+    }
     const int r0 = rb * RB * 4, j0 = cg * SCAN_CP;
     // weights: column j0 + lane % 16, k = kw0 + 64 c + 16 (lane / 16) + 0..15 (zero beyond H; columns
     // beyond H repeat the last one and are never stored)
@@ -226,7 +156,8 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
     for (int r = 0; r < RB; ++r) {
       const int row = min(r0 + 4 * r + (lane & 3), B - 1);
 #pragma unroll
-      for (int c = 0; c < NCH; ++c) off[r * NCH + c] = ((unsigned)row * W + kk[c]) * 4u;
+      for (int c = 0; c < NCH; ++c)
+        off[r * NCH + c] = ((unsigned)row * W + kk[c]) * 4u;
       if (ADJ) koff[r] = (unsigned)row * a.kw;
     }
     // output element of this lane
@@ -389,33 +320,10 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
                  ((ps[g][4] + ps[g][5]) + (ps[g][6] + ps[g][7]));
         }
         float out, outc = 0.f;
-        if constexpr (KIND == SCAN_GRU) {
-          const float rg = sigmoidf_(cp[0] + s[0] + bias[0]);
-          const float zg = sigmoidf_(cp[1] + s[1] + bias[1]);
-          const float n = tanhf_(cp[2] + rg * (s[2] + bias[2]));
-          const float c = a.gamma * (1.0f - zg);
-          out = a.implicit_ ? (prev + c * n) * fast_rcp(1.0f + c) : prev + c * (n - prev);
-        } else if constexpr (KIND == SCAN_LSTM) {
-          const float ig = sigmoidf_(s[0] + cp[0] + bias[0]);
-          const float fg = sigmoidf_(s[1] + cp[1] + bias[1]);
-          const float gg = tanhf_(s[2] + cp[2] + bias[2]);
-          const float og = sigmoidf_(s[3] + cp[3] + bias[3]);
-          if (a.implicit_) {
-            outc = (prevc + a.gamma * ig * gg) * fast_rcp(1.0f + a.gamma * (1.0f - fg));
-            out = (prev + a.gamma * og * tanhf_(outc)) * fast_rcp(1.0f + a.gamma);
-          } else {
-            outc = prevc + a.gamma * (ig * gg - (1.0f - fg) * prevc);
-            out = prev + a.gamma * (og * tanhf_(outc) - prev);
-          }
-          outc += cgc;
-        } else if constexpr (KIND == SCAN_ODE) {
-          out = prev + a.gamma * (sigmoidf_(s[0] + cp[0]) - 0.5f * prev);
-        } else {
-          out = ckd * prev + s[0];
-        }
-        out += cgv;
+        scan_element<KIND>(a, s, cp, bias, ckd, prev, prevc, cgv, cgc, out, outc);
         float* dst = a.u + out_pt(i) * BW + eo;
-        scan_store(dst, out, ok);
+        const uintx4 quad = scan_quad(out);
+        if (ok && (tid & 3) == 0) scan_store_agent(dst, quad);
         if (KIND == SCAN_LSTM && ok) {
           if (ITEMS)                                   // (read by the workgroup of the next step)
             __hip_atomic_store((unsigned*)dst + H, scan_bits(outc), __ATOMIC_RELAXED,
@@ -432,20 +340,41 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
   } while (ITEMS);
 }
 
-// Marks the points the solve will write and clears its control words.
-__global__ __launch_bounds__(256) void scan_mark_kernel(uintx4* p, long long n4, int* ctl) {
-  if (blockIdx.x == 0 && threadIdx.x < 4) ctl[threadIdx.x] = 0;
+// Marks the points the solve will write, clears its control words and fills the rings (ring4 units of
+// four floats; see kernels_scan_xcd.hip): slot 0 is the state u0 the solve starts from (adjoint: its
+// products with the coefficients k0 of the first step), the others are marked.
+__global__ __launch_bounds__(256) void scan_mark_kernel(uintx4* p, long long n4, ScanArgs a,
+                                                        const float* u0, const float* k0, int W, int rows,
+                                                        int hp) {
+  if (blockIdx.x == 0 && threadIdx.x < CTL_WORDS) a.ctl[threadIdx.x] = 0;
   const uintx4 s = {SENTINEL, SENTINEL, SENTINEL, SENTINEL};
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n4; i += 256LL * gridDim.x)
-    p[i] = s;
+  const long long t0 = (long long)blockIdx.x * 256 + threadIdx.x, dt = 256LL * gridDim.x;
+  for (long long i = t0; i < n4; i += dt) p[i] = s;
+  const int vec4 = rows / 4 * hp, nvec = k0 ? 3 : 1;   // units of a vector: [row quad][k / 4][row]
+  for (long long i = t0; i < a.ring4; i += dt) {
+    const int q = (int)(i % vec4), vec = (int)(i / vec4 % nvec);
+    const long long slot = i / vec4 / nvec;
+    const int k = q % hp / 4 * 4;
+    uintx4 v = s;
+    if (k >= a.H) {
+      v = uintx4{0, 0, 0, 0};
+    } else if ((slot & 3) == 0) {
+      const int row = (int)(slot >> 2) * rows + q / hp * 4 + (q & 3);
+      floatx4 f = zero4();
+      if (row < a.B) {
+        f = ldg4(u0 + (long long)row * W + k);
+        if (k0) f *= ldg4(k0 + (long long)row * a.kw + vec * a.H + k);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = scan_bits(f[e]);
+    }
+    ((uintx4*)a.ring)[i] = v;
+  }
 }
 
 // ---------------------------------------------------------------------------
 // launch
 // ---------------------------------------------------------------------------
-struct ScanShape {
-  int nch, nw, rb, nrb, ncg;
-};
 // Workgroups that can be resident whatever the kernel's registers: one per CU of the current device
 // (a partition of the GPU has fewer than the whole).
 static int scan_max_wg() {
@@ -461,17 +390,50 @@ static int scan_max_wg() {
   return n < SCAN_MAXWG ? n : SCAN_MAXWG;
 }
 static ScanShape scan_shape(int B, int H) {
-  const int max_wg = scan_max_wg();
+  const int max_wg = scan_max_wg(), quads = (B + 3) / 4;
   ScanShape s;
   s.nch = H > 64 * SCAN_MAXW ? 2 : 1;
   s.nw = (H + 64 * s.nch - 1) / (64 * s.nch);
   s.ncg = (H + SCAN_CP - 1) / SCAN_CP;
-  const int quads = (B + 3) / 4;
   s.rb = 1;
   while (s.rb < 8 && (quads + s.rb - 1) / s.rb * s.ncg > max_wg) s.rb *= 2;
   s.nrb = (quads + s.rb - 1) / s.rb;
   if (s.nw < s.rb) s.nw = s.rb;                       // wave r finishes row group r
   return s;
+}
+
+// A row block per XCD (kernels_scan_xcd.hip): false if the shape does not fit or gains nothing.
+// Up to 512 columns, 16 per workgroup, us per step here : all CUs through memory, forward / adjoint:
+// 32 x 512 1.27 / 1.28 : 1.81 / 2.54, 64 x 512 1.9 / 2.1 : 3.7 / 4.0, 16 x 256 0.97 / 0.91 : 1.50 / 1.59,
+// 3 x 500 1.22 / 1.23 : 2.00 / 2.23, LSTM 32 x 512 1.54 : 2.87.  Beyond, 32 per workgroup fill the
+// registers of a CU and the fp32 matrix pipe takes half of the step: 32 x 1024 2.6 / 2.9 : 5.8 / 6.0, 16 x
+// 768 2.6 / 2.9 : 2.9 / 3.4, but 8 x 1024 2.7 / 3.0 : 3.0 / 3.6, and a second solve on another stream,
+// for which the other form leaves half of the CUs, would wait: only where that form takes more.
+static bool scan_shape_xcd(int kind, int B, int H, ScanShape& s) {
+  if (scan_max_wg() != SCAN_XCDS * SCAN_XCD_CUS) return false;
+  const int quads = (B + 3) / 4;
+  s.ct = H > 512 ? 2 : 1;
+  s.hp = H > 512 ? 1024 : H > 256 ? 512 : 256;
+  s.ncg = (H + s.ct * SCAN_CP - 1) / (s.ct * SCAN_CP);
+  const int fit = SCAN_XCD_CUS / s.ncg * SCAN_XCDS;    // row blocks, each with all its columns in one XCD
+  if (fit == 0) return false;
+  s.rb = (quads + fit - 1) / fit;
+  if (s.ct == 2) {
+    const int ncg16 = (H + SCAN_CP - 1) / SCAN_CP;
+    // (registers: four gates do not fit, nor do two quads of the adjoint's products)
+    if (kind == SCAN_LSTM || quads * ncg16 <= SCAN_MAXWG / 2 || (kind == SCAN_ADJOINT && s.rb > 1))
+      return false;
+  }
+  if (s.rb > 2) return false;
+  s.nrb = (quads + s.rb - 1) / s.rb;
+  s.gpx = (s.nrb + SCAN_XCDS - 1) / SCAN_XCDS;
+  s.nx = (s.nrb + s.gpx - 1) / s.gpx;
+  return true;
+}
+size_t scan_ring_floats(int kind, int B, int H) {
+  ScanShape s;
+  return scan_shape_xcd(kind, B, H, s) ? (size_t)16 * s.rb * s.nrb * s.hp * (kind == SCAN_ADJOINT ? 3 : 1)
+                                       : 0;
 }
 
 // Up to 64 rows (the few-row range of the step kernels) of 16 to 1024 columns.  A solve costs
@@ -485,18 +447,20 @@ bool scan_covers(int kind, long long N, int B, int H) {
   return s.rb <= limit && s.nrb * s.ncg <= scan_max_wg();
 }
 
+// xs: the shape of the form with a row block per XCD, null: this form
 template <int KIND, int NCH, int RB, class WT>
-static void launch_scan_shape(const ScanArgs& a, dim3 grid, dim3 block, int nrb, hipStream_t st) {
-  hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT, false>), grid, block, 0, st, a, nrb);
-  hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT, true>), grid, block, 0, st, a, nrb);
+static void launch_scan_shape(const ScanArgs& a, const ScanShape& s, const ScanShape* xs, hipStream_t st) {
+  const dim3 grid((unsigned)(s.nrb * s.ncg)), block(64 * s.nw);
+  if (xs) (void)launch_scan_xcd(KIND, a, *xs, st);
+  else hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT, false>), grid, block, 0, st, a, s.nrb, 0);
+  hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT, true>), grid, block, 0, st, a, s.nrb,
+                     xs ? xs->gpx * xs->rb : 0);
 }
 template <int KIND, class WT>
-static void launch_scan_kind(const ScanArgs& a, hipStream_t st) {
+static void launch_scan_kind(const ScanArgs& a, const ScanShape* xs, hipStream_t st) {
   const ScanShape s = scan_shape(a.B, a.H);
-  const dim3 grid((unsigned)(s.nrb * s.ncg)), block(64 * s.nw);
-#define MG_SCAN_CASE(NCH, RB)                                                                  \
-  if (s.nch == NCH && s.rb == RB)                                                              \
-    launch_scan_shape<KIND, NCH, RB, WT>(a, grid, block, s.nrb, st);
+#define MG_SCAN_CASE(NCH, RB) \
+  if (s.nch == NCH && s.rb == RB) launch_scan_shape<KIND, NCH, RB, WT>(a, s, xs, st);
   MG_SCAN_CASE(1, 1)
   MG_SCAN_CASE(1, 2)
   MG_SCAN_CASE(1, 4)
@@ -518,21 +482,29 @@ hipError_t launch_scan(int kind, const ScanArgs& a0, hipStream_t st) {
   const int W = kind == SCAN_LSTM ? 2 * a.H : a.H;
   const int prof = kind == SCAN_GRU ? 4 : kind == SCAN_ADJOINT ? 5 : kind == SCAN_LSTM ? 9 : 8;
   prof_begin(prof, st, a.B, STEP_RELAX);
-  const long long n4 = (long long)a.N * a.B * W / 4;
+  ScanShape xshape{};
+  const bool xcd = a.ring && scan_shape_xcd(kind, a.B, a.H, xshape);
+  const ScanShape* xs = xcd ? &xshape : nullptr;
+  if (!xcd) a.ring = nullptr;
+  a.ring4 = xcd ? (long long)scan_ring_floats(kind, a.B, a.H) / 4 : 0;
+  const long long n4 = (long long)a.N * a.B * W / 4, BW = (long long)a.B * W;
   const long long nb = (n4 + 255) / 256;
   hipLaunchKernelGGL(scan_mark_kernel, dim3((unsigned)(nb < 4096 ? nb : 4096)), dim3(256), 0, st,
-                     (uintx4*)(a.u + (kind == SCAN_ADJOINT ? 0 : (long long)a.B * W)), n4, a.ctl);
+                     (uintx4*)(a.u + (kind == SCAN_ADJOINT ? 0 : BW)), n4, a,
+                     a.u + (kind == SCAN_ADJOINT ? a.N * BW : 0),
+                     kind == SCAN_ADJOINT ? a.kap + (long long)a.N * a.B * a.kw : nullptr, W,
+                     4 * xshape.rb, xshape.hp);
   const bool h16 = a.bf16 == 1;
   if (kind == SCAN_GRU) {
-    if (h16) launch_scan_kind<SCAN_GRU, bf16_t>(a, st);
-    else launch_scan_kind<SCAN_GRU, float>(a, st);
+    if (h16) launch_scan_kind<SCAN_GRU, bf16_t>(a, xs, st);
+    else launch_scan_kind<SCAN_GRU, float>(a, xs, st);
   } else if (kind == SCAN_ADJOINT) {
-    if (h16) launch_scan_kind<SCAN_ADJOINT, bf16_t>(a, st);
-    else launch_scan_kind<SCAN_ADJOINT, float>(a, st);
+    if (h16) launch_scan_kind<SCAN_ADJOINT, bf16_t>(a, xs, st);
+    else launch_scan_kind<SCAN_ADJOINT, float>(a, xs, st);
   } else if (kind == SCAN_LSTM) {
-    launch_scan_kind<SCAN_LSTM, float>(a, st);
+    launch_scan_kind<SCAN_LSTM, float>(a, xs, st);
   } else {
-    launch_scan_kind<SCAN_ODE, float>(a, st);
+    launch_scan_kind<SCAN_ODE, float>(a, xs, st);
   }
   const double rows = (double)a.N * a.B;
   const int ng = kind == SCAN_LSTM ? 4 : kind == SCAN_ODE ? 1 : 3;

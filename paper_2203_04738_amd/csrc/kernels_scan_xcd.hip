@@ -1,0 +1,354 @@
+// Serial propagation of a few rows as one launch, each block of rows inside one XCD.
+//
+// The rows of a batch do not meet in a serial solve, so a block of rows needs no other XCD than the one
+// that computes it, if that XCD holds all recurrent weights (its 32 CUs have 16 MB of registers).  The
+// state then travels through the L2 of the XCD instead of the memory side (see kernels_scan.hip for the
+// rest of the scheme, which is the same: weights in registers, row quads, waves split K).
+//
+// Exchange.  A row block has a ring of four state rows, [slot][row quad][k / 4][row][4]: a workgroup's
+// columns of a quad are contiguous, and so are 64 k of a quad for the wave that loads them.  (The adjoint
+// has three vectors per slot, the products of the state with the coefficients of the step: who makes
+// an element multiplies it, and nobody else loads the coefficients.)  Slot i % 4
+// receives state i; every word is marked (SENTINEL) before it is written and polled until it has changed.
+// With state i + 1 a workgroup marks its part of slot i - 1 again: it has seen all of state i, so every
+// workgroup has read all of state i - 1.  The mark is in the L2 before the workgroup's part of state i + 2
+// is sent (its epilogue waves wait for their stores when they poll for state i + 1), and nobody looks at
+// that slot for the mark's successor, state i + 3, before it has seen all of state i + 2.  Stores go to
+// the L2 (vector stores pass through the L1), polls at agent scope pass by the L1.  The ring stays in L2:
+// rows of the output array polled there instead cost 0.83 us per exchange (each line is fetched from
+// memory first), the ring 0.53 us, the exchange through memory 1.37 us (32 workgroups of 16 columns, four
+// rows; the exchange alone).
+//
+// Which XCD a workgroup runs on it reads from the hardware (XCC_ID).  The launch has enough workgroups
+// to fill what it needs on every XCD; the XCD whose workgroups have all arrived takes the next group of
+// row blocks (xcd_role), the others leave when all are taken.  A group that is taken has all its
+// workgroups resident and needs nothing else.  If an XCD does not fill up in time, its workgroups leave
+// and the takeover launch solves the row blocks that are left (scan_kernel<.., true>), with the same bits.
+#include "scan_exchange.h"
+
+namespace mg {
+
+// Stores to the L2 of this XCD.
+__device__ inline void ring_store(float* p, uintx4 v) {
+  asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
+}
+// XCD this wave runs on (hardware register XCC_ID, bits 2:0).
+__device__ inline int scan_xcd() { return __builtin_amdgcn_s_getreg((2 << 11) | (0 << 6) | 20); }
+// One thread per workgroup.  The group of row blocks the XCD of this workgroup takes, -1: none.  The
+// workgroup that completes the `per` workgroups of an XCD claims the next of the `need` groups for it;
+// the others wait for that, until all groups are given away, or until the time limit, when they close
+// their XCD (nobody may start there any more) and leave the rest to the launch behind.
+__device__ inline int xcd_role(int* ctl, int xcd, int ticket, int per, int need, long long wait_ticks) {
+  if (ticket >= per) return -1;
+  unsigned* word = (unsigned*)ctl + CTL_WORD;
+  const int sh = 4 * xcd;
+  const long long t0 = ticks();
+  while (true) {
+    unsigned w = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned v = (w >> sh) & 15;
+    if (v) return v == XCD_CLOSED ? -1 : (int)v - 1;
+    const int n = xcd_groups(w);
+    if (n >= need) return -1;
+    const bool closes = ticket < per - 1 && ticks() - t0 >= wait_ticks;
+    if (closes || ticket == per - 1) {
+      const unsigned mine = closes ? XCD_CLOSED : (unsigned)n + 1;
+      if (__hip_atomic_compare_exchange_strong(word, &w, w | (mine << sh), __ATOMIC_RELAXED,
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+        if (!closes) return n;
+        __hip_atomic_store(ctl + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return -1;
+      }
+      continue;
+    }
+    __builtin_amdgcn_s_sleep(1);
+  }
+}
+
+// A 16-byte load at agent scope (passes by the L1), never merged with another one.
+__device__ inline uintx4 ring_load(__amdgpu_buffer_rsrc_t ring, unsigned off, unsigned slot) {
+  constexpr int SC1_VOLATILE = (1 << 4) | (1 << 31);
+  return __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(ring, (int)off, (int)slot,
+                                                                          SC1_VOLATILE));
+}
+constexpr int WAIT_VMCNT_0 = 0x0f70;                   // (no other counter)
+template <int NL>
+__device__ inline bool ring_waits(const uintx4 (&v)[NL]) {
+  unsigned top = 0;                                    // SENTINEL is the largest word
+#pragma unroll
+  for (int q = 0; q < NL; ++q)
+    top = max(max(max(top, v[q][0]), max(v[q][1], v[q][2])), v[q][3]);
+  return top == SENTINEL;
+}
+// NW waves of NV x NCH chunks of 64 k (NV sums over NCH chunks each: what a wave of scan_kernel sums, so
+// the bits are the same); RB row quads, CT tiles of 16 columns per workgroup.  Wave e < RB CT finishes
+// the elements of quad e % RB, tile e / RB (waves of their own for that are no faster: 1.38 against 1.35
+// us per step at 32 x 512, where they make nine of eight).
+template <int KIND, int CT, int NV, int NCH, int NW, int RB, class WT>
+__global__ __launch_bounds__(64 * NW) void xcd_scan_kernel(ScanArgs a, ScanShape sh) {
+  constexpr int NG = ScanGates<KIND>::value;
+  constexpr bool ADJ = KIND == SCAN_ADJOINT;
+  constexpr int NS = ADJ ? 1 : NG;
+  constexpr int AG = ScanVectors<KIND>::value;
+  constexpr int NC = NV * NCH, NL = AG * RB * NC;
+  constexpr int NP = NG == 1 ? 2 : 1;
+  constexpr int HP = 64 * NC * NW;                     // columns of a ring row, zero from H on
+  constexpr unsigned VEC = RB * HP * 4, SLOT = AG * VEC;    // floats
+  __shared__ float part[2][NW * NV][RB * CT][NS][64];
+  __shared__ int stop, role;
+  const int H = a.H, B = a.B, N = a.N;
+  const int W = KIND == SCAN_LSTM ? 2 * H : H;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  if (tid == 0) {
+    const int x = scan_xcd();
+    const int ticket = __hip_atomic_fetch_add(a.ctl + CTL_TICKETS + x, 1, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+    const int g = xcd_role(a.ctl, x, ticket, sh.gpx * sh.ncg, sh.nx, a.wait_ticks);
+    const int r = g * sh.gpx + ticket / sh.ncg;
+    role = g < 0 || r >= sh.nrb ? -1 : ticket % sh.ncg * sh.nrb + r;
+    stop = 0;
+  }
+  __syncthreads();
+  const int unit = __builtin_amdgcn_readfirstlane(role);
+  if (unit < 0) return;
+  const int rb = unit % sh.nrb, cg = unit / sh.nrb;
+  const int r0 = rb * RB * 4, j0 = cg * CT * SCAN_CP;
+  const long long BW = (long long)B * W;
+  auto in_pt = [&](int i) { return (long long)(ADJ ? N - i : i); };
+  auto out_pt = [&](int i) { return (long long)(ADJ ? N - i - 1 : i + 1); };
+  float* const ring = a.ring + (long long)rb * 4 * SLOT;
+  const __amdgpu_buffer_rsrc_t rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(ring, 0, 4 * SLOT * 4, 0x00027000);
+
+  const int kw0 = wv * 64 * NC;
+  const bool epi = wv < RB * CT;
+  const int er = wv % RB, et = wv / RB;
+  // weights: column j0 + 16 t + lane % 16, k = kw0 + 64 c + 16 (lane / 16) + 0..15 (zero beyond H;
+  // columns beyond H repeat the last one and are never stored)
+  float w[NC][CT * NG][16];
+#pragma unroll
+  for (int t = 0; t < CT; ++t) {
+    const int j = min(j0 + t * SCAN_CP + (lane & 15), H - 1);
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int k = kw0 + 64 * c + 16 * (lane >> 4) + 4 * q;
+          const int kc = min(k, H - 4);
+          const WT* p = (const WT*)a.Wt +
+                        (ADJ ? (long long)j * 3 * H + g * H + kc : ((long long)g * H + j) * H + kc);
+          const floatx4 v = k < H ? ldg4w(p) : zero4();
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            w[c][t * NG + g][4 * q + e] = v[e];
+            if (sizeof(WT) == 2) asm volatile("" : "+v"(w[c][t * NG + g][4 * q + e]));   // (as floats)
+          }
+        }
+  }
+  // polled operand: row quad r, row lane % 4, k = kw0 + 64 c + 4 (lane / 4) + 0..3; lanes beyond the
+  // rows read a row that is there (their sums are not stored)
+  unsigned off[RB];
+#pragma unroll
+  for (int r = 0; r < RB; ++r) {
+    const int row = min(r0 + 4 * r + (lane & 3), B - 1) - r0;
+    off[r] = (unsigned)(((row >> 2) * (HP >> 2) + (kw0 >> 2) + (lane >> 2)) * 16 + (row & 3) * 4) * 4u;
+  }
+  // element of this lane; lane q of four stores 16 bytes: 0 the new state (adjoint: 0..2 its products
+  // with the three coefficients of the next step) to the ring, 1 (0..2) the mark, 2 (3) the output
+  const int orow = r0 + 4 * er + quad_row(lane), oj = j0 + et * SCAN_CP + (lane & 15);
+  const int erow = min(orow, B - 1), ej = min(oj, H - 1), q4 = lane & 3;
+  const bool ok = epi && orow < B && oj < H;
+  const unsigned eo = (unsigned)erow * W + ej;
+  const unsigned po = (unsigned)erow * (ADJ ? a.kw : NG * H) + ej;
+  const unsigned quado = (unsigned)((er * (HP >> 2) + (ej >> 2)) * 16 + quad_row(lane) * 4);
+  const unsigned kqo = (unsigned)erow * (ADJ ? a.kw : 0) + min(q4, 2) * H + (ej & ~3);
+  constexpr int OUT_LANE = ADJ ? 3 : 2;
+  constexpr uintx4 MARK = {SENTINEL, SENTINEL, SENTINEL, SENTINEL};
+  float* const lane_base = q4 == OUT_LANE ? a.u + (eo & ~3u) : ring + quado + (ADJ ? q4 * VEC : 0);
+  float bias[NG], p[NG], kd = 0.f, g = 0.f, gc = 0.f;
+  floatx4 kq = zero4();
+#pragma unroll
+  for (int q = 0; q < NG; ++q) {
+    bias[q] = (KIND == SCAN_GRU || KIND == SCAN_LSTM) && epi ? a.b_h[q * H + ej] : 0.f;
+    p[q] = 0.f;
+  }
+  // what step i needs beside the state (kq: of the step behind it)
+  auto request = [&](int i) {
+    if (ADJ) {
+      kd = (a.kap + in_pt(i) * B * a.kw + 3 * H)[po];
+      kq = ldg4(a.kap + in_pt(min(i + 1, N - 1)) * B * a.kw + kqo);
+    } else {
+      const float* pr = a.P + ((long long)(i + 1) * a.pstep - 1) * B * ((long long)NG * H);
+#pragma unroll
+      for (int q = 0; q < NG; ++q) p[q] = (pr + q * H)[po];
+    }
+    if (a.g) {
+      const float* gr = a.g + out_pt(i) * BW;
+      g = gr[eo];
+      if (KIND == SCAN_LSTM) gc = (gr + H)[eo];
+    }
+  };
+  float prev = 0.f, prevc = 0.f;                       // element of the row the step starts from
+  if (epi) {
+    request(0);
+    const float* u0 = a.u + in_pt(0) * BW;
+    prev = u0[eo];
+    if (KIND == SCAN_LSTM) prevc = (u0 + H)[eo];
+  }
+
+  for (int i = 0; i < N; ++i) {
+    const unsigned slot = (unsigned)(i & 3) * (SLOT * 4);
+    uintx4 v[NL];
+    auto load = [&]() {
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+          for (int g2 = 0; g2 < AG; ++g2)
+            v[(c * RB + r) * AG + g2] = ring_load(rsrc, off[r] + c * 1024 + g2 * VEC * 4, slot);
+    };
+    load();
+    bool leave = false;
+    for (int polls = 1; __any(ring_waits(v)); ++polls) {
+      if ((polls & 127) == 0) {
+        if (polls >= SCAN_MAX_POLLS) {
+          __hip_atomic_store(a.ctl + CTL_ABORT, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(a.ctl + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        leave = ctl_load(a.ctl + CTL_ABORT) != 0;
+        if (leave) break;
+      }
+      load();
+    }
+    if (leave) {
+      stop = 1;                                        // (seen by the epilogue waves behind the barrier)
+      __syncthreads();
+      return;
+    }
+    // the marks this wave made in the step before are in the L2 (the loads above are younger: no wait)
+    __builtin_amdgcn_s_waitcnt(WAIT_VMCNT_0);
+    float cp[NG];
+#pragma unroll
+    for (int q = 0; q < NG; ++q) cp[q] = p[q];
+    const float cgv = g, cgc = gc, ckd = kd;
+    const floatx4 ckq = kq;
+    if (epi) request(min(i + 1, N - 1));
+    // where this lane stores 16 bytes (see above)
+    const int sl = ADJ ? (i + 1) & 3 : (i + 1 + 2 * (q4 & 1)) & 3;
+    const long long so = q4 == OUT_LANE ? out_pt(i) * BW : (long long)(sl * (int)SLOT);
+    float* sp = lane_base + so;
+    asm volatile("" : "+v"(sp));                       // (computed before the barrier)
+    float (*pt)[RB * CT][NS][64] = part[i & 1];
+#pragma unroll
+    for (int h = 0; h < NV; ++h) {
+      floatx4 acc[RB][CT * NG][NP];
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int q = 0; q < CT * NG; ++q)
+#pragma unroll
+          for (int n = 0; n < NP; ++n) acc[r][q][n] = zero4();
+#pragma unroll
+      for (int c = h * NCH; c < (h + 1) * NCH; ++c)
+        quad_mma<RB, CT * NG, NP>(
+            acc, [&](int r, int q) { return __builtin_bit_cast(floatx4, v[(c * RB + r) * AG + (ADJ ? q % NG : 0)]); },
+            [&](int q) -> const float (&)[16] { return w[c][q]; });
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int t = 0; t < CT; ++t) {
+          floatx4 sum[NG];
+#pragma unroll
+          for (int q = 0; q < NG; ++q)
+            sum[q] = NP > 1 ? acc[r][t * NG + q][0] + acc[r][t * NG + q][NP - 1] : acc[r][t * NG + q][0];
+          if (ADJ) {
+            pt[wv * NV + h][t * RB + r][0][lane] = quad_fold(sum[0] + sum[NG > 1 ? 1 : 0] + sum[NG - 1]);
+          } else {
+#pragma unroll
+            for (int q = 0; q < NG; ++q)
+              pt[wv * NV + h][t * RB + r][ADJ ? 0 : q][lane] = quad_fold(sum[q]);
+          }
+        }
+    }
+    __syncthreads();
+    if (epi) {
+      // partial sums (every read in flight before the first addition)
+      float s[NS], ps[NS][SCAN_MAXW];
+#pragma unroll
+      for (int q = 0; q < NS; ++q)
+#pragma unroll
+        for (int n = 0; n < SCAN_MAXW; ++n) ps[q][n] = n < NW * NV ? pt[n < NW * NV ? n : 0][wv][q][lane] : 0.f;
+      const int stopped = stop;
+#pragma unroll
+      for (int q = 0; q < NS; ++q)
+        s[q] = ((ps[q][0] + ps[q][1]) + (ps[q][2] + ps[q][3])) +
+               ((ps[q][4] + ps[q][5]) + (ps[q][6] + ps[q][7]));
+      float out, outc = 0.f;
+      scan_element<KIND>(a, s, cp, bias, ckd, prev, prevc, cgv, cgc, out, outc);
+      const uintx4 quad = scan_quad(out);
+      if (stopped) return;
+      if constexpr (ADJ) {
+        uintx4 pr;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const unsigned b = scan_bits(ckq[e] * __uint_as_float(quad[e]));
+          pr[e] = q4 == OUT_LANE ? quad[e] : b;
+        }
+        if (ok) {
+          ring_store(sp, pr);
+          if (q4 != OUT_LANE) ring_store(lane_base + (i + 3 & 3) * (int)SLOT, MARK);
+        }
+      } else {
+        uintx4 d;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[e] = q4 == 1 ? SENTINEL : quad[e];
+        if (ok && q4 <= OUT_LANE) ring_store(sp, d);
+        if (KIND == SCAN_LSTM && ok) (a.u + out_pt(i) * BW + H)[eo] = outc;
+      }
+      prev = out;
+      prevc = outc;
+    }
+  }
+}
+
+template <int KIND, int CT, int NV, int NCH, int NW, int RB, class WT>
+static void launch(const ScanArgs& a, const ScanShape& s, hipStream_t st) {
+  // (workgroups go to the XCDs in turn)
+  hipLaunchKernelGGL((xcd_scan_kernel<KIND, CT, NV, NCH, NW, RB, WT>),
+                     dim3((unsigned)(SCAN_XCDS * s.gpx * s.ncg)), dim3(64 * NW), 0, st, a, s);
+}
+template <int KIND, class WT>
+static void launch_kind(const ScanArgs& a, const ScanShape& s, hipStream_t st) {
+  if (s.ct == 1 && s.hp == 256 && s.rb == 1) return launch<KIND, 1, 1, 1, 4, 1, WT>(a, s, st);
+  if (s.ct == 1 && s.hp == 256 && s.rb == 2) return launch<KIND, 1, 1, 1, 4, 2, WT>(a, s, st);
+  if (s.ct == 1 && s.hp == 512 && s.rb == 1) return launch<KIND, 1, 1, 1, 8, 1, WT>(a, s, st);
+  if (s.ct == 1 && s.hp == 512 && s.rb == 2) return launch<KIND, 1, 1, 1, 8, 2, WT>(a, s, st);
+  if constexpr (KIND == SCAN_ADJOINT)
+    if (s.ct == 2 && s.rb == 1) return launch<KIND, 2, 2, 2, 4, 1, WT>(a, s, st);
+  if constexpr (KIND == SCAN_GRU || KIND == SCAN_ODE) {
+    if (s.ct == 2 && s.rb == 1) return launch<KIND, 2, 1, 2, 8, 1, WT>(a, s, st);
+    if (s.ct == 2 && s.rb == 2) return launch<KIND, 2, 2, 2, 4, 2, WT>(a, s, st);
+  }
+}
+
+hipError_t launch_scan_xcd(int kind, const ScanArgs& a, const ScanShape& s, hipStream_t st) {
+  const bool h16 = a.bf16 == 1;
+  if (kind == SCAN_GRU) {
+    if (h16) launch_kind<SCAN_GRU, bf16_t>(a, s, st);
+    else launch_kind<SCAN_GRU, float>(a, s, st);
+  } else if (kind == SCAN_ADJOINT) {
+    if (h16) launch_kind<SCAN_ADJOINT, bf16_t>(a, s, st);
+    else launch_kind<SCAN_ADJOINT, float>(a, s, st);
+  } else if (kind == SCAN_LSTM) {
+    launch_kind<SCAN_LSTM, float>(a, s, st);
+  } else {
+    launch_kind<SCAN_ODE, float>(a, s, st);
+  }
+  return hipGetLastError();
+}
+
+}  // namespace mg
