@@ -236,7 +236,7 @@ constexpr size_t CTL_BYTES = 256;         // head of the partials: control words
 // Null if it has room in neither.
 static float* scan_ring(const mgrit_gru_cfg& c, const Layout& lay, const Forms& f, char* base,
                         int kind, int hidden) {
-  const size_t need = align_up(scan_ring_floats(kind, c.B, hidden) * sizeof(float));
+  const size_t need = align_up(scan_ring_floats(kind, c.B, hidden, kform(c.dtype)) * sizeof(float));
   if (need == 0) return nullptr;
   if (CTL_BYTES + f.part_bytes + need <= lay.total_part)
     return (float*)(base + lay.part + lay.total_part - need);

@@ -66,7 +66,8 @@ __device__ inline float scan_own(const float* p) {
 // ITEMS: the workgroup takes (step, unit) items from the counter until none are left; otherwise it
 // takes every step of the unit it was launched as, once all workgroups of the solve are resident, and
 // leaves what remains to the launch with ITEMS behind it if they are not (see the top of the file).
-template <int KIND, int NCH, int RB, class WT, bool ITEMS>
+// TERMS (items behind xcd_scan_kernel on bf16 weights): its contraction, for the same bits.
+template <int KIND, int NCH, int RB, class WT, bool ITEMS, bool TERMS>
 __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int nrb, int xcd_quads) {
   constexpr int NG = ScanGates<KIND>::value;
   constexpr bool ADJ = KIND == SCAN_ADJOINT;
@@ -76,6 +77,7 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
   __shared__ float part[2][SCAN_MAXW][RB][NS][64];
   __shared__ int stop[2];
   __shared__ long long item;
+  __shared__ uintx4 frag[TERMS ? SCAN_MAXW : 1][TERMS ? 128 : 1];   // 64 k of a quad in terms, per wave
   const int H = a.H, B = a.B, N = a.N;
   const int W = KIND == SCAN_LSTM ? 2 * H : H;        // state row
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6;
@@ -123,7 +125,19 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
     // weights: column j0 + lane % 16, k = kw0 + 64 c + 16 (lane / 16) + 0..15 (zero beyond H; columns
     // beyond H repeat the last one and are never stored)
     float w[NG][NCH][16];
-    {
+    bf16x8 wt[NG][NCH][2];
+    if constexpr (TERMS) {
+      const int j = min(j0 + (lane & 15), H - 1);
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+            wt[g][c][b] = term_weights((const bf16_t*)a.Wt + ((long long)g * H + j) * H,
+                                       kw0 + 64 * c + 32 * b + 8 * (lane >> 4), H);
+      frag[wv][(lane >> 5) * 64 + (lane >> 3 & 3) * 16 + 12 + (lane & 3)] = uintx4{0, 0, 0, 0};
+    } else {
       const int j = min(j0 + (lane & 15), H - 1);
 #pragma unroll
       for (int g = 0; g < NG; ++g)
@@ -285,6 +299,38 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
         for (int g = 0; g < NG; ++g)
 #pragma unroll
           for (int q = 0; q < NP; ++q) acc[r][g][q] = zero4();
+      if constexpr (TERMS) {
+        // each wave sorts its rows into fragments through LDS of its own
+        typedef unsigned u2 __attribute__((ext_vector_type(2)));
+        u2* const put = (u2*)frag[wv] + ((lane >> 5) * 64 + (lane >> 3 & 3) * 16 + (lane & 3)) * 2 +
+                         (lane >> 2 & 1);
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+          floatx4 sum[NG];
+#pragma unroll
+          for (int g = 0; g < NG; ++g) sum[g] = zero4();
+#pragma unroll
+          for (int c = 0; c < NCH; ++c) {
+            StateTerms t[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t[e] = state_terms(op[c][r][0][e]);
+            auto lo = [](unsigned a0, unsigned a1) { return (a0 & 0xffffu) | (a1 << 16); };
+            auto hi = [](unsigned a0, unsigned a1) { return (a0 >> 16) | (a1 & 0xffff0000u); };
+            put[0] = u2{lo(t[0].t01, t[1].t01), lo(t[2].t01, t[3].t01)};
+            put[8] = u2{hi(t[0].t01, t[1].t01), hi(t[2].t01, t[3].t01)};
+            put[16] = u2{lo(t[0].t2, t[1].t2), lo(t[2].t2, t[3].t2)};
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            const uintx4 f[2] = {frag[wv][lane], frag[wv][64 + lane]};
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+              for (int g = 0; g < NG; ++g) sum[g] = term_mma(f[b], wt[g][c][b], sum[g]);
+          }
+#pragma unroll
+          for (int g = 0; g < NG; ++g) part[buf][wv][r][g][lane] = term_fold(sum[g]);
+        }
+      } else {
 #pragma unroll
       for (int c = 0; c < NCH; ++c)
         quad_mma<RB, NG, NP>(acc, [&](int r, int g) { return op[c][r][ADJ ? g : 0]; },
@@ -301,6 +347,7 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
 #pragma unroll
           for (int g = 0; g < NG; ++g) part[buf][wv][r][ADJ ? 0 : g][lane] = quad_fold(sum[g]);
         }
+      }
       }
       __syncthreads();
       const int stopped = stop[buf];
@@ -345,11 +392,33 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
 // products with the coefficients k0 of the first step), the others are marked.
 __global__ __launch_bounds__(256) void scan_mark_kernel(uintx4* p, long long n4, ScanArgs a,
                                                         const float* u0, const float* k0, int W, int rows,
-                                                        int hp) {
+                                                        int hp, int terms) {
   if (blockIdx.x == 0 && threadIdx.x < CTL_WORDS) a.ctl[threadIdx.x] = 0;
   const uintx4 s = {SENTINEL, SENTINEL, SENTINEL, SENTINEL};
   const long long t0 = (long long)blockIdx.x * 256 + threadIdx.x, dt = 256LL * gridDim.x;
   for (long long i = t0; i < n4; i += dt) p[i] = s;
+  if (terms) {     // [row block][slot][row quad][k / 32][k / 8 % 4][term][row] of eight bf16
+    for (long long i = t0; i < a.ring4; i += dt) {
+      const int row4 = (int)(i & 3), t = (int)(i >> 2 & 3), k = (int)(i / 16 % (hp / 8)) * 8;
+      const long long q = i / 16 / (hp / 8);
+      const int quads = rows / 4, row = ((int)(q / quads / 4) * quads + (int)(q % quads)) * 4 + row4;
+      uintx4 v = s;
+      if (t == 3 || k >= a.H) {
+        v = uintx4{0, 0, 0, 0};
+      } else if ((q / quads & 3) == 0) {
+        unsigned h[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const StateTerms x = state_terms(row < a.B ? u0[(long long)row * W + k + e] : 0.f);
+          h[e] = t == 0 ? x.t01 & 0xffffu : t == 1 ? x.t01 >> 16 : x.t2;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = h[2 * e] | (h[2 * e + 1] << 16);
+      }
+      ((uintx4*)a.ring)[i] = v;
+    }
+    return;
+  }
   const int vec4 = rows / 4 * hp, nvec = k0 ? 3 : 1;   // units of a vector: [row quad][k / 4][row]
   for (long long i = t0; i < a.ring4; i += dt) {
     const int q = (int)(i % vec4), vec = (int)(i / vec4 % nvec);
@@ -409,9 +478,12 @@ static ScanShape scan_shape(int B, int H) {
 // registers of a CU and the fp32 matrix pipe takes half of the step: 32 x 1024 2.6 / 2.9 : 5.8 / 6.0, 16 x
 // 768 2.6 / 2.9 : 2.9 / 3.4, but 8 x 1024 2.7 / 3.0 : 3.0 / 3.6, and a second solve on another stream,
 // for which the other form leaves half of the CUs, would wait: only where that form takes more.
-static bool scan_shape_xcd(int kind, int B, int H, ScanShape& s) {
+// GRU on bf16 weights contracts terms of the state (ScanTerms): 8 x 512 1.01 : 2.00, 1 x 1024 1.42 : 2.25, 8 x
+// 1024 1.53 : 3.02, 64 x 1024 2.3 : 9.4, at any number of rows (two solves of 8 x 1024 at once 0.89 : 1.82 ms).
+static bool scan_shape_xcd(int kind, int B, int H, int bf16, ScanShape& s) {
   if (scan_max_wg() != SCAN_XCDS * SCAN_XCD_CUS) return false;
   const int quads = (B + 3) / 4;
+  s.terms = kind == SCAN_GRU && bf16 == 1;
   s.ct = H > 512 ? 2 : 1;
   s.hp = H > 512 ? 1024 : H > 256 ? 512 : 256;
   s.ncg = (H + s.ct * SCAN_CP - 1) / (s.ct * SCAN_CP);
@@ -421,7 +493,8 @@ static bool scan_shape_xcd(int kind, int B, int H, ScanShape& s) {
   if (s.ct == 2) {
     const int ncg16 = (H + SCAN_CP - 1) / SCAN_CP;
     // (registers: four gates do not fit, nor do two quads of the adjoint's products)
-    if (kind == SCAN_LSTM || quads * ncg16 <= SCAN_MAXWG / 2 || (kind == SCAN_ADJOINT && s.rb > 1))
+    if (kind == SCAN_LSTM || (!s.terms && quads * ncg16 <= SCAN_MAXWG / 2) ||
+        (kind == SCAN_ADJOINT && s.rb > 1))
       return false;
   }
   if (s.rb > 2) return false;
@@ -430,10 +503,10 @@ static bool scan_shape_xcd(int kind, int B, int H, ScanShape& s) {
   s.nx = (s.nrb + s.gpx - 1) / s.gpx;
   return true;
 }
-size_t scan_ring_floats(int kind, int B, int H) {
+size_t scan_ring_floats(int kind, int B, int H, int bf16) {
   ScanShape s;
-  return scan_shape_xcd(kind, B, H, s) ? (size_t)16 * s.rb * s.nrb * s.hp * (kind == SCAN_ADJOINT ? 3 : 1)
-                                       : 0;
+  if (!scan_shape_xcd(kind, B, H, bf16, s)) return 0;
+  return (size_t)16 * s.rb * s.nrb * s.hp * (kind == SCAN_ADJOINT ? 3 : s.terms ? 2 : 1);
 }
 
 // Up to 64 rows (the few-row range of the step kernels) of 16 to 1024 columns.  A solve costs
@@ -452,8 +525,15 @@ template <int KIND, int NCH, int RB, class WT>
 static void launch_scan_shape(const ScanArgs& a, const ScanShape& s, const ScanShape* xs, hipStream_t st) {
   const dim3 grid((unsigned)(s.nrb * s.ncg)), block(64 * s.nw);
   if (xs) (void)launch_scan_xcd(KIND, a, *xs, st);
-  else hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT, false>), grid, block, 0, st, a, s.nrb, 0);
-  hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT, true>), grid, block, 0, st, a, s.nrb,
+  else hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT, false, false>), grid, block, 0, st, a, s.nrb, 0);
+  if constexpr (ScanTerms<KIND, WT>::value) {
+    if (xs) {
+      hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT, true, true>), grid, block, 0, st, a, s.nrb,
+                         xs->gpx * xs->rb);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT, true, false>), grid, block, 0, st, a, s.nrb,
                      xs ? xs->gpx * xs->rb : 0);
 }
 template <int KIND, class WT>
@@ -483,17 +563,17 @@ hipError_t launch_scan(int kind, const ScanArgs& a0, hipStream_t st) {
   const int prof = kind == SCAN_GRU ? 4 : kind == SCAN_ADJOINT ? 5 : kind == SCAN_LSTM ? 9 : 8;
   prof_begin(prof, st, a.B, STEP_RELAX);
   ScanShape xshape{};
-  const bool xcd = a.ring && scan_shape_xcd(kind, a.B, a.H, xshape);
+  const bool xcd = a.ring && scan_shape_xcd(kind, a.B, a.H, a.bf16, xshape);
   const ScanShape* xs = xcd ? &xshape : nullptr;
   if (!xcd) a.ring = nullptr;
-  a.ring4 = xcd ? (long long)scan_ring_floats(kind, a.B, a.H) / 4 : 0;
+  a.ring4 = xcd ? (long long)scan_ring_floats(kind, a.B, a.H, a.bf16) / 4 : 0;
   const long long n4 = (long long)a.N * a.B * W / 4, BW = (long long)a.B * W;
   const long long nb = (n4 + 255) / 256;
   hipLaunchKernelGGL(scan_mark_kernel, dim3((unsigned)(nb < 4096 ? nb : 4096)), dim3(256), 0, st,
                      (uintx4*)(a.u + (kind == SCAN_ADJOINT ? 0 : BW)), n4, a,
                      a.u + (kind == SCAN_ADJOINT ? a.N * BW : 0),
                      kind == SCAN_ADJOINT ? a.kap + (long long)a.N * a.B * a.kw : nullptr, W,
-                     4 * xshape.rb, xshape.hp);
+                     4 * xshape.rb, xshape.hp, xshape.terms);
   const bool h16 = a.bf16 == 1;
   if (kind == SCAN_GRU) {
     if (h16) launch_scan_kind<SCAN_GRU, bf16_t>(a, xs, st);

@@ -19,6 +19,12 @@
 // memory first), the ring 0.53 us, the exchange through memory 1.37 us (32 workgroups of 16 columns, four
 // rows; the exchange alone).
 //
+// On bf16 weights the GRU contracts on the bf16 matrix pipe, which is 16 times as fast: the state travels
+// as three bf16 terms (exact: state_terms), which fill 12 of the 16 rows of v_mfma_f32_16x16x32_bf16 for
+// four state rows, [slot][row quad][k / 32][k / 8 % 4][term][row][8]; products of terms and weights are
+// exact, the sums fp32.  8 x 1024: 0.3 instead of 1.3 us of MFMAs per step, half the registers; states
+// 1.07e-7 from 64 bits (fp32 MFMAs 1.09e-7; 8 x 512 1.05 : 1.06, 3 x 64 1.02 : 1.03).
+//
 // Which XCD a workgroup runs on it reads from the hardware (XCC_ID).  The launch has enough workgroups
 // to fill what it needs on every XCD; the XCD whose workgroups have all arrived takes the next group of
 // row blocks (xcd_role), the others leave when all are taken.  A group that is taken has all its
@@ -64,6 +70,10 @@ __device__ inline int xcd_role(int* ctl, int xcd, int ticket, int per, int need,
   }
 }
 
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+__device__ inline void ring_store(float* p, uintx2 v) {
+  asm volatile("global_store_dwordx2 %0, %1, off\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
+}
 // A 16-byte load at agent scope (passes by the L1), never merged with another one.
 __device__ inline uintx4 ring_load(__amdgpu_buffer_rsrc_t ring, unsigned off, unsigned slot) {
   constexpr int SC1_VOLATILE = (1 << 4) | (1 << 31);
@@ -89,10 +99,12 @@ __global__ __launch_bounds__(64 * NW) void xcd_scan_kernel(ScanArgs a, ScanShape
   constexpr bool ADJ = KIND == SCAN_ADJOINT;
   constexpr int NS = ADJ ? 1 : NG;
   constexpr int AG = ScanVectors<KIND>::value;
-  constexpr int NC = NV * NCH, NL = AG * RB * NC;
+  constexpr int NC = NV * NCH, NL = (ScanTerms<KIND, WT>::value ? 2 : AG) * RB * NC;
   constexpr int NP = NG == 1 ? 2 : 1;
   constexpr int HP = 64 * NC * NW;                     // columns of a ring row, zero from H on
-  constexpr unsigned VEC = RB * HP * 4, SLOT = AG * VEC;    // floats
+  constexpr bool TERMS = ScanTerms<KIND, WT>::value;
+  constexpr int KB = 2 * NC;                           // TERMS: blocks of 32 k per wave
+  constexpr unsigned VEC = RB * HP * 4, SLOT = TERMS ? 2 * VEC : AG * VEC;    // floats
   __shared__ float part[2][NW * NV][RB * CT][NS][64];
   __shared__ int stop, role;
   const int H = a.H, B = a.B, N = a.N;
@@ -127,9 +139,19 @@ __global__ __launch_bounds__(64 * NW) void xcd_scan_kernel(ScanArgs a, ScanShape
   // weights: column j0 + 16 t + lane % 16, k = kw0 + 64 c + 16 (lane / 16) + 0..15 (zero beyond H;
   // columns beyond H repeat the last one and are never stored)
   float w[NC][CT * NG][16];
+  bf16x8 wt[KB][CT * NG];
 #pragma unroll
   for (int t = 0; t < CT; ++t) {
     const int j = min(j0 + t * SCAN_CP + (lane & 15), H - 1);
+    if constexpr (TERMS) {
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int b = 0; b < KB; ++b)
+          wt[b][t * NG + g] = term_weights((const bf16_t*)a.Wt + ((long long)g * H + j) * H,
+                                           kw0 + 32 * b + 8 * (lane >> 4), H);
+      continue;
+    }
 #pragma unroll
     for (int g = 0; g < NG; ++g)
 #pragma unroll
@@ -154,8 +176,12 @@ __global__ __launch_bounds__(64 * NW) void xcd_scan_kernel(ScanArgs a, ScanShape
 #pragma unroll
   for (int r = 0; r < RB; ++r) {
     const int row = min(r0 + 4 * r + (lane & 3), B - 1) - r0;
-    off[r] = (unsigned)(((row >> 2) * (HP >> 2) + (kw0 >> 2) + (lane >> 2)) * 16 + (row & 3) * 4) * 4u;
+    if (TERMS)
+      off[r] = (unsigned)(((row >> 2) * (HP >> 5) + (kw0 >> 5)) * 64 + (lane & ~3) + (row & 3)) * 16u;
+    else
+      off[r] = (unsigned)(((row >> 2) * (HP >> 2) + (kw0 >> 2) + (lane >> 2)) * 16 + (row & 3) * 4) * 4u;
   }
+  // (terms: lane l reads term l / 4 % 4 of row l % 4, k = kw0 + 32 b + 8 (l / 16) + 0..7)
   // element of this lane; lane q of four stores 16 bytes: 0 the new state (adjoint: 0..2 its products
   // with the three coefficients of the next step) to the ring, 1 (0..2) the mark, 2 (3) the output
   const int orow = r0 + 4 * er + quad_row(lane), oj = j0 + et * SCAN_CP + (lane & 15);
@@ -163,9 +189,12 @@ __global__ __launch_bounds__(64 * NW) void xcd_scan_kernel(ScanArgs a, ScanShape
   const bool ok = epi && orow < B && oj < H;
   const unsigned eo = (unsigned)erow * W + ej;
   const unsigned po = (unsigned)erow * (ADJ ? a.kw : NG * H) + ej;
-  const unsigned quado = (unsigned)((er * (HP >> 2) + (ej >> 2)) * 16 + quad_row(lane) * 4);
+  const unsigned quado =
+      TERMS ? (unsigned)((((er * (HP >> 5) + (ej >> 5)) * 4 + (ej >> 3 & 3)) * 16 + min(q4, 2) * 4 +
+                          quad_row(lane)) * 4 + (ej >> 2 & 1) * 2)
+            : (unsigned)((er * (HP >> 2) + (ej >> 2)) * 16 + quad_row(lane) * 4);
   const unsigned kqo = (unsigned)erow * (ADJ ? a.kw : 0) + min(q4, 2) * H + (ej & ~3);
-  constexpr int OUT_LANE = ADJ ? 3 : 2;
+  constexpr int OUT_LANE = ADJ || TERMS ? 3 : 2;
   constexpr uintx4 MARK = {SENTINEL, SENTINEL, SENTINEL, SENTINEL};
   float* const lane_base = q4 == OUT_LANE ? a.u + (eo & ~3u) : ring + quado + (ADJ ? q4 * VEC : 0);
   float bias[NG], p[NG], kd = 0.f, g = 0.f, gc = 0.f;
@@ -203,12 +232,19 @@ __global__ __launch_bounds__(64 * NW) void xcd_scan_kernel(ScanArgs a, ScanShape
     const unsigned slot = (unsigned)(i & 3) * (SLOT * 4);
     uintx4 v[NL];
     auto load = [&]() {
+      if constexpr (TERMS) {
+#pragma unroll
+        for (int b = 0; b < KB; ++b)
+#pragma unroll
+          for (int r = 0; r < RB; ++r) v[b * RB + r] = ring_load(rsrc, off[r] + b * 1024, slot);
+        return;
+      }
 #pragma unroll
       for (int c = 0; c < NC; ++c)
 #pragma unroll
         for (int r = 0; r < RB; ++r)
 #pragma unroll
-          for (int g2 = 0; g2 < AG; ++g2)
+          for (int g2 = 0; g2 < (TERMS ? 0 : AG); ++g2)
             v[(c * RB + r) * AG + g2] = ring_load(rsrc, off[r] + c * 1024 + g2 * VEC * 4, slot);
     };
     load();
@@ -238,13 +274,30 @@ __global__ __launch_bounds__(64 * NW) void xcd_scan_kernel(ScanArgs a, ScanShape
     const floatx4 ckq = kq;
     if (epi) request(min(i + 1, N - 1));
     // where this lane stores 16 bytes (see above)
-    const int sl = ADJ ? (i + 1) & 3 : (i + 1 + 2 * (q4 & 1)) & 3;
+    const int sl = ADJ || TERMS ? (i + 1) & 3 : (i + 1 + 2 * (q4 & 1)) & 3;
     const long long so = q4 == OUT_LANE ? out_pt(i) * BW : (long long)(sl * (int)SLOT);
     float* sp = lane_base + so;
     asm volatile("" : "+v"(sp));                       // (computed before the barrier)
     float (*pt)[RB * CT][NS][64] = part[i & 1];
+    if constexpr (TERMS) {
+      floatx4 acc[RB][CT * NG];
 #pragma unroll
-    for (int h = 0; h < NV; ++h) {
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int q = 0; q < CT * NG; ++q) acc[r][q] = zero4();
+#pragma unroll
+      for (int b = 0; b < KB; ++b)
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+          for (int q = 0; q < CT * NG; ++q) acc[r][q] = term_mma(v[b * RB + r], wt[b][q], acc[r][q]);
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int q = 0; q < CT * NG; ++q) pt[wv][q / NG * RB + r][q % NG][lane] = term_fold(acc[r][q]);
+    }
+#pragma unroll
+    for (int h = 0; h < (TERMS ? 0 : NV); ++h) {
       floatx4 acc[RB][CT * NG][NP];
 #pragma unroll
       for (int r = 0; r < RB; ++r)
@@ -300,7 +353,29 @@ __global__ __launch_bounds__(64 * NW) void xcd_scan_kernel(ScanArgs a, ScanShape
         }
         if (ok) {
           ring_store(sp, pr);
-          if (q4 != OUT_LANE) ring_store(lane_base + (i + 3 & 3) * (int)SLOT, MARK);
+          if (q4 != OUT_LANE) ring_store(lane_base + ((i + 3) & 3) * (int)SLOT, MARK);
+        }
+      } else if constexpr (TERMS) {
+        // lane q < 3 of four stores term q of the four columns
+        const StateTerms x = state_terms(out);
+        unsigned y[4];
+#define MG_GATHER(e, ctrl)                                                        \
+  {                                                                               \
+    const unsigned y01 = __builtin_amdgcn_mov_dpp(x.t01, ctrl, 0xf, 0xf, true);   \
+    const unsigned y2 = __builtin_amdgcn_mov_dpp(x.t2, ctrl, 0xf, 0xf, true);     \
+    y[e] = q4 == 2 ? y2 : y01;                                                    \
+  }
+        MG_GATHER(0, 0x00) MG_GATHER(1, 0x55) MG_GATHER(2, 0xaa) MG_GATHER(3, 0xff)
+#undef MG_GATHER
+        const unsigned half = q4 == 1 ? 0x07060302u : 0x05040100u;
+        const uintx2 d = {__builtin_amdgcn_perm(y[1], y[0], half), __builtin_amdgcn_perm(y[3], y[2], half)};
+        if (ok) {
+          if (q4 != OUT_LANE) {
+            ring_store(sp, d);
+            ring_store(lane_base + ((i + 3) & 3) * (int)SLOT, uintx2{SENTINEL, SENTINEL});
+          } else {
+            ring_store(sp, quad);
+          }
         }
       } else {
         uintx4 d;
@@ -331,7 +406,11 @@ static void launch_kind(const ScanArgs& a, const ScanShape& s, hipStream_t st) {
     if (s.ct == 2 && s.rb == 1) return launch<KIND, 2, 2, 2, 4, 1, WT>(a, s, st);
   if constexpr (KIND == SCAN_GRU || KIND == SCAN_ODE) {
     if (s.ct == 2 && s.rb == 1) return launch<KIND, 2, 1, 2, 8, 1, WT>(a, s, st);
-    if (s.ct == 2 && s.rb == 2) return launch<KIND, 2, 2, 2, 4, 2, WT>(a, s, st);
+    if constexpr (ScanTerms<KIND, WT>::value) {
+      if (s.ct == 2 && s.rb == 2) return launch<KIND, 2, 1, 2, 8, 2, WT>(a, s, st);
+    } else {
+      if (s.ct == 2 && s.rb == 2) return launch<KIND, 2, 2, 2, 4, 2, WT>(a, s, st);
+    }
   }
 }
 

@@ -18,7 +18,7 @@ struct ScanArgs {
   const float* g;      // right-hand side, laid out like u (may be null)
   int* ctl;            // device words: [0] workgroups that have arrived, [1] not all came in time,
                        // [2..3] (64 bits) next item, the rest in kernels_scan.hip
-  float* ring;         // scan_ring_floats(kind, B, H) floats, or null: exchange through memory
+  float* ring;         // scan_ring_floats(...) floats, or null: exchange through memory
   long long ring4;     // (set by launch_scan)
   int N, B, H, kw;
   long long pstep;     // forward: step k reads projection point k * pstep - 1
@@ -31,7 +31,7 @@ struct ScanArgs {
 // True if a solve of N steps over B rows of hidden width H runs as one launch.
 bool scan_covers(int kind, long long N, int B, int H);
 // Scratch with which the exchange runs inside the XCDs (0: this shape does not).
-size_t scan_ring_floats(int kind, int B, int H);
+size_t scan_ring_floats(int kind, int B, int H, int bf16);
 hipError_t launch_scan(int kind, const ScanArgs& a, hipStream_t s);
 
 }  // namespace mg

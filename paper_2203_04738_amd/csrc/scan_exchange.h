@@ -29,6 +29,13 @@ struct ScanShape {
   int ct, hp;          // kernels_scan_xcd.hip: tiles of 16 columns per workgroup, columns of a ring row
                        // (256, 512 or 1024),
   int gpx, nx;         // row blocks per XCD, XCDs needed
+  int terms;           // the contraction is on terms (ScanTerms)
+};
+// bf16 weights, GRU, a row block per XCD: the contraction runs on the bf16 matrix pipe, the state as its
+// three bf16 terms (below).
+template <int KIND, class WT>
+struct ScanTerms {
+  static constexpr bool value = KIND == SCAN_GRU && sizeof(WT) == 2;
 };
 // control words beyond the four of ScanArgs: XCDs given away (xcd_groups), a wait passed its bound,
 // workgroups that have arrived per XCD
@@ -107,6 +114,40 @@ __device__ inline uintx4 scan_quad(float val) {
   v[3] = __builtin_amdgcn_mov_dpp(b, 0xff, 0xf, 0xf, true);
   return v;
 }
+// Exact terms of a state value on the bf16 matrix pipe, whose 16 rows hold four state rows three times:
+// row 4 t + r is term t of row r, rows 12..15 are zero.  x = t0 + 2^-8 t1 + 2^-16 t2, each term eight bits
+// of the value (cut, not rounded: nothing overflows, and the scaled lower terms have the exponent of the
+// value, so that none of them is subnormal where the value is not).  Not finite: the first alone.
+struct StateTerms {
+  unsigned t01, t2;                                    // bf16 t0 (low half) and t1; t2
+};
+__device__ inline StateTerms state_terms(float x) {
+  const unsigned b = x == x ? __float_as_uint(x) : 0x7fc00000u;    // (no bf16 pair is SENTINEL)
+  const bool finite = (b & 0x7f800000u) != 0x7f800000u;
+  const float r1 = (x - __uint_as_float(b & 0xffff0000u)) * 256.f;
+  const unsigned b1 = finite ? __float_as_uint(r1) : 0u;
+  const float r2 = (r1 - __uint_as_float(b1 & 0xffff0000u)) * 256.f;
+  const unsigned b2 = finite ? __float_as_uint(r2) : 0u;
+  return {(b >> 16) | (b1 & 0xffff0000u), b2 >> 16};
+}
+// Sum of the terms' rows of a 16 x 16 block: as quad_fold, with the weights of the terms.
+__device__ inline float term_fold(const floatx4& a) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  auto u = [](float f) { return __float_as_uint(f); };
+  auto fold = [](u2 s, float w) { return fmaf(__uint_as_float(s[1]), w, __uint_as_float(s[0])); };
+  const float x01 = fold(__builtin_amdgcn_permlane32_swap(u(a[0]), u(a[1]), false, false), 0x1p-16f);
+  const float x23 = fold(__builtin_amdgcn_permlane32_swap(u(a[2]), u(a[3]), false, false), 0x1p-16f);
+  return fold(__builtin_amdgcn_permlane16_swap(u(x01), u(x23), false, false), 0x1p-8f);
+}
+__device__ inline floatx4 term_mma(const uintx4& state, const bf16x8& w, const floatx4& acc) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, state), w, acc, 0, 0, 0);
+}
+// Weights of a block of 32 k: column l % 16, k = 8 (l / 16) + 0..7; zero beyond H (a multiple of 8).
+__device__ inline bf16x8 term_weights(const bf16_t* row, int k, int H) {
+  const bf16x8 v = ldg8h(row + min(k, H - 8));
+  return k < H ? v : __builtin_bit_cast(bf16x8, uintx4{0, 0, 0, 0});
+}
+
 __device__ inline void scan_store_agent(float* p, uintx4 v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }

@@ -10,8 +10,8 @@ import paper_2203_04738_amd as mg
 from oracle import demo_ode_oracle as oo
 from oracle import lstm_oracle as lo
 from oracle import mgrit_gru_oracle as orc
-from paper_2203_04738_amd.binding import MgritGruCfg
-from synthetic_inputs import random_lstm, random_ode, random_small
+from paper_2203_04738_amd.binding import MGRIT_BF16, MGRIT_F32, MgritGruCfg
+from synthetic_inputs import random_lstm, random_ode, random_small, round_to_bf16
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -33,10 +33,16 @@ def _rel(a, b):
     return float(np.max(np.abs(a - b)) / np.max(np.abs(b)))
 
 
-def _gru(B, H, steps):
+def _gru(B, H, steps, half=False):
     d = random_small(B * 1000 + H, steps, B, 8, H, scale=0.7 / np.sqrt(H))
-    t = {k: torch.from_numpy(v).to(DEV) for k, v in d.items()}
-    cfg = MgritGruCfg(steps, B, 8, H)
+    t = {}
+    for k, v in d.items():
+        if half and k in ("x", "W", "U"):
+            d[k] = round_to_bf16(v)
+        t[k] = torch.from_numpy(d[k]).to(DEV)
+        if half and k in ("x", "W", "U"):
+            t[k] = t[k].to(torch.bfloat16)
+    cfg = MgritGruCfg(steps, B, 8, H, dtype=MGRIT_BF16 if half else MGRIT_F32)
     ws = torch.empty(mg.mgrit_gru_workspace_bytes(cfg), dtype=torch.uint8, device=DEV)
     g = [torch.empty(3 * H, 8, device=DEV), torch.empty(3 * H, H, device=DEV),
          torch.empty(3 * H, device=DEV), torch.empty(3 * H, device=DEV)]
@@ -76,14 +82,46 @@ def test_against_the_oracles(gh, B, H, ct, rb):
     assert _rel(h, oo.ode_serial_scan(d["A"], d["Bw"], d["b"], d["d"], d["h0"], 0.25)) <= 1e-5
 
 
+@pytest.mark.parametrize("B,H,ct", [(3, 72, 1), (60, 200, 1), (41, 264, 1), (8, 520, 2), (2, 1024, 2),
+                                    (64, 1000, 2)])
+def test_state_in_terms_on_bf16_weights(gh, B, H, ct):
+    # exact products of the fp32 state with the weights, fp32 sums: the fp32 bar
+    print("xcd case terms", B, H, flush=True)
+    d, t, cfg, ws, p, h, *_ = _gru(B, H, T, half=True)
+    P = (d["W"], d["U"], d["b_i"], d["b_h"])
+
+    def solve():
+        gh.expect_kernels(lambda: mg.gru_serial_scan(cfg, *p, t["h0"], h, ws), f"xcd_scan_kernel<0, {ct}, ")
+        return h
+
+    assert _rel(solve(), orc.serial_scan(*P, d["x"], d["h0"])) <= 1e-5
+    if B > 2:                       # row 1: a NaN with every bit set; row 2: infinite
+        clean = h.clone()
+        t["h0"].view(torch.int32)[1, 3] = -1
+        t["h0"][2, 5] = float("inf")
+        solve()
+        keep = [b for b in range(B) if b not in (1, 2)]
+        assert torch.equal(h[:, keep], clean[:, keep])
+        assert torch.isnan(h[1:, 1]).all() and not torch.isfinite(h[1:, 2, 5]).any()
+    # large states: no term overflows
+    d["h0"] = (np.random.default_rng(1).uniform(1, 3, (B, H)) * 2.0 ** 120).astype(np.float32)
+    t["h0"].copy_(torch.from_numpy(d["h0"]))
+    with np.errstate(over="ignore"):
+        want = orc.serial_scan(*P, d["x"], d["h0"])
+    assert _rel(solve(), want) <= 1e-5
+
+
 @pytest.mark.parametrize("B,H", [(60, 200), (32, 512), (30, 1000)])
 def test_any_part_may_be_taken_over(B, H, monkeypatch):
     # limits around the time the workgroups need to arrive: some XCDs take their rows, some do not
     def solve():
-        d, t, cfg, ws, p, h, w, g = _gru(B, H, 40)
-        mg.gru_serial_scan(cfg, *p, t["h0"], h, ws)
-        mg.gru_serial_scan_backward(cfg, *p, h, t["dL_dhT"], w, *g, ws)
-        return h, w, *g
+        out = []
+        for half in (False, True):
+            d, t, cfg, ws, p, h, w, g = _gru(B, H, 40, half)
+            mg.gru_serial_scan(cfg, *p, t["h0"], h, ws)
+            mg.gru_serial_scan_backward(cfg, *p, h, t["dL_dhT"], w, *g, ws)
+            out += [h, w, *g]
+        return out
 
     print("xcd case takeover", B, H, flush=True)
     want = solve()
