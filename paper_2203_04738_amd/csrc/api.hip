@@ -535,7 +535,7 @@ static int vcycle_fwd(const FwdCtx& x, int l, bool f_points_current = false, boo
       CHECK_HIP(launch_phi_sweep(a, (int)N, a.mode, a.mode, S, x.s));
       return MGRIT_OK;
     }
-    if (!keep && scan_covers(kind, N, x.c->B, hidden)) {
+    if (!keep && scan_covers(kind, N, x.c->B, hidden, kform(x.c->dtype), x.ring != nullptr)) {
       ScanArgs a;
       std::memset(&a, 0, sizeof(a));
       a.Wt = x.U;
@@ -865,7 +865,7 @@ static int vcycle_bwd(const BwdCtx& x, int l, bool f_points_current = false,
     // with them, a caller's w formed in place of dL_dh, goes step by step)
     const long long words = (N + 1) * x.c->B * x.c->H;
     const bool in_place = x.gl[l] && x.gl[l] < x.wl[l] + words && x.wl[l] < x.gl[l] + words;
-    if (!in_place && scan_covers(SCAN_ADJOINT, N, x.c->B, x.c->H)) {
+    if (!in_place && scan_covers(SCAN_ADJOINT, N, x.c->B, x.c->H, kform(x.c->dtype), x.ring != nullptr)) {
       ScanArgs a;
       std::memset(&a, 0, sizeof(a));
       a.Wt = x.UT;

@@ -473,13 +473,18 @@ static ScanShape scan_shape(int B, int H) {
 
 // A row block per XCD (kernels_scan_xcd.hip): false if the shape does not fit or gains nothing.
 // Up to 512 columns, 16 per workgroup, us per step here : all CUs through memory, forward / adjoint:
-// 32 x 512 1.27 / 1.28 : 1.81 / 2.54, 64 x 512 1.9 / 2.1 : 3.7 / 4.0, 16 x 256 0.97 / 0.91 : 1.50 / 1.59,
+// 32 x 512 1.27 / 1.27 : 1.81 / 2.54, 64 x 512 1.9 / 1.9 : 3.7 / 4.0, 16 x 256 0.97 / 0.91 : 1.50 / 1.59,
 // 3 x 500 1.22 / 1.23 : 2.00 / 2.23, LSTM 32 x 512 1.54 : 2.87.  Beyond, 32 per workgroup fill the
 // registers of a CU and the fp32 matrix pipe takes half of the step: 32 x 1024 2.6 / 2.9 : 5.8 / 6.0, 16 x
 // 768 2.6 / 2.9 : 2.9 / 3.4, but 8 x 1024 2.7 / 3.0 : 3.0 / 3.6, and a second solve on another stream,
 // for which the other form leaves half of the CUs, would wait: only where that form takes more.
+// More rows than one quad for each XCD follow each other within the step, up to four quads; the step launches
+// (a launch per step above 64 rows) : this, us per step of the whole call: scan 100 x 512 13.3 : 4.4, 100 x
+// 1000 26.0 : 10.8, 64 x 1000 10.2 : 6.1, 256 x 256 9.0 : 3.3, LSTM 100 x 200 10.7 : 2.5, ODE 100 x 512 7.3 :
+// 2.5, scan + back-propagation 100 x 512 33.6 : 10.8, 100 x 1000 67.9 : 33.5.
 // GRU on bf16 weights contracts terms of the state (ScanTerms): 8 x 512 1.01 : 2.00, 1 x 1024 1.42 : 2.25, 8 x
 // 1024 1.53 : 3.02, 64 x 1024 2.3 : 9.4, at any number of rows (two solves of 8 x 1024 at once 0.89 : 1.82 ms).
+constexpr int SCAN_XCD_MAX_QUADS = 4;                  // per row block
 static bool scan_shape_xcd(int kind, int B, int H, int bf16, ScanShape& s) {
   if (scan_max_wg() != SCAN_XCDS * SCAN_XCD_CUS) return false;
   const int quads = (B + 3) / 4;
@@ -492,12 +497,9 @@ static bool scan_shape_xcd(int kind, int B, int H, int bf16, ScanShape& s) {
   s.rb = (quads + fit - 1) / fit;
   if (s.ct == 2) {
     const int ncg16 = (H + SCAN_CP - 1) / SCAN_CP;
-    // (registers: four gates do not fit, nor do two quads of the adjoint's products)
-    if (kind == SCAN_LSTM || (!s.terms && quads * ncg16 <= SCAN_MAXWG / 2) ||
-        (kind == SCAN_ADJOINT && s.rb > 1))
-      return false;
+    if (kind == SCAN_LSTM || (!s.terms && quads * ncg16 <= SCAN_MAXWG / 2)) return false;   // (LSTM: registers)
   }
-  if (s.rb > 2) return false;
+  if (s.rb > SCAN_XCD_MAX_QUADS) return false;
   s.nrb = (quads + s.rb - 1) / s.rb;
   s.gpx = (s.nrb + SCAN_XCDS - 1) / SCAN_XCDS;
   s.nx = (s.nrb + s.gpx - 1) / s.gpx;
@@ -509,15 +511,19 @@ size_t scan_ring_floats(int kind, int B, int H, int bf16) {
   return (size_t)16 * s.rb * s.nrb * s.hp * (kind == SCAN_ADJOINT ? 3 : s.terms ? 2 : 1);
 }
 
-// Up to 64 rows (the few-row range of the step kernels) of 16 to 1024 columns.  A solve costs
-// three launches (mark, scan, items) whatever its length: below eight steps the chain of step launches
-// is as fast.
-bool scan_covers(int kind, long long N, int B, int H) {
-  if (N < 8 || N > (1LL << 30) || B > 64 || H < 16 || H > 128 * SCAN_MAXW) return false;
-  const ScanShape s = scan_shape(B, H);
-  // registers: the adjoint holds three coefficient rows per state row, the LSTM four gates
-  const int limit = kind == SCAN_ADJOINT && s.nch == 2 ? 2 : 4;
-  return s.rb <= limit && s.nrb * s.ncg <= scan_max_wg();
+// Registers of scan_kernel: the adjoint holds three coefficient rows per state row, the LSTM four gates.
+static int scan_max_quads(int kind, int nch) { return kind == SCAN_ADJOINT && nch == 2 ? 2 : 4; }
+
+// 16 to 1024 columns, up to 64 rows (the few-row range of the step kernels), with a row block per XCD up
+// to 16 rows for each.  A solve costs three launches (mark, scan, items) whatever its length: below eight
+// steps the chain of step launches is as fast.
+bool scan_covers(int kind, long long N, int B, int H, int bf16, bool ring) {
+  if (N < 8 || N > (1LL << 30) || H < 16 || H > 128 * SCAN_MAXW) return false;
+  ScanShape s;
+  if (ring && scan_shape_xcd(kind, B, H, bf16, s)) return true;
+  if (B > 64) return false;
+  s = scan_shape(B, H);
+  return s.rb <= scan_max_quads(kind, s.nch) && s.nrb * s.ncg <= scan_max_wg();
 }
 
 // xs: the shape of the form with a row block per XCD, null: this form
@@ -538,9 +544,14 @@ static void launch_scan_shape(const ScanArgs& a, const ScanShape& s, const ScanS
 }
 template <int KIND, class WT>
 static void launch_scan_kind(const ScanArgs& a, const ScanShape* xs, hipStream_t st) {
-  const ScanShape s = scan_shape(a.B, a.H);
+  ScanShape s = scan_shape(a.B, a.H);
+  const int max_rb = scan_max_quads(KIND, s.nch);
+  if (s.rb > max_rb) {                                // (behind xs: any number of workgroups will do)
+    s.rb = max_rb;
+    s.nrb = ((a.B + 3) / 4 + s.rb - 1) / s.rb;
+  }
 #define MG_SCAN_CASE(NCH, RB) \
-  if (s.nch == NCH && s.rb == RB) launch_scan_shape<KIND, NCH, RB, WT>(a, s, xs, st);
+  if (s.nch == NCH && s.rb == RB) return launch_scan_shape<KIND, NCH, RB, WT>(a, s, xs, st);
   MG_SCAN_CASE(1, 1)
   MG_SCAN_CASE(1, 2)
   MG_SCAN_CASE(1, 4)

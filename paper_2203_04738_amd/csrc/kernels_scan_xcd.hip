@@ -89,17 +89,27 @@ __device__ inline bool ring_waits(const uintx4 (&v)[NL]) {
     top = max(max(max(top, v[q][0]), max(v[q][1], v[q][2])), v[q][3]);
   return top == SENTINEL;
 }
+// x in another register, now: left to the compiler, the copy comes behind the load that overwrites x, and
+// waits for it.
+__device__ inline float moved(float x) {
+  float y;
+  asm volatile("v_mov_b32 %0, %1" : "=v"(y) : "v"(x));
+  return y;
+}
 // NW waves of NV x NCH chunks of 64 k (NV sums over NCH chunks each: what a wave of scan_kernel sums, so
-// the bits are the same); RB row quads, CT tiles of 16 columns per workgroup.  Wave e < RB CT finishes
-// the elements of quad e % RB, tile e / RB (waves of their own for that are no faster: 1.38 against 1.35
-// us per step at 32 x 512, where they make nine of eight).
+// the bits are the same); RB row quads one after the other, CT tiles of 16 columns per workgroup.  The
+// waves also finish the elements (waves of their own for that are no faster: 1.38 against 1.35 us per
+// step at 32 x 512, where they make nine of eight).
 template <int KIND, int CT, int NV, int NCH, int NW, int RB, class WT>
-__global__ __launch_bounds__(64 * NW) void xcd_scan_kernel(ScanArgs a, ScanShape sh) {
+__device__ __forceinline__ void xcd_solve(const ScanArgs& a, const ScanShape& sh) {
   constexpr int NG = ScanGates<KIND>::value;
   constexpr bool ADJ = KIND == SCAN_ADJOINT;
   constexpr int NS = ADJ ? 1 : NG;
   constexpr int AG = ScanVectors<KIND>::value;
-  constexpr int NC = NV * NCH, NL = (ScanTerms<KIND, WT>::value ? 2 : AG) * RB * NC;
+  constexpr int NC = NV * NCH;
+  constexpr int NL = (ScanTerms<KIND, WT>::value ? 2 : AG) * NC;     // loads per row quad
+  constexpr bool AHEAD = RB > 1 && NL <= 8;            // (registers)
+  constexpr int NE = (RB * CT + NW - 1) / NW;          // elements a lane finishes
   constexpr int NP = NG == 1 ? 2 : 1;
   constexpr int HP = 64 * NC * NW;                     // columns of a ring row, zero from H on
   constexpr bool TERMS = ScanTerms<KIND, WT>::value;
@@ -134,8 +144,6 @@ __global__ __launch_bounds__(64 * NW) void xcd_scan_kernel(ScanArgs a, ScanShape
       __builtin_amdgcn_make_buffer_rsrc(ring, 0, 4 * SLOT * 4, 0x00027000);
 
   const int kw0 = wv * 64 * NC;
-  const bool epi = wv < RB * CT;
-  const int er = wv % RB, et = wv / RB;
   // weights: column j0 + 16 t + lane % 16, k = kw0 + 64 c + 16 (lane / 16) + 0..15 (zero beyond H;
   // columns beyond H repeat the last one and are never stored)
   float w[NC][CT * NG][16];
@@ -182,142 +190,153 @@ __global__ __launch_bounds__(64 * NW) void xcd_scan_kernel(ScanArgs a, ScanShape
       off[r] = (unsigned)(((row >> 2) * (HP >> 2) + (kw0 >> 2) + (lane >> 2)) * 16 + (row & 3) * 4) * 4u;
   }
   // (terms: lane l reads term l / 4 % 4 of row l % 4, k = kw0 + 32 b + 8 (l / 16) + 0..7)
-  // element of this lane; lane q of four stores 16 bytes: 0 the new state (adjoint: 0..2 its products
-  // with the three coefficients of the next step) to the ring, 1 (0..2) the mark, 2 (3) the output
-  const int orow = r0 + 4 * er + quad_row(lane), oj = j0 + et * SCAN_CP + (lane & 15);
-  const int erow = min(orow, B - 1), ej = min(oj, H - 1), q4 = lane & 3;
-  const bool ok = epi && orow < B && oj < H;
-  const unsigned eo = (unsigned)erow * W + ej;
-  const unsigned po = (unsigned)erow * (ADJ ? a.kw : NG * H) + ej;
-  const unsigned quado =
-      TERMS ? (unsigned)((((er * (HP >> 5) + (ej >> 5)) * 4 + (ej >> 3 & 3)) * 16 + min(q4, 2) * 4 +
-                          quad_row(lane)) * 4 + (ej >> 2 & 1) * 2)
-            : (unsigned)((er * (HP >> 2) + (ej >> 2)) * 16 + quad_row(lane) * 4);
-  const unsigned kqo = (unsigned)erow * (ADJ ? a.kw : 0) + min(q4, 2) * H + (ej & ~3);
+  // elements of this lane: wave e (and e + NW) finishes quad e % RB, tile e / RB.  Lane q of four stores 16
+  // bytes: 0 the new state (adjoint: 0..2 its products with the three coefficients of the next step; terms:
+  // 0..2 eight bytes each) to the ring, 1 (0..2) the mark, 2 (3) the output
   constexpr int OUT_LANE = ADJ || TERMS ? 3 : 2;
   constexpr uintx4 MARK = {SENTINEL, SENTINEL, SENTINEL, SENTINEL};
-  float* const lane_base = q4 == OUT_LANE ? a.u + (eo & ~3u) : ring + quado + (ADJ ? q4 * VEC : 0);
-  float bias[NG], p[NG], kd = 0.f, g = 0.f, gc = 0.f;
-  floatx4 kq = zero4();
-#pragma unroll
-  for (int q = 0; q < NG; ++q) {
-    bias[q] = (KIND == SCAN_GRU || KIND == SCAN_LSTM) && epi ? a.b_h[q * H + ej] : 0.f;
-    p[q] = 0.f;
-  }
+  const int q4 = lane & 3;
+  auto mine = [&](int n) { return wv + n * NW < RB * CT; };
+  bool ok[NE];
+  unsigned eo[NE], po[NE], kqo[NE];
+  float* base[NE];
+  float bias[NE][NG], prev[NE], prevc[NE];             // prev: element of the row the step starts from
+  float p[NE][NG], kd[NE], g[NE], gc[NE];
+  floatx4 kq[NE];
   // what step i needs beside the state (kq: of the step behind it)
-  auto request = [&](int i) {
+  auto request = [&](int n, int i) {
     if (ADJ) {
-      kd = (a.kap + in_pt(i) * B * a.kw + 3 * H)[po];
-      kq = ldg4(a.kap + in_pt(min(i + 1, N - 1)) * B * a.kw + kqo);
+      kd[n] = (a.kap + in_pt(i) * B * a.kw + 3 * H)[po[n]];
+      kq[n] = ldg4(a.kap + in_pt(min(i + 1, N - 1)) * B * a.kw + kqo[n]);
     } else {
       const float* pr = a.P + ((long long)(i + 1) * a.pstep - 1) * B * ((long long)NG * H);
 #pragma unroll
-      for (int q = 0; q < NG; ++q) p[q] = (pr + q * H)[po];
+      for (int q = 0; q < NG; ++q) p[n][q] = (pr + q * H)[po[n]];
     }
     if (a.g) {
       const float* gr = a.g + out_pt(i) * BW;
-      g = gr[eo];
-      if (KIND == SCAN_LSTM) gc = (gr + H)[eo];
+      g[n] = gr[eo[n]];
+      if (KIND == SCAN_LSTM) gc[n] = (gr + H)[eo[n]];
     }
   };
-  float prev = 0.f, prevc = 0.f;                       // element of the row the step starts from
-  if (epi) {
-    request(0);
-    const float* u0 = a.u + in_pt(0) * BW;
-    prev = u0[eo];
-    if (KIND == SCAN_LSTM) prevc = (u0 + H)[eo];
+#pragma unroll
+  for (int n = 0; n < NE; ++n) {
+    const int e = wv + n * NW, er = e % RB, et = e / RB;
+    const int orow = r0 + 4 * er + quad_row(lane), oj = j0 + et * SCAN_CP + (lane & 15);
+    const int erow = min(orow, B - 1), ej = min(oj, H - 1);
+    ok[n] = mine(n) && orow < B && oj < H;
+    eo[n] = (unsigned)erow * W + ej;
+    po[n] = (unsigned)erow * (ADJ ? a.kw : NG * H) + ej;
+    kqo[n] = (unsigned)erow * (ADJ ? a.kw : 0) + min(q4, 2) * H + (ej & ~3);
+    const unsigned quado =
+        TERMS ? (unsigned)((((er * (HP >> 5) + (ej >> 5)) * 4 + (ej >> 3 & 3)) * 16 + min(q4, 2) * 4 +
+                            quad_row(lane)) * 4 + (ej >> 2 & 1) * 2)
+              : (unsigned)((er * (HP >> 2) + (ej >> 2)) * 16 + quad_row(lane) * 4);
+    base[n] = q4 == OUT_LANE ? a.u + (eo[n] & ~3u) : ring + quado + (ADJ ? q4 * VEC : 0);
+    kd[n] = g[n] = gc[n] = prev[n] = prevc[n] = 0.f;
+    kq[n] = zero4();
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+      bias[n][q] = (KIND == SCAN_GRU || KIND == SCAN_LSTM) && mine(n) ? a.b_h[q * H + ej] : 0.f;
+      p[n][q] = 0.f;
+    }
+    if (mine(n)) {
+      request(n, 0);
+      const float* u0 = a.u + in_pt(0) * BW;           // element of the row the step starts from
+      prev[n] = u0[eo[n]];
+      if (KIND == SCAN_LSTM) prevc[n] = (u0 + H)[eo[n]];
+    }
   }
 
   for (int i = 0; i < N; ++i) {
     const unsigned slot = (unsigned)(i & 3) * (SLOT * 4);
-    uintx4 v[NL];
-    auto load = [&]() {
+    uintx4 v[AHEAD ? 2 : 1][NL];                       // a quad (and the one behind it on its way)
+    auto load = [&](uintx4 (&d)[NL], int r) {
+#pragma unroll
+      for (int c = 0; c < NL / (TERMS ? 1 : AG); ++c)
+#pragma unroll
+        for (int g2 = 0; g2 < (TERMS ? 1 : AG); ++g2)
+          d[c * (TERMS ? 1 : AG) + g2] = ring_load(rsrc, off[r] + c * 1024 + g2 * VEC * 4, slot);
+    };
+    float (*pt)[RB * CT][NS][64] = part[i & 1];
+    float cp[NE][NG] = {}, cgv[NE], cgc[NE] = {}, ckd[NE] = {};
+    floatx4 ckq[NE];
+    float* sp[NE];
+    load(v[0], 0);
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+      uintx4 (&vr)[NL] = v[AHEAD ? r & 1 : 0];
+      bool leave = false;
+      for (int polls = 1; __any(ring_waits(vr)); ++polls) {
+        if ((polls & 127) == 0) {
+          if (polls >= SCAN_MAX_POLLS) {
+            __hip_atomic_store(a.ctl + CTL_ABORT, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(a.ctl + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+          leave = ctl_load(a.ctl + CTL_ABORT) != 0;
+          if (leave) break;
+        }
+        load(vr, r);
+      }
+      if (leave) {      // the other waves see it behind the barrier, which does not wait for waves that ended
+        stop = 1;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_endpgm();
+      }
+      if (r == 0) {
+        // the marks this wave made in the step before are in the L2 (the loads above are younger: no wait)
+        __builtin_amdgcn_s_waitcnt(WAIT_VMCNT_0);
+      }
+      if (AHEAD && r + 1 < RB) load(v[AHEAD ? (r + 1) & 1 : 0], r + 1);
+      if (r == 0) {
+#pragma unroll
+        for (int n = 0; n < NE; ++n) {
+          cgv[n] = moved(g[n]);
+          if constexpr (ADJ) {
+            ckd[n] = moved(kd[n]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) ckq[n][q] = moved(kq[n][q]);
+          } else {
+#pragma unroll
+            for (int q = 0; q < NG; ++q) cp[n][q] = moved(p[n][q]);
+          }
+          if constexpr (KIND == SCAN_LSTM) cgc[n] = moved(gc[n]);
+          if (mine(n)) request(n, min(i + 1, N - 1));
+          // where this lane stores 16 bytes
+          const int sl = ADJ || TERMS ? (i + 1) & 3 : (i + 1 + 2 * (q4 & 1)) & 3;
+          sp[n] = base[n] + (q4 == OUT_LANE ? out_pt(i) * BW : (long long)(sl * (int)SLOT));
+          asm volatile("" : "+v"(sp[n]));              // (computed before the barrier)
+        }
+      }
       if constexpr (TERMS) {
+        floatx4 acc[CT * NG];
+#pragma unroll
+        for (int q = 0; q < CT * NG; ++q) acc[q] = zero4();
 #pragma unroll
         for (int b = 0; b < KB; ++b)
 #pragma unroll
-          for (int r = 0; r < RB; ++r) v[b * RB + r] = ring_load(rsrc, off[r] + b * 1024, slot);
-        return;
+          for (int q = 0; q < CT * NG; ++q) acc[q] = term_mma(vr[b], wt[b][q], acc[q]);
+#pragma unroll
+        for (int q = 0; q < CT * NG; ++q) pt[wv][q / NG * RB + r][q % NG][lane] = term_fold(acc[q]);
       }
 #pragma unroll
-      for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int r = 0; r < RB; ++r)
-#pragma unroll
-          for (int g2 = 0; g2 < (TERMS ? 0 : AG); ++g2)
-            v[(c * RB + r) * AG + g2] = ring_load(rsrc, off[r] + c * 1024 + g2 * VEC * 4, slot);
-    };
-    load();
-    bool leave = false;
-    for (int polls = 1; __any(ring_waits(v)); ++polls) {
-      if ((polls & 127) == 0) {
-        if (polls >= SCAN_MAX_POLLS) {
-          __hip_atomic_store(a.ctl + CTL_ABORT, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_store(a.ctl + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        leave = ctl_load(a.ctl + CTL_ABORT) != 0;
-        if (leave) break;
-      }
-      load();
-    }
-    if (leave) {
-      stop = 1;                                        // (seen by the epilogue waves behind the barrier)
-      __syncthreads();
-      return;
-    }
-    // the marks this wave made in the step before are in the L2 (the loads above are younger: no wait)
-    __builtin_amdgcn_s_waitcnt(WAIT_VMCNT_0);
-    float cp[NG];
-#pragma unroll
-    for (int q = 0; q < NG; ++q) cp[q] = p[q];
-    const float cgv = g, cgc = gc, ckd = kd;
-    const floatx4 ckq = kq;
-    if (epi) request(min(i + 1, N - 1));
-    // where this lane stores 16 bytes (see above)
-    const int sl = ADJ || TERMS ? (i + 1) & 3 : (i + 1 + 2 * (q4 & 1)) & 3;
-    const long long so = q4 == OUT_LANE ? out_pt(i) * BW : (long long)(sl * (int)SLOT);
-    float* sp = lane_base + so;
-    asm volatile("" : "+v"(sp));                       // (computed before the barrier)
-    float (*pt)[RB * CT][NS][64] = part[i & 1];
-    if constexpr (TERMS) {
-      floatx4 acc[RB][CT * NG];
-#pragma unroll
-      for (int r = 0; r < RB; ++r)
-#pragma unroll
-        for (int q = 0; q < CT * NG; ++q) acc[r][q] = zero4();
-#pragma unroll
-      for (int b = 0; b < KB; ++b)
-#pragma unroll
-        for (int r = 0; r < RB; ++r)
-#pragma unroll
-          for (int q = 0; q < CT * NG; ++q) acc[r][q] = term_mma(v[b * RB + r], wt[b][q], acc[r][q]);
-#pragma unroll
-      for (int r = 0; r < RB; ++r)
-#pragma unroll
-        for (int q = 0; q < CT * NG; ++q) pt[wv][q / NG * RB + r][q % NG][lane] = term_fold(acc[r][q]);
-    }
-#pragma unroll
-    for (int h = 0; h < (TERMS ? 0 : NV); ++h) {
-      floatx4 acc[RB][CT * NG][NP];
-#pragma unroll
-      for (int r = 0; r < RB; ++r)
+      for (int h = 0; h < (TERMS ? 0 : NV); ++h) {
+        floatx4 acc[1][CT * NG][NP];
 #pragma unroll
         for (int q = 0; q < CT * NG; ++q)
 #pragma unroll
-          for (int n = 0; n < NP; ++n) acc[r][q][n] = zero4();
+          for (int n = 0; n < NP; ++n) acc[0][q][n] = zero4();
 #pragma unroll
-      for (int c = h * NCH; c < (h + 1) * NCH; ++c)
-        quad_mma<RB, CT * NG, NP>(
-            acc, [&](int r, int q) { return __builtin_bit_cast(floatx4, v[(c * RB + r) * AG + (ADJ ? q % NG : 0)]); },
-            [&](int q) -> const float (&)[16] { return w[c][q]; });
-#pragma unroll
-      for (int r = 0; r < RB; ++r)
+        for (int c = h * NCH; c < (h + 1) * NCH; ++c)
+          quad_mma<1, CT * NG, NP>(
+              acc, [&](int, int q) { return __builtin_bit_cast(floatx4, vr[c * AG + (ADJ ? q % NG : 0)]); },
+              [&](int q) -> const float (&)[16] { return w[c][q]; });
 #pragma unroll
         for (int t = 0; t < CT; ++t) {
           floatx4 sum[NG];
 #pragma unroll
           for (int q = 0; q < NG; ++q)
-            sum[q] = NP > 1 ? acc[r][t * NG + q][0] + acc[r][t * NG + q][NP - 1] : acc[r][t * NG + q][0];
+            sum[q] = NP > 1 ? acc[0][t * NG + q][0] + acc[0][t * NG + q][NP - 1] : acc[0][t * NG + q][0];
           if (ADJ) {
             pt[wv * NV + h][t * RB + r][0][lane] = quad_fold(sum[0] + sum[NG > 1 ? 1 : 0] + sum[NG - 1]);
           } else {
@@ -326,91 +345,108 @@ __global__ __launch_bounds__(64 * NW) void xcd_scan_kernel(ScanArgs a, ScanShape
               pt[wv * NV + h][t * RB + r][ADJ ? 0 : q][lane] = quad_fold(sum[q]);
           }
         }
+      }
+      if (!AHEAD && r + 1 < RB) load(v[0], r + 1);
     }
     __syncthreads();
-    if (epi) {
+#pragma unroll
+    for (int n = 0; n < NE; ++n) {
+      if (!mine(n)) continue;
       // partial sums (every read in flight before the first addition)
       float s[NS], ps[NS][SCAN_MAXW];
 #pragma unroll
       for (int q = 0; q < NS; ++q)
 #pragma unroll
-        for (int n = 0; n < SCAN_MAXW; ++n) ps[q][n] = n < NW * NV ? pt[n < NW * NV ? n : 0][wv][q][lane] : 0.f;
+        for (int m = 0; m < SCAN_MAXW; ++m)
+          ps[q][m] = m < NW * NV ? pt[m < NW * NV ? m : 0][wv + n * NW][q][lane] : 0.f;
       const int stopped = stop;
 #pragma unroll
       for (int q = 0; q < NS; ++q)
         s[q] = ((ps[q][0] + ps[q][1]) + (ps[q][2] + ps[q][3])) +
                ((ps[q][4] + ps[q][5]) + (ps[q][6] + ps[q][7]));
       float out, outc = 0.f;
-      scan_element<KIND>(a, s, cp, bias, ckd, prev, prevc, cgv, cgc, out, outc);
+      scan_element<KIND>(a, s, cp[n], bias[n], ckd[n], prev[n], prevc[n], cgv[n], cgc[n], out, outc);
       const uintx4 quad = scan_quad(out);
       if (stopped) return;
       if constexpr (ADJ) {
         uintx4 pr;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const unsigned b = scan_bits(ckq[e] * __uint_as_float(quad[e]));
+          const unsigned b = scan_bits(ckq[n][e] * __uint_as_float(quad[e]));
           pr[e] = q4 == OUT_LANE ? quad[e] : b;
         }
-        if (ok) {
-          ring_store(sp, pr);
-          if (q4 != OUT_LANE) ring_store(lane_base + ((i + 3) & 3) * (int)SLOT, MARK);
+        if (ok[n]) {
+          ring_store(sp[n], pr);
+          if (q4 != OUT_LANE) ring_store(base[n] + ((i + 3) & 3) * (int)SLOT, MARK);
         }
       } else if constexpr (TERMS) {
         // lane q < 3 of four stores term q of the four columns
-        const StateTerms x = state_terms(out);
+        const StateTerms st = state_terms(out);
         unsigned y[4];
 #define MG_GATHER(e, ctrl)                                                        \
   {                                                                               \
-    const unsigned y01 = __builtin_amdgcn_mov_dpp(x.t01, ctrl, 0xf, 0xf, true);   \
-    const unsigned y2 = __builtin_amdgcn_mov_dpp(x.t2, ctrl, 0xf, 0xf, true);     \
+    const unsigned y01 = __builtin_amdgcn_mov_dpp(st.t01, ctrl, 0xf, 0xf, true);  \
+    const unsigned y2 = __builtin_amdgcn_mov_dpp(st.t2, ctrl, 0xf, 0xf, true);    \
     y[e] = q4 == 2 ? y2 : y01;                                                    \
   }
         MG_GATHER(0, 0x00) MG_GATHER(1, 0x55) MG_GATHER(2, 0xaa) MG_GATHER(3, 0xff)
 #undef MG_GATHER
         const unsigned half = q4 == 1 ? 0x07060302u : 0x05040100u;
         const uintx2 d = {__builtin_amdgcn_perm(y[1], y[0], half), __builtin_amdgcn_perm(y[3], y[2], half)};
-        if (ok) {
+        if (ok[n]) {
           if (q4 != OUT_LANE) {
-            ring_store(sp, d);
-            ring_store(lane_base + ((i + 3) & 3) * (int)SLOT, uintx2{SENTINEL, SENTINEL});
+            ring_store(sp[n], d);
+            ring_store(base[n] + ((i + 3) & 3) * (int)SLOT, uintx2{SENTINEL, SENTINEL});
           } else {
-            ring_store(sp, quad);
+            ring_store(sp[n], quad);
           }
         }
       } else {
         uintx4 d;
 #pragma unroll
         for (int e = 0; e < 4; ++e) d[e] = q4 == 1 ? SENTINEL : quad[e];
-        if (ok && q4 <= OUT_LANE) ring_store(sp, d);
-        if (KIND == SCAN_LSTM && ok) (a.u + out_pt(i) * BW + H)[eo] = outc;
+        if (ok[n] && q4 <= OUT_LANE) ring_store(sp[n], d);
+        if (KIND == SCAN_LSTM && ok[n]) (a.u + out_pt(i) * BW + H)[eo[n]] = outc;
       }
-      prev = out;
-      prevc = outc;
+      prev[n] = out;
+      prevc[n] = outc;
     }
   }
 }
 
 template <int KIND, int CT, int NV, int NCH, int NW, int RB, class WT>
+__global__ __launch_bounds__(64 * NW) void xcd_scan_kernel(ScanArgs a, ScanShape sh) {
+  xcd_solve<KIND, CT, NV, NCH, NW, RB, WT>(a, sh);
+}
+template <int KIND, int CT, int NV, int NCH, int NW, int RB, class WT>
+__global__ __launch_bounds__(64 * NW) void adj_xcd_scan_kernel(ScanArgs a, ScanShape sh) {
+  xcd_solve<KIND, CT, NV, NCH, NW, RB, WT>(a, sh);
+}
+
+template <int KIND, int CT, int NV, int NCH, int NW, int RB, class WT>
 static void launch(const ScanArgs& a, const ScanShape& s, hipStream_t st) {
   // (workgroups go to the XCDs in turn)
-  hipLaunchKernelGGL((xcd_scan_kernel<KIND, CT, NV, NCH, NW, RB, WT>),
-                     dim3((unsigned)(SCAN_XCDS * s.gpx * s.ncg)), dim3(64 * NW), 0, st, a, s);
+  const dim3 grid((unsigned)(SCAN_XCDS * s.gpx * s.ncg)), block(64 * NW);
+  if constexpr (KIND == SCAN_ADJOINT)
+    hipLaunchKernelGGL((adj_xcd_scan_kernel<KIND, CT, NV, NCH, NW, RB, WT>), grid, block, 0, st, a, s);
+  else
+    hipLaunchKernelGGL((xcd_scan_kernel<KIND, CT, NV, NCH, NW, RB, WT>), grid, block, 0, st, a, s);
+}
+template <int KIND, int CT, int NV, int NCH, int NW, class WT>
+static void launch_rows(const ScanArgs& a, const ScanShape& s, hipStream_t st) {
+  if (s.rb == 1) launch<KIND, CT, NV, NCH, NW, 1, WT>(a, s, st);
+  else if (s.rb == 2) launch<KIND, CT, NV, NCH, NW, 2, WT>(a, s, st);
+  else if (s.rb == 3) launch<KIND, CT, NV, NCH, NW, 3, WT>(a, s, st);
+  else launch<KIND, CT, NV, NCH, NW, 4, WT>(a, s, st);
 }
 template <int KIND, class WT>
 static void launch_kind(const ScanArgs& a, const ScanShape& s, hipStream_t st) {
-  if (s.ct == 1 && s.hp == 256 && s.rb == 1) return launch<KIND, 1, 1, 1, 4, 1, WT>(a, s, st);
-  if (s.ct == 1 && s.hp == 256 && s.rb == 2) return launch<KIND, 1, 1, 1, 4, 2, WT>(a, s, st);
-  if (s.ct == 1 && s.hp == 512 && s.rb == 1) return launch<KIND, 1, 1, 1, 8, 1, WT>(a, s, st);
-  if (s.ct == 1 && s.hp == 512 && s.rb == 2) return launch<KIND, 1, 1, 1, 8, 2, WT>(a, s, st);
-  if constexpr (KIND == SCAN_ADJOINT)
-    if (s.ct == 2 && s.rb == 1) return launch<KIND, 2, 2, 2, 4, 1, WT>(a, s, st);
-  if constexpr (KIND == SCAN_GRU || KIND == SCAN_ODE) {
-    if (s.ct == 2 && s.rb == 1) return launch<KIND, 2, 1, 2, 8, 1, WT>(a, s, st);
-    if constexpr (ScanTerms<KIND, WT>::value) {
-      if (s.ct == 2 && s.rb == 2) return launch<KIND, 2, 1, 2, 8, 2, WT>(a, s, st);
-    } else {
-      if (s.ct == 2 && s.rb == 2) return launch<KIND, 2, 2, 2, 4, 2, WT>(a, s, st);
-    }
+  if (s.ct == 1 && s.hp == 256) return launch_rows<KIND, 1, 1, 1, 4, WT>(a, s, st);
+  if (s.ct == 1 && s.hp == 512) return launch_rows<KIND, 1, 1, 1, 8, WT>(a, s, st);
+  if constexpr (KIND == SCAN_ADJOINT) {
+    if (s.ct == 2) launch_rows<KIND, 2, 2, 2, 4, WT>(a, s, st);
+  } else if constexpr (KIND != SCAN_LSTM) {
+    if (s.ct == 2) launch_rows<KIND, 2, 1, 2, 8, WT>(a, s, st);
   }
 }
 

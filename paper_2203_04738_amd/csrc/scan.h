@@ -29,7 +29,8 @@ struct ScanArgs {
 };
 
 // True if a solve of N steps over B rows of hidden width H runs as one launch.
-bool scan_covers(int kind, long long N, int B, int H);
+// bf16: the weights' form, as in ScanArgs; ring: there is space for scan_ring_floats(...) floats.
+bool scan_covers(int kind, long long N, int B, int H, int bf16, bool ring);
 // Scratch with which the exchange runs inside the XCDs (0: this shape does not).
 size_t scan_ring_floats(int kind, int B, int H, int bf16);
 hipError_t launch_scan(int kind, const ScanArgs& a, hipStream_t s);

@@ -16,9 +16,10 @@ from synthetic_inputs import random_lstm, random_ode, random_small, round_to_bf1
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 T = 11
-# B, H -> column tiles, row quads per block (both as the kernel's template arguments say)
+# B, H -> column tiles, row quads per block, as the kernel's template arguments say
 SHAPES = [(3, 136, 1, 1), (60, 200, 1, 1), (41, 260, 1, 2), (32, 512, 1, 1), (30, 1000, 2, 1),
-          (64, 520, 2, 2)]
+          (64, 520, 2, 2), (90, 512, 1, 3), (125, 388, 1, 4), (255, 132, 1, 3), (70, 1024, 2, 3),
+          (101, 516, 2, 4)]
 
 
 @pytest.fixture(scope="module")
@@ -57,14 +58,15 @@ def test_against_the_oracles(gh, B, H, ct, rb):
     P = (d["W"], d["U"], d["b_i"], d["b_h"])
 
     def kernel(kind):
-        return f"xcd_scan_kernel<{kind}, {ct}, "
+        inner = "2, 2, 4" if ct == 2 and kind == 1 else "1, 2, 8" if ct == 2 else \
+            f"1, 1, {4 if H <= 256 else 8}"
+        return f"xcd_scan_kernel<{kind}, {ct}, {inner}, {rb}, "
 
     gh.expect_kernels(lambda: mg.gru_serial_scan(cfg, *p, t["h0"], h, ws), kernel(0))
     want = orc.serial_scan(*P, d["x"], d["h0"])
     assert _rel(h, want) <= 1e-5
-    # (two quads of 32 columns: the adjoint goes another way)
     gh.expect_kernels(lambda: mg.gru_serial_scan_backward(cfg, *p, h, t["dL_dhT"], w, *g, ws),
-                      kernel(1) if ct * rb < 4 else "adj_")
+                      "adj_" + kernel(1))
     for got, ref in zip((w, *g), orc.serial_bptt(*P, d["x"], want, d["dL_dhT"])):
         assert _rel(got, ref) <= 1e-5
     d = random_lstm(1, T, B, 8, H, scale=0.7 / np.sqrt(H))
@@ -73,7 +75,7 @@ def test_against_the_oracles(gh, B, H, ct, rb):
     u = torch.full((T + 1, B, 2 * H), 7.0, device=DEV)
     gh.expect_kernels(lambda: mg.lstm_serial_scan(cfg, t["W"], t["U"], t["b_i"], t["b_h"], t["x"],
                                                   t["u0"], u, lws),
-                      kernel(2) if ct == 1 else "scan_kernel<2, ")
+                      kernel(2) if ct == 1 else "scan_kernel<2, " if B <= 64 else "lstm_step_kernel")
     assert _rel(u, lo.lstm_serial_scan(d["W"], d["U"], d["b_i"], d["b_h"], d["x"], d["u0"])) <= 1e-5
     d = random_ode(2, T, B, 8, H)
     t = {k: torch.from_numpy(v).to(DEV) for k, v in d.items()}
@@ -83,7 +85,7 @@ def test_against_the_oracles(gh, B, H, ct, rb):
 
 
 @pytest.mark.parametrize("B,H,ct", [(3, 72, 1), (60, 200, 1), (41, 264, 1), (8, 520, 2), (2, 1024, 2),
-                                    (64, 1000, 2)])
+                                    (64, 1000, 2), (100, 264, 1), (99, 1024, 2)])
 def test_state_in_terms_on_bf16_weights(gh, B, H, ct):
     # exact products of the fp32 state with the weights, fp32 sums: the fp32 bar
     print("xcd case terms", B, H, flush=True)
@@ -111,7 +113,7 @@ def test_state_in_terms_on_bf16_weights(gh, B, H, ct):
     assert _rel(solve(), want) <= 1e-5
 
 
-@pytest.mark.parametrize("B,H", [(60, 200), (32, 512), (30, 1000)])
+@pytest.mark.parametrize("B,H", [(60, 200), (32, 512), (30, 1000), (100, 512), (100, 1000)])
 def test_any_part_may_be_taken_over(B, H, monkeypatch):
     # limits around the time the workgroups need to arrive: some XCDs take their rows, some do not
     def solve():
