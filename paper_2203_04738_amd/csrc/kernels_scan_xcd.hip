@@ -89,6 +89,15 @@ __device__ inline bool ring_waits(const uintx4 (&v)[NL]) {
     top = max(max(max(top, v[q][0]), max(v[q][1], v[q][2])), v[q][3]);
   return top == SENTINEL;
 }
+// Units of 64 clocks between the barrier of a step and the first look for the next state of a wave that
+// does not finish elements: about what the sums, the gates, the stores and their way to the L2 take.
+// Looks before that fail, hold up the stores in the L2, and the one that would succeed waits for the last
+// of them.  us per step without : with (every value from 1 to 14 was tried): adjoint 32 x 512 1.29 : 1.15,
+// 16 x 256 0.91 : 0.87, GRU 32 x 512 1.30 : 1.19, 3 x 500 1.24 : 1.14, 16 x 256 0.98 : 0.97, 8 x 512 on bf16
+// weights 1.01 : 0.95, LSTM 32 x 512 1.56 : 1.50; two to four quads a step hide it.
+__device__ constexpr int first_look(int kind, int ct) {
+  return kind == SCAN_GRU ? (ct == 2 ? 13 : 10) : kind == SCAN_LSTM ? 12 : 6;
+}
 // x in another register, now: left to the compiler, the copy comes behind the load that overwrites x, and
 // waits for it.
 __device__ inline float moved(float x) {
@@ -262,6 +271,7 @@ __device__ __forceinline__ void xcd_solve(const ScanArgs& a, const ScanShape& sh
     float cp[NE][NG] = {}, cgv[NE], cgc[NE] = {}, ckd[NE] = {};
     floatx4 ckq[NE];
     float* sp[NE];
+    if (i > 0 && !mine(0)) __builtin_amdgcn_s_sleep(first_look(KIND, CT));
     load(v[0], 0);
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
