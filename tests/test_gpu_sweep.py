@@ -83,3 +83,31 @@ def test_kept_coefficients_and_a_serial_scan_of_many_rows(gh):
             out = orc.mgrit_backward(*P, d["x"], h, d["dL_dhT"], z, 4, 3, 2)
             want = (h, out[0])
         assert gh.rel_err(got[0], want[0]) <= 1e-5 and gh.rel_err(got[1], want[1]) <= 1e-5
+
+
+@pytest.mark.parametrize("T,B,H,cf,levels,fine", [(16, 513, 20, 4, 2, 1), (16, 514, 64, 4, 2, 0),
+                                                  (24, 700, 68, 3, 2, 1), (32, 2049, 100, 4, 3, 1),
+                                                  (16, 521, 128, 4, 2, 1), (9, 2050, 36, 3, 1, 1)])
+def test_sixteen_rows_at_a_time(gh, T, B, H, cf, levels, fine):
+    # more than 2048 rows per launch: ragged blocks of rows, columns and K, one to many blocks per
+    # workgroup (the last: a serial scan), all modes (with and without kept coefficients)
+    print("sweep case sixteen", T, B, H, cf, levels, fine, flush=True)
+    d = random_small(T + B + H, T, B, 8, H, scale=0.3 / np.sqrt(H))
+    run = gh.GpuRun(d, cf=cf, levels=levels, fine_relax=fine)
+    P, z = (d["W"], d["U"], d["b_i"], d["b_h"]), np.zeros((T + 1, B, H))
+    h_ref, _ = orc.mgrit_forward(*P, d["x"], d["h0"], z, cf, levels, 2, fine_relax_fcf=bool(fine))
+    out = orc.mgrit_backward(*P, d["x"], h_ref, d["dL_dhT"], z, cf, levels, 2, fine_relax_fcf=bool(fine))
+    box = []
+    nch = 1 if H <= 64 else 2
+    gh.expect_kernels(lambda: box.append(run.forward_iterates(2, per_call=2)),
+                      f"phi_sweep_kernel16<{nch}>")
+    assert gh.rel_err(box[0][0][-1], h_ref) <= 1e-5
+    box = []
+    gh.expect_kernels(lambda: box.append(run.backward_iterates(h_ref, 2, per_call=2)),
+                      f"adj_sweep_kernel16<{nch}>")
+    wits, _, grads = box[0]
+    for got, want in zip((wits[-1],) + grads, (out[0],) + tuple(out[2:6])):
+        assert gh.rel_err(got, want) <= 1e-5
+    if levels > 1:
+        got = run.forward_then_backward_reusing_coeffs(2, 2)
+        assert gh.rel_err(got[0], h_ref) <= 1e-5 and gh.rel_err(got[1], out[0]) <= 1e-5
