@@ -548,15 +548,6 @@ __global__ __launch_bounds__(AdjSkMaxNT<CT>::value) void adj_skinny_kernel(AdjAr
 typedef TileCfg<2, 2, 2, 2, 1> AdjBig;    // 128 x 128, 256 threads
 typedef TileCfg<2, 2, 1, 1, 1> AdjMid;    //  64 x 64, 256 threads
 typedef TileCfg<1, 1, 1, 1, 1, 128, 1, 4> AdjSmall;  //  32 x 32, 4 waves splitting K
-// bf16: 8 waves of 32 x 64 each (one K-slice in flight measured 5 % faster than three with
-// the register budget planned for one workgroup per CU)
-typedef TileCfgB<4, 2, 1, 2, 1, true, 1, 1, 2> AdjBigB;
-typedef TileCfgB<2, 2, 1, 1, 1, true> AdjMidB;
-typedef TileCfgB<1, 1, 1, 1, 1, true, 4> AdjSmallB;
-// the same tiles with kappa * w as one bf16 term
-typedef TileCfgB<4, 2, 1, 2, 1, true, 1, 1, 2, 1, 64, false> AdjBigF;
-typedef TileCfgB<2, 2, 1, 1, 1, true, 1, 1, 2, 1, 64, false> AdjMidF;
-typedef TileCfgB<1, 1, 1, 1, 1, true, 4, 1, 2, 1, 64, false> AdjSmallF;
 // three-term operands (K-slices of 32)
 typedef TileCfgB<2, 2, 2, 2, 1, true, 1, 1, 2, 3, 32> AdjBigS;
 // the same tile with 8 waves of 32 x 64 each: half the accumulators per wave, so that two
@@ -568,39 +559,64 @@ typedef TileCfgB<4, 2, 1, 2, 1, true, 1, 1, 2, 3, 32> AdjBigS8;
 typedef TileCfgB<2, 2, 1, 2, 1, true, 1, 1, 2, 3, 32> AdjWideS;
 typedef TileCfgB<2, 2, 1, 1, 1, true, 2, 1, 2, 3, 32> AdjMidS;
 
-template <class C, class CB, class CF>
-static void launch_adj_cfg(const AdjArgs& a, hipStream_t s) {
+template <class C>
+static void launch_adj_f32(const AdjArgs& a, hipStream_t s) {
   const long long R = (long long)a.nk * a.B;
   dim3 grid((unsigned)xcd_grid((R + C::TM - 1) / C::TM, (a.H + C::TN - 1) / C::TN));
-  dim3 block(a.bf16 == 1 ? CB::NT : C::NT);
-  static_assert(CF::TM == CB::TM && CF::TN == CB::TN && CF::NT == CB::NT, "tile shapes must agree");
-  static_assert(C::TM == CB::TM && C::TN == CB::TN, "tile shapes must agree");
-  if (a.bf16 == 1 && a.one_term) {
-    if (a.mode == STEP_RELAX)
-      hipLaunchKernelGGL((adj_step_kernel_bf16<CF, STEP_RELAX>), grid, block, 0, s, a);
-    else
-      hipLaunchKernelGGL((adj_step_kernel_bf16<CF, STEP_RESID>), grid, block, 0, s, a);
-  } else if (a.bf16 == 1) {
-    if (a.mode == STEP_RELAX)
-      hipLaunchKernelGGL((adj_step_kernel_bf16<CB, STEP_RELAX>), grid, block, 0, s, a);
-    else
-      hipLaunchKernelGGL((adj_step_kernel_bf16<CB, STEP_RESID>), grid, block, 0, s, a);
-  } else {
-    if (a.mode == STEP_RELAX)
-      hipLaunchKernelGGL((adj_step_kernel<C, STEP_RELAX>), grid, block, 0, s, a);
-    else
-      hipLaunchKernelGGL((adj_step_kernel<C, STEP_RESID>), grid, block, 0, s, a);
-  }
+  if (a.mode == STEP_RELAX)
+    hipLaunchKernelGGL((adj_step_kernel<C, STEP_RELAX>), grid, dim3(C::NT), 0, s, a);
+  else
+    hipLaunchKernelGGL((adj_step_kernel<C, STEP_RESID>), grid, dim3(C::NT), 0, s, a);
 }
 
 template <class C>
-static void launch_adj_x3(const AdjArgs& a, hipStream_t s) {
+static void launch_adj_terms(const AdjArgs& a, hipStream_t s) {
   const long long R = (long long)a.nk * a.B;
   dim3 grid((unsigned)xcd_grid((R + C::TM - 1) / C::TM, (a.H + C::TN - 1) / C::TN));
   if (a.mode == STEP_RELAX)
     hipLaunchKernelGGL((adj_step_kernel_bf16<C, STEP_RELAX>), grid, dim3(C::NT), 0, s, a);
   else
     hipLaunchKernelGGL((adj_step_kernel_bf16<C, STEP_RESID>), grid, dim3(C::NT), 0, s, a);
+}
+
+// bf16 weights, kappa * w as one bf16 term (A2: two).  Every column tile forms the products again (8 bytes
+// of coefficients and state per element against 2 of a weight), so tiles are as wide as they can be with
+// a workgroup for each CU; where even small tiles leave CUs idle, groups of waves split K.  The tile with
+// the smallest number of rounds over the 256 CUs times its time for one: us of a launch of exactly one
+// round at K = 3072, one term (two terms are in the same order).  us with 128 x 128, 64 x 64 and 32 x 32
+// tiles only : these, one term: 512 rows x 1024 31.3 : 23.7, 1024 x 1024 48 : 35.5, 2048 x 1024 61 : 52, 4096 x
+// 1024 90 : 71, 8192 x 1024 174 : 115, 2048 x 512 25.9 : 19.3, 16384 x 512 103 : 74, 4096 x 256 15.6 : 12.7, 1500 x
+// 200 10.8 : 9.3, 32768 x 296 114 : 99; two terms: 512 x 1024 32 : 27, 2048 x 1024 63 : 57, 8192 x 1024 198 : 144,
+// 16384 x 512 112 : 85, 1500 x 200 11.9 : 10.1.
+template <bool A2>
+static void launch_adj_half(const AdjArgs& a, hipStream_t s) {
+  const long long R = (long long)a.nk * a.B;
+  static const struct {
+    int tm, tn, us;
+  } tile[] = {{32, 32, 22}, {32, 64, 25}, {32, 128, 34}, {64, 64, 38}, {64, 128, 51}, {64, 256, 72},
+              {128, 128, 90}, {128, 256, 115}};
+  int best = 0;
+  long long cost = 0;
+  for (int i = 0; i < 8; ++i) {
+    const long long n = ((R + tile[i].tm - 1) / tile[i].tm) * ((a.H + tile[i].tn - 1) / tile[i].tn);
+    const long long c = (n + 255) / 256 * tile[i].us;
+    if (i == 0 || c < cost) {
+      best = i;
+      cost = c;
+    }
+  }
+  switch (best) {
+    case 0: return launch_adj_terms<TileCfgB<1, 1, 1, 1, 1, true, 4, 1, 2, 1, 64, A2>>(a, s);
+    case 1: return launch_adj_terms<TileCfgB<1, 2, 1, 1, 1, true, 4, 1, 2, 1, 64, A2>>(a, s);
+    case 2: return launch_adj_terms<TileCfgB<1, 4, 1, 1, 1, true, 2, 1, 2, 1, 64, A2>>(a, s);
+    case 3:   // (up to three K-slices of 64: nothing to split; 25600 rows x 64, two terms, 15.0 split : 12.3)
+      if (a.H <= 64) return launch_adj_terms<TileCfgB<2, 2, 1, 1, 1, true, 1, 1, 2, 1, 64, A2>>(a, s);
+      return launch_adj_terms<TileCfgB<2, 2, 1, 1, 1, true, 2, 1, 2, 1, 64, A2>>(a, s);
+    case 4: return launch_adj_terms<TileCfgB<2, 2, 1, 2, 1, true, 2, 1, 2, 1, 64, A2>>(a, s);
+    case 5: return launch_adj_terms<TileCfgB<2, 4, 1, 2, 1, true, 1, 1, 2, 1, 128, A2>>(a, s);
+    case 6: return launch_adj_terms<TileCfgB<4, 2, 1, 2, 1, true, 1, 1, 2, 1, 64, A2>>(a, s);
+    default: return launch_adj_terms<TileCfgB<2, 4, 2, 2, 1, true, 1, 1, 2, 1, 64, A2>>(a, s);
+  }
 }
 
 // Rows per workgroup of the few-row adjoint step: every workgroup streams the
@@ -650,27 +666,30 @@ hipError_t launch_adj_step(const AdjArgs& a, hipStream_t s) {
       launch_adj_skinny<2>(a, grid, s);
     else
       launch_adj_skinny<1>(a, grid, s);
-  } else if (tiles(AdjBig::TM, AdjBig::TN) >= (a.bf16 == 1 ? 256 : 384)) {
+  } else if (a.bf16 == 1) {
+    if (a.one_term) launch_adj_half<false>(a, s);
+    else launch_adj_half<true>(a, s);
+  } else if (tiles(AdjBig::TM, AdjBig::TN) >= 384) {
     if (a.bf16 == 2 && a.mode == STEP_RELAX)
-      launch_adj_x3<AdjBigS8>(a, s);
+      launch_adj_terms<AdjBigS8>(a, s);
     else if (a.bf16 == 2)
-      launch_adj_x3<AdjBigS>(a, s);
+      launch_adj_terms<AdjBigS>(a, s);
     else
-      launch_adj_cfg<AdjBig, AdjBigB, AdjBigF>(a, s);
+      launch_adj_f32<AdjBig>(a, s);
   }
   // three terms, by what fills the chip (us, 64 x 64 without the split : 64 x 128 : 64 x 64 split):
   // 3200 rows x 1000 (400 wide tiles) 247 : 179 : 207, 4096 x 1024 (512) 215 : 169 : 193,
   // 4096 x 512 (256) 65 : 69 : 56, 1024 x 1024 (256 tiles of 64 x 64) 101 : 121 : 75, 800 x 1000 (208)
   // 99 with 32 x 32 tiles, 82 split
   else if (a.bf16 == 2 && tiles(AdjWideS::TM, AdjWideS::TN) >= 384)
-    launch_adj_x3<AdjWideS>(a, s);
+    launch_adj_terms<AdjWideS>(a, s);
   else if (a.bf16 == 2 && R > 32 && tiles(AdjMidS::TM, AdjMidS::TN) >= 192)
-    launch_adj_x3<AdjMidS>(a, s);
+    launch_adj_terms<AdjMidS>(a, s);
   else if (R > 32 && tiles(AdjMid::TM, AdjMid::TN) >= 256)
-    launch_adj_cfg<AdjMid, AdjMidB, AdjMidF>(a, s);
+    launch_adj_f32<AdjMid>(a, s);
   else   // (three terms included: 32 x 32 tiles are faster in fp32, see launch_phi_cfg, and no less
          // accurate, see gemm_nt_tile)
-    launch_adj_cfg<AdjSmall, AdjSmallB, AdjSmallF>(a, s);
+    launch_adj_f32<AdjSmall>(a, s);
   prof_end(kind, 6.0 * (double)R * a.H * a.H, 28.0 * (double)R * a.H, s);
   return hipGetLastError();
 }

@@ -10,7 +10,7 @@ import paper_2203_04738_amd as mg
 from oracle import lstm_oracle as lo
 from oracle import mgrit_gru_oracle as orc
 from paper_2203_04738_amd.binding import MgritGruCfg
-from synthetic_inputs import random_lstm, random_small
+from synthetic_inputs import random_lstm, random_small, round_to_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -96,6 +96,35 @@ def test_gru_tiles(gh, B, H, phi, adj, adj_resid, value):
     # (linear: the row with the huge terminal value is huge altogether)
     for i in range(len(r)):
         assert gh.rel_err(w[:, r[i]], want[:, i]) <= 1e-5, ("w", r[i])
+
+
+@pytest.mark.parametrize("form,tol", [("bf16", 2e-2), ("bf16s2", 1e-4)])
+@pytest.mark.parametrize("B,H,adj", [(250, 264, "1, 1, 1, 1, 1, true, 4, 1, 2, 1, 64"),
+                                     (250, 520, "1, 2, 1, 1, 1, true, 4, 1, 2, 1, 64"),
+                                     (457, 520, "1, 4, 1, 1, 1, true, 2, 1, 2, 1, 64"),
+                                     (4111, 40, "2, 2, 1, 1, 1, true, 1, 1, 2, 1, 64"),
+                                     (829, 520, "2, 2, 1, 1, 1, true, 2, 1, 2, 1, 64"),
+                                     (921, 520, "2, 2, 1, 2, 1, true, 2, 1, 2, 1, 64"),
+                                     (1665, 520, "2, 4, 1, 2, 1, true, 1, 1, 2, 1, 128"),
+                                     (8215, 104, "4, 2, 1, 2, 1, true, 1, 1, 2, 1, 64"),
+                                     (8215, 200, "2, 4, 2, 2, 1, true, 1, 1, 2, 1, 64")])
+def test_adjoint_tiles_on_bf16_weights(gh, B, H, adj, form, tol):
+    """Every tile of the rule with row, column and K tails, relaxation and residual; the bars of the two
+    forms are those of the oracle parity tests."""
+    print("bf16 adjoint tiles", B, H, form, flush=True)
+    d, r = _problem(B, H), _rows(B)
+    for k in ("x", "W", "U"):
+        d[k] = round_to_bf16(d[k])
+    P, z, _ = _oracle(d, r)
+    run = gh.GpuRun(d, cf=CF, levels=2, dtype=form)
+    h = run.forward_iterates(1)[0][-1]
+    box = []
+    two = "true" if form == "bf16s2" else "false"
+    gh.expect_kernels(lambda: box.append(run.backward_iterates(h, 1)),
+                      *(f"adj_step_kernel_bf16<mg::TileCfgB<{adj}, {two}, false>, {m}" for m in (0, 1)))
+    want = orc.mgrit_backward(*P, d["x"][:, r], h[:, r], d["dL_dhT"][r], z, CF, 2, 1)[0]
+    for i in range(len(r)):
+        assert gh.rel_err(box[0][0][-1][:, r[i]], want[:, i]) <= tol, ("w", r[i])
 
 
 @pytest.mark.parametrize("value", [None, BIG_VALUE])
