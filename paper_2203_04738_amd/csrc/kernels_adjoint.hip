@@ -748,7 +748,7 @@ struct GradArgs {
   int B, H, N;         // N = H (dU) or D (dW)
   int third_off;       // 2H (k_q, dU) or 4H (k_n, dW)
   int mtiles, ntiles;  // output tiles along 3H and N
-  int splits;          // row splits (a multiple of 8, or fewer than 8)
+  int splits;          // row splits
 };
 
 // acc += sum over the rows k in [kbeg, kend) of S[k, m] Bm[k, n], m = m0.., n = n0..; colsum: this
@@ -1332,28 +1332,30 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_tr_kernel(GradArgs a) {
       }
 }
 
-// The same partial products for fp32 operands carried as three bf16 terms each (see
-// gemm_core_bf16.h): S and the second operand (h or x) are split on their way to LDS and six
-// of the nine term products are kept.  K-slices of 32 rows; waves 0-1 stage S (the product
-// kappa * w, transposed in registers as above), waves 2-3 stage the second operand.
+// The same partial products for fp32 operands carried as three bf16 terms each (see gemm_core_bf16.h):
+// S and the second operand (h or x) are split on their way to LDS and six of the nine term products are
+// kept.  Staging as in grad_gemm_tr_kernel: LDS rows in memory order, fragments from the transpose read.
+// NB: 32-column blocks of a wave; 4: tiles of 128 x 256, 2: of 128 x 128.  Every operand element is loaded,
+// multiplied and split once per tile that uses it; the wide tile does that a quarter less often per MFMA.
+// Two workgroups' tiles of terms (72 KB each) fit the LDS without padding only: columns are exchanged by
+// bits 0-1 of the row instead, so that the four rows of a read fall on different banks.
+// (Tiles of 128 x 128 with operands transposed in registers, half of whose LDS cycles were bank conflicts,
+// took 1.00 ms for a gradient of 65536 rows, 1536 x 768 on average, now 0.77; 12800 rows, 3000 x 1000
+// 0.53, now 0.42: 184 TFLOP/s.)
 constexpr int HS_TK = 32;
-constexpr int HS_LD = HS_TK + 8;
+template <int NB>
 __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
-  __shared__ __attribute__((aligned(16))) bf16_t As[3][GT * HS_LD];
-  __shared__ __attribute__((aligned(16))) bf16_t Bs[3][GT * HS_LD];
+  constexpr int GN = 64 * NB;
+  __shared__ __attribute__((aligned(16))) bf16_t As[3][HS_TK * GT];
+  __shared__ __attribute__((aligned(16))) bf16_t Bs[3][HS_TK * GN];
   const int H = a.H, N = a.N, M = 3 * a.H;
   const int tiles = a.mtiles * a.ntiles;
-  int tile, z;
-  if (a.splits % NXCD == 0) {
-    const int j = blockIdx.x / NXCD;
-    tile = j % tiles;
-    z = (j / tiles) * NXCD + blockIdx.x % NXCD;
-  } else {
-    tile = blockIdx.x % tiles;
-    z = blockIdx.x / tiles;
-  }
+  // an XCD gets consecutive items, split by split: its rows of S and Bm enter one L2 only
+  const int item = (blockIdx.x % NXCD) * (gridDim.x / NXCD) + blockIdx.x / NXCD;
+  if (item >= tiles * a.splits) return;
+  const int tile = item % tiles, z = item / tiles;
   const int nt = tile / a.mtiles;
-  const int m0 = (tile % a.mtiles) * GT, n0 = nt * GT;
+  const int m0 = (tile % a.mtiles) * GT, n0 = nt * GN;
   const long long kbeg = (long long)z * a.Kper;
   long long kend = kbeg + a.Kper;
   if (kend > a.Ktot) kend = a.Ktot;
@@ -1361,70 +1363,93 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
   const int wm = wave >> 1, wn = wave & 1, li = lane & 31, lh = lane >> 5;
   const long long rowoff = a.B;           // kap0 / w rows are one time point ahead
 
-  floatx16 acc[2][2];
+  // wave: rows wm * 64 .., columns (j / 2) * 128 + wn * 64 + (j % 2) * 32 .. of block j
+  floatx16 acc[2][NB];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  // staging block of a thread: columns c4*4..+3 of its operand, rows k8*8..+7 of the slice
-  const bool is_a = tid < 128;             // uniform per wave
-  const int c4 = tid & 31, k8 = (tid >> 5) & 3;
-  const int col = (is_a ? m0 : n0) + c4 * 4;
-  const bool c_ok = col < (is_a ? M : N);
-  const int cc = c_ok ? col : 0;
-  const int gate = cc / H, jcol = cc - gate * H;            // (A threads)
-  const int src = gate == 2 ? a.third_off + jcol : cc;
-  // Rows four apart are 320 bytes apart, i.e. 64 modulo the 256 bytes the banks span: the
-  // 16-byte chunk a thread writes is therefore exchanged with another chunk of its rows,
-  // chosen by bits 2-3 of the column block (the readers undo it with bits 4-5 of the row),
-  // so that sixteen neighbouring lanes cover all banks once.
-  bf16_t* dst = (is_a ? &As[0][0] : &Bs[0][0]) + (c4 * 4) * HS_LD + (k8 ^ ((c4 >> 2) & 3)) * 8;
-
-  // first operand row k of this thread: a coefficient row (A) or a row of h / x (B)
-  const float* base0 = is_a ? a.kap0 + rowoff * (5LL * H) + src : (const float*)a.Bm + cc;
-  const long long stride0 = is_a ? 5LL * H : (long long)N;
-  floatx4 r0[8], r1[8];
-  float colsum[4] = {0.f, 0.f, 0.f, 0.f};
+  // staging of S: columns m4*4..+3, slice rows k8 + 8r; of the second operand: c4*4..+3, rows kf + KS r
+  constexpr int CL = GN / 4, KS = 256 / CL, NR = HS_TK / KS;
+  static_assert(KS % 4 == 0, "one exchange of columns per thread");
+  const int m4 = tid & 31, k8 = tid >> 5;
+  const int c4 = tid % CL, kf = tid / CL;
+  const int m = m0 + m4 * 4, n = n0 + c4 * 4;
+  const bool m_ok = m < M, n_ok = n < N;
+  const int mc = m_ok ? m : 0, nc = n_ok ? n : 0;
+  const int gate = mc / H, jcol = mc - gate * H;
+  const int src = gate == 2 ? a.third_off + jcol : mc;
+  bf16_t* const adst = &As[0][k8 * GT + ((m4 * 4) ^ ((k8 & 3) << 5))];
+  bf16_t* const bdst = &Bs[0][kf * GN + ((c4 * 4) ^ ((kf & 3) << 5))];
+  const float* const kbase = a.kap0 + rowoff * (5LL * H) + src;
+  const float* const wbase = a.w + rowoff * H + jcol;
+  const float* const bbase = (const float*)a.Bm + nc;
+  floatx4 rk[4], rw[4], rb[NR];
+  float colsum[2] = {0.f, 0.f};           // of columns m4*4 + 2 lh, + 1: both row groups of the wave
   auto fetch = [&](long long k0) {
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      long long k = k0 + k8 * 8 + r;
+    for (int r = 0; r < 4; ++r) {
+      long long k = k0 + k8 + 8 * r;
       if (k >= kend) k = kend - 1;
-      r0[r] = ldg4(base0 + k * stride0);
-      floatx4 t = zero4();
-      if (is_a) t = ldg4(a.w + (k + rowoff) * H + jcol);
-      r1[r] = t;
+      rk[r] = ldg4(kbase + k * (5LL * H));
+      rw[r] = ldg4(wbase + k * H);
+    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      long long k = k0 + kf + KS * r;
+      if (k >= kend) k = kend - 1;
+      rb[r] = ldg4(bbase + k * N);
+    }
+  };
+  auto put = [](bf16_t* dst, int plane, floatx4 v) {
+    typedef unsigned uintx2_ __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] *= SPLIT3_SCALE;
+    float x[4] = {v[0], v[1], v[2], v[3]};
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const uintx2_ w = {round2_bf16(x[0], x[1]), round2_bf16(x[2], x[3])};
+      *reinterpret_cast<uintx2_*>(dst + t * plane) = w;
+      if (t < 2) {
+        minus2_bf16(x[0], x[1], w[0]);
+        minus2_bf16(x[2], x[3], w[1]);
+      }
     }
   };
   auto stash = [&](long long k0) {
-    floatx4 p[8];
+    floatx4 p[4];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const bool ok = c_ok && k0 + k8 * 8 + r < kend;
-      p[r] = ok ? (is_a ? r0[r] * r1[r] : r0[r]) : zero4();
+    for (int r = 0; r < 4; ++r) {
+      p[r] = (m_ok && k0 + k8 + 8 * r < kend) ? rk[r] * rw[r] : zero4();
+      put(adst + 8 * r * GT, HS_TK * GT, p[r]);
     }
+    // a tree of eight rows: one addition per slice into the long sum (four rows: bias gradients 2-15 %
+    // further from 64 bits).  The halves of the wave exchange two columns each.  Only the first column
+    // tile reports it.
+    if (nt == 0) {
+      const floatx4 t = (p[0] + p[1]) + (p[2] + p[3]);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      F32x8 v;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        v.lo4[r] = p[r][e] * SPLIT3_SCALE;
-        v.hi4[r] = p[4 + r][e] * SPLIT3_SCALE;
+      for (int e = 0; e < 2; ++e) {
+        const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(t[e]), __float_as_uint(t[2 + e]),
+                                                        false, false);
+        colsum[e] += __uint_as_float(x[0]) + __uint_as_float(x[1]);
       }
-      // (a tree: one addition per slice into the long sum; only the first column tile reports it)
-      if (is_a && nt == 0)
-        colsum[e] += ((p[0][e] + p[1][e]) + (p[2][e] + p[3][e])) +
-                     ((p[4][e] + p[5][e]) + (p[6][e] + p[7][e]));
-      bf16x8 t0, t1, t2;
-      split_bf16_3(v, t0, t1, t2);
-      *reinterpret_cast<bf16x8*>(dst + e * HS_LD) = t0;
-      *reinterpret_cast<bf16x8*>(dst + GT * HS_LD + e * HS_LD) = t1;
-      *reinterpret_cast<bf16x8*>(dst + 2 * GT * HS_LD + e * HS_LD) = t2;
     }
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+      put(bdst + KS * r * GN, HS_TK * GN, (n_ok && k0 + kf + KS * r < kend) ? rb[r] : zero4());
   };
+  // transpose reads: see grad_gemm_tr_kernel
+  const int i16 = lane & 15, half = (lane >> 4) & 1, rr = i16 >> 2;
+  int aoff[2], boff[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    aoff[i] = (lh * 8 + rr) * GT + ((wm * 64 + i * 32 + half * 16 + 4 * (i16 & 3)) ^ (rr << 5));
+    boff[i] = (lh * 8 + rr) * GN + ((wn * 64 + i * 32 + half * 16 + 4 * (i16 & 3)) ^ (rr << 5));
+  }
 
   if (kbeg < kend) {
     fetch(kbeg);
@@ -1437,29 +1462,27 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
       __builtin_amdgcn_s_setprio(2);
 #pragma unroll
       for (int c = 0; c < HS_TK / 16; ++c) {
-        bf16x8 fa[3][2], fb[3][2];
+        bf16x8 fa[3][2];
 #pragma unroll
         for (int t = 0; t < 3; ++t)
 #pragma unroll
-          for (int i = 0; i < 2; ++i) {
-            const int ch = ((2 * c + lh) ^ ((2 * i + (li >> 4)) & 3)) * 8;
-            fa[t][i] = *reinterpret_cast<const bf16x8*>(
-                &As[t][(wm * 64 + i * 32 + li) * HS_LD + ch]);
-            fb[t][i] = *reinterpret_cast<const bf16x8*>(
-                &Bs[t][(wn * 64 + i * 32 + li) * HS_LD + ch]);
-          }
+          for (int i = 0; i < 2; ++i) fa[t][i] = lds_tr8(&As[t][aoff[i] + c * 16 * GT], GT);
 #pragma unroll
-        for (int t = 0; t < 3; ++t)
+        for (int j = 0; j < NB; ++j) {
+          bf16x8 fb[3];
 #pragma unroll
-          for (int u = 0; u < 3; ++u) {
-            if (t + u > 2) continue;
+          for (int u = 0; u < 3; ++u)
+            fb[u] = lds_tr8(&Bs[u][boff[j & 1] + c * 16 * GN + (j >> 1) * 128], GN);
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+          for (int t = 0; t < 3; ++t)
 #pragma unroll
-              for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[t][i], fb[u][j], acc[i][j],
-                                                                    0, 0, 0);
-          }
+            for (int u = 0; u < 3; ++u) {
+              if (t + u > 2) continue;
+#pragma unroll
+              for (int i = 0; i < 2; ++i)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[t][i], fb[u], acc[i][j], 0, 0, 0);
+            }
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_setprio(0);
@@ -1476,49 +1499,55 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < NB; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           acc[i][j][e] *= SPLIT3_UNSCALE;
           t = fmaf(acc[i][j][e], 0.f, t);
         }
     if (__syncthreads_or(t != t)) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
       static_assert(sizeof(As) >= GTK * GLD * sizeof(float), "fp32 slice must fit");
-      floatx4 unused = zero4();
-      grad_contract_f32<float>(a, m0, n0, kbeg, kend, (float*)&As[0][0], (float*)&Bs[0][0], acc,
-                               unused);
+#pragma unroll
+      for (int hb = 0; hb < NB / 2; ++hb) {
+        if (n0 + hb * 128 >= N) break;                 // (uniform)
+        floatx16 full[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) full[i][j][e] = 0.f;
+        floatx4 unused = zero4();
+        grad_contract_f32<float>(a, m0, n0 + hb * 128, kbeg, kend, (float*)&As[0][0],
+                                 (float*)&Bs[0][0], full, unused);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[i][2 * hb + j] = full[i][j];
+      }
     }
   }
-  // column sums of S: the four row groups of a column meet in LDS (the A tiles are free now)
+  // column sums of S: the four waves' sums of a column meet in LDS (the A tiles are free now)
   float* red = reinterpret_cast<float*>(&As[0][0]);      // [4][GT] floats
   __syncthreads();
-  if (is_a) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) red[k8 * GT + c4 * 4 + e] = colsum[e];
-  }
+  for (int e = 0; e < 2; ++e) red[wave * GT + m4 * 4 + 2 * lh + e] = colsum[e];
   __syncthreads();
-  if (tid < GT && m0 + tid < M) {
+  if (nt == 0 && tid < GT && m0 + tid < M) {
     float sum = 0.f;
 #pragma unroll
     for (int q = 0; q < 4; ++q) sum += red[q * GT + tid];
-    // every column tile holds the same sums: the first one reports them
-    if (nt == 0) a.bpart[(long long)z * M + m0 + tid] = sum;
+    a.bpart[(long long)z * M + m0 + tid] = sum;
   }
   float* out = a.part + (long long)z * M * N;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int mm = m0 + wm * 64 + i * 32 + 8 * (e / 4) + 4 * lh + (e & 3);
-        const int nn = n0 + wn * 64 + j * 32 + li;
+        const int nn = n0 + (j >> 1) * 128 + wn * 64 + (j & 1) * 32 + li;
         if (mm < M && nn < N) out[(long long)mm * N + nn] = acc[i][j][e];
       }
 }
@@ -1623,6 +1652,38 @@ static int grad_splits(long long Ktot, int M, int N, int bf16) {
   return (int)best;
 }
 
+// Tile columns and row splits of the three-term kernel, at most `cap` splits (what the partials have room
+// for): the least of rounds over the 512 workgroup slots x (slices x us per slice + 10) + what the partials
+// cost.  us per slice of 32 rows, measured: a workgroup alone on its CU 2.17 (128 columns) and 3.45 (256), two
+// of them 2.9 and 5.1; partials are written and read at 6 TB/s.  Predicted : measured us of one gradient,
+// 128 / 256 columns at their best splits: 12800 rows, 1512 x 504 136 : 132 / 133 : 136; 4096, 1536 x 512
+// 58 : 54 / 65 : 59; 12800, 888 x 296 67 : 63 / 86 : 77; 8192, 3072 x 1024 331 : 319 / 296 : 292; 65536,
+// 1536 x 512 623 : 599 / 541 : 540.
+struct GradX3 {
+  int cols, splits;
+};
+static GradX3 grad_x3_shape(long long Ktot, int M, int N, int cap) {
+  constexpr double LONE[2] = {2.17, 3.45}, TWO[2] = {2.9, 5.1};
+  GradX3 best = {0, 1};
+  double least = 0;
+  for (int wide = 0; wide < (N > GT ? 2 : 1); ++wide) {
+    const int gn = GT << wide;
+    const long long tiles = (long long)((M + GT - 1) / GT) * ((N + gn - 1) / gn);
+    for (int sp = 1; sp <= cap; ++sp) {
+      const long long n = tiles * sp, rest = n % 512;
+      const double slices = (double)((Ktot + 32LL * sp - 1) / (32LL * sp));
+      const double slot = slices * TWO[wide] + 10, tail = slices * LONE[wide] + 10;
+      const double us = (double)(n / 512) * slot + (rest == 0 ? 0.0 : rest <= 256 ? tail : slot) +
+                        (double)sp * M * N * 8 / 6e6;
+      if (best.cols == 0 || us < least) {
+        least = us;
+        best = {gn, sp};
+      }
+    }
+  }
+  return best;
+}
+
 size_t grad_partial_floats(int T, int B, int D, int H, int bf16) {
   const long long Ktot = (long long)T * B;
   const size_t zu = (size_t)grad_splits(Ktot, 3 * H, H, bf16);
@@ -1656,20 +1717,28 @@ hipError_t launch_param_grads(const float* kap0, const float* w, const float* h,
     a.Ktot = Ktot;
     a.B = B;
     a.H = H;
-    const int splits = grad_splits(Ktot, M, a.N, sform);
+    int splits = grad_splits(Ktot, M, a.N, sform);
+    int gn = grad_tile_n(a.N, bf16);
+    if (bf16 == 2) {
+      const GradX3 shape = grad_x3_shape(Ktot, M, a.N, splits);
+      gn = shape.cols;
+      splits = shape.splits;
+    }
+    a.mtiles = (M + GT - 1) / GT;
+    a.ntiles = (a.N + gn - 1) / gn;
     long long per = (Ktot + splits - 1) / splits;
     const int slice = bf16 == 1 ? HB_TK : GTK;      // (both multiples of the 32 of bf16 = 2)
     a.Kper = (per + slice - 1) / slice * slice;
-    a.mtiles = (M + GT - 1) / GT;
-    const int gn = grad_tile_n(a.N, bf16);
-    a.ntiles = (a.N + gn - 1) / gn;
     a.splits = splits;
     a.bpart = bpart[which];
     nbpart[which] = splits;
     if (which == 0) bpart[1] = bpart[0] + (size_t)nbpart[0] * M;
     dim3 grid((unsigned)((long long)a.mtiles * a.ntiles * splits));
-    if (bf16 == 2)
-      hipLaunchKernelGGL(grad_gemm_x3_kernel, grid, dim3(256), 0, s, a);
+    if (bf16 == 2) grid.x = (grid.x + NXCD - 1) / NXCD * NXCD;
+    if (bf16 == 2 && gn == 2 * GT)
+      hipLaunchKernelGGL(grad_gemm_x3_kernel<4>, grid, dim3(256), 0, s, a);
+    else if (bf16 == 2)
+      hipLaunchKernelGGL(grad_gemm_x3_kernel<2>, grid, dim3(256), 0, s, a);
     else if (bf16 && gn == TR_GN && which == 1 && one_term)
       hipLaunchKernelGGL((grad_gemm_tr_kernel<true, true>), grid, dim3(256), 0, s, a);
     else if (bf16 && gn == TR_GN && one_term)

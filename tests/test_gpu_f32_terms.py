@@ -133,6 +133,25 @@ def test_gradients_of_adjoints_beyond_the_terms(gh):
         assert gh.rel_err(got, want) <= 1e-5, name
 
 
+@pytest.mark.parametrize("loss", [1.0, 1e35])
+def test_gradients_on_wide_and_narrow_tiles(gh, loss):
+    """1320 = 41 x 32 + 8 rows; dW, 3096 x 1000, on tiles of 256 columns and dU, 3096 x 1032, on tiles of
+    128, neither a whole number of them.  1e35: sums beyond the terms, taken again in fp32."""
+    T, B, D, H = 40, 33, 1000, 1032
+    print("wide and narrow gradient tiles", loss, flush=True)
+    d = random_small(7, T, B, D, H, scale=0.3 / np.sqrt(H))
+    d["dL_dhT"] = (d["dL_dhT"] * loss).astype(np.float32)
+    P = (d["W"], d["U"], d["b_i"], d["b_h"])
+    h = orc.serial_scan(*P, d["x"], d["h0"]).astype(np.float32)
+    want = orc.serial_bptt(*P, d["x"], h, d["dL_dhT"])
+    run = gh.GpuRun(d)
+    box = []
+    gh.expect_kernels(lambda: box.append(run.serial_backward(h)), "grad_gemm_x3_kernel<4>",
+                      "grad_gemm_x3_kernel<2>")
+    for name, g, r in zip(("w", "dW", "dU", "db_i", "db_h"), box[0], want):
+        assert gh.rel_err(g, r) <= 1e-5, name
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "fp32x3"])
 @pytest.mark.parametrize("what", ["dL_dhT", "x", "W"])
 def test_operands_far_below_one(gh, what, dtype):
