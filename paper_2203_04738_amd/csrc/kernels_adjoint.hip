@@ -751,11 +751,18 @@ struct GradArgs {
   int splits;          // row splits
 };
 
+// Both gradients in one launch of the fp32 kernel: workgroups from `first` on belong to dW.
+struct GradPair {
+  GradArgs g[2];
+  unsigned first;
+  float *db_i, *db_h;  // one split: the sums are the gradients (g[].part = dU, dW), biases go here; else null
+};
+
 // acc += sum over the rows k in [kbeg, kend) of S[k, m] Bm[k, n], m = m0.., n = n0..; colsum: this
 // thread's share of the column sums of S.  Both operands are read with the contracted index k
 // slowest, so an LDS slice is stored [k][m] and a lane reads its MFMA operand as one float per
 // k-pair.  As, Bs: GTK * GLD floats each.
-template <class BT>
+template <class BT, bool SKIP>
 __device__ inline void grad_contract_f32(const GradArgs& a, int m0, int n0, long long kbeg,
                                          long long kend, float* As, float* Bs,
                                          floatx16 (&acc)[2][2], floatx4& colsum) {
@@ -805,6 +812,10 @@ __device__ inline void grad_contract_f32(const GradArgs& a, int m0, int n0, long
       bv[j] = Bs[(2 * p + lh) * GLD + wn * 64 + ((j ^ lh) << 5) + li];
   };
 
+  // SKIP: 32 x 32 blocks of this wave that hold no outputs are left out (a layer of 32 columns fills one
+  // of two)
+  const int mi = M - m0 - wm * 64, nj = N - n0 - wn * 64;
+  const bool full = !SKIP || (mi > 32 && nj > 32);
   if (kbeg < kend) {
     fetch(kbeg);
     stash(kbeg);
@@ -815,25 +826,37 @@ __device__ inline void grad_contract_f32(const GradArgs& a, int m0, int n0, long
       __builtin_amdgcn_sched_barrier(0);
       float av[2][2], bv[2][2];
       __builtin_amdgcn_s_setprio(2);      // MFMA phase first at issue (see gemm_core.h)
-      frags(0, av[0], bv[0]);
+      if (full) {
+        frags(0, av[0], bv[0]);
 #pragma unroll
-      for (int p = 0; p < GTK / 2; ++p) {
-        if (p + 1 < GTK / 2) frags(p + 1, av[(p + 1) & 1], bv[(p + 1) & 1]);
+        for (int p = 0; p < GTK / 2; ++p) {
+          if (p + 1 < GTK / 2) frags(p + 1, av[(p + 1) & 1], bv[(p + 1) & 1]);
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+          for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[p & 1][i], bv[p & 1][j],
-                                                             acc[i][j], 0, 0, 0);
-        if (p + 1 < GTK / 2) {
-          // one LDS read of the next k-pair, one MFMA of this pair, four times
+            for (int j = 0; j < 2; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[p & 1][i], bv[p & 1][j],
+                                                               acc[i][j], 0, 0, 0);
+          if (p + 1 < GTK / 2) {
+            // one LDS read of the next k-pair, one MFMA of this pair, four times
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            for (int q = 0; q < 4; ++q) {
+              __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            }
           }
+          __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
+      } else if (mi > 0 && nj > 0) {
+#pragma unroll 4
+        for (int p = 0; p < GTK / 2; ++p) {
+          frags(p, av[0], bv[0]);
+          acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[0][0], bv[0][0], acc[0][0], 0, 0, 0);
+          if (mi > 32)
+            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[0][1], bv[0][0], acc[1][0], 0, 0, 0);
+          if (nj > 32)
+            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[0][0], bv[0][1], acc[0][1], 0, 0, 0);
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_setprio(0);
@@ -850,20 +873,25 @@ __device__ inline void grad_contract_f32(const GradArgs& a, int m0, int n0, long
 // 1-D grid: workgroups go round-robin over the 8 XCDs, so split z is given to XCD
 // z % 8 and all output tiles of a split run on that XCD: its rows of S and Bm are
 // fetched into one L2 only.
-template <class BT>
-__global__ __launch_bounds__(256, 3) void grad_gemm_kernel(GradArgs a) {
+// SKIP: for small problems, see grad_contract_f32 (its branches spill four registers).
+template <class BT, bool SKIP>
+__global__ __launch_bounds__(256, 3) void grad_gemm_kernel(GradPair pair) {
   __shared__ __attribute__((aligned(16))) float As[GTK * GLD];
   __shared__ __attribute__((aligned(16))) float Bs[GTK * GLD];
+  const int which = blockIdx.x >= pair.first ? 1 : 0;
+  const GradArgs& a = pair.g[which];
+  const int bid = (int)(blockIdx.x - (which ? pair.first : 0));
   const int N = a.N, M = 3 * a.H;
   const int tiles = a.mtiles * a.ntiles;
+  if (bid >= tiles * a.splits) return;      // (`first` is a multiple of the XCDs)
   int tile, z;
   if (a.splits % NXCD == 0) {
-    const int j = blockIdx.x / NXCD;
+    const int j = bid / NXCD;
     tile = j % tiles;
-    z = (j / tiles) * NXCD + blockIdx.x % NXCD;
+    z = (j / tiles) * NXCD + bid % NXCD;
   } else {
-    tile = blockIdx.x % tiles;
-    z = blockIdx.x / tiles;
+    tile = bid % tiles;
+    z = bid / tiles;
   }
   const int m0 = (tile % a.mtiles) * GT, n0 = (tile / a.mtiles) * GT;
   const long long kbeg = (long long)z * a.Kper;
@@ -883,7 +911,7 @@ __global__ __launch_bounds__(256, 3) void grad_gemm_kernel(GradArgs a) {
   // Bias gradients are the column sums of S: every thread adds up the products it stages
   // (its four columns, its rows of every slice); the eight row groups meet in LDS at the end.
   floatx4 colsum = zero4();
-  grad_contract_f32<BT>(a, m0, n0, kbeg, kend, As, Bs, acc, colsum);
+  grad_contract_f32<BT, SKIP>(a, m0, n0, kbeg, kend, As, Bs, acc, colsum);
   const int nt = tile / a.mtiles;
   {
     float* red = As;                    // [8][GT] floats (the slices are no longer read)
@@ -896,7 +924,15 @@ __global__ __launch_bounds__(256, 3) void grad_gemm_kernel(GradArgs a) {
 #pragma unroll
       for (int q = 0; q < 8; ++q) sum += red[q * GT + tid];
       // every column tile holds the same sums: the first one reports them
-      if (nt == 0) a.bpart[(long long)z * M + m0 + tid] = sum;
+      if (nt == 0) {
+        const int c = m0 + tid, H = a.H;
+        if (!pair.db_h) {
+          a.bpart[(long long)z * M + c] = sum;
+        } else {                          // as in bias_reduce
+          if (which == 0) pair.db_h[c] = sum;
+          if ((which == 0) == (c < 2 * H)) pair.db_i[c] = sum;
+        }
+      }
     }
   }
   float* out = a.part + (long long)z * M * N;
@@ -1518,7 +1554,7 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) full[i][j][e] = 0.f;
         floatx4 unused = zero4();
-        grad_contract_f32<float>(a, m0, n0 + hb * 128, kbeg, kend, (float*)&As[0][0],
+        grad_contract_f32<float, false>(a, m0, n0 + hb * 128, kbeg, kend, (float*)&As[0][0],
                                  (float*)&Bs[0][0], full, unused);
 #pragma unroll
         for (int i = 0; i < 2; ++i)
@@ -1556,13 +1592,12 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
 // of the chip idle and a thread's additions wait for one load after the other, so G thread rows of a
 // workgroup share the splits (eight loads in flight each) and meet in LDS, in a fixed order.
 template <int G>
-__global__ __launch_bounds__(256) void reduce_partials_kernel(const floatx4* __restrict__ part,
-                                                              floatx4* __restrict__ out,
-                                                              long long n4, int splits) {
+__device__ inline void reduce_partials(const floatx4* __restrict__ part, floatx4* __restrict__ out,
+                                       long long n4, int splits, unsigned block) {
   constexpr int CW = 256 / G;
   __shared__ floatx4 red[G > 1 ? G : 1][CW];
   const int c = threadIdx.x % CW, grp = threadIdx.x / CW;
-  const long long i = (long long)blockIdx.x * CW + c;
+  const long long i = (long long)block * CW + c;
   floatx4 s = zero4();
   if (i < n4) {
     int z = grp;
@@ -1584,16 +1619,22 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const floatx4* __r
   }
   if (i < n4) out[i] = s;
 }
+template <int G>
+__global__ __launch_bounds__(256) void reduce_partials_kernel(const floatx4* __restrict__ part,
+                                                              floatx4* __restrict__ out,
+                                                              long long n4, int splits) {
+  reduce_partials<G>(part, out, n4, splits, blockIdx.x);
+}
 
 // Bias gradients from the column sums the two gradient GEMMs leave behind, one row per
 // row split: pu[nu][3H] (columns k_r w, k_z w, k_q w) and pw[nw][3H] (k_r w, k_z w, k_n w).
 // A workgroup covers 32 columns; its eight thread rows share the splits and meet in LDS.
-__global__ void __launch_bounds__(256)
-bias_reduce_kernel(const float* __restrict__ pu, int nu, const float* __restrict__ pw, int nw,
-                   float* __restrict__ db_i, float* __restrict__ db_h, int H) {
+__device__ inline void bias_reduce(const float* __restrict__ pu, int nu, const float* __restrict__ pw,
+                                   int nw, float* __restrict__ db_i, float* __restrict__ db_h, int H,
+                                   unsigned block) {
   __shared__ float red[2][8][32];
   const int lane = threadIdx.x & 31, grp = threadIdx.x >> 5;
-  const int c = blockIdx.x * 32 + lane;
+  const int c = block * 32 + lane;
   float su = 0.f, sw = 0.f;
   if (c < 3 * H) {
     for (int z = grp; z < nu; z += 8) su += pu[(long long)z * 3 * H + c];
@@ -1614,6 +1655,24 @@ bias_reduce_kernel(const float* __restrict__ pu, int nu, const float* __restrict
     db_h[c] = su;
     db_i[c] = c < 2 * H ? su : sw;
   }
+}
+__global__ void __launch_bounds__(256)
+bias_reduce_kernel(const float* pu, int nu, const float* pw, int nw, float* db_i, float* db_h, int H) {
+  bias_reduce(pu, nu, pw, nw, db_i, db_h, H, blockIdx.x);
+}
+// The three together, where both GEMMs ran in one launch: bu and bw workgroups for dU and dW.
+template <int G>
+__global__ __launch_bounds__(256) void reduce_pair_kernel(GradPair pair, floatx4* dU, floatx4* dW,
+                                                          float* db_i, float* db_h, unsigned bu,
+                                                          unsigned bw) {
+  const GradArgs &u = pair.g[0], &w = pair.g[1];
+  const unsigned b = blockIdx.x;
+  if (b < bu)
+    reduce_partials<G>((const floatx4*)u.part, dU, 3LL * u.H * u.N / 4, u.splits, b);
+  else if (b < bu + bw)
+    reduce_partials<G>((const floatx4*)w.part, dW, 3LL * w.H * w.N / 4, w.splits, b - bu);
+  else
+    bias_reduce(u.bpart, u.splits, w.bpart, w.splits, db_i, db_h, u.H, b - bu - bw);
 }
 
 // Row splits of a gradient GEMM.  Enough workgroups for at least two per slot (256 CUs x
@@ -1699,6 +1758,72 @@ hipError_t launch_param_grads(const float* kap0, const float* w, const float* h,
   const long long Ktot = (long long)T * B;
   const int M = 3 * H;
   prof_begin(3, s);
+  auto done = [&] {
+    prof_end(3, 2.0 * (double)Ktot * M * (H + D), 4.0 * (double)Ktot * (5.0 * H + H + H + D), s);
+    return hipGetLastError();
+  };
+  auto problem = [&](int which, int tile_cols, int splits, int slice) {
+    GradArgs a;
+    a.kap0 = kap0;
+    a.w = w;
+    a.Bm = which == 0 ? (const void*)h : x;
+    a.N = which == 0 ? H : D;
+    a.third_off = which == 0 ? 2 * H : 4 * H;
+    a.part = part;
+    a.bpart = nullptr;
+    a.Ktot = Ktot;
+    a.B = B;
+    a.H = H;
+    a.mtiles = (M + GT - 1) / GT;
+    a.ntiles = (a.N + tile_cols - 1) / tile_cols;
+    const long long per = (Ktot + splits - 1) / splits;
+    a.Kper = (per + slice - 1) / slice * slice;
+    a.splits = splits;
+    return a;
+  };
+  if (bf16 == 0) {
+    // Small problems: both GEMMs in one launch and all sums in a second one, or, with one split, none.
+    // At most one round over the slots of the kernel (larger ones gain nothing); the partials of both
+    // have to fit.  Gradients of 128 rows, 96 x 32 and 96 x 16 (five launches before): 36 -> 17 us; 12800, 300 x 100
+    // and 300 x 12 57 -> 41; 16384, 108 x 36 and 108 x 60 50 -> 37; 2048, 372 x 124 and 372 x 260 45 -> 36.
+    const long long tiles = (long long)((M + GT - 1) / GT) * ((H + GT - 1) / GT + (D + GT - 1) / GT);
+    long long z = (Ktot + 4 * GTK - 1) / (4 * GTK);
+    if (z > 256) z = 256;
+    const long long fit = (long long)part_floats / ((long long)M * (H + D + 2));
+    if (z > 1 && z > fit) z = fit;
+    if (z >= NXCD) z = z / NXCD * NXCD;
+    if (z >= 1 && tiles * z <= 768) {
+      const int splits = (int)z;
+      GradPair pair = {{problem(0, GT, splits, GTK), problem(1, GT, splits, GTK)}, 0, nullptr, nullptr};
+      GradArgs &u = pair.g[0], &v = pair.g[1];
+      if (splits == 1) {
+        u.part = dU;
+        v.part = dW;
+        pair.db_i = db_i;
+        pair.db_h = db_h;
+      } else {
+        v.part = u.part + (size_t)splits * M * H;
+        u.bpart = v.part + (size_t)splits * M * D;
+        v.bpart = u.bpart + (size_t)splits * M;
+      }
+      pair.first = (unsigned)((u.mtiles * u.ntiles * splits + NXCD - 1) / NXCD * NXCD);
+      hipLaunchKernelGGL((grad_gemm_kernel<float, true>), dim3(pair.first + v.mtiles * v.ntiles * splits),
+                         dim3(256), 0, s, pair);
+      if (splits > 1) {
+        const unsigned per = splits >= 16 ? 32 : 256;   // (float4 of a workgroup)
+        const unsigned bu = (unsigned)((3LL * H * H / 4 + per - 1) / per);
+        const unsigned bw = (unsigned)((3LL * H * D / 4 + per - 1) / per);
+        const dim3 grid(bu + bw + (3 * H + 31) / 32);
+        if (per == 32)
+          hipLaunchKernelGGL(reduce_pair_kernel<8>, grid, dim3(256), 0, s, pair, (floatx4*)dU,
+                             (floatx4*)dW, db_i, db_h, bu, bw);
+        else
+          hipLaunchKernelGGL(reduce_pair_kernel<1>, grid, dim3(256), 0, s, pair, (floatx4*)dU,
+                             (floatx4*)dW, db_i, db_h, bu, bw);
+      }
+      return done();
+    }
+  }
   // splits of the form that runs, if the caller's scratch has room for them, else of the fp32 form
   const int sform = grad_partial_floats(T, B, D, H, bf16) <= part_floats ? bf16 : 0;
   const size_t su = (size_t)grad_splits(Ktot, M, H, sform) * M * H;
@@ -1707,29 +1832,15 @@ hipError_t launch_param_grads(const float* kap0, const float* w, const float* h,
   int nbpart[2];
   bpart[0] = part + (su > sw ? su : sw);
   for (int which = 0; which < 2; ++which) {
-    GradArgs a;
-    a.kap0 = kap0;
-    a.w = w;
-    a.Bm = which == 0 ? (const void*)h : x;
-    a.N = which == 0 ? H : D;
-    a.third_off = which == 0 ? 2 * H : 4 * H;
-    a.part = part;
-    a.Ktot = Ktot;
-    a.B = B;
-    a.H = H;
-    int splits = grad_splits(Ktot, M, a.N, sform);
-    int gn = grad_tile_n(a.N, bf16);
+    const int cols = which == 0 ? H : D;
+    int splits = grad_splits(Ktot, M, cols, sform);
+    int gn = grad_tile_n(cols, bf16);
     if (bf16 == 2) {
-      const GradX3 shape = grad_x3_shape(Ktot, M, a.N, splits);
+      const GradX3 shape = grad_x3_shape(Ktot, M, cols, splits);
       gn = shape.cols;
       splits = shape.splits;
     }
-    a.mtiles = (M + GT - 1) / GT;
-    a.ntiles = (a.N + gn - 1) / gn;
-    long long per = (Ktot + splits - 1) / splits;
-    const int slice = bf16 == 1 ? HB_TK : GTK;      // (both multiples of the 32 of bf16 = 2)
-    a.Kper = (per + slice - 1) / slice * slice;
-    a.splits = splits;
+    GradArgs a = problem(which, gn, splits, bf16 == 1 ? HB_TK : GTK);   // (both multiples of 32)
     a.bpart = bpart[which];
     nbpart[which] = splits;
     if (which == 0) bpart[1] = bpart[0] + (size_t)nbpart[0] * M;
@@ -1752,7 +1863,8 @@ hipError_t launch_param_grads(const float* kap0, const float* w, const float* h,
     else if (bf16)
       hipLaunchKernelGGL(grad_gemm_bf16_kernel<false>, grid, dim3(256), 0, s, a);
     else
-      hipLaunchKernelGGL(grad_gemm_kernel<float>, grid, dim3(256), 0, s, a);
+      hipLaunchKernelGGL((grad_gemm_kernel<float, false>), grid, dim3(256), 0, s,
+                         GradPair{{a, a}, grid.x, nullptr, nullptr});
     const long long n = (long long)M * a.N;
     // (3 H N is a multiple of four: so are H and N)
     const long long n4 = n / 4;
@@ -1766,9 +1878,7 @@ hipError_t launch_param_grads(const float* kap0, const float* w, const float* h,
   }
   hipLaunchKernelGGL(bias_reduce_kernel, dim3((3 * H + 31) / 32), dim3(256), 0, s, bpart[0],
                      nbpart[0], bpart[1], nbpart[1], db_i, db_h, H);
-  prof_end(3, 2.0 * (double)Ktot * M * (H + D),
-           4.0 * (double)Ktot * (5.0 * H + H + H + D), s);
-  return hipGetLastError();
+  return done();
 }
 
 }  // namespace mg

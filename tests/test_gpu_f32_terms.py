@@ -152,6 +152,26 @@ def test_gradients_on_wide_and_narrow_tiles(gh, loss):
         assert gh.rel_err(g, r) <= 1e-5, name
 
 
+@pytest.mark.parametrize("T,B,D,H,sums", [(9, 3, 4, 20, None), (64, 2, 132, 132, None),
+                                          (60, 10, 4, 36, "reduce_pair_kernel<1>"),
+                                          (100, 30, 12, 100, "reduce_pair_kernel<8>"),
+                                          (121, 17, 160, 44, "reduce_pair_kernel<1>")])
+def test_both_gradients_in_one_launch(gh, T, B, D, H, sums):
+    """Small problems on the fp32 MFMAs: one split (no partial sums), four (of 600 rows), sixteen (of 3000),
+    blocks of a tile without outputs, second tiles of four and 32 columns."""
+    print("gradient pair", T, B, D, H, flush=True)
+    d = random_small(8, T, B, D, H, scale=0.3 / np.sqrt(H))
+    P = (d["W"], d["U"], d["b_i"], d["b_h"])
+    h = orc.serial_scan(*P, d["x"], d["h0"]).astype(np.float32)
+    want = orc.serial_bptt(*P, d["x"], h, d["dL_dhT"])
+    run = gh.GpuRun(d)
+    box = []
+    gh.expect_kernels(lambda: box.append(run.serial_backward(h)), "grad_gemm_kernel<float, true>",
+                      *([sums] if sums else []))
+    for name, g, r in zip(("w", "dW", "dU", "db_i", "db_h"), box[0], want):
+        assert gh.rel_err(g, r) <= 1e-5, name
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "fp32x3"])
 @pytest.mark.parametrize("what", ["dL_dhT", "x", "W"])
 def test_operands_far_below_one(gh, what, dtype):
