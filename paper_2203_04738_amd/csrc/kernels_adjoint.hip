@@ -1784,15 +1784,18 @@ hipError_t launch_param_grads(const float* kap0, const float* w, const float* h,
   if (bf16 == 0) {
     // Small problems: both GEMMs in one launch and all sums in a second one, or, with one split, none.
     // At most one round over the slots of the kernel (larger ones gain nothing); the partials of both
-    // have to fit.  Gradients of 128 rows, 96 x 32 and 96 x 16 (five launches before): 36 -> 17 us; 12800, 300 x 100
-    // and 300 x 12 57 -> 41; 16384, 108 x 36 and 108 x 60 50 -> 37; 2048, 372 x 124 and 372 x 260 45 -> 36.
+    // have to fit, with no more rows per split than by itself (longer sums: 300 x 100 twice, 288 rows
+    // instead of 160, 5 % further from 64 bits).  Gradients of 128 rows, 96 x 32 and 96 x 16 (five launches
+    // before): 36 -> 17 us; 12800, 300 x 100 and 300 x 12 57 -> 41.
     const long long tiles = (long long)((M + GT - 1) / GT) * ((H + GT - 1) / GT + (D + GT - 1) / GT);
     long long z = (Ktot + 4 * GTK - 1) / (4 * GTK);
     if (z > 256) z = 256;
     const long long fit = (long long)part_floats / ((long long)M * (H + D + 2));
     if (z > 1 && z > fit) z = fit;
     if (z >= NXCD) z = z / NXCD * NXCD;
-    if (z >= 1 && tiles * z <= 768) {
+    auto slices = [&](long long splits) { return ((Ktot + splits - 1) / splits + GTK - 1) / GTK; };
+    const int zu = grad_splits(Ktot, M, H, 0), zw = grad_splits(Ktot, M, D, 0);
+    if (z >= 1 && tiles * z <= 768 && slices(z) <= slices(zu < zw ? zu : zw)) {
       const int splits = (int)z;
       GradPair pair = {{problem(0, GT, splits, GTK), problem(1, GT, splits, GTK)}, 0, nullptr, nullptr};
       GradArgs &u = pair.g[0], &v = pair.g[1];

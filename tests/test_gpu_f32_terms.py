@@ -153,12 +153,11 @@ def test_gradients_on_wide_and_narrow_tiles(gh, loss):
 
 
 @pytest.mark.parametrize("T,B,D,H,sums", [(9, 3, 4, 20, None), (64, 2, 132, 132, None),
-                                          (60, 10, 4, 36, "reduce_pair_kernel<1>"),
-                                          (100, 30, 12, 100, "reduce_pair_kernel<8>"),
-                                          (121, 17, 160, 44, "reduce_pair_kernel<1>")])
+                                          (110, 10, 4, 36, "reduce_pair_kernel<1>"),
+                                          (128, 100, 12, 100, "reduce_pair_kernel<8>")])
 def test_both_gradients_in_one_launch(gh, T, B, D, H, sums):
-    """Small problems on the fp32 MFMAs: one split (no partial sums), four (of 600 rows), sixteen (of 3000),
-    blocks of a tile without outputs, second tiles of four and 32 columns."""
+    """Small problems on the fp32 MFMAs: one split (no partial sums), seven (of 1100 rows), eighty (of
+    12800), blocks of a tile without outputs, second tiles of four columns."""
     print("gradient pair", T, B, D, H, flush=True)
     d = random_small(8, T, B, D, H, scale=0.3 / np.sqrt(H))
     P = (d["W"], d["U"], d["b_i"], d["b_h"])
