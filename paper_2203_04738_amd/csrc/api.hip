@@ -399,6 +399,11 @@ static bool single_fused(const mgrit_gru_cfg& c, int nk) {
   return sweeps_fused(c, (long long)nk * c.B) && c.H <= 64 && (long long)nk * c.B <= 4096;
 }
 
+// The closing F-sweep of a cycle is one launch, which takes the coarse level's points over by itself.
+static bool closing_fused(const mgrit_gru_cfg& c, long long nint) {
+  return c.cf > 1 && sweeps_fused(c, nint * c.B) && (c.cf > 2 || single_fused(c, (int)nint));
+}
+
 // F-relaxation (Alg. 1) or, with include_c, FC-relaxation on level l: sub-step j
 // advances every interval from point i*cf+j-1 to i*cf+j.  All intervals move in one
 // launch, so the C-sweep reads only values written by earlier launches (Jacobi in
@@ -430,7 +435,7 @@ static bool forward_leaves_coeffs(int l, int L) { return l >= 1 && l < L && (l =
 static int relax_fwd(const FwdCtx& x, int l, bool include_c, bool f_points_current = false,
                      bool emit = false, bool zero_c = false, bool* rhs_fused = nullptr,
                      bool first_done = false, const PhiArgs* resid = nullptr,
-                     bool* resid_done = nullptr) {
+                     bool* resid_done = nullptr, const float* coarse = nullptr) {
   const long long cf = x.c->cf, S = x.lay->S[l];
   const int nint = (int)(x.lay->N[l] / cf);
   if (rhs_fused) *rhs_fused = false;
@@ -497,7 +502,7 @@ static int relax_fwd(const FwdCtx& x, int l, bool include_c, bool f_points_curre
         *resid_done = true;
         ++n;
       }
-      CHECK_HIP(launch_phi_sweep(a, n, rest, last, S, x.s));
+      CHECK_HIP(launch_phi_sweep(a, n, rest, last, S, x.s, coarse));
       if (j < cf) j = cf - 1;
       continue;
     }
@@ -627,10 +632,13 @@ static int vcycle_fwd(const FwdCtx& x, int l, bool f_points_current = false, boo
   if ((rc = vcycle_fwd(x, l + 1, false, last, false, child_first_done))) return rc;
   // line 5 at the coarse points: u'_{cf j} + (v_j - u'_{cf j}) = v_j.  F-points
   // would receive the same correction but are overwritten by line 6.
-  CHECK_HIP(launch_copy_points(x.ul[l], x.ul[l + 1], Idx{cf, cf}, Idx{1, 1}, Nc,
-                               (long long)x.c->B * x.c->H, x.s));
+  const bool fused = closing_fused(*x.c, Nc);
+  if (!fused)
+    CHECK_HIP(launch_copy_points(x.ul[l], x.ul[l + 1], Idx{cf, cf}, Idx{1, 1}, Nc,
+                                 (long long)x.c->B * x.c->H, x.s));
   // line 6
-  return relax_fwd(x, l, false, false, last);
+  return relax_fwd(x, l, false, false, last, false, nullptr, false, nullptr, nullptr,
+                   fused ? x.ul[l + 1] : nullptr);
 }
 
 static int run_projection(const mgrit_gru_cfg* c, const Layout& lay, const Forms& f, char* base,
@@ -792,7 +800,8 @@ static AdjArgs adj_base(const BwdCtx& x, int l) {
 // resid, resid_done: as in relax_fwd.
 static int relax_bwd(const BwdCtx& x, int l, bool include_c, bool f_points_current = false,
                      long long* lo = nullptr, bool first_done = false,
-                     const AdjArgs* resid = nullptr, bool* resid_done = nullptr) {
+                     const AdjArgs* resid = nullptr, bool* resid_done = nullptr,
+                     const float* coarse = nullptr) {
   const long long cf = x.c->cf;
   const int nint = (int)(x.lay->N[l] / cf);
   long long i0 = 0;                        // first interval that can hold non-zero values
@@ -825,7 +834,7 @@ static int relax_bwd(const BwdCtx& x, int l, bool include_c, bool f_points_curre
         *resid_done = true;
         ++n;
       }
-      CHECK_HIP(launch_adj_sweep(a, n, STEP_RELAX, last, x.s));
+      CHECK_HIP(launch_adj_sweep(a, n, STEP_RELAX, last, x.s, coarse));
       if (j < cf) j = cf - 1;
       continue;
     }
@@ -944,8 +953,11 @@ static int vcycle_bwd(const BwdCtx& x, int l, bool f_points_current = false,
   // on the coarse level iterate and right-hand side are zero below iR
   if ((rc = vcycle_bwd(x, l + 1, false, iR / cf * cf, child_first_done))) return rc;
   // correction at the coarse points: w'_{cf i} + e_i (the coarse solve carries e below iR too)
-  CHECK_HIP(launch_add_points(x.wl[l], x.wl[l + 1], Idx{0, cf}, Idx{0, 1}, Nc, BH, x.s));
-  return relax_bwd(x, l, false);
+  const bool fused = closing_fused(*x.c, Nc);
+  if (!fused)
+    CHECK_HIP(launch_add_points(x.wl[l], x.wl[l + 1], Idx{0, cf}, Idx{0, 1}, Nc, BH, x.s));
+  return relax_bwd(x, l, false, false, nullptr, false, nullptr, nullptr,
+                   fused ? x.wl[l + 1] : nullptr);
 }
 
 static int backward_impl(const mgrit_gru_cfg* cin, bool serial, const void* W, const void* U,

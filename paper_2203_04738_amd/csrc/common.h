@@ -131,9 +131,12 @@ hipError_t launch_adj_step(const AdjArgs& a, hipStream_t s);
 // `mid`.  The coarse arrays (uc, gc, wc, norm, index a) serve whichever sub-step's mode uses them; in a
 // sweep that keeps coefficients uc is the coefficient array.  GRU, fp32 weights, H <= 128.
 constexpr int SWEEP_MAX_H = 128;
+// coarse: the sweep closes a cycle and first takes over the solution of the coarse level (adjoint: adds
+// its error), point i of `coarse` for the coarse point i of this level; all intervals, from its first sub-step.
 hipError_t launch_phi_sweep(const PhiArgs& first, int n, int mid, int last, long long pstep,
-                            hipStream_t s);
-hipError_t launch_adj_sweep(const AdjArgs& first, int n, int mid, int last, hipStream_t s);
+                            hipStream_t s, const float* coarse = nullptr);
+hipError_t launch_adj_sweep(const AdjArgs& first, int n, int mid, int last, hipStream_t s,
+                            const float* coarse = nullptr);
 
 // P[M,N] = X[M,K] W[N,K]^T + bias[N]
 // X, W: float (bf16 = 0) or bf16 (bf16 = 1); bf16 = 2: X, W float, W3 the three bf16 terms

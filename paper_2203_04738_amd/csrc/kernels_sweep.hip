@@ -33,7 +33,38 @@ constexpr int SWP_MAXWG = 256;               // one workgroup per CU (registers)
 struct SweepSteps {
   int n, mid, last, blocks;                  // blocks of rows
   long long pstep;
+  const float* coarse;                       // not null: points of the coarse level to take over first
 };
+
+// The correction at the coarse points rides on the sweep that starts from them: interval i starts from
+// point i of the coarse level and leaves it at its point of this level (the last interval the last point
+// too, from which no interval starts).  Adjoint: w + e, interval i starts from point i + 1, and the first one
+// corrects point 0.  Training call without the six launches: 64 x 2 x 32 columns, two levels, three cycles 257 ->
+// 254 us; two layers of 128 x 100 x 100, twelve launches, 1050 -> 1041.
+__device__ inline floatx4 take_over(const PhiArgs& a, const SweepSteps& sw, long long r, bool ok, int c) {
+  const int B = a.B;
+  const long long pt = r / B, b = r - pt * B;
+  auto level = [&](long long q) { return a.u + (a.in.at(q) * B + b) * a.H + c; };
+  if (pt == a.nk - 1 && ok)
+    *reinterpret_cast<floatx4*>(level(pt + 1)) = ldg4(sw.coarse + (r + B) * a.H + c);
+  if (pt == 0) return ldg4(level(0));
+  const floatx4 v = ldg4(sw.coarse + r * a.H + c);
+  if (ok) *reinterpret_cast<floatx4*>(level(pt)) = v;
+  return v;
+}
+__device__ inline float corrected(const AdjArgs& a, const SweepSteps& sw, long long r, bool ok, int c) {
+  const int B = a.B;
+  const long long pt = r / B, b = r - pt * B;
+  const long long step = a.in.at(1) - a.in.at(0);
+  auto level = [&](long long q) { return a.w + ((a.in.at(0) + (q - 1) * step) * B + b) * a.H + c; };
+  if (pt == 0 && ok) *level(0) += sw.coarse[r * a.H + c];
+  float v = *level(pt + 1);
+  if (pt < a.nk - 1) {
+    v += sw.coarse[(r + B) * a.H + c];
+    if (ok) *level(pt + 1) = v;
+  }
+  return v;
+}
 
 // Weights of this lane: column min(16 wave + lane % 16, H - 1), k = 64 c + 16 (lane / 16) + 0..15
 // (zero beyond H); at(g, j, k) points at four of them.
@@ -112,7 +143,8 @@ __global__ __launch_bounds__(256 * NCH, 2) void phi_sweep_kernel(PhiArgs a, Swee
     for (int e = tid; e < 4 * h4; e += blockDim.x) {
       const int r = min(4 * q + e / h4, R - 1), pt = r / B;
       *reinterpret_cast<floatx4*>(&hs[0][e / h4][e % h4 * 4]) =
-          ldg4(a.u_in + (a.in.at(pt) * B + (r - pt * B)) * H + e % h4 * 4);
+          sw.coarse ? take_over(a, sw, r, 4 * q + e / h4 < R, e % h4 * 4)
+                    : ldg4(a.u_in + (a.in.at(pt) * B + (r - pt * B)) * H + e % h4 * 4);
     }
     // output elements of this lane (rows beyond the launch repeat its last row and store nothing)
     const int rr = 4 * q + row, r = min(rr, R - 1);
@@ -257,7 +289,8 @@ __global__ __launch_bounds__(256 * NCH, 2) void phi_sweep_kernel16(PhiArgs a, Sw
     for (int e = tid; e < 16 * h4; e += blockDim.x) {
       const int r = min(16 * q + e / h4, R - 1), pt = r / B;
       *reinterpret_cast<floatx4*>(&hs[0][e / h4][e % h4 * 4]) =
-          ldg4(a.u_in + (a.in.at(pt) * B + (r - pt * B)) * H + e % h4 * 4);
+          sw.coarse ? take_over(a, sw, r, 16 * q + e / h4 < R, e % h4 * 4)
+                    : ldg4(a.u_in + (a.in.at(pt) * B + (r - pt * B)) * H + e % h4 * 4);
     }
     // output elements of this lane (rows beyond the launch repeat its last row and store nothing):
     // rows of the arrays
@@ -414,8 +447,15 @@ __global__ __launch_bounds__(256 * NCH, 2) void adj_sweep_kernel(AdjArgs a, Swee
     const int h4 = H / 4;
     for (int e = tid; e < 4 * h4; e += blockDim.x) {
       const int r = min(4 * q + e / h4, R - 1), pt = r / B;
-      *reinterpret_cast<floatx4*>(&ws[0][e / h4][e % h4 * 4]) =
-          ldg4(a.w_in + (a.in.at(pt) * B + (r - pt * B)) * H + e % h4 * 4);
+      floatx4 v;
+      if (sw.coarse) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          v[c] = corrected(a, sw, r, 4 * q + e / h4 < R, e % h4 * 4 + c);
+      } else {
+        v = ldg4(a.w_in + (a.in.at(pt) * B + (r - pt * B)) * H + e % h4 * 4);
+      }
+      *reinterpret_cast<floatx4*>(&ws[0][e / h4][e % h4 * 4]) = v;
     }
     const int rr = 4 * q + row, r = min(rr, R - 1);
     const long long pt = r / B;
@@ -544,7 +584,9 @@ __global__ __launch_bounds__(256 * NCH, 2) void adj_sweep_kernel16(AdjArgs a, Sw
     Ops ops = request(0);
     float state[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) state[v] = a.w_in[(long long)ri[v] * H + cc];
+    for (int v = 0; v < 4; ++v)
+      state[v] = sw.coarse ? corrected(a, sw, min(16 * q + row0 + v, R - 1), ok[v], cc)
+                           : a.w_in[(long long)ri[v] * H + cc];
     __syncthreads();                          // the last block's reads of the products are done
     for (int j = 0; j < sw.n; ++j) {
       const int mode = j == 0 ? a.mode : j == sw.n - 1 ? sw.last : sw.mid, buf = j & 1;
@@ -630,7 +672,7 @@ static bool sweep_wide(int R) { return R > 2 * 4 * SWP_MAXWG; }
   const bool wide = sweep_wide(R);                                                            \
   const int blocks = wide ? (R + 15) / 16 : (R + 3) / 4;                                      \
   const dim3 grid((unsigned)std::min(blocks, SWP_MAXWG)), block(64 * ((a.H + 15) / 16));      \
-  const SweepSteps sw{n, mid, last, blocks, pstep};                                           \
+  const SweepSteps sw{n, mid, last, blocks, pstep, coarse};                                   \
   auto launch = [&] {                                                                         \
     if (a.H <= 64 && wide) hipLaunchKernelGGL((ROWS1), grid, block, 0, s, a, sw);             \
     else if (a.H <= 64) hipLaunchKernelGGL((QUADS1), grid, block, 0, s, a, sw);               \
@@ -639,14 +681,15 @@ static bool sweep_wide(int R) { return R > 2 * 4 * SWP_MAXWG; }
   };
 
 hipError_t launch_phi_sweep(const PhiArgs& a, int n, int mid, int last, long long pstep,
-                            hipStream_t s) {
+                            hipStream_t s, const float* coarse) {
   if (a.nk <= 0 || n <= 0) return hipSuccess;
   if (a.H > SWEEP_MAX_H || a.bf16 == 1) return hipErrorInvalidValue;
   MG_SWEEP_LAUNCH(phi_sweep_kernel<1>, phi_sweep_kernel<2>, phi_sweep_kernel16<1>, phi_sweep_kernel16<2>)
   return record_sweep(R <= 64 ? 4 : 0, R, a.H, 20.0, n, a.mode, mid, last, s, launch);
 }
 
-hipError_t launch_adj_sweep(const AdjArgs& a, int n, int mid, int last, hipStream_t s) {
+hipError_t launch_adj_sweep(const AdjArgs& a, int n, int mid, int last, hipStream_t s,
+                            const float* coarse) {
   if (a.nk <= 0 || n <= 0) return hipSuccess;
   if (a.H > SWEEP_MAX_H || a.bf16 == 1) return hipErrorInvalidValue;
   const long long pstep = 0;

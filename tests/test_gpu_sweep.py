@@ -40,6 +40,13 @@ def test_cycles_of_narrow_layers(gh, T, B, H, cf, levels, fine, prop):
             assert gh.rel_err(got, want) <= 1e-5
 
 
+@pytest.mark.parametrize("T,B,H,cf,levels", [(4, 3, 12, 4, 2), (16, 5, 100, 4, 3), (2, 6, 64, 2, 2),
+                                             (8, 514, 20, 8, 2), (4, 2050, 128, 4, 2)])
+def test_closing_sweeps_of_a_single_interval(gh, T, B, H, cf, levels):
+    # the sweep that takes over the coarse points: its first interval is also its last
+    test_cycles_of_narrow_layers(gh, T, B, H, cf, levels, 1, 0)
+
+
 @pytest.mark.parametrize("T,B,H,cf,levels,fine,dtype",
                          [(16, 2048, 20, 4, 2, 1, "fp32"), (16, 2049, 20, 4, 2, 1, "fp32"),
                           (8, 2049, 128, 2, 3, 0, "fp32"), (16, 2049, 24, 4, 2, 1, "fp32x3")])
