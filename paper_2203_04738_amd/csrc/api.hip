@@ -231,12 +231,24 @@ constexpr long long TERMS_MIN_ROWS = 1024;
 constexpr int TERMS_MIN_H = 128, TERMS_MIN_D = 64;
 constexpr size_t CTL_BYTES = 256;         // head of the partials: control words of the serial solves
 
+// Whether a serial solve on bf16 weights contracts terms of the state (kernels_scan_xcd.hip): scans, whose
+// states come no further from 64 bits so, and any solve of more than 64 rows, which the step launches
+// contract with a state of one or two terms (512 x 100 x 520, two levels, two terms: 9.5e-7 from 64 bits
+// there, 7.7e-7 here).  The coarsest level of a multilevel call of up to 64 rows keeps the fp32 MFMAs: the
+// steps of its finer levels round the state to bf16, so that a sum rounded otherwise here moves their results by
+// 7e-4 (4096 x 8 x 1024, cf 8), and the backward residual norm, the one output whose error that changed,
+// was no closer (root mean square over five inputs 1.9e-5, fp32 1.8e-5).
+static bool scan_terms(const mgrit_gru_cfg& c, int kind) {
+  return kind == SCAN_GRU && kform(c.dtype) == 1 && (c.levels == 1 || c.B > 64);
+}
+
 // Scratch of the serial solves' exchange: the end of the space of the gradient partials, behind the
 // control words and the terms, or the space of W^T, which the input gradients fill after every solve.
 // Null if it has room in neither.
 static float* scan_ring(const mgrit_gru_cfg& c, const Layout& lay, const Forms& f, char* base,
                         int kind, int hidden) {
-  const size_t need = align_up(scan_ring_floats(kind, c.B, hidden, kform(c.dtype)) * sizeof(float));
+  const size_t need =
+      align_up(scan_ring_floats(kind, c.B, hidden, scan_terms(c, kind)) * sizeof(float));
   if (need == 0) return nullptr;
   if (CTL_BYTES + f.part_bytes + need <= lay.total_part)
     return (float*)(base + lay.part + lay.total_part - need);
@@ -540,7 +552,7 @@ static int vcycle_fwd(const FwdCtx& x, int l, bool f_points_current = false, boo
       CHECK_HIP(launch_phi_sweep(a, (int)N, a.mode, a.mode, S, x.s));
       return MGRIT_OK;
     }
-    if (!keep && scan_covers(kind, N, x.c->B, hidden, kform(x.c->dtype), x.ring != nullptr)) {
+    if (!keep && scan_covers(kind, N, x.c->B, hidden, scan_terms(*x.c, kind), x.ring != nullptr)) {
       ScanArgs a;
       std::memset(&a, 0, sizeof(a));
       a.Wt = x.U;
@@ -557,6 +569,7 @@ static int vcycle_fwd(const FwdCtx& x, int l, bool f_points_current = false, boo
       a.gamma = (float)S * x.dt;
       a.implicit_ = x.c->propagator == MGRIT_PROP_IMPLICIT || x.c->propagator == PROP_LSTM_IMPLICIT;
       a.bf16 = kform(x.c->dtype);
+      a.terms = scan_terms(*x.c, kind);
       CHECK_HIP(launch_scan(kind, a, x.s));
       return MGRIT_OK;
     }
@@ -874,7 +887,7 @@ static int vcycle_bwd(const BwdCtx& x, int l, bool f_points_current = false,
     // with them, a caller's w formed in place of dL_dh, goes step by step)
     const long long words = (N + 1) * x.c->B * x.c->H;
     const bool in_place = x.gl[l] && x.gl[l] < x.wl[l] + words && x.wl[l] < x.gl[l] + words;
-    if (!in_place && scan_covers(SCAN_ADJOINT, N, x.c->B, x.c->H, kform(x.c->dtype), x.ring != nullptr)) {
+    if (!in_place && scan_covers(SCAN_ADJOINT, N, x.c->B, x.c->H, false, x.ring != nullptr)) {
       ScanArgs a;
       std::memset(&a, 0, sizeof(a));
       a.Wt = x.UT;

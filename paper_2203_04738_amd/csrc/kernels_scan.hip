@@ -66,7 +66,7 @@ __device__ inline float scan_own(const float* p) {
 // ITEMS: the workgroup takes (step, unit) items from the counter until none are left; otherwise it
 // takes every step of the unit it was launched as, once all workgroups of the solve are resident, and
 // leaves what remains to the launch with ITEMS behind it if they are not (see the top of the file).
-// TERMS (items behind xcd_scan_kernel on bf16 weights): its contraction, for the same bits.
+// TERMS (items behind an xcd_scan_kernel on terms): its contraction, for the same bits.
 template <int KIND, int NCH, int RB, class WT, bool ITEMS, bool TERMS>
 __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int nrb, int xcd_quads) {
   constexpr int NG = ScanGates<KIND>::value;
@@ -482,13 +482,13 @@ static ScanShape scan_shape(int B, int H) {
 // (a launch per step above 64 rows) : this, us per step of the whole call: scan 100 x 512 13.3 : 4.4, 100 x
 // 1000 26.0 : 10.8, 64 x 1000 10.2 : 6.1, 256 x 256 9.0 : 3.3, LSTM 100 x 200 10.7 : 2.5, ODE 100 x 512 7.3 :
 // 2.5, scan + back-propagation 100 x 512 33.6 : 10.8, 100 x 1000 67.9 : 33.5.
-// GRU on bf16 weights contracts terms of the state (ScanTerms): 8 x 512 1.01 : 2.00, 1 x 1024 1.42 : 2.25, 8 x
+// On terms of the state (ScanArgs): 8 x 512 1.01 : 2.00, 1 x 1024 1.42 : 2.25, 8 x
 // 1024 1.53 : 3.02, 64 x 1024 2.3 : 9.4, at any number of rows (two solves of 8 x 1024 at once 0.89 : 1.82 ms).
 constexpr int SCAN_XCD_MAX_QUADS = 4;                  // per row block
-static bool scan_shape_xcd(int kind, int B, int H, int bf16, ScanShape& s) {
+static bool scan_shape_xcd(int kind, int B, int H, bool terms, ScanShape& s) {
   if (scan_max_wg() != SCAN_XCDS * SCAN_XCD_CUS) return false;
   const int quads = (B + 3) / 4;
-  s.terms = kind == SCAN_GRU && bf16 == 1;
+  s.terms = terms;
   s.ct = H > 512 ? 2 : 1;
   s.hp = H > 512 ? 1024 : H > 256 ? 512 : 256;
   s.ncg = (H + s.ct * SCAN_CP - 1) / (s.ct * SCAN_CP);
@@ -505,9 +505,9 @@ static bool scan_shape_xcd(int kind, int B, int H, int bf16, ScanShape& s) {
   s.nx = (s.nrb + s.gpx - 1) / s.gpx;
   return true;
 }
-size_t scan_ring_floats(int kind, int B, int H, int bf16) {
+size_t scan_ring_floats(int kind, int B, int H, bool terms) {
   ScanShape s;
-  if (!scan_shape_xcd(kind, B, H, bf16, s)) return 0;
+  if (!scan_shape_xcd(kind, B, H, terms, s)) return 0;
   return (size_t)16 * s.rb * s.nrb * s.hp * (kind == SCAN_ADJOINT ? 3 : s.terms ? 2 : 1);
 }
 
@@ -517,10 +517,10 @@ static int scan_max_quads(int kind, int nch) { return kind == SCAN_ADJOINT && nc
 // 16 to 1024 columns, up to 64 rows (the few-row range of the step kernels), with a row block per XCD up
 // to 16 rows for each.  A solve costs three launches (mark, scan, items) whatever its length: below eight
 // steps the chain of step launches is as fast.
-bool scan_covers(int kind, long long N, int B, int H, int bf16, bool ring) {
+bool scan_covers(int kind, long long N, int B, int H, bool terms, bool ring) {
   if (N < 8 || N > (1LL << 30) || H < 16 || H > 128 * SCAN_MAXW) return false;
   ScanShape s;
-  if (ring && scan_shape_xcd(kind, B, H, bf16, s)) return true;
+  if (ring && scan_shape_xcd(kind, B, H, terms, s)) return true;
   if (B > 64) return false;
   s = scan_shape(B, H);
   return s.rb <= scan_max_quads(kind, s.nch) && s.nrb * s.ncg <= scan_max_wg();
@@ -532,8 +532,8 @@ static void launch_scan_shape(const ScanArgs& a, const ScanShape& s, const ScanS
   const dim3 grid((unsigned)(s.nrb * s.ncg)), block(64 * s.nw);
   if (xs) (void)launch_scan_xcd(KIND, a, *xs, st);
   else hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT, false, false>), grid, block, 0, st, a, s.nrb, 0);
-  if constexpr (ScanTerms<KIND, WT>::value) {
-    if (xs) {
+  if constexpr (KIND == SCAN_GRU && sizeof(WT) == 2) {
+    if (xs && xs->terms) {
       hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT, true, true>), grid, block, 0, st, a, s.nrb,
                          xs->gpx * xs->rb);
       return;
@@ -574,10 +574,10 @@ hipError_t launch_scan(int kind, const ScanArgs& a0, hipStream_t st) {
   const int prof = kind == SCAN_GRU ? 4 : kind == SCAN_ADJOINT ? 5 : kind == SCAN_LSTM ? 9 : 8;
   prof_begin(prof, st, a.B, STEP_RELAX);
   ScanShape xshape{};
-  const bool xcd = a.ring && scan_shape_xcd(kind, a.B, a.H, a.bf16, xshape);
+  const bool xcd = a.ring && scan_shape_xcd(kind, a.B, a.H, a.terms, xshape);
   const ScanShape* xs = xcd ? &xshape : nullptr;
   if (!xcd) a.ring = nullptr;
-  a.ring4 = xcd ? (long long)scan_ring_floats(kind, a.B, a.H, a.bf16) / 4 : 0;
+  a.ring4 = xcd ? (long long)scan_ring_floats(kind, a.B, a.H, a.terms) / 4 : 0;
   const long long n4 = (long long)a.N * a.B * W / 4, BW = (long long)a.B * W;
   const long long nb = (n4 + 255) / 256;
   hipLaunchKernelGGL(scan_mark_kernel, dim3((unsigned)(nb < 4096 ? nb : 4096)), dim3(256), 0, st,

@@ -19,11 +19,14 @@
 // memory first), the ring 0.53 us, the exchange through memory 1.37 us (32 workgroups of 16 columns, four
 // rows; the exchange alone).
 //
-// On bf16 weights the GRU contracts on the bf16 matrix pipe, which is 16 times as fast: the state travels
-// as three bf16 terms (exact: state_terms), which fill 12 of the 16 rows of v_mfma_f32_16x16x32_bf16 for
-// four state rows, [slot][row quad][k / 32][k / 8 % 4][term][row][8]; products of terms and weights are
-// exact, the sums fp32.  8 x 1024: 0.3 instead of 1.3 us of MFMAs per step, half the registers; states
-// 1.07e-7 from 64 bits (fp32 MFMAs 1.09e-7; 8 x 512 1.05 : 1.06, 3 x 64 1.02 : 1.03).
+// TERMS: a serial scan of the GRU on bf16 weights contracts on the bf16 matrix pipe, which is 16 times as
+// fast: the state travels as three bf16 terms (exact: state_terms), which fill 12 of the 16 rows of
+// v_mfma_f32_16x16x32_bf16 for four state rows, [slot][row quad][k / 32][k / 8 % 4][term][row][8]; products
+// of terms and weights are exact, the sums fp32.  8 x 1024: 0.3 instead of 1.3 us of MFMAs per step, half
+// the registers.  The instruction rounds its sums down where the fp32 one rounds to nearest; it makes fewer
+// of them, and the states are no further from 64 bits (five inputs each: 1024 steps of 8 x 1024 1.07e-7
+// against 1.09e-7 with fp32 MFMAs, 2048 of 1 x 512 1.04 : 1.05, 1024 of 3 x 264 1.03 : 1.04), nor to one
+// side of it (sum of the errors over sum of their sizes, mean of the five -0.3 % : -0.2 % at 8 x 1024).
 //
 // Which XCD a workgroup runs on it reads from the hardware (XCC_ID).  The launch has enough workgroups
 // to fill what it needs on every XCD; the XCD whose workgroups have all arrived takes the next group of
@@ -109,19 +112,18 @@ __device__ inline float moved(float x) {
 // the bits are the same); RB row quads one after the other, CT tiles of 16 columns per workgroup.  The
 // waves also finish the elements (waves of their own for that are no faster: 1.38 against 1.35 us per
 // step at 32 x 512, where they make nine of eight).
-template <int KIND, int CT, int NV, int NCH, int NW, int RB, class WT>
+template <int KIND, int CT, int NV, int NCH, int NW, int RB, class WT, bool TERMS>
 __device__ __forceinline__ void xcd_solve(const ScanArgs& a, const ScanShape& sh) {
   constexpr int NG = ScanGates<KIND>::value;
   constexpr bool ADJ = KIND == SCAN_ADJOINT;
   constexpr int NS = ADJ ? 1 : NG;
   constexpr int AG = ScanVectors<KIND>::value;
   constexpr int NC = NV * NCH;
-  constexpr int NL = (ScanTerms<KIND, WT>::value ? 2 : AG) * NC;     // loads per row quad
+  constexpr int NL = (TERMS ? 2 : AG) * NC;     // loads per row quad
   constexpr bool AHEAD = RB > 1 && NL <= 8;            // (registers)
   constexpr int NE = (RB * CT + NW - 1) / NW;          // elements a lane finishes
   constexpr int NP = NG == 1 ? 2 : 1;
   constexpr int HP = 64 * NC * NW;                     // columns of a ring row, zero from H on
-  constexpr bool TERMS = ScanTerms<KIND, WT>::value;
   constexpr int KB = 2 * NC;                           // TERMS: blocks of 32 k per wave
   constexpr unsigned VEC = RB * HP * 4, SLOT = TERMS ? 2 * VEC : AG * VEC;    // floats
   __shared__ float part[2][NW * NV][RB * CT][NS][64];
@@ -424,46 +426,49 @@ __device__ __forceinline__ void xcd_solve(const ScanArgs& a, const ScanShape& sh
   }
 }
 
-template <int KIND, int CT, int NV, int NCH, int NW, int RB, class WT>
+template <int KIND, int CT, int NV, int NCH, int NW, int RB, class WT, bool TERMS>
 __global__ __launch_bounds__(64 * NW) void xcd_scan_kernel(ScanArgs a, ScanShape sh) {
-  xcd_solve<KIND, CT, NV, NCH, NW, RB, WT>(a, sh);
+  xcd_solve<KIND, CT, NV, NCH, NW, RB, WT, TERMS>(a, sh);
 }
-template <int KIND, int CT, int NV, int NCH, int NW, int RB, class WT>
+template <int KIND, int CT, int NV, int NCH, int NW, int RB, class WT, bool TERMS>
 __global__ __launch_bounds__(64 * NW) void adj_xcd_scan_kernel(ScanArgs a, ScanShape sh) {
-  xcd_solve<KIND, CT, NV, NCH, NW, RB, WT>(a, sh);
+  xcd_solve<KIND, CT, NV, NCH, NW, RB, WT, TERMS>(a, sh);
 }
 
-template <int KIND, int CT, int NV, int NCH, int NW, int RB, class WT>
+template <int KIND, int CT, int NV, int NCH, int NW, int RB, class WT, bool TERMS>
 static void launch(const ScanArgs& a, const ScanShape& s, hipStream_t st) {
   // (workgroups go to the XCDs in turn)
   const dim3 grid((unsigned)(SCAN_XCDS * s.gpx * s.ncg)), block(64 * NW);
   if constexpr (KIND == SCAN_ADJOINT)
-    hipLaunchKernelGGL((adj_xcd_scan_kernel<KIND, CT, NV, NCH, NW, RB, WT>), grid, block, 0, st, a, s);
+    hipLaunchKernelGGL((adj_xcd_scan_kernel<KIND, CT, NV, NCH, NW, RB, WT, TERMS>), grid, block, 0, st, a, s);
   else
-    hipLaunchKernelGGL((xcd_scan_kernel<KIND, CT, NV, NCH, NW, RB, WT>), grid, block, 0, st, a, s);
+    hipLaunchKernelGGL((xcd_scan_kernel<KIND, CT, NV, NCH, NW, RB, WT, TERMS>), grid, block, 0, st, a, s);
 }
-template <int KIND, int CT, int NV, int NCH, int NW, class WT>
+template <int KIND, int CT, int NV, int NCH, int NW, class WT, bool TERMS>
 static void launch_rows(const ScanArgs& a, const ScanShape& s, hipStream_t st) {
-  if (s.rb == 1) launch<KIND, CT, NV, NCH, NW, 1, WT>(a, s, st);
-  else if (s.rb == 2) launch<KIND, CT, NV, NCH, NW, 2, WT>(a, s, st);
-  else if (s.rb == 3) launch<KIND, CT, NV, NCH, NW, 3, WT>(a, s, st);
-  else launch<KIND, CT, NV, NCH, NW, 4, WT>(a, s, st);
+  if (s.rb == 1) launch<KIND, CT, NV, NCH, NW, 1, WT, TERMS>(a, s, st);
+  else if (s.rb == 2) launch<KIND, CT, NV, NCH, NW, 2, WT, TERMS>(a, s, st);
+  if constexpr (KIND != SCAN_GRU || sizeof(WT) == 4 || TERMS) {     // (otherwise up to 64 rows: two quads)
+    if (s.rb == 3) launch<KIND, CT, NV, NCH, NW, 3, WT, TERMS>(a, s, st);
+    else if (s.rb == 4) launch<KIND, CT, NV, NCH, NW, 4, WT, TERMS>(a, s, st);
+  }
 }
-template <int KIND, class WT>
+template <int KIND, class WT, bool TERMS = false>
 static void launch_kind(const ScanArgs& a, const ScanShape& s, hipStream_t st) {
-  if (s.ct == 1 && s.hp == 256) return launch_rows<KIND, 1, 1, 1, 4, WT>(a, s, st);
-  if (s.ct == 1 && s.hp == 512) return launch_rows<KIND, 1, 1, 1, 8, WT>(a, s, st);
+  if (s.ct == 1 && s.hp == 256) return launch_rows<KIND, 1, 1, 1, 4, WT, TERMS>(a, s, st);
+  if (s.ct == 1 && s.hp == 512) return launch_rows<KIND, 1, 1, 1, 8, WT, TERMS>(a, s, st);
   if constexpr (KIND == SCAN_ADJOINT) {
-    if (s.ct == 2) launch_rows<KIND, 2, 2, 2, 4, WT>(a, s, st);
+    if (s.ct == 2) launch_rows<KIND, 2, 2, 2, 4, WT, TERMS>(a, s, st);
   } else if constexpr (KIND != SCAN_LSTM) {
-    if (s.ct == 2) launch_rows<KIND, 2, 1, 2, 8, WT>(a, s, st);
+    if (s.ct == 2) launch_rows<KIND, 2, 1, 2, 8, WT, TERMS>(a, s, st);
   }
 }
 
 hipError_t launch_scan_xcd(int kind, const ScanArgs& a, const ScanShape& s, hipStream_t st) {
   const bool h16 = a.bf16 == 1;
   if (kind == SCAN_GRU) {
-    if (h16) launch_kind<SCAN_GRU, bf16_t>(a, s, st);
+    if (s.terms) launch_kind<SCAN_GRU, bf16_t, true>(a, s, st);
+    else if (h16) launch_kind<SCAN_GRU, bf16_t>(a, s, st);
     else launch_kind<SCAN_GRU, float>(a, s, st);
   } else if (kind == SCAN_ADJOINT) {
     if (h16) launch_kind<SCAN_ADJOINT, bf16_t>(a, s, st);

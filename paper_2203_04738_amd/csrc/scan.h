@@ -25,14 +25,16 @@ struct ScanArgs {
   float gamma;
   int implicit_;       // GRU / LSTM: implicit form of the step
   int bf16;            // 1: Wt is bf16
+  int terms;           // GRU on bf16 weights: inside the XCDs, contract terms of the state (see
+                       // kernels_scan_xcd.hip); more than 64 rows always do
   long long wait_ticks;   // limit of the wait for all workgroups to arrive (100 MHz ticks)
 };
 
 // True if a solve of N steps over B rows of hidden width H runs as one launch.
-// bf16: the weights' form, as in ScanArgs; ring: there is space for scan_ring_floats(...) floats.
-bool scan_covers(int kind, long long N, int B, int H, int bf16, bool ring);
+// terms: as in ScanArgs; ring: there is space for scan_ring_floats(...) floats.
+bool scan_covers(int kind, long long N, int B, int H, bool terms, bool ring);
 // Scratch with which the exchange runs inside the XCDs (0: this shape does not).
-size_t scan_ring_floats(int kind, int B, int H, int bf16);
+size_t scan_ring_floats(int kind, int B, int H, bool terms);
 hipError_t launch_scan(int kind, const ScanArgs& a, hipStream_t s);
 
 }  // namespace mg

@@ -29,13 +29,7 @@ struct ScanShape {
   int ct, hp;          // kernels_scan_xcd.hip: tiles of 16 columns per workgroup, columns of a ring row
                        // (256, 512 or 1024),
   int gpx, nx;         // row blocks per XCD, XCDs needed
-  int terms;           // the contraction is on terms (ScanTerms)
-};
-// bf16 weights, GRU, a row block per XCD: the contraction runs on the bf16 matrix pipe, the state as its
-// three bf16 terms (below).
-template <int KIND, class WT>
-struct ScanTerms {
-  static constexpr bool value = KIND == SCAN_GRU && sizeof(WT) == 2;
+  int terms;           // the contraction is on terms (ScanArgs)
 };
 // control words beyond the four of ScanArgs: XCDs given away (xcd_groups), a wait passed its bound,
 // workgroups that have arrived per XCD
