@@ -526,24 +526,33 @@ bool scan_covers(int kind, long long N, int B, int H, bool terms, bool ring) {
   return s.rb <= scan_max_quads(kind, s.nch) && s.nrb * s.ncg <= scan_max_wg();
 }
 
-// xs: the shape of the form with a row block per XCD, null: this form
+// xs: the shape of the form with a row block per XCD, null: this form.  Each launch's error is looked at
+// by itself: the items take a solve that never started for one that is done.
 template <int KIND, int NCH, int RB, class WT>
-static void launch_scan_shape(const ScanArgs& a, const ScanShape& s, const ScanShape* xs, hipStream_t st) {
+static hipError_t launch_scan_shape(const ScanArgs& a, const ScanShape& s, const ScanShape* xs,
+                                    hipStream_t st) {
   const dim3 grid((unsigned)(s.nrb * s.ncg)), block(64 * s.nw);
-  if (xs) (void)launch_scan_xcd(KIND, a, *xs, st);
-  else hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT, false, false>), grid, block, 0, st, a, s.nrb, 0);
+  hipError_t err;
+  if (xs) {
+    err = launch_scan_xcd(KIND, a, *xs, st);
+  } else {
+    hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT, false, false>), grid, block, 0, st, a, s.nrb, 0);
+    err = hipGetLastError();
+  }
+  if (err != hipSuccess) return err;
   if constexpr (KIND == SCAN_GRU && sizeof(WT) == 2) {
     if (xs && xs->terms) {
       hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT, true, true>), grid, block, 0, st, a, s.nrb,
                          xs->gpx * xs->rb);
-      return;
+      return hipGetLastError();
     }
   }
   hipLaunchKernelGGL((scan_kernel<KIND, NCH, RB, WT, true, false>), grid, block, 0, st, a, s.nrb,
                      xs ? xs->gpx * xs->rb : 0);
+  return hipGetLastError();
 }
 template <int KIND, class WT>
-static void launch_scan_kind(const ScanArgs& a, const ScanShape* xs, hipStream_t st) {
+static hipError_t launch_scan_kind(const ScanArgs& a, const ScanShape* xs, hipStream_t st) {
   ScanShape s = scan_shape(a.B, a.H);
   const int max_rb = scan_max_quads(KIND, s.nch);
   if (s.rb > max_rb) {                                // (behind xs: any number of workgroups will do)
@@ -561,6 +570,7 @@ static void launch_scan_kind(const ScanArgs& a, const ScanShape* xs, hipStream_t
     MG_SCAN_CASE(2, 4)
   }
 #undef MG_SCAN_CASE
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_scan(int kind, const ScanArgs& a0, hipStream_t st) {
@@ -585,23 +595,25 @@ hipError_t launch_scan(int kind, const ScanArgs& a0, hipStream_t st) {
                      a.u + (kind == SCAN_ADJOINT ? a.N * BW : 0),
                      kind == SCAN_ADJOINT ? a.kap + (long long)a.N * a.B * a.kw : nullptr, W,
                      4 * xshape.rb, xshape.hp, xshape.terms);
+  hipError_t err = hipGetLastError();
   const bool h16 = a.bf16 == 1;
-  if (kind == SCAN_GRU) {
-    if (h16) launch_scan_kind<SCAN_GRU, bf16_t>(a, xs, st);
-    else launch_scan_kind<SCAN_GRU, float>(a, xs, st);
+  if (err != hipSuccess) {
+    // (nothing is marked)
+  } else if (kind == SCAN_GRU) {
+    err = h16 ? launch_scan_kind<SCAN_GRU, bf16_t>(a, xs, st) : launch_scan_kind<SCAN_GRU, float>(a, xs, st);
   } else if (kind == SCAN_ADJOINT) {
-    if (h16) launch_scan_kind<SCAN_ADJOINT, bf16_t>(a, xs, st);
-    else launch_scan_kind<SCAN_ADJOINT, float>(a, xs, st);
+    err = h16 ? launch_scan_kind<SCAN_ADJOINT, bf16_t>(a, xs, st)
+              : launch_scan_kind<SCAN_ADJOINT, float>(a, xs, st);
   } else if (kind == SCAN_LSTM) {
-    launch_scan_kind<SCAN_LSTM, float>(a, xs, st);
+    err = launch_scan_kind<SCAN_LSTM, float>(a, xs, st);
   } else {
-    launch_scan_kind<SCAN_ODE, float>(a, xs, st);
+    err = launch_scan_kind<SCAN_ODE, float>(a, xs, st);
   }
   const double rows = (double)a.N * a.B;
   const int ng = kind == SCAN_LSTM ? 4 : kind == SCAN_ODE ? 1 : 3;
   const double bytes = kind == SCAN_ADJOINT ? 28.0 : kind == SCAN_GRU ? 20.0 : kind == SCAN_LSTM ? 32.0 : 16.0;
   prof_end(prof, 2.0 * ng * rows * a.H * a.H, bytes * rows * a.H, st);
-  return hipGetLastError();
+  return err;
 }
 
 }  // namespace mg

@@ -8,6 +8,7 @@ import sys
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+MGRIT_E_LAUNCH = -7
 CALL = """
 import ctypes, sys
 ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
@@ -62,3 +63,16 @@ def test_coarsest_level_on_bf16_weights_keeps_the_fp32_contraction(runtime, B, H
     assert rc == 0 and len(scans) == 2
     assert "xcd_scan_kernel" in scans[0]
     assert all(name.split(">(")[0].endswith("true") for name in scans), scans
+
+
+@pytest.mark.parametrize("entry,kernel", [("scan", "mg::xcd_scan_kernel<0"), ("scan", "scan_mark_kernel"),
+                                          ("scan", "mg::scan_kernel<0"), ("scan_backward", "adj_xcd_scan_kernel<1"),
+                                          ("scan_backward", "scan_mark_kernel"),
+                                          ("scan_backward", "mg::scan_kernel<1")])
+def test_a_solve_that_cannot_be_launched_is_reported(runtime, entry, kernel):
+    # (a later launch that succeeds must not hide it: the rows would hold the marks of unwritten ones)
+    c = cfg(64, 32, 64, 512)
+    rc, got = call(runtime, entry, *c)
+    assert rc == 0 and any(kernel in name for _, name in got), got
+    rc, _ = call(runtime, entry, *c, FAKE_HIP_FAIL=kernel)
+    assert rc == MGRIT_E_LAUNCH
