@@ -61,6 +61,24 @@ __device__ inline float scan_own(const float* p) {
     b = __hip_atomic_load((const unsigned*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return __uint_as_float(b);
 }
+// Weights of gate g, chunk c: column j, k = k0 + 64 c + 0..15 (zero beyond H, a multiple of 4).
+template <int KIND, int NG, int NCH, class WT>
+__device__ inline void scan_weights(float (&w)[NG][NCH][16], const WT* Wt, int H, int j, int k0) {
+#pragma unroll
+  for (int g = 0; g < NG; ++g)
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int k = k0 + 64 * c + 4 * q;
+        const int kc = min(k, H - 4);
+        const WT* p = Wt + (KIND == SCAN_ADJOINT ? (long long)j * 3 * H + g * H + kc
+                                                 : ((long long)g * H + j) * H + kc);
+        const floatx4 v = k < H ? ldg4w(p) : zero4();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[g][c][4 * q + e] = v[e];
+      }
+}
 // NCH: chunks of 64 k per wave; RB: groups of four rows per workgroup.  Registers: NG 16 NCH
 // weights; one workgroup per CU is planned for (two waves per SIMD at eight waves).
 // ITEMS: the workgroup takes (step, unit) items from the counter until none are left; otherwise it
@@ -125,7 +143,8 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
     // weights: column j0 + lane % 16, k = kw0 + 64 c + 16 (lane / 16) + 0..15 (zero beyond H; columns
     // beyond H repeat the last one and are never stored)
     float w[NG][NCH][16];
-    bf16x8 wt[NG][NCH][2];
+    bf16x8 wt[NG][NCH * 2];
+    bool plain = false;                               // TERMS: contract in fp32 all the same (per wave)
     if constexpr (TERMS) {
       const int j = min(j0 + (lane & 15), H - 1);
 #pragma unroll
@@ -134,25 +153,12 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
         for (int c = 0; c < NCH; ++c)
 #pragma unroll
           for (int b = 0; b < 2; ++b)
-            wt[g][c][b] = term_weights((const bf16_t*)a.Wt + ((long long)g * H + j) * H,
-                                       kw0 + 64 * c + 32 * b + 8 * (lane >> 4), H);
+            wt[g][2 * c + b] = term_weights((const bf16_t*)a.Wt + ((long long)g * H + j) * H,
+                                            kw0 + 64 * c + 32 * b + 8 * (lane >> 4), H);
       frag[wv][(lane >> 5) * 64 + (lane >> 3 & 3) * 16 + 12 + (lane & 3)] = uintx4{0, 0, 0, 0};
+      plain = term_weights_infinite(wt);
     } else {
-      const int j = min(j0 + (lane & 15), H - 1);
-#pragma unroll
-      for (int g = 0; g < NG; ++g)
-#pragma unroll
-        for (int c = 0; c < NCH; ++c)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int k = kw0 + 64 * c + 16 * (lane >> 4) + 4 * q;
-            const int kc = min(k, H - 4);             // H is a multiple of 4
-            const WT* p = (const WT*)a.Wt +
-                          (ADJ ? (long long)j * 3 * H + g * H + kc : ((long long)g * H + j) * H + kc);
-            const floatx4 v = k < H ? ldg4w(p) : zero4();
-#pragma unroll
-            for (int e = 0; e < 4; ++e) w[g][c][4 * q + e] = v[e];
-          }
+      scan_weights<KIND>(w, (const WT*)a.Wt, H, min(j0 + (lane & 15), H - 1), kw0 + 16 * (lane >> 4));
     }
     // polled operand: rows r0 + 4 r + lane % 4, k = kw0 + 64 c + 4 (lane / 4) + 0..3; lanes beyond
     // the rows or columns read a valid place and contribute nothing
@@ -300,54 +306,74 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
 #pragma unroll
           for (int q = 0; q < NP; ++q) acc[r][g][q] = zero4();
       if constexpr (TERMS) {
-        // each wave sorts its rows into fragments through LDS of its own
-        typedef unsigned u2 __attribute__((ext_vector_type(2)));
-        u2* const put = (u2*)frag[wv] + ((lane >> 5) * 64 + (lane >> 3 & 3) * 16 + (lane & 3)) * 2 +
-                         (lane >> 2 & 1);
+        if (!plain) {
+          // each wave sorts its rows into fragments through LDS of its own
+          typedef unsigned u2 __attribute__((ext_vector_type(2)));
+          u2* const put = (u2*)frag[wv] + ((lane >> 5) * 64 + (lane >> 3 & 3) * 16 + (lane & 3)) * 2 +
+                           (lane >> 2 & 1);
+#pragma unroll
+          for (int r = 0; r < RB; ++r) {
+            floatx4 sum[NG];
+#pragma unroll
+            for (int g = 0; g < NG; ++g) sum[g] = zero4();
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) {
+              StateTerms t[4];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) t[e] = state_terms(op[c][r][0][e]);
+              auto lo = [](unsigned a0, unsigned a1) { return (a0 & 0xffffu) | (a1 << 16); };
+              auto hi = [](unsigned a0, unsigned a1) { return (a0 >> 16) | (a1 & 0xffff0000u); };
+              put[0] = u2{lo(t[0].t01, t[1].t01), lo(t[2].t01, t[3].t01)};
+              put[8] = u2{hi(t[0].t01, t[1].t01), hi(t[2].t01, t[3].t01)};
+              put[16] = u2{lo(t[0].t2, t[1].t2), lo(t[2].t2, t[3].t2)};
+              __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+              const uintx4 f[2] = {frag[wv][lane], frag[wv][64 + lane]};
+              __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+#pragma unroll
+              for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int g = 0; g < NG; ++g) sum[g] = term_mma(f[b], wt[g][2 * c + b], sum[g]);
+            }
+#pragma unroll
+            for (int g = 0; g < NG; ++g) part[buf][wv][r][g][lane] = term_fold(sum[g]);
+          }
+        } else {                                       // (registers: a gate and a chunk at a time)
+#pragma unroll
+          for (int g = 0; g < NG; ++g) {
+            floatx4 sum[RB][1][1];
+#pragma unroll
+            for (int r = 0; r < RB; ++r) sum[r][0][0] = zero4();
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) {
+              asm volatile("" ::: "memory");
+              float w1[1][1][16];
+              scan_weights<KIND>(w1, (const WT*)a.Wt + (long long)g * H * H, H, min(j0 + (lane & 15), H - 1),
+                                 kw0 + 64 * c + 16 * (lane >> 4));
+              quad_mma<RB, 1, 1>(sum, [&](int r, int) { return op[c][r][0]; },
+                                 [&](int) -> const float (&)[16] { return w1[0][0]; });
+            }
+#pragma unroll
+            for (int r = 0; r < RB; ++r) part[buf][wv][r][g][lane] = quad_fold(sum[r][0][0]);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+          quad_mma<RB, NG, NP>(acc, [&](int r, int g) { return op[c][r][ADJ ? g : 0]; },
+                               [&](int g) -> const float (&)[16] { return w[g][c]; });
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
           floatx4 sum[NG];
 #pragma unroll
-          for (int g = 0; g < NG; ++g) sum[g] = zero4();
+          for (int g = 0; g < NG; ++g)
+            sum[g] = NP > 1 ? acc[r][g][0] + acc[r][g][NP - 1] : acc[r][g][0];
+          if (ADJ) {
+            part[buf][wv][r][0][lane] = quad_fold(sum[0] + sum[NG > 1 ? 1 : 0] + sum[NG - 1]);
+          } else {
 #pragma unroll
-          for (int c = 0; c < NCH; ++c) {
-            StateTerms t[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) t[e] = state_terms(op[c][r][0][e]);
-            auto lo = [](unsigned a0, unsigned a1) { return (a0 & 0xffffu) | (a1 << 16); };
-            auto hi = [](unsigned a0, unsigned a1) { return (a0 >> 16) | (a1 & 0xffff0000u); };
-            put[0] = u2{lo(t[0].t01, t[1].t01), lo(t[2].t01, t[3].t01)};
-            put[8] = u2{hi(t[0].t01, t[1].t01), hi(t[2].t01, t[3].t01)};
-            put[16] = u2{lo(t[0].t2, t[1].t2), lo(t[2].t2, t[3].t2)};
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-            const uintx4 f[2] = {frag[wv][lane], frag[wv][64 + lane]};
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-              for (int g = 0; g < NG; ++g) sum[g] = term_mma(f[b], wt[g][c][b], sum[g]);
+            for (int g = 0; g < NG; ++g) part[buf][wv][r][ADJ ? 0 : g][lane] = quad_fold(sum[g]);
           }
-#pragma unroll
-          for (int g = 0; g < NG; ++g) part[buf][wv][r][g][lane] = term_fold(sum[g]);
         }
-      } else {
-#pragma unroll
-      for (int c = 0; c < NCH; ++c)
-        quad_mma<RB, NG, NP>(acc, [&](int r, int g) { return op[c][r][ADJ ? g : 0]; },
-                             [&](int g) -> const float (&)[16] { return w[g][c]; });
-#pragma unroll
-      for (int r = 0; r < RB; ++r) {
-        floatx4 sum[NG];
-#pragma unroll
-        for (int g = 0; g < NG; ++g)
-          sum[g] = NP > 1 ? acc[r][g][0] + acc[r][g][NP - 1] : acc[r][g][0];
-        if (ADJ) {
-          part[buf][wv][r][0][lane] = quad_fold(sum[0] + sum[NG > 1 ? 1 : 0] + sum[NG - 1]);
-        } else {
-#pragma unroll
-          for (int g = 0; g < NG; ++g) part[buf][wv][r][ADJ ? 0 : g][lane] = quad_fold(sum[g]);
-        }
-      }
       }
       __syncthreads();
       const int stopped = stop[buf];

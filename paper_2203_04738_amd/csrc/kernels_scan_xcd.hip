@@ -28,6 +28,9 @@
 // against 1.09e-7 with fp32 MFMAs, 2048 of 1 x 512 1.04 : 1.05, 1024 of 3 x 264 1.03 : 1.04), nor to one
 // side of it (sum of the errors over sum of their sizes, mean of the five -0.3 % : -0.2 % at 8 x 1024).
 //
+// An infinite weight cannot be contracted so (term_weights_infinite): the workgroup that holds one gives up
+// the solve, and the takeover launch contracts those weights in fp32.
+//
 // Which XCD a workgroup runs on it reads from the hardware (XCC_ID).  The launch has enough workgroups
 // to fill what it needs on every XCD; the XCD whose workgroups have all arrived takes the next group of
 // row blocks (xcd_role), the others leave when all are taken.  A group that is taken has all its
@@ -188,6 +191,17 @@ __device__ __forceinline__ void xcd_solve(const ScanArgs& a, const ScanShape& sh
             if (sizeof(WT) == 2) asm volatile("" : "+v"(w[c][t * NG + g][4 * q + e]));   // (as floats)
           }
         }
+  }
+  if constexpr (TERMS) {
+    if (term_weights_infinite(wt)) {      // (out like a wave that has waited too long, below)
+      if (lane == 0) {
+        __hip_atomic_store(a.ctl + CTL_ABORT, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(a.ctl + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      stop = 1;
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_endpgm();
+    }
   }
   // polled operand: row quad r, row lane % 4, k = kw0 + 64 c + 4 (lane / 4) + 0..3; lanes beyond the
   // rows read a row that is there (their sums are not stored)

@@ -141,6 +141,22 @@ __device__ inline bf16x8 term_weights(const bf16_t* row, int k, int H) {
   const bf16x8 v = ldg8h(row + min(k, H - 8));
   return k < H ? v : __builtin_bit_cast(bf16x8, uintx4{0, 0, 0, 0});
 }
+// Whether a weight of the wave is infinite (the same answer in every lane): its product with a zero term,
+// which most states have, is NaN, so terms cannot carry it, and fp32 MFMAs contract in their place.
+template <int NB, int NQ>
+__device__ inline bool term_weights_infinite(const bf16x8 (&w)[NB][NQ]) {
+  bool inf = false;
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const uintx4 v = __builtin_bit_cast(uintx4, w[b][q]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        inf |= (v[e] & 0x7fffu) == 0x7f80u || (v[e] & 0x7fff0000u) == 0x7f800000u;
+    }
+  return __any(inf);
+}
 
 __device__ inline void scan_store_agent(float* p, uintx4 v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");

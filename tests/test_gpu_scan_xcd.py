@@ -130,3 +130,24 @@ def test_any_part_may_be_taken_over(B, H, monkeypatch):
     for ticks in (0, 30, 100, 200, 300, 400, 600, 1000):
         monkeypatch.setenv("MGRIT_SCAN_WAIT_TICKS", str(ticks))
         assert all(torch.equal(a, b) for a, b in zip(solve(), want)), ticks
+
+
+@pytest.mark.parametrize("B,H", [(3, 72), (8, 520), (60, 512), (99, 1024)])
+def test_infinite_bf16_weights(gh, B, H):
+    # an infinite weight saturates a gate; it makes no NaN where the state it meets is not zero, though
+    # most states have terms that are (r, z and n gate, first and last K slice, first and last column)
+    print("xcd case infinite weights", B, H, flush=True)
+    d, t, cfg, ws, p, h, *_ = _gru(B, H, T, half=True)
+    d["h0"] = np.where(np.arange(H) % 2, 0.5, -0.75).astype(np.float32) + 0 * d["h0"]
+    # (columns of states that stay away from zero, whose sign is beyond doubt)
+    away = np.abs(orc.serial_scan(d["W"], d["U"], d["b_i"], d["b_h"], d["x"], d["h0"])).min((0, 1))
+    low, mid, high = (np.argmax(away[i:i + H // 3]) + i for i in (0, H // 3, H - H // 3))
+    for row, k, sign in ((1, low, 1), (H + 5, high, -1), (3 * H - 2, mid, 1), (H - 1, high, 1)):
+        d["U"][row, k] = sign * np.inf
+    t["U"].copy_(torch.from_numpy(d["U"]))
+    t["h0"].copy_(torch.from_numpy(d["h0"]))
+    with np.errstate(over="ignore"):
+        want = orc.serial_scan(d["W"], d["U"], d["b_i"], d["b_h"], d["x"], d["h0"])
+    assert np.isfinite(want).all() and np.abs(want[:, :, [low, mid, high]]).min() > 1e-4
+    mg.gru_serial_scan(cfg, *p, t["h0"], h, ws)
+    assert _rel(h, want) <= 1e-5
