@@ -111,13 +111,19 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
   int unit = blockIdx.x, first = 0, last = N;
   int done = 0;                                       // row quads before this one are solved
   if (ITEMS) {
+    // (the workspace is left as if the rows had gone through the output array alone: its bytes do not
+    // tell who has solved)
     for (long long q = (long long)blockIdx.x * blockDim.x + tid; q < a.ring4;
          q += (long long)gridDim.x * blockDim.x)
       ((uintx4*)a.ring)[q] = uintx4{0, 0, 0, 0};
-    if (ctl_load(a.ctl + 1) == 0) return;             // all were resident: the solve is done
-    if (a.ring && ctl_load(a.ctl + CTL_ABORT) == 0)
-      done = xcd_groups((unsigned)ctl_load(a.ctl + CTL_WORD)) * xcd_quads;
-    if (done * 4 >= B) return;
+    // done: all were resident, or the XCDs have taken every row block
+    if (a.ring) {
+      if (ctl_load(a.ctl + CTL_ABORT) == 0)
+        done = xcd_groups((unsigned)ctl_load(a.ctl + CTL_WORD)) * xcd_quads;
+      if (done * 4 >= B) return;
+    } else if (ctl_load(a.ctl + 1) == 0) {
+      return;
+    }
     if (tid == 0) mine = ctl_take(a.ctl);
   }
   if (tid < 2) stop[tid] = 0;
@@ -415,11 +421,13 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
 
 // Marks the points the solve will write, clears its control words and fills the rings (ring4 units of
 // four floats; see kernels_scan_xcd.hip): slot 0 is the state u0 the solve starts from (adjoint: its
-// products with the coefficients k0 of the first step), the others are marked.
+// products with the coefficients k0 of the first step), the others are marked.  closed: XCDs that take no
+// part, as in CTL_WORD.
 __global__ __launch_bounds__(256) void scan_mark_kernel(uintx4* p, long long n4, ScanArgs a,
                                                         const float* u0, const float* k0, int W, int rows,
-                                                        int hp, int terms) {
-  if (blockIdx.x == 0 && threadIdx.x < CTL_WORDS) a.ctl[threadIdx.x] = 0;
+                                                        int hp, int terms, unsigned closed) {
+  if (blockIdx.x == 0 && threadIdx.x < CTL_WORDS)
+    a.ctl[threadIdx.x] = threadIdx.x == CTL_WORD ? (int)closed : 0;
   const uintx4 s = {SENTINEL, SENTINEL, SENTINEL, SENTINEL};
   const long long t0 = (long long)blockIdx.x * 256 + threadIdx.x, dt = 256LL * gridDim.x;
   for (long long i = t0; i < n4; i += dt) p[i] = s;
@@ -484,6 +492,12 @@ static int scan_max_wg() {
   }
   return n < SCAN_MAXWG ? n : SCAN_MAXWG;
 }
+// MGRIT_SCAN_XCDS in the environment: a mask of the XCDs that may take row blocks, none of them: exchange
+// through memory (tests: both forms and every way of sharing a solve between them and the takeover).
+static unsigned scan_xcds() {
+  const char* e = std::getenv("MGRIT_SCAN_XCDS");
+  return e ? (unsigned)std::strtoul(e, nullptr, 0) & 0xffu : 0xffu;
+}
 static ScanShape scan_shape(int B, int H) {
   const int max_wg = scan_max_wg(), quads = (B + 3) / 4;
   ScanShape s;
@@ -512,7 +526,7 @@ static ScanShape scan_shape(int B, int H) {
 // 1024 1.53 : 3.02, 64 x 1024 2.3 : 9.4, at any number of rows (two solves of 8 x 1024 at once 0.89 : 1.82 ms).
 constexpr int SCAN_XCD_MAX_QUADS = 4;                  // per row block
 static bool scan_shape_xcd(int kind, int B, int H, bool terms, ScanShape& s) {
-  if (scan_max_wg() != SCAN_XCDS * SCAN_XCD_CUS) return false;
+  if (scan_max_wg() != SCAN_XCDS * SCAN_XCD_CUS || scan_xcds() == 0) return false;
   const int quads = (B + 3) / 4;
   s.terms = terms;
   s.ct = H > 512 ? 2 : 1;
@@ -616,11 +630,14 @@ hipError_t launch_scan(int kind, const ScanArgs& a0, hipStream_t st) {
   a.ring4 = xcd ? (long long)scan_ring_floats(kind, a.B, a.H, a.terms) / 4 : 0;
   const long long n4 = (long long)a.N * a.B * W / 4, BW = (long long)a.B * W;
   const long long nb = (n4 + 255) / 256;
+  unsigned closed = 0;
+  for (int x = 0; x < SCAN_XCDS; ++x)
+    if (xcd && !(scan_xcds() >> x & 1)) closed |= XCD_CLOSED << 4 * x;
   hipLaunchKernelGGL(scan_mark_kernel, dim3((unsigned)(nb < 4096 ? nb : 4096)), dim3(256), 0, st,
                      (uintx4*)(a.u + (kind == SCAN_ADJOINT ? 0 : BW)), n4, a,
                      a.u + (kind == SCAN_ADJOINT ? a.N * BW : 0),
                      kind == SCAN_ADJOINT ? a.kap + (long long)a.N * a.B * a.kw : nullptr, W,
-                     4 * xshape.rb, xshape.hp, xshape.terms);
+                     4 * xshape.rb, xshape.hp, xshape.terms, closed);
   hipError_t err = hipGetLastError();
   const bool h16 = a.bf16 == 1;
   if (err != hipSuccess) {

@@ -34,8 +34,9 @@
 // Which XCD a workgroup runs on it reads from the hardware (XCC_ID).  The launch has enough workgroups
 // to fill what it needs on every XCD; the XCD whose workgroups have all arrived takes the next group of
 // row blocks (xcd_role), the others leave when all are taken.  A group that is taken has all its
-// workgroups resident and needs nothing else.  If an XCD does not fill up in time, its workgroups leave
-// and the takeover launch solves the row blocks that are left (scan_kernel<.., true>), with the same bits.
+// workgroups resident and needs nothing else.  If an XCD does not fill up in time, its workgroups leave.
+// The takeover launch solves the row blocks that no XCD has taken, for whatever reason
+// (scan_kernel<.., true>), with the same bits.
 #include "scan_exchange.h"
 
 namespace mg {
@@ -66,9 +67,7 @@ __device__ inline int xcd_role(int* ctl, int xcd, int ticket, int per, int need,
       const unsigned mine = closes ? XCD_CLOSED : (unsigned)n + 1;
       if (__hip_atomic_compare_exchange_strong(word, &w, w | (mine << sh), __ATOMIC_RELAXED,
                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-        if (!closes) return n;
-        __hip_atomic_store(ctl + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return -1;
+        return closes ? -1 : n;
       }
       continue;
     }
@@ -194,10 +193,7 @@ __device__ __forceinline__ void xcd_solve(const ScanArgs& a, const ScanShape& sh
   }
   if constexpr (TERMS) {
     if (term_weights_infinite(wt)) {      // (out like a wave that has waited too long, below)
-      if (lane == 0) {
-        __hip_atomic_store(a.ctl + CTL_ABORT, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(a.ctl + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
+      if (lane == 0) __hip_atomic_store(a.ctl + CTL_ABORT, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       stop = 1;
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       __builtin_amdgcn_endpgm();
@@ -295,10 +291,8 @@ __device__ __forceinline__ void xcd_solve(const ScanArgs& a, const ScanShape& sh
       bool leave = false;
       for (int polls = 1; __any(ring_waits(vr)); ++polls) {
         if ((polls & 127) == 0) {
-          if (polls >= SCAN_MAX_POLLS) {
+          if (polls >= SCAN_MAX_POLLS)
             __hip_atomic_store(a.ctl + CTL_ABORT, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(a.ctl + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          }
           leave = ctl_load(a.ctl + CTL_ABORT) != 0;
           if (leave) break;
         }

@@ -16,8 +16,8 @@ struct ScanArgs {
   const float* kap;    // coefficient rows [N + 1, B, kw] (adjoint)
   float* u;            // state array [N + 1, B, H] (LSTM: [N + 1, B, 2H])
   const float* g;      // right-hand side, laid out like u (may be null)
-  int* ctl;            // device words: [0] workgroups that have arrived, [1] not all came in time,
-                       // [2..3] (64 bits) next item, the rest in kernels_scan.hip
+  int* ctl;            // device words: [0] workgroups that have arrived, [1] not all came in time (both for
+                       // the exchange through memory), [2..3] (64 bits) next item, the rest in scan_exchange.h
   float* ring;         // scan_ring_floats(...) floats, or null: exchange through memory
   long long ring4;     // (set by launch_scan)
   int N, B, H, kw;

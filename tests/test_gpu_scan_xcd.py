@@ -115,7 +115,8 @@ def test_state_in_terms_on_bf16_weights(gh, B, H, ct):
 
 @pytest.mark.parametrize("B,H", [(60, 200), (32, 512), (30, 1000), (100, 512), (100, 1000)])
 def test_any_part_may_be_taken_over(B, H, monkeypatch):
-    # limits around the time the workgroups need to arrive: some XCDs take their rows, some do not
+    # limits around the time the workgroups need to arrive (who solves what is chance here; the cases of
+    # test_some_xcds_solve_and_the_takeover_the_rest choose it)
     def solve():
         out = []
         for half in (False, True):
@@ -151,3 +152,55 @@ def test_infinite_bf16_weights(gh, B, H):
     assert np.isfinite(want).all() and np.abs(want[:, :, [low, mid, high]]).min() > 1e-4
     mg.gru_serial_scan(cfg, *p, t["h0"], h, ws)
     assert _rel(h, want) <= 1e-5
+
+
+def _groups(ws, cfg, width, gates):
+    """Groups of row blocks that XCDs have taken, from the control words a scan has left at the head of the
+    gradient partials (behind projection, coefficients, U^T and W^T)."""
+    def up(n):
+        return -(-n // 256) * 256
+
+    T_, B, D, H = cfg.T, cfg.B, cfg.D, width
+    at = up(T_ * B * 3 * H * 4) + up((T_ + 1) * B * H * 20) + up(3 * H * H * 4) + up(3 * H * D * 4)
+    ctl = ws[at:at + 64].view(torch.int32).cpu().numpy().astype(np.int64)
+    nibbles = [(int(ctl[4]) >> 4 * x) & 15 for x in range(8)]
+    assert sum(0 < v < 15 for v in nibbles) <= sum(ctl[8:] > 0)     # (words of such a solve: tickets per XCD)
+    return sum(0 < v < 15 for v in nibbles)
+
+
+@pytest.mark.parametrize("xcds", [0x01, 0x5a, 0x7f])
+@pytest.mark.parametrize("B,H,need", [(60, 200, 8), (41, 260, 6), (32, 512, 8), (30, 1000, 8), (100, 512, 7),
+                                      (255, 132, 8), (100, 200, 7), (100, 1000, 7)])
+def test_some_xcds_solve_and_the_takeover_the_rest(B, H, need, xcds, monkeypatch):
+    # all kinds, above 64 rows the takeover's grid is larger than the chip; `need` XCDs solve alone
+    def solve():
+        out, taken = [], []
+        for half in ((False, True) if H % 8 == 0 else (False,)):
+            d, t, cfg, ws, p, h, w, g = _gru(B, H, 24, half)
+            mg.gru_serial_scan(cfg, *p, t["h0"], h, ws)
+            taken.append(_groups(ws, cfg, H, 3))
+            mg.gru_serial_scan_backward(cfg, *p, h, t["dL_dhT"], w, *g, ws)
+            out += [h, w, *g]
+        cfg = MgritGruCfg(24, B, 8, H)
+        lws = torch.empty(mg.mgrit_lstm_workspace_bytes(cfg), dtype=torch.uint8, device=DEV)
+        if H <= 512:
+            t = {k: torch.from_numpy(v).to(DEV) for k, v in
+                 random_lstm(1, 24, B, 8, H, scale=0.7 / np.sqrt(H)).items()}
+            u = torch.full((25, B, 2 * H), 7.0, device=DEV)
+            mg.lstm_serial_scan(cfg, t["W"], t["U"], t["b_i"], t["b_h"], t["x"], t["u0"], u, lws)
+            taken.append(_groups(lws, cfg, 2 * H, 4))
+            out.append(u)
+        t = {k: torch.from_numpy(v).to(DEV) for k, v in random_ode(2, 24, B, 8, H).items()}
+        o = torch.full((25, B, H), 7.0, device=DEV)
+        mg.ode_serial_scan(cfg, 0.25, t["A"], t["Bw"], t["b"], t["d"], t["h0"], o, lws)
+        taken.append(_groups(lws, cfg, H, 1))
+        return out + [o], taken
+
+    print("xcd case shared", B, H, hex(xcds), flush=True)
+    monkeypatch.setenv("MGRIT_SCAN_WAIT_TICKS", "2000000")     # (20 ms: whoever may start does)
+    want, taken = solve()
+    assert all(torch.isfinite(a).all() for a in want) and set(taken) == {need}
+    monkeypatch.setenv("MGRIT_SCAN_XCDS", str(xcds))
+    got, taken = solve()
+    assert set(taken) == {min(need, bin(xcds).count("1"))}
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
