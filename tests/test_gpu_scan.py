@@ -1,8 +1,10 @@
 """Serial propagation as one launch (kernels_scan.hip) against the oracles, at the edges of its
 shapes: partly filled row quads, column groups and K chunks, several row groups per workgroup, one
-and two chunks per wave.  GRU layers of up to 128 columns with fp32 weights run their serial solves in
-the sweep kernels (kernels_sweep.hip); every case checks which of the two has run.  Bar: 1e-5 of the
-largest value (fp32 arithmetic throughout, also on bf16 weights, which the oracle reads as they are)."""
+and two chunks per wave.  Every case runs twice: as it is dispatched, which is inside the XCDs
+(kernels_scan_xcd.hip) for most, and with the exchange through memory, the form for the other shapes, for
+scratch without room and for parts of a GPU.  GRU layers of up to 128 columns with fp32 weights run their
+serial solves in the sweep kernels (kernels_sweep.hip); every case checks which kernel has run.  Bar: 1e-5
+of the largest value (fp32 sums throughout, also on bf16 weights, which the oracle reads as they are)."""
 import numpy as np
 import pytest
 import torch
@@ -17,19 +19,39 @@ from synthetic_inputs import random_lstm, random_ode, random_small, round_to_bf1
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 T = 9
-# B, H: the sweep kernels up to 128 columns; above, quads 1..16, column groups 9..64: (1, 132), (3, 140)
-# and (33, 196) one row group per workgroup and a ragged last column group and K chunk, (33, 512) and
-# (64, 500) two row groups, (64, 1024) four, (3, 1000) and (8, 516) two chunks per wave with a ragged tail
+# B, H: the sweep kernels up to 128 columns; above, quads 1..16, column groups 9..64, through memory: (1,
+# 132), (3, 140) and (33, 196) one row group per workgroup and a ragged last column group and K chunk, (33,
+# 512) and (64, 500) two row groups, (64, 1024) four, (3, 1000) and (8, 516) two chunks per wave with a
+# ragged tail (four row groups of one chunk: only with fewer CUs than a whole GPU has)
 SHAPES = [(1, 16), (3, 20), (4, 64), (5, 68), (33, 128), (1, 132), (3, 140), (33, 196), (32, 512),
           (33, 512), (64, 500), (3, 1000), (8, 516), (9, 1024), (64, 1024)]
-SCAN = {"gru": "scan_kernel<0,", "adjoint": "scan_kernel<1,", "lstm": "scan_kernel<2,",
-        "ode": "scan_kernel<3,"}
+KINDS = ("gru", "adjoint", "lstm", "ode")
+NO_ROOM = {("ode", 3, 20), ("gru", 5, 24), ("adjoint", 5, 24)}     # for a ring in the scratch
 
 
 @pytest.fixture(scope="module")
 def gh():
     import gpu_harness
     return gpu_harness
+
+
+@pytest.fixture(params=["dispatched", "memory"])
+def form(request, monkeypatch):
+    if request.param == "memory":
+        monkeypatch.setenv("MGRIT_SCAN_XCDS", "0")
+    return request.param
+
+
+def _kernel(form, kind, B, H, half=False):
+    """Name of the kernel that solves (not of the takeover behind it, whose fifth argument is true)."""
+    k, quads, cols = KINDS.index(kind), -(-B // 4), -(-H // 16)
+    wide = H > 512 and (kind == "lstm" or (not (half and kind == "gru") and quads * cols <= 128))
+    if form == "memory" or wide or (kind, B, H) in NO_ROOM:
+        rb = 1
+        while -(-quads // rb) * cols > 256:
+            rb *= 2
+        return f"mg::scan_kernel<{k}, {1 + (H > 512)}, {rb}, {'unsigned short' if half else 'float'}, false, "
+    return f"{'adj_' if kind == 'adjoint' else 'mg::'}xcd_scan_kernel<{k}, {1 + (H > 512)}, "
 
 
 def _rel(a, b):
@@ -57,22 +79,23 @@ def _gru(B, H, half=False, steps=T, seed=0):
     return d, t, cfg, ws, (t["W"], t["U"], t["b_i"], t["b_h"], t["x"])
 
 
-def _check_gru(gh, B, H, half=False):
+def _check_gru(gh, form, B, H, half=False):
     one_launch = half or H > 128
     d, t, cfg, ws, p = _gru(B, H, half)
     P = (d["W"], d["U"], d["b_i"], d["b_h"])
     h = torch.full((T + 1, B, H), 7.0, device=DEV)
     gh.expect_kernels(lambda: mg.gru_serial_scan(cfg, *p, t["h0"], h, ws),
-                      SCAN["gru"] if one_launch else "phi_sweep_kernel")
+                      _kernel(form, "gru", B, H, half) if one_launch else "phi_sweep_kernel")
     want = orc.serial_scan(*P, d["x"], d["h0"])
     assert _rel(h, want) <= 1e-5
     w = torch.full((T + 1, B, H), 7.0, device=DEV)
     g = [torch.empty(3 * H, 8, device=DEV), torch.empty(3 * H, H, device=DEV),
          torch.empty(3 * H, device=DEV), torch.empty(3 * H, device=DEV)]
-    # (the adjoint of more than 32 rows x 1024 would need more registers: step by step)
+    # (the adjoint of more than 32 rows x 1024 through memory would need more registers: step by step)
     gh.expect_kernels(lambda: mg.gru_serial_scan_backward(cfg, *p, h, t["dL_dhT"], w, *g, ws),
                       "adj_sweep_kernel" if not one_launch else
-                      "adj_" if B > 32 and H > 1000 else SCAN["adjoint"])
+                      "adj_skinny_kernel" if form == "memory" and B > 32 and H > 1000 else
+                      _kernel(form, "adjoint", B, H, half))
     out = orc.serial_bptt(*P, d["x"], want, d["dL_dhT"])
     # bf16 weights: more than 64 rows of coefficient vectors come from the tile kernels, which
     # carry the state as two bf16 terms there (2^-17 per product: the 1e-4 bar of that form)
@@ -81,48 +104,48 @@ def _check_gru(gh, B, H, half=False):
 
 
 @pytest.mark.parametrize("B,H", SHAPES)
-def test_gru_and_adjoint(gh, B, H):
-    print("scan case", B, H, flush=True)
-    _check_gru(gh, B, H)
+def test_gru_and_adjoint(gh, form, B, H):
+    print("scan case", form, B, H, flush=True)
+    _check_gru(gh, form, B, H)
 
 
 @pytest.mark.parametrize("B,H", [(5, 24), (8, 1024)])
-def test_gru_and_adjoint_bf16_weights(gh, B, H):
-    print("scan case bf16", B, H, flush=True)
-    _check_gru(gh, B, H, half=True)
+def test_gru_and_adjoint_bf16_weights(gh, form, B, H):
+    print("scan case bf16", form, B, H, flush=True)
+    _check_gru(gh, form, B, H, half=True)
 
 
 @pytest.mark.parametrize("B,H", [(3, 20), (32, 512), (64, 500), (5, 1000), (64, 1024)])
-def test_lstm_and_ode(gh, B, H):
-    print("scan case lstm, ode", B, H, flush=True)
+def test_lstm_and_ode(gh, form, B, H):
+    print("scan case lstm, ode", form, B, H, flush=True)
     d = random_lstm(1, T, B, 8, H, scale=0.7 / np.sqrt(H))
     t = _dev(d)
     cfg = MgritGruCfg(T, B, 8, H)
     ws = torch.empty(mg.mgrit_lstm_workspace_bytes(cfg), dtype=torch.uint8, device=DEV)
     u = torch.full((T + 1, B, 2 * H), 7.0, device=DEV)
     gh.expect_kernels(lambda: mg.lstm_serial_scan(cfg, t["W"], t["U"], t["b_i"], t["b_h"], t["x"],
-                                                  t["u0"], u, ws), SCAN["lstm"])
+                                                  t["u0"], u, ws), _kernel(form, "lstm", B, H))
     assert _rel(u, lo.lstm_serial_scan(d["W"], d["U"], d["b_i"], d["b_h"], d["x"], d["u0"])) <= 1e-5
     d = random_ode(2, T, B, 8, H)
     t = _dev(d)
     h = torch.full((T + 1, B, H), 7.0, device=DEV)
     gh.expect_kernels(lambda: mg.ode_serial_scan(cfg, 0.25, t["A"], t["Bw"], t["b"], t["d"], t["h0"],
-                                                 h, ws), SCAN["ode"])
+                                                 h, ws), _kernel(form, "ode", B, H))
     assert _rel(h, oo.ode_serial_scan(d["A"], d["Bw"], d["b"], d["d"], d["h0"], 0.25)) <= 1e-5
 
 
 @pytest.mark.parametrize("B,H", [(5, 68), (5, 140), (32, 512)])
-def test_a_solve_that_is_given_up_is_repaired(gh, B, H, monkeypatch):
+def test_a_solve_that_is_given_up_is_repaired(gh, form, B, H, monkeypatch):
     # a wait limit of zero: the workgroups leave at once, the launch behind solves (that it does is
     # checked in test_results_do_not_depend_on_who_computes_them; 68 columns: LSTM and ODE only)
     monkeypatch.setenv("MGRIT_SCAN_WAIT_TICKS", "0")
-    print("scan case without waiting", B, H, flush=True)
-    _check_gru(gh, B, H)
-    test_lstm_and_ode(gh, B, H)
+    print("scan case without waiting", form, B, H, flush=True)
+    _check_gru(gh, form, B, H)
+    test_lstm_and_ode(gh, form, B, H)
 
 
 @pytest.mark.parametrize("B,H", [(3, 136), (32, 512), (9, 1000), (64, 1024)])
-def test_results_do_not_depend_on_who_computes_them(B, H, monkeypatch):
+def test_results_do_not_depend_on_who_computes_them(form, B, H, monkeypatch):
     # every output but the residual norms is reproducible bit for bit, so a solve whose workgroups
     # are not all resident (here: that does not wait for them) gives the bits of any other
     def solve():
@@ -143,7 +166,7 @@ def test_results_do_not_depend_on_who_computes_them(B, H, monkeypatch):
         mg.ode_serial_scan(cfg, 0.25, t["A"], t["Bw"], t["b"], t["d"], t["h0"], o, lws)
         return [h, w, u, o, *g], left
 
-    print("scan case bits", B, H, flush=True)
+    print("scan case bits", form, B, H, flush=True)
     want, left = solve()
     monkeypatch.setenv("MGRIT_SCAN_WAIT_TICKS", "0")
     got, left0 = solve()
@@ -152,7 +175,23 @@ def test_results_do_not_depend_on_who_computes_them(B, H, monkeypatch):
     assert 0 < int((left0 != left).sum()) <= 16
 
 
-def _nan_case(gh, kind, B, H, call, x, state0, out, alone):
+@pytest.mark.parametrize("B,H", [(8, 512), (64, 256), (12, 1024)])
+def test_coarsest_level_on_bf16_weights_is_the_same_inside_the_xcds(B, H, monkeypatch):
+    # (in fp32 either way, unlike a scan)
+    def solve(levels):
+        d, t, cfg, ws, p = _gru(B, H, True, steps=64)
+        cfg = MgritGruCfg(64, B, 8, H, cf=4, levels=levels, dtype=MGRIT_BF16_STATE2)
+        ws = torch.empty(mg.mgrit_gru_workspace_bytes(cfg), dtype=torch.uint8, device=DEV)
+        h, res = torch.zeros(65, B, H, device=DEV), torch.zeros(1, device=DEV)
+        mg.mgrit_gru_forward(cfg, *p, t["h0"], h, res, ws)
+        return h
+
+    two, one = solve(2), solve(1)
+    monkeypatch.setenv("MGRIT_SCAN_XCDS", "0")
+    assert torch.equal(two, solve(2)) and not torch.equal(one, solve(1))
+
+
+def _nan_case(gh, form, kind, B, H, call, x, state0, out, alone):
     """Row 2 starts as the NaN with every bit set (the pattern that marks unwritten rows), row 1 meets
     it in its data at step 4: both carry NaN from there on, the others keep their bits.  (If the
     pattern were stored, every consumer would wait for it until the time limit.)"""
@@ -161,7 +200,7 @@ def _nan_case(gh, kind, B, H, call, x, state0, out, alone):
     state0.view(torch.int32)[2, :] = -1
     if x is not None:
         x.view(torch.int32)[4, 1, :] = -1
-    gh.expect_kernels(call, SCAN[kind] if alone else "phi_sweep_kernel")
+    gh.expect_kernels(call, _kernel(form, kind, B, H) if alone else "phi_sweep_kernel")
     keep = [b for b in range(B) if b not in (1, 2)]
     assert torch.equal(out[:, keep], clean[:, keep])
     return clean
@@ -169,14 +208,14 @@ def _nan_case(gh, kind, B, H, call, x, state0, out, alone):
 
 @pytest.mark.parametrize("wait", [None, "0"])
 @pytest.mark.parametrize("H", [72, 136])
-def test_a_nan_with_every_bit_set_passes_through(gh, H, wait, monkeypatch):
+def test_a_nan_with_every_bit_set_passes_through(gh, form, H, wait, monkeypatch):
     if wait:
         monkeypatch.setenv("MGRIT_SCAN_WAIT_TICKS", wait)
     B, alone = 6, H > 128
-    print("scan case nan", H, wait, flush=True)
+    print("scan case nan", form, H, wait, flush=True)
     d, t, cfg, ws, p = _gru(B, H)
     h = torch.empty(T + 1, B, H, device=DEV)
-    clean = _nan_case(gh, "gru", B, H, lambda: mg.gru_serial_scan(cfg, *p, t["h0"], h, ws), t["x"],
+    clean = _nan_case(gh, form, "gru", B, H, lambda: mg.gru_serial_scan(cfg, *p, t["h0"], h, ws), t["x"],
                       t["h0"], h, alone)
     assert torch.isnan(h[:, 2]).all() and torch.isnan(h[5:, 1]).all()
     assert torch.equal(h[:5, 1], clean[:5, 1])
@@ -193,17 +232,17 @@ def test_a_nan_with_every_bit_set_passes_through(gh, H, wait, monkeypatch):
     back()
     clean = w.clone()
     t["dL_dhT"].view(torch.int32)[2, :] = -1
-    gh.expect_kernels(back, SCAN["adjoint"] if alone else "adj_sweep_kernel")
+    gh.expect_kernels(back, _kernel(form, "adjoint", B, H) if alone else "adj_sweep_kernel")
     assert torch.isnan(w[:, 2]).all() and torch.equal(w[:, [0, 1, 3, 4, 5]], clean[:, [0, 1, 3, 4, 5]])
     t = _dev(random_lstm(1, T, B, 8, H, scale=0.7 / np.sqrt(H)))
     lws = torch.empty(mg.mgrit_lstm_workspace_bytes(cfg), dtype=torch.uint8, device=DEV)
     u = torch.empty(T + 1, B, 2 * H, device=DEV)
-    clean = _nan_case(gh, "lstm", B, H, lambda: mg.lstm_serial_scan(
+    clean = _nan_case(gh, form, "lstm", B, H, lambda: mg.lstm_serial_scan(
         cfg, t["W"], t["U"], t["b_i"], t["b_h"], t["x"], t["u0"], u, lws), t["x"], t["u0"], u, True)
     assert torch.isnan(u[:, 2]).all() and torch.isnan(u[5:, 1]).all()
     assert torch.equal(u[:5, 1], clean[:5, 1])
     t = _dev(random_ode(2, T, B, 8, H))
-    clean = _nan_case(gh, "ode", B, H, lambda: mg.ode_serial_scan(
+    clean = _nan_case(gh, form, "ode", B, H, lambda: mg.ode_serial_scan(
         cfg, 0.25, t["A"], t["Bw"], t["b"], t["d"], t["h0"], h, lws), t["d"], t["h0"], h, True)
     assert torch.isnan(h[:, 2]).all() and torch.isnan(h[5:, 1]).all()
     assert torch.equal(h[:5, 1], clean[:5, 1])
