@@ -421,9 +421,11 @@ static bool closing_fused(const mgrit_gru_cfg& c, long long nint) {
 // launch, so the C-sweep reads only values written by earlier launches (Jacobi in
 // the coarse points).
 // One level (the serial scan): whether the scan writes the adjoint coefficients along
-// the way when asked to keep them.  With few rows per step the scan runs in the few-row
-// kernels, where the five extra vectors per step cost more than one pass over all steps
-// in the tile kernel afterwards; forward and backward calls decide by the same rule.
+// the way when asked to keep them.  With few rows per step the scan is one launch or runs in
+// the few-row kernels, where the five extra vectors per step cost more than one pass over all
+// steps in the tile kernel afterwards; forward and backward calls decide by the same rule.
+// (Asked to keep them, a scan of more than 64 rows goes step by step, in the tile kernels, also
+// where without them it would be one launch.)
 static bool serial_scan_keeps_coeffs(const mgrit_gru_cfg& c) { return c.B > 64; }
 
 // Levels >= 1 whose coefficient vectors the forward call leaves (with MGRIT_KEEP_COEFFS and

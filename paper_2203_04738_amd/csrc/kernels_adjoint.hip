@@ -582,9 +582,10 @@ static void launch_adj_terms(const AdjArgs& a, hipStream_t s) {
 // bf16 weights, kappa * w as one bf16 term (A2: two).  Every column tile forms the products again (8 bytes
 // of coefficients and state per element against 2 of a weight), so tiles are as wide as they can be with
 // a workgroup for each CU; where even small tiles leave CUs idle, groups of waves split K.  The tile with
-// the smallest number of rounds over the 256 CUs times its time for one: us of a launch of exactly one
-// round at K = 3072, one term (two terms are in the same order).  us with 128 x 128, 64 x 64 and 32 x 32
-// tiles only : these, one term: 512 rows x 1024 31.3 : 23.7, 1024 x 1024 48 : 35.5, 2048 x 1024 61 : 52, 4096 x
+// the smallest number of rounds over the 256 CUs of a whole GPU times its time for one: us of a launch of
+// exactly one round at K = 3072, one term.  Only their ratios count; those of two terms and of other K were not
+// measured, the rule as a whole was (K = 600 to 3072), us with 128 x 128, 64 x 64 and 32 x 32 tiles only :
+// these, one term: 512 rows x 1024 31.3 : 23.7, 1024 x 1024 48 : 35.5, 2048 x 1024 61 : 52, 4096 x
 // 1024 90 : 71, 8192 x 1024 174 : 115, 2048 x 512 25.9 : 19.3, 16384 x 512 103 : 74, 4096 x 256 15.6 : 12.7, 1500 x
 // 200 10.8 : 9.3, 32768 x 296 114 : 99; two terms: 512 x 1024 32 : 27, 2048 x 1024 63 : 57, 8192 x 1024 198 : 144,
 // 16384 x 512 112 : 85, 1500 x 200 11.9 : 10.1.
@@ -1377,7 +1378,7 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_tr_kernel(GradArgs a) {
 // bits 0-1 of the row instead, so that the four rows of a read fall on different banks.
 // (Tiles of 128 x 128 with operands transposed in registers, half of whose LDS cycles were bank conflicts,
 // took 1.00 ms for a gradient of 65536 rows, 1536 x 768 on average, now 0.77; 12800 rows, 3000 x 1000
-// 0.53, now 0.42: 184 TFLOP/s.)
+// 0.53, now 0.42: 184 TFLOP/s; the wide tile spills 31 registers of 256.)
 constexpr int HS_TK = 32;
 template <int NB>
 __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {

@@ -25,9 +25,9 @@
 // the rule and what both measure are at scan_shape_xcd); this file has the form for the others, what both
 // share on the host, and the launch that takes over what neither could start.
 //
-// Measured against the chain of step launches: scan of 512 steps x 8 x 1024 on bf16 weights 3.20 -> 1.61
-// ms, of 777 steps x 3 x 500 3.09 -> 1.61 ms (2.0 us per step: about 1.3 us of exchange, 0.3 us of MFMAs,
-// the rest LDS sums and gates).
+// Of a step of 3 x 500, 2.0 us, about 1.3 us are the exchange, 0.3 us MFMAs, the rest LDS sums and gates.
+// us per step of the shapes that are left to this form: 8 x 1024 3.1 (adjoint, gradients included, 4.3; on
+// bf16 weights 3.9), 3 x 1000 2.7, LSTM 8 x 1000 3.4.
 //
 // Residency.  Each workgroup keeps its columns for the whole solve, which needs all of them resident
 // at once: each announces itself and waits, with a time limit, until all have arrived before it takes
@@ -39,9 +39,13 @@
 // loaded again for every item.  The arithmetic of an element is the same code on the same operands, so
 // the results do not depend on which launch computes them, bit for bit; an element both have computed
 // is written twice with one value.  Measured with the takeover forced (chain of step launches : this :
-// all resident, us per step): 8 x 1024 bf16 5.9 : 8.5 : 3.1, 64 x 1024 17.6 : 12.4 : 10.0, 3 x 500 4.1 :
-// 3.6 : 2.1, 16 x 256 4.0 : 3.8 : 1.6, LSTM 32 x 512 5.2 : 6.7 : 3.0; three streams at once, ms: bptt of
-// 256 x 32 x 1024 24.0 : 23.4, scans of 256 x 64 x 1024 9.8 : 11.5, LSTM 512 x 32 x 512 6.3 : 9.2.
+// all resident in this form, us per step): 8 x 1024 on bf16 weights, contracted in fp32, 5.9 : 8.5 : 3.1, 64 x
+// 1024 17.6 : 12.4 : 10.0, 3 x 500 4.1 : 3.6 : 2.1, 16 x 256 4.0 : 3.8 : 1.6, LSTM 32 x 512 5.2 : 6.7 : 3.0;
+// three streams at once, ms: bptt of 256 x 32 x 1024 24.0 : 23.4, scans of 256 x 64 x 1024 9.8 : 11.5, LSTM 512
+// x 32 x 512 6.3 : 9.2.  Behind the form inside the XCDs, one XCD allowed and no wait (chain : this : inside the
+// XCDs): 100 x 512 13.3 : 12.4 : 3.5, 100 x 1000 26.0 : 24.3 : 9.9, LSTM 100 x 200 10.7 : 5.4 : 1.8, ODE 100 x
+// 512 7.3 : 6.9 : 1.8, back-propagation 100 x 512 20.3 : 13.6 : 5.3 and 100 x 1000 41.9 : 50.2 : 22.5; on terms
+// (this : inside) 100 x 512 10.6 : 2.5, 100 x 1000 16.7 : 4.5, 1 x 1024 2.4 : 1.4.
 #include <atomic>
 #include <cstdlib>
 
@@ -517,7 +521,9 @@ static ScanShape scan_shape(int B, int H) {
 // 3 x 500 1.22 / 1.23 : 2.00 / 2.23, LSTM 32 x 512 1.54 : 2.87.  Beyond, 32 per workgroup fill the
 // registers of a CU and the fp32 matrix pipe takes half of the step: 32 x 1024 2.6 / 2.9 : 5.8 / 6.0, 16 x
 // 768 2.6 / 2.9 : 2.9 / 3.4, but 8 x 1024 2.7 / 3.0 : 3.0 / 3.6, and a second solve on another stream,
-// for which the other form leaves half of the CUs, would wait: only where that form takes more.
+// for which the other form leaves half of the CUs, would wait: only where that form takes more.  Beside other
+// work (4096^3 bf16 products on another stream, this : the other form, us per step) it stays the faster one:
+// 32 x 512 2.7 : 3.2, 3 x 500 2.0 : 2.5, 32 x 1000 3.8 : 6.4, 64 x 512 4.0 : 5.6, 8 x 1024 on bf16 weights 2.4 : 3.8.
 // More rows than one quad for each XCD follow each other within the step, up to four quads; the step launches
 // (a launch per step above 64 rows) : this, us per step of the whole call: scan 100 x 512 13.3 : 4.4, 100 x
 // 1000 26.0 : 10.8, 64 x 1000 10.2 : 6.1, 256 x 256 9.0 : 3.3, LSTM 100 x 200 10.7 : 2.5, ODE 100 x 512 7.3 :

@@ -113,7 +113,9 @@ __device__ inline float moved(float x) {
 // NW waves of NV x NCH chunks of 64 k (NV sums over NCH chunks each: what a wave of scan_kernel sums, so
 // the bits are the same); RB row quads one after the other, CT tiles of 16 columns per workgroup.  The
 // waves also finish the elements (waves of their own for that are no faster: 1.38 against 1.35 us per
-// step at 32 x 512, where they make nine of eight).
+// step at 32 x 512, where they make nine of eight).  With two column tiles the weights leave few registers:
+// the adjoint spills 50 to 59 of 512 with three or four quads and 14 with two on bf16 weights, the fp32
+// contraction of the GRU 4 to 7 of 256 with two or more; the times at scan_shape_xcd are with that.
 template <int KIND, int CT, int NV, int NCH, int NW, int RB, class WT, bool TERMS>
 __device__ __forceinline__ void xcd_solve(const ScanArgs& a, const ScanShape& sh) {
   constexpr int NG = ScanGates<KIND>::value;

@@ -14,9 +14,9 @@
 // api.hip).  Where the workgroups would have three quads or more one after the other, they take sixteen
 // rows at a time through v_mfma_f32_16x16x4_f32 instead (phi_sweep_kernel16, adj_sweep_kernel16): the
 // weights are held the same way, the sums need no adding up over lanes, and the latency of a sub-step is
-// paid for sixteen rows.  The quad kernels take the serial solves of these layers (one interval, N sub-steps), whose
-// state then travels through LDS instead of memory.  Workgroups loop over quads of rows, so that the
-// weights are loaded once per workgroup.
+// paid for sixteen rows.  The serial solves of these layers (one interval, N sub-steps) are such sweeps too, on
+// the quad kernels up to 2048 rows; their state then travels through LDS instead of memory.  Workgroups loop
+// over quads of rows, so that the weights are loaded once per workgroup.
 #include <algorithm>
 #include <type_traits>
 

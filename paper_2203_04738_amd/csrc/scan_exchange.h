@@ -14,7 +14,7 @@ constexpr int SCAN_MAXW = 8;                 // waves per workgroup
 constexpr int SCAN_MAXWG = 256;              // workgroups of a solve at most (one per CU)
 constexpr int SCAN_CP = 16;                  // hidden columns per workgroup
 // Limit of the wait for all workgroups, in ticks of the 100 MHz clock: half a microsecond per step (a
-// quarter of the solve), 50 us (several times what an arrival on a free GPU takes) to 5 ms.
+// quarter of a solve through memory, a fifth to a half of one inside the XCDs), 50 us (several times what an arrival on a free GPU takes) to 5 ms.
 constexpr long long SCAN_ARRIVE_PER_STEP = 50, SCAN_ARRIVE_MIN = 5000, SCAN_ARRIVE_MAX = 500000;
 constexpr long long SCAN_STEP_TICKS = 200000000;     // 2 s: bound of a single wait, all resident
 constexpr int SCAN_MAX_POLLS = 1 << 24;              // the same, items from the counter (counted in
@@ -27,7 +27,7 @@ struct ScanShape {
   int ncg;             // column groups
   int nch, nw;         // kernels_scan.hip: chunks of 64 k per wave, waves that split K
   int ct, hp;          // kernels_scan_xcd.hip: tiles of 16 columns per workgroup, columns of a ring row
-                       // (256, 512 or 1024),
+                       // (256, 512 or 1024)
   int gpx, nx;         // row blocks per XCD, XCDs needed
   int terms;           // the contraction is on terms (ScanArgs)
 };
@@ -207,7 +207,7 @@ __device__ inline void scan_element(const ScanArgs& a, const float (&s)[NS], con
   out += g;
 }
 
-// The form with a row block per XCD (s.xcd); a.ring and a.ring4 are set.
+// The form with a row block per XCD; a.ring and a.ring4 are set.
 hipError_t launch_scan_xcd(int kind, const ScanArgs& a, const ScanShape& s, hipStream_t st);
 
 }  // namespace mg
