@@ -423,7 +423,8 @@ __global__ __launch_bounds__(64 * SCAN_MAXW, 2) void scan_kernel(ScanArgs a, int
   } while (ITEMS);
 }
 
-// Marks the points the solve will write, clears its control words and fills the rings (ring4 units of
+// Marks the points the solve will write (behind a solve inside the XCDs only the takeover reads these marks,
+// 21 us for 2048 x 32 x 512), clears its control words and fills the rings (ring4 units of
 // four floats; see kernels_scan_xcd.hip): slot 0 is the state u0 the solve starts from (adjoint: its
 // products with the coefficients k0 of the first step), the others are marked.  closed: XCDs that take no
 // part, as in CTL_WORD.
