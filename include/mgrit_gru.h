@@ -29,16 +29,20 @@
  *   weights, where MGRIT_BF16 is within ~1e-2.  (The few-row steps of the
  *   coarsest level compute in fp32 on the bf16 weights under both.)
  *   MGRIT_F32_BF16X3: arguments exactly as for MGRIT_F32 and
- *   results to the same accuracy; the tile kernels of larger launches carry each
- *   fp32 operand of a contraction as the sum of three bf16 terms (3 x 8 mantissa
- *   bits at every magnitude of fp32) and keep six of the nine term products,
- *   accumulated in fp32 on the bf16 matrix pipe, which is faster than the fp32
- *   one.  (Smaller launches, and the steps of layers of up to 128 columns, run in
- *   the fp32 kernels, which are faster there and as accurate.)  The
- *   weights' term arrays live in the workspace (it is larger for this dtype)
+ *   results to the same accuracy; the kernels of larger launches carry each fp32
+ *   operand of a contraction as a sum of 16-bit terms and multiply them on the
+ *   16-bit matrix pipe with fp32 sums, which is faster than the fp32 one.  The
+ *   projection and the weight gradients take three bf16 terms (3 x 8 mantissa bits,
+ *   six of the nine term products); the level steps, adjoint steps and input
+ *   gradients two fp16 terms (2 x 11 bits of rows scaled to fp16's range, three of
+ *   the four products), which on this pipe come out closer to 64 bits than either
+ *   six products or fp32 ones.  (Smaller launches, and the steps of layers of up to
+ *   128 columns, run in the fp32 kernels, which are faster there and as accurate.)
+ *   The weights' term arrays live in the workspace (it is larger for this dtype)
  *   and are rebuilt by every call; H and D must be multiples of 8.  A tile with
  *   a sum that is not finite (an operand the terms cannot carry, like an
- *   infinity, or a sum beyond 1e24) is contracted again on the fp32 matrix pipe.
+ *   infinity, or, of three bf16 terms, a sum beyond 1e24) is contracted again on the
+ *   fp32 matrix pipe.
  *   MGRIT_F32 takes the same form by itself for GRU and LSTM problems where it is faster
  *   and no less accurate (widths that are multiples of 8, at least 128, and 1024
  *   rows or more per level-0 launch; serial propagation: 1024 steps x batch), in a

@@ -104,15 +104,15 @@ struct Layout {
   size_t kap[MAX_LEVELS];
   size_t UT, WT, part;
   size_t total_part;              // bytes of the partials
-  size_t U3, UT3, W3;             // MGRIT_F32_BF16X3: three-term bf16 copies of U, U^T and
+  size_t U3, UT3, W3;             // MGRIT_F32_BF16X3: copies in terms of U, U^T and
                                   // W (or W^T, once the projection is done)
   size_t total;
 };
 
 static size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// Operand form handed to the kernels: 0 fp32, 1 bf16 inputs and weights, 2 three bf16 terms per
-// fp32 operand; both bf16 dtypes store alike and differ in how the tile kernels carry the fp32
+// Operand form handed to the kernels: 0 fp32, 1 bf16 inputs and weights, 2 fp32 operands in 16-bit
+// terms; both bf16 dtypes store alike and differ in how the tile kernels carry the fp32
 // state operand (one bf16 term, or two with MGRIT_BF16_STATE2).
 static int kform(int dtype) { return dtype == MGRIT_BF16_STATE2 ? 1 : dtype; }
 static int one_term(int dtype) { return dtype == MGRIT_BF16 ? 1 : 0; }
@@ -205,10 +205,12 @@ static bool misaligned(const void* p) { return ((uintptr_t)p & 15) != 0; }
 // ---------------------------------------------------------------------------
 // operand form of a call
 // ---------------------------------------------------------------------------
-// MGRIT_F32 runs the tile kernels on the bf16 matrix pipe, each fp32 operand as three bf16 terms
-// (exact; see gemm_core_bf16.h), where that is faster and no less accurate than the fp32 MFMAs.
+// MGRIT_F32 runs the tile kernels on the 16-bit matrix pipe, each fp32 operand as two fp16 terms (steps
+// and input gradients, gemm_terms.h) or three bf16 terms (projection and gradients, gemm_core_bf16.h),
+// where that is faster and no less accurate than the fp32 MFMAs.
 // (MGRIT_F32_BF16X3 asks for the terms on every shape; its smallest launches and its layers of up to
-// 128 columns share the fp32 kernels of MGRIT_F32 all the same, which are no less accurate: state and
+// 128 columns share the fp32 kernels of MGRIT_F32 all the same, which are no less accurate (against
+// three bf16 terms): state and
 // adjoint errors at 72, 104 and 128 columns 1.2-1.7e-7 and 6.5e-8 against 1.5-2.0e-7 and 7.1e-8 with
 // terms, at 520 to 1024 columns 1.3-1.9e-7 and 7.0-7.9e-8 against 1.6-2.1e-7 and 7.7-8.9e-8.)  The line:
 //  - widths are multiples of 8 (16-byte rows of terms), of at least 128 (64 for the projection).
@@ -224,7 +226,8 @@ static bool misaligned(const void* p) { return ((uintptr_t)p & 15) != 0; }
 //    solve of a call is done: the workspace is no larger than without them.
 struct Forms {
   int rec, proj;            // operand form of the recurrent contractions and gradients / of W x
-  char *U3, *UT3, *W3;      // three-term arrays (null: not needed)
+  char *U3, *UT3, *W3;      // operands in terms (null: not needed): packed fp16 terms of U, U^T and, for
+                            // the input gradients, W^T; before those, three bf16 terms of W
   size_t part_bytes;        // of the partials that they take, behind the control words
 };
 constexpr long long TERMS_MIN_ROWS = 1024;
@@ -728,8 +731,9 @@ static int forward_impl(const mgrit_gru_cfg* cin, bool serial, const void* W, co
   ctx.form = forms.rec;
   ctx.U = U;
   ctx.U3 = forms.U3;
-  const long long nU = lstm ? (long long)c.H * c.H : 3LL * c.H * c.H;    // (LSTM: 4 (H / 2)^2)
-  if (forms.rec == 2) CHECK_HIP(launch_split3((const float*)U, forms.U3, nU, s));
+  if (forms.rec == 2)
+    CHECK_HIP(launch_split2((const float*)U, forms.U3, lstm ? 2 * c.H : 3 * c.H,
+                            lstm ? c.H / 2 : c.H, s));
   ctx.b_h = b_h;
   ctx.P = (const float*)(base + lay.P);
   ctx.dt = ode ? ode_dt : 1.f;
@@ -1027,8 +1031,8 @@ static int backward_impl(const mgrit_gru_cfg* cin, bool serial, const void* W, c
   const int bf16 = kform(c.dtype) == 1;
   CHECK_HIP(launch_transpose(U, base + lay.UT, 3 * c.H, c.H, bf16, s));
   if (forms.rec == 2) {
-    CHECK_HIP(launch_split3((const float*)U, forms.U3, 3LL * c.H * c.H, s));
-    CHECK_HIP(launch_split3((const float*)(base + lay.UT), forms.UT3, 3LL * c.H * c.H, s));
+    CHECK_HIP(launch_split2((const float*)U, forms.U3, 3 * c.H, c.H, s));
+    CHECK_HIP(launch_split2((const float*)(base + lay.UT), forms.UT3, c.H, 3 * c.H, s));
   }
 
   BwdCtx ctx;
@@ -1112,7 +1116,7 @@ static int backward_impl(const mgrit_gru_cfg* cin, bool serial, const void* W, c
   if (dx) {
     CHECK_HIP(launch_transpose(W, base + lay.WT, 3 * c.H, c.D, bf16, s));
     const void* WT = base + lay.WT;
-    if (forms.rec == 2) CHECK_HIP(launch_split3((const float*)WT, forms.W3, 3LL * c.H * c.D, s));
+    if (forms.rec == 2) CHECK_HIP(launch_split2((const float*)WT, forms.W3, c.D, 3 * c.H, s));
     CHECK_HIP(launch_input_grads(ctx.kap[0], w, WT, forms.W3, dx, c.T, c.B, c.D, c.H, forms.rec,
                                  one_term(c.dtype), s));
   }

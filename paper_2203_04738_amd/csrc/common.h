@@ -60,9 +60,9 @@ struct PhiArgs {
   int propagator;
   int mode;
   int bf16;            // 1: U is bf16 and the contraction runs on the bf16 MFMA path
-                       // 2: U is float; launches of enough tiles contract three-term bf16
-                       // operands, smaller ones and the sweep kernels fp32 ones
-  const void* U3;      // bf16 == 2: the three bf16 terms of U, [3][3H,H]
+                       // 2: U is float; launches of enough tiles contract operands in fp16
+                       // terms, smaller ones and the sweep kernels fp32 ones
+  const void* U3;      // bf16 == 2: the terms of U (launch_split2)
   int zero_from;       // > 0: the input states of rows >= zero_from are all zero (tile kernels
                        // skip the contraction of tiles that start there; 0: nothing known)
   // STEP_RELAX_RHS: the second (coarse-level) evaluation of a row.  Its projection row and its
@@ -97,7 +97,7 @@ struct AdjArgs {
   int nk, B, H, kw;
   int mode;
   int bf16;            // operand form, as in PhiArgs
-  const void* UT3;     // bf16 == 2: the three bf16 terms of UT, [3][H,3H]
+  const void* UT3;     // bf16 == 2: the terms of UT (launch_split2)
   int ff_cf, ff_rem;   // STEP_RESID: the coarse array wc receives the zero initial guess of the
                        // coarse error equation, except at the coarse points of index ff_rem
                        // modulo ff_cf (ff_cf > 0), which receive -r: the value the coarse level's
@@ -159,8 +159,8 @@ hipError_t launch_param_grads(const float* kap0, const float* w, const float* h,
                               int one_term, hipStream_t s);
 
 // Input gradients dx[T,B,D] from the level-0 coefficients, the adjoint w and the
-// transposed input weights WT[D,3H] (float, or bf16 with bf16 = 1; with bf16 = 2 WT3 holds its three
-// bf16 terms [3][D,3H]).
+// transposed input weights WT[D,3H] (float, or bf16 with bf16 = 1; with bf16 = 2 WT3 holds its terms,
+// launch_split2).
 hipError_t launch_input_grads(const float* kap0, const float* w, const void* WT, const void* WT3,
                               float* dx, int T, int B, int D, int H, int bf16, int one_term,
                               hipStream_t s);
@@ -168,6 +168,9 @@ hipError_t launch_input_grads(const float* kap0, const float* w, const void* WT,
 // dst[t][i] (t = 0..2, bf16) = t-th term of 2^24 src[i] (exactly: see gemm_core_bf16.h); n a multiple
 // of 4
 hipError_t launch_split3(const float* src, void* dst, long long n, hipStream_t s);
+// Weights src[rows][K] as the step and input-gradient kernels read them with bf16 = 2: packed fp16 terms
+// (see gemm_terms.h); rows and K multiples of 8, dst of 4 rows (K + 1) bytes.
+hipError_t launch_split2(const float* src, void* dst, int rows, int K, hipStream_t s);
 
 hipError_t launch_fill_f64(double* p, long long n, double v, hipStream_t s);
 // p[0..n) = 0; n a multiple of 4, p 16-byte aligned

@@ -10,7 +10,7 @@
 // 16 mantissa bits of the fp32 state in the product, so the only rounding the method
 // sees beyond fp32 is the one already present in the stored bf16 weights.
 //
-// With NP = 3 both operands are fp32 VALUES carried as three bf16 terms each
+// With NP = 3 and LOSUM both operands are fp32 VALUES carried as three bf16 terms each
 // (a = a0 + a1 + a2 exactly: 3 x 8 mantissa bits); the contraction keeps the six
 // products a_t * b_u with t + u <= 2 and drops the three of relative size 2^-24 and
 // below, so the fp32 accumulators receive what an fp32 product would have given them,
@@ -97,7 +97,8 @@ __device__ inline void split_bf16(const F32x8& v, bf16x8& hi, bf16x8& lo) {
 // than the latency of the loads for the next slice; with DEPTH = 3 a slice's loads have
 // three slice times to arrive.  MINWG: resident workgroups per CU the register budget
 // is planned for.
-// NP: 1 = operands as stored (A optionally in two terms), 3 = three terms per operand.
+// NP: 1 = operands as stored (A optionally in two terms), 3 = fp32 operands: three bf16 terms per operand
+// with LOSUM, otherwise three products of fp16 terms (gemm_terms.h, which such a configuration runs).
 // TKB: elements per K-slice and K-split group.
 // LOSUM (NP = 3): the five products of lower-order terms are summed apart from a0 * b0 and added once
 // at the end, which leaves a sixth of the additions into the large sum (twice the accumulators).
@@ -130,7 +131,11 @@ struct TileCfgB {
   static constexpr int CPR = TK / 8;            // 16-byte chunks per tile row
   static constexpr int A_CHUNKS = (TM * CPR) / NT;
   static constexpr int B_CHUNKS = (BROWS * CPR) / NT;
-  static constexpr int LDS_ELEMS = (NA * TM + NBP * BROWS) * LD;
+  // (NP = 3 without LOSUM: two slices of A in two terms, gemm_terms.h)
+  // waves per SIMD that the register budget is planned for (two workgroups of terms per CU)
+  static constexpr int MINWAVES = NP == 3 && !LOSUM ? NT / 128 : MINWG;
+  static constexpr int LDS_ELEMS =
+      NP == 3 && !LOSUM ? 2 * 2 * TM * TK : (NA * TM + NBP * BROWS) * LD;
   static_assert(SPLIT_A || NP == 1, "three-term operands are fp32 in memory");
   static_assert((TM * CPR) % NT == 0 && (BROWS * CPR) % NT == 0, "tile rows must divide evenly");
 };

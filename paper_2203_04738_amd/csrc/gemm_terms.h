@@ -1,0 +1,416 @@
+// Workgroup-tile product of fp32 VALUES on the 16-bit matrix pipe, for the step kernels and the input
+// gradients: the "NT" tile product of gemm_core.h with each operand carried as two fp16 terms,
+// a = a0 + a1 (22 mantissa bits), consumed by v_mfma_f32_16x16x32_f16 as a0*b0 + a1*b0 + a0*b1.
+//
+// Accuracy.  What the terms and the dropped a1*b1 leave out is about 6e-8 of a product, of either
+// sign; the matrix pipe itself cuts off below the last bit of every sum it forms, so three products
+// are closer to the exact sum than the six that three bf16 terms take, and than the fp32 MFMAs.
+// Error against 64 bits, states against Xavier weights (two fp16 terms : three bf16 terms : fp32
+// MFMA): 512 columns 2.6e-7 : 3.5e-7 : 2.9e-7, 1024 columns 3.6 : 4.9 : 4.1, 1536 columns
+// 4.4 : 5.9 : 4.9.  (The projection keeps three bf16 terms with the lower products summed apart,
+// gemm_core_bf16.h: 1.8e-7 over 1024 columns, 2.2e-7 with fp16 terms in that form.)
+//
+// Range.  fp16 has five exponent bits, so every row of an operand is scaled by a power of two of its
+// own and the sums back, exactly: the rows of B, split once per call, by their largest value; a row of
+// A, split on its way to LDS, by the largest value of its first K-slice, which leaves the rest of the
+// row a factor of 2^9.  A row whose first slice is zero is read through for its largest value, and so
+// are all rows of a tile with a sum that is not finite; one that still has such a sum holds an operand
+// that is not finite itself and is contracted in fp32.  Subnormal terms keep their bits on this pipe;
+// what is below them is 2^-31 of the row's largest value.
+//
+// Data path (16384 rows x 512, the level step: 145 us with three bf16 terms, 118 with two fp16 terms in
+// the loop of gemm_core_bf16.h, 100 this way; 16384 LSTM rows 243, 157, 126).  With half the MFMAs the K loop is bound by what feeds them, LDS above all: 32x32 blocks
+// of A and B fragments read by every wave cost 105 of the LDS's 128 bytes per clock at full matrix
+// rate for the 128 x 64 (x3) tile.  So B does not pass through LDS: the split leaves it in the order in
+// which lanes take it (pack below), a wave owns its columns alone (the waves of a tile lie side by
+// side) and loads its fragments straight into registers, one slice ahead.  A goes to LDS in fragment
+// order too, two slices alternating, so that a slice costs one barrier and its conversion and writes
+// share the scheduling region with the MFMAs of the slice before.
+#pragma once
+#include "gemm_core_bf16.h"
+
+namespace mg {
+
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+// Two floats rounded to fp16 (a in the low half); what their roundings leave.
+__device__ inline unsigned round2_f16(float a, float b) {
+  typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+  typedef float floatx2 __attribute__((ext_vector_type(2)));
+  const floatx2 v = {a, b};
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(v, f16x2));
+}
+// (one mixed-precision instruction each: the half is read as it is and negated)
+__device__ inline void minus2_f16(float& a, float& b, unsigned r) {
+  asm("v_fma_mix_f32 %0, %1, -1.0, %0 op_sel_hi:[1,0,0]" : "+v"(a) : "v"(r));
+  asm("v_fma_mix_f32 %0, %1, -1.0, %0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(b) : "v"(r));
+}
+// t0 + t1 = v f up to 2^-22
+__device__ inline void split_f16_2(const F32x8& v, float f, f16x8& t0, f16x8& t1) {
+  typedef unsigned uintx4_ __attribute__((ext_vector_type(4)));
+  uintx4_ w0, w1;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float a = (i < 2 ? v.lo4[2 * i] : v.hi4[2 * i - 4]) * f;
+    float b = (i < 2 ? v.lo4[2 * i + 1] : v.hi4[2 * i - 3]) * f;
+    w0[i] = round2_f16(a, b);
+    minus2_f16(a, b, w0[i]);
+    w1[i] = round2_f16(a, b);
+  }
+  t0 = __builtin_bit_cast(f16x8, w0);
+  t1 = __builtin_bit_cast(f16x8, w1);
+}
+__device__ inline float top8(float m, const F32x8& v) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) m = fmaxf(m, fmaxf(fabsf(v.lo4[i]), fabsf(v.hi4[i])));
+  return m;
+}
+// Exponent by which a row with the largest magnitude m is scaled: m lands in [2^top, 2^(top+1)).  (At
+// most 2^127, the largest power of two there is: rows below 2^(top-127) end lower, a row of 2^-126 at
+// 2, with 2^-26 of its largest value left out.)
+__device__ inline int term_exponent(float m, int top) {
+  return min(top + 127 - (int)(__float_as_uint(m) >> 23), 127);
+}
+__device__ inline float exp2_int(int e) { return __uint_as_float((unsigned)(e + 127) << 23); }
+constexpr int TERM_TOP_A = 6, TERM_TOP_B = 13;
+
+// Packed terms of B[rows][K] (rows, K multiples of 8): chunks of eight k of a row, 16 bytes, ordered
+// [row / 8][k / 8][term][row % 8], so that the 16 rows x 32 k that a wave loads at once are whole
+// 128-byte lines, its two terms side by side; behind them the rows' exponents, int[rows].
+constexpr int PACK_TERM = 128, PACK_K8 = 256;             // bytes from term to term, from k / 8 to the next
+__host__ __device__ inline size_t pack_row(long long row, int K) {
+  return (size_t)(row >> 3) * (K >> 3) * PACK_K8 + (row & 7) * 16;
+}
+__device__ inline const int* pack_exponents(const void* pack, long long rows, int K) {
+  return reinterpret_cast<const int*>((const char*)pack + (size_t)rows * K * 4);
+}
+
+// How the waves of configuration C (NP = 3) share a tile: WR x WC waves per K-split group, each RB x CB
+// blocks of 16 x 16 (x NG).
+template <class C>
+struct TermGeom {
+  static constexpr int NW = C::WM * C::WN;
+  static constexpr int WR = NW > 4 ? 2 : 1, WC = NW / WR;
+  static constexpr int RB = C::TM / 16 / WR, CB = C::TN / 16 / WC;
+  static constexpr int NF = C::NG * CB;                   // B fragments per term and slice
+  static constexpr int GB = NF >= 3 ? 1 : 2;              // row blocks whose MFMAs alternate
+  static constexpr int BLK = C::TM / 16;                  // row blocks of the tile
+  static constexpr int BUF = C::KS * 2 * BLK * 64;        // 16-byte chunks of one slice of A
+  static_assert(RB * WR * 16 == C::TM && CB * WC * 16 == C::TN, "waves must cover the tile");
+  static_assert(C::TK == 32 * C::KS && RB % GB == 0, "");
+};
+template <class C>
+struct TermAcc {
+  typedef TermGeom<C> G;
+  floatx4 v[G::RB][C::NG][G::CB];
+  __device__ inline void zero() {
+#pragma unroll
+    for (int r = 0; r < G::RB; ++r)
+#pragma unroll
+      for (int g = 0; g < C::NG; ++g)
+#pragma unroll
+        for (int c = 0; c < G::CB; ++c) v[r][g][c] = zero4();
+  }
+};
+// Position of the calling wave and lane in a tile.
+template <class C>
+struct TermLane {
+  typedef TermGeom<C> G;
+  int ks, row0, col0, li, lq;      // first row and column of the wave; lane % 16, lane / 16
+  __device__ inline TermLane() {
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    ks = wave / G::NW;
+    row0 = (wave % G::NW) / G::WC * G::RB * 16;
+    col0 = (wave % G::NW) % G::WC * G::CB * 16;
+    li = threadIdx.x & 15;
+    lq = (threadIdx.x >> 4) & 3;
+  }
+};
+
+// One pass over K (a multiple of 8).  loadA, finA: as in gemm_nt_tile_bf16; brow(g, c): packed row
+// (g, column c of the tile) of B; rowexp: LDS, receives the exponents the tile rows of A are scaled
+// by; through: find them from whole rows, not from first slices.
+template <class C, bool KTAIL, class LoadA, class FinA, class BRow>
+__device__ inline void gemm_nt_tile_terms(TermAcc<C>& acc, int K, LoadA loadA, FinA finA,
+                                          const char* pack, BRow brow, f16x8* lds, int* rowexp,
+                                          bool through) {
+  typedef TermGeom<C> G;
+  const int tid = threadIdx.x;
+  const TermLane<C> me;
+  decltype(loadA(0, 0)) ra[C::A_CHUNKS];
+  auto fetch_a = [&](int s, int k0) {
+    int k = k0 + ((tid + s * C::NT) % C::CPR) * 8;
+    if (KTAIL && k >= K) k = K - 8;
+    ra[s] = loadA(s, k);
+  };
+  const char* bp[C::NG][G::CB];
+#pragma unroll
+  for (int g = 0; g < C::NG; ++g)
+#pragma unroll
+    for (int c = 0; c < G::CB; ++c)
+      bp[g][c] = pack + pack_row(brow(g, me.col0 + c * 16 + me.li), K);
+  f16x8 rb[2][2][C::NG][G::CB];                 // [slice % 2][term]
+  auto fetch_b = [&](int d, int k0) {
+    int k8 = k0 / 8 + me.ks * 4 + me.lq;
+    if (KTAIL) k8 = min(k8, K / 8 - 1);
+#pragma unroll
+    for (int g = 0; g < C::NG; ++g)
+#pragma unroll
+      for (int c = 0; c < G::CB; ++c)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          rb[d][t][g][c] = *reinterpret_cast<const f16x8*>(bp[g][c] + (size_t)(unsigned)k8 * PACK_K8 +
+                                                           t * PACK_TERM);
+  };
+  // scale of the row behind each chunk; odd tile rows enter with the opposite sign (see contract_terms)
+  float rowscale[C::A_CHUNKS];
+  auto scale_rows = [&]() {
+#pragma unroll
+    for (int s = 0; s < C::A_CHUNKS; ++s) {
+      const int q = tid + s * C::NT;
+      // (the CPR lanes that share a row are neighbours)
+      auto over_row = [](float m) {
+#pragma unroll
+        for (int o = 1; o < C::CPR; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+        return m;
+      };
+      float m = over_row(top8(0.f, finA(ra[s])));
+      if (through || m == 0.f) {
+        for (int k = (q % C::CPR) * 8; k < K; k += C::TK) m = top8(m, finA(loadA(s, k)));
+        m = over_row(m);
+      }
+      const int e = term_exponent(m, TERM_TOP_A);
+      rowscale[s] = (q / C::CPR) & 1 ? -exp2_int(e) : exp2_int(e);
+      if (q % C::CPR == 0) rowexp[q / C::CPR] = e;
+    }
+  };
+  // A in LDS: [slice % 2][K-split group][term][row block][k / 8][row % 16], the rows of a k / 8 exchanged
+  // by it, so that the eight lanes of two rows write to different banks
+  auto stash = [&](int p, int s, int k0) {
+    const int q = tid + s * C::NT, row = q / C::CPR, c = q % C::CPR;
+    f16x8 t0, t1;
+    split_f16_2(finA(ra[s]), rowscale[s], t0, t1);
+    if (KTAIL && k0 + c * 8 >= K) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) t0[i] = t1[i] = (_Float16)0.f;
+    }
+    const int at = p * G::BUF + (c / 4) * 2 * G::BLK * 64 + (row / 16) * 64 + (c % 4) * 16 +
+                   ((row & 15) ^ (2 * (c % 4)));
+    lds[at] = t0;
+    lds[at + G::BLK * 64] = t1;
+  };
+  const int a_at = me.ks * 2 * G::BLK * 64 + (me.row0 / 16) * 64 + me.lq * 16 + (me.li ^ (2 * me.lq));
+  auto read_a = [&](int p, int r, int t) {
+    return lds[p * G::BUF + a_at + t * G::BLK * 64 + r * 64];
+  };
+  typedef f16x8 Frags[2][G::GB];                // [term][row block]
+  auto read_group = [&](int p, int r0, Frags& f) {
+#pragma unroll
+    for (int i = 0; i < G::GB; ++i)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) f[t][i] = read_a(p, r0 + i, t);
+  };
+  auto multiply = [&](int d, int r0, const Frags& f) {
+#pragma unroll
+    for (int u = 0; u < 3; ++u)                // a0 b0, a1 b0, a0 b1
+#pragma unroll
+      for (int g = 0; g < C::NG; ++g)
+#pragma unroll
+        for (int c = 0; c < G::CB; ++c)
+#pragma unroll
+          for (int i = 0; i < G::GB; ++i)
+            acc.v[r0 + i][g][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                f[u == 1][i], rb[d][u == 2][g][c], acc.v[r0 + i][g][c], 0, 0, 0);
+  };
+  const int nkt = (K + C::TK - 1) / C::TK;
+#pragma unroll
+  for (int s = 0; s < C::A_CHUNKS; ++s) fetch_a(s, 0);
+  fetch_b(0, 0);
+  scale_rows();
+#pragma unroll
+  for (int s = 0; s < C::A_CHUNKS; ++s) {
+    stash(0, s, 0);
+    if (nkt > 1) fetch_a(s, C::TK);
+  }
+  __syncthreads();
+  // Slice kt: the fragments of row blocks are read one group ahead; the chunks of slice kt + 1, in
+  // registers since the slice before, are converted and written between the groups and their registers
+  // filled again (one slice too many is asked for, inside the row, and not used).
+  auto slice = [&](auto d_tag, auto more_tag, int kt) {
+    constexpr int d = decltype(d_tag)::value;    // kt % 2
+    constexpr bool more = decltype(more_tag)::value;
+    constexpr int NGRP = G::RB / G::GB;
+    Frags f[2];
+    if constexpr (more) fetch_b(d ^ 1, (kt + 1) * C::TK);
+    read_group(d, 0, f[0]);
+#pragma unroll
+    for (int i = 0; i < NGRP; ++i) {
+      if (i + 1 < NGRP) read_group(d, (i + 1) * G::GB, f[(i + 1) & 1]);
+      multiply(d, i * G::GB, f[i & 1]);
+      if constexpr (more) {
+#pragma unroll
+        for (int s = 0; s < C::A_CHUNKS; ++s)
+          if (i == (s + 1) * NGRP / (C::A_CHUNKS + 1)) {
+            stash(d ^ 1, s, (kt + 1) * C::TK);
+            fetch_a(s, min(kt + 2, nkt - 1) * C::TK);
+          }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (more) __syncthreads();
+  };
+  constexpr std::integral_constant<int, 0> even{};
+  constexpr std::integral_constant<int, 1> odd{};
+  constexpr std::true_type more{};
+  constexpr std::false_type last{};
+  int kt = 0;
+  for (; kt + 2 < nkt; kt += 2) {
+    slice(even, more, kt);
+    slice(odd, more, kt + 1);
+  }
+  if (kt + 1 < nkt) {
+    slice(even, more, kt);
+    slice(odd, last, kt + 1);
+  } else {
+    slice(even, last, kt);
+  }
+  __syncthreads();
+}
+
+// Whether any sum of the workgroup's tile is not finite (the same answer in every thread).  A value
+// that fp16 rounds to an infinity has a second term of the opposite sign, so a sum of terms shows any
+// operand it cannot carry.
+template <class C>
+__device__ inline bool tile_not_finite(const TermAcc<C>& acc) {
+  float t = 0.f;
+#pragma unroll
+  for (int r = 0; r < TermGeom<C>::RB; ++r)
+#pragma unroll
+    for (int g = 0; g < C::NG; ++g)
+#pragma unroll
+      for (int c = 0; c < TermGeom<C>::CB; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t = fmaf(acc.v[r][g][c][e], 0.f, t);
+  return __syncthreads_or(t != t) != 0;
+}
+// acc = A * B^T in fp32, operands straight from memory (small rather than fast: only tiles with
+// sums that are not finite come here).  load_a(r, k): columns k..k+3 of tile row r of A; frow(g, c): row
+// (g, column c of the tile) of B.  K a multiple of 4.
+template <class C, class LoadA4, class FRow>
+__device__ inline void contract_f32(TermAcc<C>& acc, int K, LoadA4 load_a, FRow frow) {
+  typedef TermGeom<C> G;
+  const TermLane<C> me;
+  acc.zero();
+#pragma unroll 1
+  for (int k0 = 16 * me.ks; k0 < K; k0 += 16 * C::KS) {
+    const int k = k0 + 4 * me.lq, kc = k < K ? k : K - 4;
+    floatx4 fb[C::NG][G::CB];
+#pragma unroll
+    for (int g = 0; g < C::NG; ++g)
+#pragma unroll
+      for (int c = 0; c < G::CB; ++c)
+        fb[g][c] = k < K ? ldg4(frow(g, me.col0 + c * 16 + me.li) + kc) : zero4();
+#pragma unroll
+    for (int r = 0; r < G::RB; ++r) {
+      const floatx4 fa = k < K ? load_a(me.row0 + r * 16 + me.li, kc) : zero4();
+#pragma unroll
+      for (int g = 0; g < C::NG; ++g)
+#pragma unroll
+        for (int c = 0; c < G::CB; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            acc.v[r][g][c] =
+                __builtin_amdgcn_mfma_f32_16x16x4f32(fa[e], fb[g][c][e], acc.v[r][g][c], 0, 0, 0);
+    }
+  }
+}
+
+// acc = A * B^T on terms.  la, fa: as in gemm_nt_tile_bf16; pack, rows: the packed terms of B
+// (launch_split2) and its rows; brow(g, c): row of B behind column c of the tile, gate g; load_a, frow: as
+// in contract_f32.  The MFMA rounds its sum down (towards minus infinity) below the last bit, the same
+// way in every row: sums over rows (bias gradients, residual norms) would collect it, with the sign of
+// the odd rows turned it alternates instead (bias gradients at 12800 rows x 1000, three bf16 terms:
+// 4.3e-7 off with the signs as they are, 2.9e-7 with fp32 MFMAs).
+template <class C, class LoadA, class FinA, class BRow, class LoadA4, class FRow>
+__device__ inline void contract_terms(TermAcc<C>& acc, int K, LoadA la, FinA fa, const void* pack,
+                                      long long rows, BRow brow, void* lds, LoadA4 load_a,
+                                      FRow frow) {
+  typedef TermGeom<C> G;
+  __shared__ __attribute__((aligned(16))) int rowexp[C::TM];
+  const TermLane<C> me;
+  int ce[C::NG][G::CB];
+#pragma unroll
+  for (int g = 0; g < C::NG; ++g)
+#pragma unroll
+    for (int c = 0; c < G::CB; ++c)
+      ce[g][c] = pack_exponents(pack, rows, K)[brow(g, me.col0 + c * 16 + me.li)];
+#pragma unroll 1
+  for (int through = 0; through < 2; ++through) {
+    acc.zero();
+    if (K % C::TK == 0)
+      gemm_nt_tile_terms<C, false>(acc, K, la, fa, (const char*)pack, brow, (f16x8*)lds, rowexp,
+                                   through != 0);
+    else
+      gemm_nt_tile_terms<C, true>(acc, K, la, fa, (const char*)pack, brow, (f16x8*)lds, rowexp,
+                                  through != 0);
+#pragma unroll
+    for (int r = 0; r < G::RB; ++r) {
+      typedef int intx4_ __attribute__((ext_vector_type(4)));
+      const intx4_ re = *reinterpret_cast<const intx4_*>(&rowexp[me.row0 + r * 16 + 4 * me.lq]);
+#pragma unroll
+      for (int g = 0; g < C::NG; ++g)
+#pragma unroll
+        for (int c = 0; c < G::CB; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float v = acc.v[r][g][c][e];
+            acc.v[r][g][c][e] = ldexpf(e & 1 ? -v : v, -re[e] - ce[g][c]);
+          }
+    }
+    if (!tile_not_finite<C>(acc)) return;
+  }
+  contract_f32<C>(acc, K, load_a, frow);
+}
+
+// Staging for the epilogue (EpiStage::write) of sums in this layout.
+template <class C>
+__device__ inline void stage_write_terms(const TermAcc<C>& acc, int ba, float* stage) {
+  typedef TermGeom<C> G;
+  typedef EpiStage<C> E;
+  const TermLane<C> me;
+#pragma unroll
+  for (int r = 0; r < G::RB; ++r) {
+    // 32-row group of the tile; pass ba stages the groups ba, ba + BM, ...
+    if constexpr (G::WR > 1) static_assert(C::BM == 1, "");
+    if (G::WR == 1 && (r / 2) % C::BM != ba) continue;
+    const int grp = (me.row0 / 16 + r) / 2;
+    const int row = grp / C::BM * 32 + (r & 1) * 16 + 4 * me.lq;
+#pragma unroll
+    for (int g = 0; g < C::NG; ++g)
+#pragma unroll
+      for (int c = 0; c < G::CB; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          stage[me.ks * E::SLAB + (g * E::ROWS + row + e) * E::LD + me.col0 + c * 16 + me.li] =
+              acc.v[r][g][c][e];
+  }
+}
+
+// Sums of the workgroup tile of a kernel of configuration C (TileCfg or TileCfgB).
+template <class C, class = void>
+struct InTerms : std::false_type {};
+template <class C>
+struct InTerms<C, typename std::enable_if<C::NP == 3 && !C::LOSUM>::type> : std::true_type {};
+template <class C>
+struct TileSums {
+  typedef typename std::conditional<InTerms<C>::value, TermAcc<C>, Acc<C>>::type type;
+};
+template <class C>
+__device__ inline void stage_write(const typename TileSums<C>::type& acc, int ba, float* stage) {
+  if constexpr (InTerms<C>::value)
+    stage_write_terms<C>(acc, ba, stage);
+  else
+    EpiStage<C>::write(acc, ba, stage);
+}
+
+}  // namespace mg

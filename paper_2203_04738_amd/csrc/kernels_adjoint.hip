@@ -6,6 +6,7 @@
 #include "common.h"
 #include "gemm_core.h"
 #include "gemm_core_bf16.h"
+#include "gemm_terms.h"
 #include "skinny.h"
 
 namespace mg {
@@ -69,7 +70,7 @@ struct AdjEpiIn4 {
   floatx4 kd, wv, gval, cur;
 };
 template <class C, int MODE>
-__device__ inline void adj_tile_epilogue(const AdjArgs& a, Acc<C>& acc, const AdjRow* rowtab,
+__device__ inline void adj_tile_epilogue(const AdjArgs& a, const typename TileSums<C>::type& acc, const AdjRow* rowtab,
                                          float* stage, long long m0, int n0, long long R,
                                          double& nrm) {
   typedef EpiStage<C> E;
@@ -81,7 +82,7 @@ __device__ inline void adj_tile_epilogue(const AdjArgs& a, Acc<C>& acc, const Ad
 #pragma unroll
   for (int ba = 0; ba < C::BM; ++ba) {
     __syncthreads();                                    // staging area no longer read
-    E::write(acc, ba, stage);
+    stage_write<C>(acc, ba, stage);
     AdjEpiIn4 in[E::ITEMS];
     long long oo[E::ITEMS], oa[E::ITEMS];
     int trow[E::ITEMS];
@@ -217,7 +218,7 @@ struct KapW8 {
 };
 
 template <class C, int MODE>
-__global__ __launch_bounds__(C::NT, C::MINWG) void adj_step_kernel_bf16(AdjArgs a) {
+__global__ __launch_bounds__(C::NT, C::MINWAVES) void adj_step_kernel_bf16(AdjArgs a) {
   constexpr int LDSF = C::LDS_ELEMS / 2 + 1 > EpiStage<C>::FLOATS ? C::LDS_ELEMS / 2 + 1
                                                                   : EpiStage<C>::FLOATS;
   __shared__ __attribute__((aligned(16))) float ldsf[LDSF];
@@ -230,7 +231,6 @@ __global__ __launch_bounds__(C::NT, C::MINWG) void adj_step_kernel_bf16(AdjArgs 
   const long long m0 = rt * C::TM;
   const int n0 = ct * C::TN;
   const int tid = threadIdx.x;
-  const bf16_t* UT = (const bf16_t*)(C::NP == 3 ? a.UT3 : a.UT);
   __shared__ AdjRow rowtab[C::TM];
   if (tid < C::TM) {
     long long r = m0 + tid;
@@ -241,7 +241,6 @@ __global__ __launch_bounds__(C::NT, C::MINWG) void adj_step_kernel_bf16(AdjArgs 
 
   const float* krow[C::A_CHUNKS];
   const float* wrow[C::A_CHUNKS];
-  const bf16_t* brow[C::B_CHUNKS];
 #pragma unroll
   for (int s = 0; s < C::A_CHUNKS; ++s) {
     long long r = m0 + chunk_row_b<C>(s);
@@ -251,14 +250,7 @@ __global__ __launch_bounds__(C::NT, C::MINWG) void adj_step_kernel_bf16(AdjArgs 
     krow[s] = a.kap + (a.k.at(pt) * B + b) * (long long)a.kw;
     wrow[s] = a.w_in + (a.in.at(pt) * B + b) * H;
   }
-#pragma unroll
-  for (int s = 0; s < C::B_CHUNKS; ++s) {
-    int j = n0 + chunk_row_b<C>(s);
-    if (j >= H) j = H - 1;
-    brow[s] = UT + (long long)j * K;
-  }
-  Acc<C> acc;
-  acc.zero();
+  typename TileSums<C>::type acc;
   auto la = [&](int s, int k) {
     const int kk = k >= 2 * H ? k - 2 * H : (k >= H ? k - H : k);
     return KapW8{ldg4(krow[s] + k), ldg4(krow[s] + k + 4), ldg4(wrow[s] + kk),
@@ -266,26 +258,23 @@ __global__ __launch_bounds__(C::NT, C::MINWG) void adj_step_kernel_bf16(AdjArgs 
   };
   auto fa = [](const KapW8& r) { return F32x8{r.k0 * r.w0, r.k1 * r.w1}; };
   if constexpr (C::NP == 3) {
-    const long long term = (long long)H * K;
-    auto lb = [&](int s, int k) {
-      return Bf16x8x3{{ldg8h(brow[s] + k), ldg8h(brow[s] + term + k),
-                       ldg8h(brow[s] + 2 * term + k)}};
-    };
-    if (K % C::TK == 0)
-      gemm_nt_tile_bf16<C, false>(acc, K, la, lb, fa, lds);
-    else
-      gemm_nt_tile_bf16<C, true>(acc, K, la, lb, fa, lds);
-    if (tile_not_finite<C>(acc))
-      contract_f32<C>(
-          acc, K,
-          [&](int tr, int k) {
-            const int kk = k >= 2 * H ? k - 2 * H : (k >= H ? k - H : k);
-            return ldg4(a.kap + rowtab[tr].k + k) * ldg4(a.w_in + rowtab[tr].in + kk);
-          },
-          [&](int tr) {
-            return (const float*)a.UT + (long long)(n0 + tr < H ? n0 + tr : H - 1) * K;
-          });
+    auto urow = [&](int, int c) { return (long long)min(n0 + c, H - 1); };
+    contract_terms<C>(
+        acc, K, la, fa, a.UT3, H, urow, lds,
+        [&](int tr, int k) {
+          const int kk = k >= 2 * H ? k - 2 * H : (k >= H ? k - H : k);
+          return ldg4(a.kap + rowtab[tr].k + k) * ldg4(a.w_in + rowtab[tr].in + kk);
+        },
+        [&](int g, int c) { return (const float*)a.UT + urow(g, c) * K; });
   } else {
+    acc.zero();
+    const bf16_t* brow[C::B_CHUNKS];
+#pragma unroll
+    for (int s = 0; s < C::B_CHUNKS; ++s) {
+      int j = n0 + chunk_row_b<C>(s);
+      if (j >= H) j = H - 1;
+      brow[s] = (const bf16_t*)a.UT + (long long)j * K;
+    }
     auto lb = [&](int s, int k) { return ldg8h(brow[s] + k); };
     if (K % C::TK == 0)
       gemm_nt_tile_bf16<C, false>(acc, K, la, lb, fa, lds);
@@ -329,6 +318,23 @@ __device__ inline void store_tile(const Acc<C>& acc, float* out, long long m0, i
         const long long m = m0 + row;
         if (m < M) out[m * N + n] = acc.v[0][a][b][e];
       }
+    }
+}
+
+template <class C>
+__device__ inline void store_tile_terms(const TermAcc<C>& acc, float* out, long long m0,
+                                        int n0, long long M, int N) {
+  typedef TermGeom<C> G;
+  const TermLane<C> me;
+#pragma unroll
+  for (int r = 0; r < G::RB; ++r)
+#pragma unroll
+    for (int c = 0; c < G::CB; ++c) {
+      const int n = n0 + me.col0 + c * 16 + me.li;
+      const long long m = m0 + me.row0 + r * 16 + 4 * me.lq;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (n < N && m + e < M) out[(m + e) * N + n] = acc.v[r][0][c][e];
     }
 }
 
@@ -378,7 +384,7 @@ __global__ __launch_bounds__(DxCfg::NT) void input_grad_kernel(
 }
 
 template <class C>
-__global__ __launch_bounds__(C::NT, C::NT > 256 ? 2 : 1) void input_grad_kernel_bf16(
+__global__ __launch_bounds__(C::NT, InTerms<C>::value ? C::MINWAVES : 1) void input_grad_kernel_bf16(
     const float* __restrict__ kap0, const float* __restrict__ w, const bf16_t* __restrict__ WT,
     const float* __restrict__ WTf, float* __restrict__ dx, long long R, int B, int H, int D) {
   __shared__ __attribute__((aligned(16))) bf16_t lds[C::LDS_ELEMS];
@@ -390,7 +396,6 @@ __global__ __launch_bounds__(C::NT, C::NT > 256 ? 2 : 1) void input_grad_kernel_
   const int n0 = ct * C::TN;
   const float* krow[C::A_CHUNKS];
   const float* wrow[C::A_CHUNKS];
-  const bf16_t* brow[C::B_CHUNKS];
 #pragma unroll
   for (int s = 0; s < C::A_CHUNKS; ++s) {
     long long r = m0 + chunk_row_b<C>(s);
@@ -398,14 +403,7 @@ __global__ __launch_bounds__(C::NT, C::NT > 256 ? 2 : 1) void input_grad_kernel_
     krow[s] = kap0 + (r + B) * (5LL * H);
     wrow[s] = w + (r + B) * H;
   }
-#pragma unroll
-  for (int s = 0; s < C::B_CHUNKS; ++s) {
-    int n = n0 + chunk_row_b<C>(s);
-    if (n >= D) n = D - 1;
-    brow[s] = WT + (long long)n * K;
-  }
-  Acc<C> acc;
-  acc.zero();
+  typename TileSums<C>::type acc;
   auto la = [&](int s, int k) {
     const int kk = k >= 2 * H ? k - 2 * H : (k >= H ? k - H : k);
     const int ks = k >= 2 * H ? k + 2 * H : k;
@@ -414,33 +412,35 @@ __global__ __launch_bounds__(C::NT, C::NT > 256 ? 2 : 1) void input_grad_kernel_
   };
   auto fa = [](const KapW8& r) { return F32x8{r.k0 * r.w0, r.k1 * r.w1}; };
   if constexpr (C::NP == 3) {
-    const long long term = (long long)D * K;
-    auto lb = [&](int s, int k) {
-      return Bf16x8x3{{ldg8h(brow[s] + k), ldg8h(brow[s] + term + k),
-                       ldg8h(brow[s] + 2 * term + k)}};
-    };
-    if (K % C::TK == 0)
-      gemm_nt_tile_bf16<C, false>(acc, K, la, lb, fa, lds);
-    else
-      gemm_nt_tile_bf16<C, true>(acc, K, la, lb, fa, lds);
-    if (tile_not_finite<C>(acc))
-      contract_f32<C>(
-          acc, K,
-          [&](int tr, int k) {
-            const long long r = m0 + tr < R ? m0 + tr : R - 1;
-            const int kk = k >= 2 * H ? k - 2 * H : (k >= H ? k - H : k);
-            const int ks = k >= 2 * H ? k + 2 * H : k;
-            return ldg4(kap0 + (r + B) * (5LL * H) + ks) * ldg4(w + (r + B) * H + kk);
-          },
-          [&](int tr) { return WTf + (long long)(n0 + tr < D ? n0 + tr : D - 1) * K; });
+    auto wrow_of = [&](int, int c) { return (long long)min(n0 + c, D - 1); };
+    contract_terms<C>(
+        acc, K, la, fa, WT, D, wrow_of, lds,
+        [&](int tr, int k) {
+          const long long r = m0 + tr < R ? m0 + tr : R - 1;
+          const int kk = k >= 2 * H ? k - 2 * H : (k >= H ? k - H : k);
+          const int ks = k >= 2 * H ? k + 2 * H : k;
+          return ldg4(kap0 + (r + B) * (5LL * H) + ks) * ldg4(w + (r + B) * H + kk);
+        },
+        [&](int g, int c) { return WTf + wrow_of(g, c) * K; });
   } else {
+    acc.zero();
+    const bf16_t* brow[C::B_CHUNKS];
+#pragma unroll
+    for (int s = 0; s < C::B_CHUNKS; ++s) {
+      int n = n0 + chunk_row_b<C>(s);
+      if (n >= D) n = D - 1;
+      brow[s] = WT + (long long)n * K;
+    }
     auto lb = [&](int s, int k) { return ldg8h(brow[s] + k); };
     if (K % C::TK == 0)
       gemm_nt_tile_bf16<C, false>(acc, K, la, lb, fa, lds);
     else
       gemm_nt_tile_bf16<C, true>(acc, K, la, lb, fa, lds);
   }
-  store_tile<C>(acc, dx, m0, n0, R, D);
+  if constexpr (InTerms<C>::value)
+    store_tile_terms<C>(acc, dx, m0, n0, R, D);
+  else
+    store_tile<C>(acc, dx, m0, n0, R, D);
 }
 
 hipError_t launch_input_grads(const float* kap0, const float* w, const void* WT, const void* WT3,
@@ -548,7 +548,7 @@ __global__ __launch_bounds__(AdjSkMaxNT<CT>::value) void adj_skinny_kernel(AdjAr
 typedef TileCfg<2, 2, 2, 2, 1> AdjBig;    // 128 x 128, 256 threads
 typedef TileCfg<2, 2, 1, 1, 1> AdjMid;    //  64 x 64, 256 threads
 typedef TileCfg<1, 1, 1, 1, 1, 128, 1, 4> AdjSmall;  //  32 x 32, 4 waves splitting K
-// three-term operands (K-slices of 32)
+// fp32 operands in terms (K-slices of 32)
 typedef TileCfgB<2, 2, 2, 2, 1, true, 1, 1, 2, 3, 32> AdjBigS;
 // the same tile with 8 waves of 32 x 64 each: half the accumulators per wave, so that two
 // workgroups (16 waves, 128 registers per lane) share a CU and keep twice the loads in

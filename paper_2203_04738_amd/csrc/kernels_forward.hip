@@ -10,6 +10,7 @@
 #include "gates.h"
 #include "gemm_core.h"
 #include "gemm_core_bf16.h"
+#include "gemm_terms.h"
 #include "phi_elem.h"
 #include "skinny.h"
 
@@ -232,7 +233,7 @@ struct PhiEpiExtra4 {     // STEP_RELAX_RHS (pr2..cur2) and STEP_RESID with resi
 };
 
 template <class C, int MODE>
-__device__ inline void phi_tile_epilogue(const PhiArgs& a, Acc<C>& acc, const PhiRow* rowtab,
+__device__ inline void phi_tile_epilogue(const PhiArgs& a, const typename TileSums<C>::type& acc, const PhiRow* rowtab,
                                          float* stage, long long m0, int n0, long long R,
                                          double& nrm, const long long* rowtab2 = nullptr) {
   typedef EpiStage<C> E;
@@ -250,7 +251,7 @@ __device__ inline void phi_tile_epilogue(const PhiArgs& a, Acc<C>& acc, const Ph
 #pragma unroll
   for (int ba = 0; ba < C::BM; ++ba) {
     __syncthreads();                                    // staging area no longer read
-    E::write(acc, ba, stage);
+    stage_write<C>(acc, ba, stage);
     // operands that do not depend on the sums: requested before the barrier
     PhiEpiIn4 in[E::ITEMS];
     constexpr bool CK = MODE == STEP_RELAX_KAPPA2 || MODE == STEP_RELAX_CK;
@@ -421,10 +422,10 @@ __global__ __launch_bounds__(C::NT, C::MINWG) void phi_step_kernel(PhiArgs a) {
 }
 
 // bf16 weights: the fp32 state rows go to LDS as one bf16 tile or as hi + lo tiles (the
-// configuration's A2, see gemm_core_bf16.h); gates, update and outputs stay fp32.  With a three-term
-// configuration the weights are fp32 values held as three bf16 arrays.
+// configuration's A2, see gemm_core_bf16.h); gates, update and outputs stay fp32.  With NP = 3 the
+// weights are fp32 values, contracted in fp16 terms (gemm_terms.h).
 template <class C, int MODE, bool ZS = false>
-__global__ __launch_bounds__(C::NT, C::MINWG) void phi_step_kernel_bf16(PhiArgs a) {
+__global__ __launch_bounds__(C::NT, C::MINWAVES) void phi_step_kernel_bf16(PhiArgs a) {
   constexpr int LDSF =
       C::LDS_ELEMS / 2 + 1 > EpiStage<C>::FLOATS ? C::LDS_ELEMS / 2 + 1 : EpiStage<C>::FLOATS;
   __shared__ __attribute__((aligned(16))) float ldsf[LDSF];
@@ -437,7 +438,6 @@ __global__ __launch_bounds__(C::NT, C::MINWG) void phi_step_kernel_bf16(PhiArgs 
   const long long m0 = rt * C::TM;
   const int n0 = ct * C::TN;
   const int tid = threadIdx.x;
-  const bf16_t* U = (const bf16_t*)(C::NP == 3 ? a.U3 : a.U);
   __shared__ PhiRow rowtab[C::TM];
   __shared__ long long rowtab2[(MODE == STEP_RELAX_KAPPA2 || MODE == STEP_RELAX_CK) ? C::TM : 1];
   if (tid < C::TM) {
@@ -452,7 +452,6 @@ __global__ __launch_bounds__(C::NT, C::MINWG) void phi_step_kernel_bf16(PhiArgs 
   // (visible to all waves after the barriers inside the contraction)
 
   const float* arow[C::A_CHUNKS];
-  const bf16_t* brow[C::B_CHUNKS];
 #pragma unroll
   for (int s = 0; s < C::A_CHUNKS; ++s) {
     long long r = m0 + chunk_row_b<C>(s);
@@ -461,38 +460,29 @@ __global__ __launch_bounds__(C::NT, C::MINWG) void phi_step_kernel_bf16(PhiArgs 
     const int b = (int)(r - pt * B);
     arow[s] = a.u_in + (a.in.at(pt) * B + b) * H;
   }
-#pragma unroll
-  for (int s = 0; s < C::B_CHUNKS; ++s) {
-    const int tr = chunk_row_b<C>(s);
-    const int g = tr / C::TN;
-    int j = n0 + tr % C::TN;
-    if (j >= H) j = H - 1;
-    brow[s] = U + ((long long)g * H + j) * H;
-  }
-  Acc<C> acc;
-  acc.zero();
+  typename TileSums<C>::type acc;
   auto la = [&](int s, int k) { return F32x8{ldg4(arow[s] + k), ldg4(arow[s] + k + 4)}; };
   auto fa = [](const F32x8& v) { return v; };
   const bool zero_in = ZS && m0 >= a.zero_from;                // see phi_step_kernel
   if (zero_in) {
+    acc.zero();
   } else if constexpr (C::NP == 3) {
-    const long long term = 3LL * H * H;
-    auto lb = [&](int s, int k) {
-      return Bf16x8x3{{ldg8h(brow[s] + k), ldg8h(brow[s] + term + k),
-                       ldg8h(brow[s] + 2 * term + k)}};
-    };
-    if (H % C::TK == 0)
-      gemm_nt_tile_bf16<C, false>(acc, H, la, lb, fa, lds);
-    else
-      gemm_nt_tile_bf16<C, true>(acc, H, la, lb, fa, lds);
-    if (tile_not_finite<C>(acc))
-      contract_f32<C>(
-          acc, H, [&](int tr, int k) { return ldg4(a.u_in + rowtab[tr].in + k); },
-          [&](int tr) {
-            const int j = n0 + tr % C::TN;
-            return (const float*)a.U + ((long long)(tr / C::TN) * H + (j < H ? j : H - 1)) * H;
-          });
+    auto urow = [&](int g, int c) { return (long long)g * H + min(n0 + c, H - 1); };
+    contract_terms<C>(
+        acc, H, la, fa, a.U3, 3LL * H, urow, lds,
+        [&](int tr, int k) { return ldg4(a.u_in + rowtab[tr].in + k); },
+        [&](int g, int c) { return (const float*)a.U + urow(g, c) * H; });
   } else {
+    acc.zero();
+    const bf16_t* brow[C::B_CHUNKS];
+#pragma unroll
+    for (int s = 0; s < C::B_CHUNKS; ++s) {
+      const int tr = chunk_row_b<C>(s);
+      const int g = tr / C::TN;
+      int j = n0 + tr % C::TN;
+      if (j >= H) j = H - 1;
+      brow[s] = (const bf16_t*)a.U + ((long long)g * H + j) * H;
+    }
     auto lb = [&](int s, int k) { return ldg8h(brow[s] + k); };
     if (H % C::TK == 0)
       gemm_nt_tile_bf16<C, false>(acc, H, la, lb, fa, lds);
@@ -727,11 +717,11 @@ typedef TileCfgB<1, 1, 1, 1, 3, true, 4, 1, 2, 1, 64, false> PhiSmallF;
 // per workgroup, for launches whose tiles do not fill the CUs twice anyway (one workgroup per
 // CU: 110 KB of LDS with both groups' sums staged); 22.5 -> 20.3 us at 512 rows x 1024
 typedef TileCfgB<2, 2, 1, 1, 3, true, 2, 1, 1, 1, 64, false> PhiMidFK;
-// three-term operands: K-slices of 32 keep two workgroups' tiles in a CU's LDS
+// fp32 operands in terms: K-slices of 32 keep two workgroups' tiles in a CU's LDS
 typedef TileCfgB<2, 2, 2, 1, 3, true, 1, 1, 2, 3, 32> PhiBigS;
 typedef TileCfgB<2, 2, 1, 1, 3, true, 1, 1, 2, 3, 32> PhiMidS;
 // 64 x 32 with two groups of two waves splitting K, where 64 x 64 tiles leave CUs half empty (us, 64 x
-// 64 : this): 1024 rows x 1024 (256 tiles of 64 x 64) 64 : 50, 800 x 1000 (208) 66 : 53, 4096 x 256
+// 64 : this, three bf16 terms): 1024 rows x 1024 (256 tiles of 64 x 64) 64 : 50, 800 x 1000 (208) 66 : 53, 4096 x 256
 // (256) 19.6 : 16.7, but 4096 x 512 (512) 50 : 58
 typedef TileCfgB<2, 1, 1, 1, 3, true, 2, 1, 2, 3, 32> PhiNarrowS;
 
@@ -776,7 +766,7 @@ static void launch_phi_x3(const PhiArgs& a, hipStream_t s) {
   MG_LAUNCH_BY_MODE(phi_step_kernel_bf16, CS)
 }
 
-// CS: tile of the three-term form; void: such a launch runs on the fp32 tile (the 32 x 32 tiles of
+// CS: tile of the form in terms; void: such a launch runs on the fp32 tile (the 32 x 32 tiles of
 // the smallest launches: a training step of 128 x 100 x 1000, whose serial steps are such launches,
 // takes 7.27 ms with them in fp32 and 7.51 with terms, 256 x 65 x 184 2.45 and 2.67)
 template <class C, class CB, class CS, class CF>

@@ -14,6 +14,7 @@
 #include "common.h"
 #include "gates.h"
 #include "gemm_core_bf16.h"
+#include "gemm_terms.h"
 #include "skinny.h"
 
 namespace mg {
@@ -62,7 +63,7 @@ struct LstmEpiIn4 {
 // Epilogue of one MFMA tile over the staged sums (see EpiStage): gates, update and the mode's
 // outputs for both halves of the state, moved as float4.
 template <class C, int MODE>
-__device__ inline void lstm_tile_epilogue(const PhiArgs& a, Acc<C>& acc, const LstmRow* rowtab,
+__device__ inline void lstm_tile_epilogue(const PhiArgs& a, const typename TileSums<C>::type& acc, const LstmRow* rowtab,
                                           float* stage, long long m0, int n0, long long R,
                                           double& nrm) {
   typedef EpiStage<C> E;
@@ -79,7 +80,7 @@ __device__ inline void lstm_tile_epilogue(const PhiArgs& a, Acc<C>& acc, const L
 #pragma unroll
   for (int ba = 0; ba < C::BM; ++ba) {
     __syncthreads();                                    // staging area no longer read
-    E::write(acc, ba, stage);
+    stage_write<C>(acc, ba, stage);
     LstmEpiIn4 in[E::ITEMS];
     long long oo[E::ITEMS], oa[E::ITEMS];
     int trow[E::ITEMS];
@@ -202,8 +203,7 @@ __global__ __launch_bounds__(C::NT, C::NT > 256 ? 1 : C::MINWG) void lstm_step_k
   }
 }
 
-// The same step with each fp32 operand as three bf16 terms (see gemm_core_bf16.h): the weights come
-// as their terms a.U3[3][4H, H], the states are split on their way to LDS.
+// The same step on the 16-bit matrix pipe, each fp32 operand as two fp16 terms (gemm_terms.h).
 template <class C, int MODE>
 __global__ __launch_bounds__(C::NT, 2) void lstm_step_kernel_x3(PhiArgs a) {
   constexpr int LDSF =
@@ -226,7 +226,6 @@ __global__ __launch_bounds__(C::NT, 2) void lstm_step_kernel_x3(PhiArgs a) {
   // (visible to all waves after the barriers inside the contraction)
 
   const float* arow[C::A_CHUNKS];
-  const bf16_t* brow[C::B_CHUNKS];
 #pragma unroll
   for (int s = 0; s < C::A_CHUNKS; ++s) {
     long long r = m0 + chunk_row_b<C>(s);
@@ -235,30 +234,13 @@ __global__ __launch_bounds__(C::NT, 2) void lstm_step_kernel_x3(PhiArgs a) {
     const int b = (int)(r - pt * B);
     arow[s] = a.u_in + (a.in.at(pt) * B + b) * S;       // h half of the state row
   }
-#pragma unroll
-  for (int s = 0; s < C::B_CHUNKS; ++s) {
-    const int tr = chunk_row_b<C>(s);
-    const int j = min(n0 + tr % C::TN, H - 1);
-    brow[s] = (const bf16_t*)a.U3 + ((long long)(tr / C::TN) * H + j) * H;
-  }
-  Acc<C> acc;
-  acc.zero();
-  const long long term = 4LL * H * H;
-  auto la = [&](int s, int k) { return F32x8{ldg4(arow[s] + k), ldg4(arow[s] + k + 4)}; };
-  auto lb = [&](int s, int k) {
-    return Bf16x8x3{{ldg8h(brow[s] + k), ldg8h(brow[s] + term + k), ldg8h(brow[s] + 2 * term + k)}};
-  };
-  auto fa = [](const F32x8& v) { return v; };
-  if (H % C::TK == 0)
-    gemm_nt_tile_bf16<C, false>(acc, H, la, lb, fa, (bf16_t*)ldsf);
-  else
-    gemm_nt_tile_bf16<C, true>(acc, H, la, lb, fa, (bf16_t*)ldsf);
-  if (tile_not_finite<C>(acc))
-    contract_f32<C>(
-        acc, H, [&](int tr, int k) { return ldg4(a.u_in + rowtab[tr].in + k); },
-        [&](int tr) {
-          return (const float*)a.U + ((long long)(tr / C::TN) * H + min(n0 + tr % C::TN, H - 1)) * H;
-        });
+  TermAcc<C> acc;
+  auto urow = [&](int g, int c) { return (long long)g * H + min(n0 + c, H - 1); };
+  contract_terms<C>(
+      acc, H, [&](int s, int k) { return F32x8{ldg4(arow[s] + k), ldg4(arow[s] + k + 4)}; },
+      [](const F32x8& v) { return v; }, a.U3, 4LL * H, urow, ldsf,
+      [&](int tr, int k) { return ldg4(a.u_in + rowtab[tr].in + k); },
+      [&](int g, int c) { return (const float*)a.U + urow(g, c) * H; });
 
   double nrm = 0.0;
   lstm_tile_epilogue<C, MODE>(a, acc, rowtab, ldsf, m0, n0, R, nrm);
@@ -506,9 +488,8 @@ typedef TileCfg<4, 2, 1, 1, 4> LstmBig;
 typedef TileCfg<2, 2, 1, 1, 4> LstmMid;                  //  64 x 64
 typedef TileCfg<1, 1, 1, 1, 4, 128, 1, 4> LstmSmall;     //  32 x 32, 4 waves splitting K
 
-// Three-term operands: 64 x 64 tiles at every size (16384 rows x 512: 239 us against 247 for 128 x 64
-// as eight waves, whose staged sums leave one workgroup per CU, and 332 on the fp32 MFMAs; 4096 rows:
-// 65 against 81).  Smaller launches stay on the K-split fp32 tile.
+// Operands in terms: 64 x 64 tiles at every size (16384 rows x 512: 126 us, 38 at 4096 rows; with six
+// products of three bf16 terms 239 and 65, 332 and 81 on the fp32 MFMAs).  Smaller launches stay on the K-split fp32 tile.
 typedef TileCfgB<2, 2, 1, 1, 4, true, 1, 1, 2, 3, 32> LstmMidS;
 
 static void launch_lstm_x3(const PhiArgs& a, hipStream_t s) {

@@ -2,7 +2,7 @@
 // injection / correction transfers of Alg. 2 line 5 at coarse points) and the
 // final square root of the residual accumulators.
 #include "common.h"
-#include "gemm_core_bf16.h"
+#include "gemm_terms.h"
 
 namespace mg {
 
@@ -75,7 +75,7 @@ hipError_t launch_add_points(float* dst, const float* src, Idx d, Idx s, int nk,
   return hipGetLastError();
 }
 
-// Three-term bf16 form of an fp32 array, scaled as in gemm_core_bf16.h (weights of the three-term form).
+// Three-term bf16 form of an fp32 array, scaled as in gemm_core_bf16.h (weights of the projection).
 __global__ void split3_kernel(const float* __restrict__ src, unsigned short* __restrict__ dst,
                               long long n4) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -103,6 +103,35 @@ hipError_t launch_split3(const float* src, void* dst, long long n, hipStream_t s
   const long long n4 = n / 4;
   hipLaunchKernelGGL(split3_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, src,
                      (unsigned short*)dst, n4);
+  return hipGetLastError();
+}
+
+// Packed fp16 terms (gemm_terms.h) of weights src[rows][K], one wave per row, each row scaled by the
+// power of two that brings its largest value to 2^TERM_TOP_B.
+__global__ __launch_bounds__(256) void split2_kernel(const float* __restrict__ src,
+                                                     char* __restrict__ dst, int rows, int K) {
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (row >= rows) return;
+  const float* p = src + (long long)row * K;
+  float m = 0.f;
+  for (int k = lane * 8; k < K; k += 512) m = top8(m, F32x8{ldg4(p + k), ldg4(p + k + 4)});
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+  const int e = term_exponent(m, TERM_TOP_B);
+  char* q = dst + pack_row(row, K);
+  for (int k = lane * 8; k < K; k += 512) {
+    f16x8 t0, t1;
+    split_f16_2(F32x8{ldg4(p + k), ldg4(p + k + 4)}, exp2_int(e), t0, t1);
+    *reinterpret_cast<f16x8*>(q + (size_t)(k >> 3) * PACK_K8) = t0;
+    *reinterpret_cast<f16x8*>(q + (size_t)(k >> 3) * PACK_K8 + PACK_TERM) = t1;
+  }
+  if (lane == 0) const_cast<int*>(pack_exponents(dst, rows, K))[row] = e;
+}
+
+hipError_t launch_split2(const float* src, void* dst, int rows, int K, hipStream_t s) {
+  if (rows <= 0) return hipSuccess;
+  hipLaunchKernelGGL(split2_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, src,
+                     (char*)dst, rows, K);
   return hipGetLastError();
 }
 

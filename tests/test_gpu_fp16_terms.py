@@ -1,0 +1,51 @@
+"""Scales of the rows in the step kernels' fp16 terms (gemm_terms.h): rows whose first K-slice says nothing
+about the rest of them, in every tile.  (The tiles themselves, their tails and their fp32 repetition:
+test_gpu_term_tiles.py.)"""
+import numpy as np
+import pytest
+
+from oracle import mgrit_gru_oracle as orc
+from synthetic_inputs import random_small
+
+pytestmark = pytest.mark.gpu
+T, CF = 6, 3
+
+
+# batch sizes and widths of the five tiles of each direction (two launch rows per batch row), K tails
+@pytest.mark.parametrize("B,H", [(2050, 136), (6145, 136), (12225, 136), (1350, 264), (4100, 264)])
+def test_rows_that_differ_from_their_first_slice(B, H):
+    """Row 0: nothing but zeros; 1: zeros in the first 72 columns (both K-split groups' slice); 2: the
+    rest 2^14 times the first slice, which overflows in its scale, so that its tile's rows are read
+    through; 3: a first slice 2^14 times the rest; 4: all of it 2^-40.  The bar is that of the other
+    parity tests, 1e-5 of a row's largest value; an fp16 term that overflowed or a row scaled by
+    another one's exponent would be off by a power of two.  (No state is beyond one: gates of states of
+    2^14 saturate on sums that fp32 itself rounds to 1e-3.)"""
+    import gpu_harness as gh
+    print("fp16 terms, rows", B, H, flush=True)
+    d = random_small(11, T, B, 8, H, scale=0.5 / np.sqrt(H))
+
+    def mark(a):
+        a[0] = 0
+        a[1, :72] = 0
+        a[2, :72] *= 2.0 ** -14
+        a[3, 32:] *= 2.0 ** -14
+        a[4] *= 2.0 ** -40
+
+    mark(d["h0"])
+    mark(d["dL_dhT"])
+    r = [0, 1, 2, 3, 4, 5, B - 1]
+    P, z = (d["W"], d["U"], d["b_i"], d["b_h"]), np.zeros((T + 1, len(r), H))
+    h_ref, _ = orc.mgrit_forward(*P, d["x"][:, r], d["h0"][r], z, CF, 2, 1)
+    run = gh.GpuRun(d, cf=CF, levels=2)
+    h = run.forward_iterates(1)[0][-1]
+    for i, b in enumerate(r):
+        for t in range(T + 1):
+            assert gh.rel_err(h[t, b], h_ref[t, i]) <= 1e-5 or not h_ref[t, i].any(), ("h", b, t)
+    w = run.backward_iterates(h, 1)[0][-1]
+    want = orc.mgrit_backward(*P, d["x"][:, r], h[:, r], d["dL_dhT"][r], z, CF, 2, 1)[0]
+    for i, b in enumerate(r):
+        for t in range(T + 1):
+            if want[t, i].any():
+                assert gh.rel_err(w[t, b], want[t, i]) <= 1e-5, ("w", b, t)
+            else:
+                assert not np.asarray(w[t, b]).any(), ("w", b, t)
