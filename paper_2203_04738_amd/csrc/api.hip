@@ -260,17 +260,20 @@ static float* scan_ring(const mgrit_gru_cfg& c, const Layout& lay, const Forms& 
 
 static Forms make_forms(const mgrit_gru_cfg& c, const Layout& lay, char* base) {
   Forms f{kform(c.dtype), kform(c.dtype), nullptr, nullptr, nullptr, 0};
+  // (packed terms are addressed with 32 bits: widths from about 18000 on, the fp32 MFMAs)
+  const bool packs = 16LL * c.H * (c.H > c.D ? c.H : c.D) < (1LL << 32);
   if (c.dtype == MGRIT_F32_BF16X3) {
     f.U3 = base + lay.U3;
     f.UT3 = base + lay.UT3;
     f.W3 = base + lay.W3;
+    if (!packs) f.rec = 0;
     return f;
   }
   const bool gru = c.propagator == MGRIT_PROP_IMPLICIT || c.propagator == MGRIT_PROP_CLASSIC;
   const bool lstm = prop_is_lstm(c.propagator);        // (c.H is the state width 2 H then)
   const int H = lstm ? c.H / 2 : c.H, gates = lstm ? 4 : 3;
   const long long rows = (long long)c.T * c.B / (c.levels > 1 ? c.cf : 1);
-  if (c.dtype != MGRIT_F32 || (!gru && !lstm) || H % 8 != 0 || H < TERMS_MIN_H ||
+  if (!packs || c.dtype != MGRIT_F32 || (!gru && !lstm) || H % 8 != 0 || H < TERMS_MIN_H ||
       rows < TERMS_MIN_ROWS)
     return f;
   const size_t u3 = align_up((size_t)6 * gates * H * H);

@@ -131,11 +131,11 @@ struct TileCfgB {
   static constexpr int CPR = TK / 8;            // 16-byte chunks per tile row
   static constexpr int A_CHUNKS = (TM * CPR) / NT;
   static constexpr int B_CHUNKS = (BROWS * CPR) / NT;
-  // (NP = 3 without LOSUM: two slices of A in two terms, gemm_terms.h)
-  // waves per SIMD that the register budget is planned for (two workgroups of terms per CU)
-  static constexpr int MINWAVES = NP == 3 && !LOSUM ? NT / 128 : MINWG;
+  // (NP = 3 without LOSUM: three slices of A in two terms, gemm_terms.h)
+  // waves per SIMD that the register budget is planned for
+  static constexpr int MINWAVES = NP == 3 && !LOSUM ? NT * MINWG / 256 : MINWG;
   static constexpr int LDS_ELEMS =
-      NP == 3 && !LOSUM ? 2 * 2 * TM * TK : (NA * TM + NBP * BROWS) * LD;
+      NP == 3 && !LOSUM ? 3 * 2 * TM * TK : (NA * TM + NBP * BROWS) * LD;
   static_assert(SPLIT_A || NP == 1, "three-term operands are fp32 in memory");
   static_assert((TM * CPR) % NT == 0 && (BROWS * CPR) % NT == 0, "tile rows must divide evenly");
 };

@@ -24,8 +24,8 @@
 // rate for the 128 x 64 (x3) tile.  So B does not pass through LDS: the split leaves it in the order in
 // which lanes take it (pack below), a wave owns its columns alone (the waves of a tile lie side by
 // side) and loads its fragments straight into registers, one slice ahead.  A goes to LDS in fragment
-// order too, two slices alternating, so that a slice costs one barrier and its conversion and writes
-// share the scheduling region with the MFMAs of the slice before.
+// order too, in three slices taking turns, so that a slice costs one barrier, its conversion and writes
+// go between the MFMAs of an earlier one, and its first fragments are read before the barrier.
 #pragma once
 #include "gemm_core_bf16.h"
 
@@ -45,20 +45,21 @@ __device__ inline void minus2_f16(float& a, float& b, unsigned r) {
   asm("v_fma_mix_f32 %0, %1, -1.0, %0 op_sel_hi:[1,0,0]" : "+v"(a) : "v"(r));
   asm("v_fma_mix_f32 %0, %1, -1.0, %0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(b) : "v"(r));
 }
-// t0 + t1 = v f up to 2^-22
-__device__ inline void split_f16_2(const F32x8& v, float f, f16x8& t0, f16x8& t1) {
+// Terms of pair i (0..3) of eight values: t0 + t1 = v f up to 2^-22.
+struct Words8 {
+  unsigned t0[4], t1[4];           // eight values' terms, two to a word
+};
+__device__ inline void split_pair(const F32x8& v, int i, float f, Words8& w) {
+  float a = (i < 2 ? v.lo4[2 * i] : v.hi4[2 * i - 4]) * f;
+  float b = (i < 2 ? v.lo4[2 * i + 1] : v.hi4[2 * i - 3]) * f;
+  w.t0[i] = round2_f16(a, b);
+  minus2_f16(a, b, w.t0[i]);
+  w.t1[i] = round2_f16(a, b);
+}
+__device__ inline f16x8 words8(const unsigned (&w)[4]) {
   typedef unsigned uintx4_ __attribute__((ext_vector_type(4)));
-  uintx4_ w0, w1;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float a = (i < 2 ? v.lo4[2 * i] : v.hi4[2 * i - 4]) * f;
-    float b = (i < 2 ? v.lo4[2 * i + 1] : v.hi4[2 * i - 3]) * f;
-    w0[i] = round2_f16(a, b);
-    minus2_f16(a, b, w0[i]);
-    w1[i] = round2_f16(a, b);
-  }
-  t0 = __builtin_bit_cast(f16x8, w0);
-  t1 = __builtin_bit_cast(f16x8, w1);
+  const uintx4_ v = {w[0], w[1], w[2], w[3]};
+  return __builtin_bit_cast(f16x8, v);
 }
 __device__ inline float top8(float m, const F32x8& v) {
 #pragma unroll
@@ -90,7 +91,7 @@ __device__ inline const int* pack_exponents(const void* pack, long long rows, in
 template <class C>
 struct TermGeom {
   static constexpr int NW = C::WM * C::WN;
-  static constexpr int WR = NW > 4 ? 2 : 1, WC = NW / WR;
+  static constexpr int WR = NW > 4 && C::TN <= 128 ? 2 : 1, WC = NW / WR;
   static constexpr int RB = C::TM / 16 / WR, CB = C::TN / 16 / WC;
   static constexpr int NF = C::NG * CB;                   // B fragments per term and slice
   static constexpr int GB = NF >= 3 ? 1 : 2;              // row blocks whose MFMAs alternate
@@ -127,40 +128,65 @@ struct TermLane {
   }
 };
 
-// One pass over K (a multiple of 8).  loadA, finA: as in gemm_nt_tile_bf16; brow(g, c): packed row
+// First k of slice i of a pass over K in memory order.
+template <class C>
+struct InOrder {
+  __device__ inline int operator()(int i) const { return i * C::TK; }
+};
+
+// Largest magnitude over the row behind chunk s of the calling thread: load(k), columns k..k+7 of the row, K
+// of them (the CPR lanes that share a row are neighbours).  Eight slices' loads at a time: a tile with
+// rows of zeros waits for this (H0, adjoints of a zero guess).
+template <class C>
+__device__ inline float over_row(float m) {
+#pragma unroll
+  for (int o = 1; o < C::CPR; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+  return m;
+}
+template <class C, class Load>
+__device__ inline float row_top(int s, int K, Load load) {
+  float m = 0.f;
+  for (int k = (threadIdx.x + s * C::NT) % C::CPR * 8; k < K; k += 8 * C::TK) {
+    F32x8 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = load(min(k + u * C::TK, K - 8));
+#pragma unroll
+    for (int u = 0; u < 8; ++u) m = top8(m, v[u]);
+  }
+  return over_row<C>(m);
+}
+
+// One pass over K (a multiple of 8).  loadA, finA: as in gemm_nt_tile_bf16, called slice after slice;
+// order(i): first k of the i-th slice; top(s, through): row_top of the row behind chunk s; brow(g, c): packed row
 // (g, column c of the tile) of B; rowexp: LDS, receives the exponents the tile rows of A are scaled
 // by; through: find them from whole rows, not from first slices.
-template <class C, bool KTAIL, class LoadA, class FinA, class BRow>
-__device__ inline void gemm_nt_tile_terms(TermAcc<C>& acc, int K, LoadA loadA, FinA finA,
-                                          const char* pack, BRow brow, f16x8* lds, int* rowexp,
-                                          bool through) {
+template <class C, class LoadA, class Top, class FinA, class Order, class BRow>
+__device__ inline void gemm_nt_tile_terms(TermAcc<C>& acc, int K, LoadA loadA, Top top, FinA finA,
+                                          Order order, const char* pack, BRow brow, f16x8* lds,
+                                          int* rowexp, bool through) {
   typedef TermGeom<C> G;
   const int tid = threadIdx.x;
   const TermLane<C> me;
-  decltype(loadA(0, 0)) ra[C::A_CHUNKS];
-  auto fetch_a = [&](int s, int k0) {
-    int k = k0 + ((tid + s * C::NT) % C::CPR) * 8;
-    if (KTAIL && k >= K) k = K - 8;
-    ra[s] = loadA(s, k);
+  decltype(loadA(0, 0)) ra[C::A_CHUNKS], ra1[C::A_CHUNKS];       // (ra1: prologue only)
+  auto load_a = [&](int s, int k0) {
+    return loadA(s, min(k0 + ((tid + s * C::NT) % C::CPR) * 8, K - 8));
   };
-  const char* bp[C::NG][G::CB];
+  // (32-bit offsets: launches on terms keep their packs below 4 GB)
+  unsigned bo[C::NG][G::CB];
 #pragma unroll
   for (int g = 0; g < C::NG; ++g)
 #pragma unroll
     for (int c = 0; c < G::CB; ++c)
-      bp[g][c] = pack + pack_row(brow(g, me.col0 + c * 16 + me.li), K);
+      bo[g][c] = (unsigned)pack_row(brow(g, me.col0 + c * 16 + me.li), K);
   f16x8 rb[2][2][C::NG][G::CB];                 // [slice % 2][term]
-  auto fetch_b = [&](int d, int k0) {
-    int k8 = k0 / 8 + me.ks * 4 + me.lq;
-    if (KTAIL) k8 = min(k8, K / 8 - 1);
-#pragma unroll
-    for (int g = 0; g < C::NG; ++g)
-#pragma unroll
-      for (int c = 0; c < G::CB; ++c)
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-          rb[d][t][g][c] = *reinterpret_cast<const f16x8*>(bp[g][c] + (size_t)(unsigned)k8 * PACK_K8 +
-                                                           t * PACK_TERM);
+  constexpr int NLB = 2 * C::NG * G::CB;        // loads of B per slice
+  auto fetch_b = [&](int d, int j, int k0) {
+    const int g = j / 2 / G::CB, c = j / 2 % G::CB, t = j % 2;
+    // (columns beyond K, a whole K-split group of them in the last slice: those of the last k / 8)
+    const int k8 = min(k0 / 8 + me.ks * 4, K / 8 - 1);
+    const unsigned lane = (unsigned)min(me.lq, K / 8 - 1 - k8) * PACK_K8;
+    rb[d][t][g][c] = *reinterpret_cast<const f16x8*>(pack + (long long)k8 * PACK_K8 +
+                                                     t * PACK_TERM + (bo[g][c] + lane));
   };
   // scale of the row behind each chunk; odd tile rows enter with the opposite sign (see contract_terms)
   float rowscale[C::A_CHUNKS];
@@ -168,36 +194,27 @@ __device__ inline void gemm_nt_tile_terms(TermAcc<C>& acc, int K, LoadA loadA, F
 #pragma unroll
     for (int s = 0; s < C::A_CHUNKS; ++s) {
       const int q = tid + s * C::NT;
-      // (the CPR lanes that share a row are neighbours)
-      auto over_row = [](float m) {
-#pragma unroll
-        for (int o = 1; o < C::CPR; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-        return m;
-      };
-      float m = over_row(top8(0.f, finA(ra[s])));
-      if (through || m == 0.f) {
-        for (int k = (q % C::CPR) * 8; k < K; k += C::TK) m = top8(m, finA(loadA(s, k)));
-        m = over_row(m);
-      }
+      float m = over_row<C>(top8(0.f, finA(ra[s])));
+      if (through || m == 0.f) m = top(s, through);
       const int e = term_exponent(m, TERM_TOP_A);
       rowscale[s] = (q / C::CPR) & 1 ? -exp2_int(e) : exp2_int(e);
       if (q % C::CPR == 0) rowexp[q / C::CPR] = e;
     }
   };
-  // A in LDS: [slice % 2][K-split group][term][row block][k / 8][row % 16], the rows of a k / 8 exchanged
+  // A in LDS: [slice % 3][K-split group][term][row block][k / 8][row % 16], the rows of a k / 8 exchanged
   // by it, so that the eight lanes of two rows write to different banks
-  auto stash = [&](int p, int s, int k0) {
+  Words8 aw[C::A_CHUNKS];
+  auto convert = [&](int j, int k0) {           // pair j of the thread's 4 A_CHUNKS
+    const int s = j / 4, c = (tid + s * C::NT) % C::CPR;
+    // (columns beyond K: zeros, or what makes the tile one that is not finite)
+    split_pair(finA(ra[s]), j % 4, k0 + c * 8 < K ? rowscale[s] : 0.f, aw[s]);
+  };
+  auto stash = [&](int p, int s) {
     const int q = tid + s * C::NT, row = q / C::CPR, c = q % C::CPR;
-    f16x8 t0, t1;
-    split_f16_2(finA(ra[s]), rowscale[s], t0, t1);
-    if (KTAIL && k0 + c * 8 >= K) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) t0[i] = t1[i] = (_Float16)0.f;
-    }
     const int at = p * G::BUF + (c / 4) * 2 * G::BLK * 64 + (row / 16) * 64 + (c % 4) * 16 +
                    ((row & 15) ^ (2 * (c % 4)));
-    lds[at] = t0;
-    lds[at + G::BLK * 64] = t1;
+    lds[at] = words8(aw[s].t0);
+    lds[at + G::BLK * 64] = words8(aw[s].t1);
   };
   const int a_at = me.ks * 2 * G::BLK * 64 + (me.row0 / 16) * 64 + me.lq * 16 + (me.li ^ (2 * me.lq));
   auto read_a = [&](int p, int r, int t) {
@@ -223,58 +240,80 @@ __device__ inline void gemm_nt_tile_terms(TermAcc<C>& acc, int K, LoadA loadA, F
                 f[u == 1][i], rb[d][u == 2][g][c], acc.v[r0 + i][g][c], 0, 0, 0);
   };
   const int nkt = (K + C::TK - 1) / C::TK;
+  // k of the slices kt + 1, kt + 2, kt + 3 (beyond the last slice: that one again, not used)
+  int o1 = order(min(1, nkt - 1)), o2 = order(min(2, nkt - 1)), o3 = order(min(3, nkt - 1));
+  const int o0 = order(0);
 #pragma unroll
-  for (int s = 0; s < C::A_CHUNKS; ++s) fetch_a(s, 0);
-  fetch_b(0, 0);
+  for (int s = 0; s < C::A_CHUNKS; ++s) ra[s] = load_a(s, o0);
+#pragma unroll
+  for (int s = 0; s < C::A_CHUNKS; ++s) ra1[s] = load_a(s, o1);
+#pragma unroll
+  for (int j = 0; j < NLB; ++j) fetch_b(0, j, o0);
+  __builtin_amdgcn_sched_barrier(0);            // (all of them in flight before the first is waited for)
   scale_rows();
 #pragma unroll
-  for (int s = 0; s < C::A_CHUNKS; ++s) {
-    stash(0, s, 0);
-    if (nkt > 1) fetch_a(s, C::TK);
-  }
+  for (int n = 0; n < 2; ++n)
+#pragma unroll
+    for (int s = 0; s < C::A_CHUNKS; ++s) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) convert(4 * s + i, n ? o1 : o0);
+      stash(n, s);
+      ra[s] = n ? load_a(s, o2) : ra1[s];
+    }
   __syncthreads();
-  // Slice kt: the fragments of row blocks are read one group ahead; the chunks of slice kt + 1, in
-  // registers since the slice before, are converted and written between the groups and their registers
-  // filled again (one slice too many is asked for, inside the row, and not used).
-  auto slice = [&](auto d_tag, auto more_tag, int kt) {
+  // Slice kt.  The fragments of a group of row blocks are read while the group before is multiplied, across
+  // the barrier too: slice kt + 1 has been in LDS since the barrier before this slice.  Everything
+  // else is dealt out over the groups, since the waves of a workgroup come to the same point together:
+  // the loads of B for the next slice over the first three quarters (they queue at the CU's one
+  // address unit: all at once they held the waves up for 500 to 900 clocks), the conversion of
+  // slice kt + 2, in registers since the slice before, pair by pair.
+  Frags f[2];
+  constexpr int NGRP = G::RB / G::GB, NPAIR = 4 * C::A_CHUNKS;
+  constexpr int BGRP = NGRP * 3 / 4 > 0 ? NGRP * 3 / 4 : 1;
+  static_assert(NGRP % 2 == 0, "a slice starts on the first set of fragments");
+  int p = 0, p1 = 1, p2 = 2;                     // LDS buffers of slices kt, kt + 1, kt + 2
+  auto slice = [&](auto d_tag, int kt) {
     constexpr int d = decltype(d_tag)::value;    // kt % 2
-    constexpr bool more = decltype(more_tag)::value;
-    constexpr int NGRP = G::RB / G::GB;
-    Frags f[2];
-    if constexpr (more) fetch_b(d ^ 1, (kt + 1) * C::TK);
-    read_group(d, 0, f[0]);
 #pragma unroll
     for (int i = 0; i < NGRP; ++i) {
-      if (i + 1 < NGRP) read_group(d, (i + 1) * G::GB, f[(i + 1) & 1]);
-      multiply(d, i * G::GB, f[i & 1]);
-      if constexpr (more) {
+      if (i + 1 < NGRP)
+        read_group(p, (i + 1) * G::GB, f[(i + 1) & 1]);
+      else
+        read_group(p1, 0, f[0]);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int s = 0; s < C::A_CHUNKS; ++s)
-          if (i == (s + 1) * NGRP / (C::A_CHUNKS + 1)) {
-            stash(d ^ 1, s, (kt + 1) * C::TK);
-            fetch_a(s, min(kt + 2, nkt - 1) * C::TK);
+      for (int j = 0; j < NLB; ++j)
+        if (j * BGRP / NLB == i) fetch_b(d ^ 1, j, o1);
+      multiply(d, i * G::GB, f[i & 1]);
+#pragma unroll
+      for (int j = 0; j < NPAIR; ++j)
+        if (j * NGRP / NPAIR == i) {
+          convert(j, o2);
+          if (j % 4 == 3) {
+            stash(p2, j / 4);
+            ra[j / 4] = load_a(j / 4, o3);
           }
-      }
+        }
       __builtin_amdgcn_sched_barrier(0);
     }
-    if constexpr (more) __syncthreads();
+    __syncthreads();
+    const int t = p;
+    p = p1;
+    p1 = p2;
+    p2 = t;
+    o1 = o2;
+    o2 = o3;
+    o3 = order(min(kt + 4, nkt - 1));
   };
   constexpr std::integral_constant<int, 0> even{};
   constexpr std::integral_constant<int, 1> odd{};
-  constexpr std::true_type more{};
-  constexpr std::false_type last{};
+  read_group(p, 0, f[0]);
   int kt = 0;
-  for (; kt + 2 < nkt; kt += 2) {
-    slice(even, more, kt);
-    slice(odd, more, kt + 1);
+  for (; kt + 1 < nkt; kt += 2) {
+    slice(even, kt);
+    slice(odd, kt + 1);
   }
-  if (kt + 1 < nkt) {
-    slice(even, more, kt);
-    slice(odd, last, kt + 1);
-  } else {
-    slice(even, last, kt);
-  }
-  __syncthreads();
+  if (kt < nkt) slice(even, kt);
 }
 
 // Whether any sum of the workgroup's tile is not finite (the same answer in every thread).  A value
@@ -282,7 +321,7 @@ __device__ inline void gemm_nt_tile_terms(TermAcc<C>& acc, int K, LoadA loadA, F
 // operand it cannot carry.
 template <class C>
 __device__ inline bool tile_not_finite(const TermAcc<C>& acc) {
-  float t = 0.f;
+  floatx4 t = zero4();                          // (four chains: one of 96 waits for each link)
 #pragma unroll
   for (int r = 0; r < TermGeom<C>::RB; ++r)
 #pragma unroll
@@ -290,8 +329,9 @@ __device__ inline bool tile_not_finite(const TermAcc<C>& acc) {
 #pragma unroll
       for (int c = 0; c < TermGeom<C>::CB; ++c)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) t = fmaf(acc.v[r][g][c][e], 0.f, t);
-  return __syncthreads_or(t != t) != 0;
+        for (int e = 0; e < 4; ++e) t[e] = fmaf(acc.v[r][g][c][e], 0.f, t[e]);
+  const float u = (t[0] + t[1]) + (t[2] + t[3]);
+  return __syncthreads_or(u != u) != 0;
 }
 // acc = A * B^T in fp32, operands straight from memory (small rather than fast: only tiles with
 // sums that are not finite come here).  load_a(r, k): columns k..k+3 of tile row r of A; frow(g, c): row
@@ -325,16 +365,17 @@ __device__ inline void contract_f32(TermAcc<C>& acc, int K, LoadA4 load_a, FRow 
   }
 }
 
-// acc = A * B^T on terms.  la, fa: as in gemm_nt_tile_bf16; pack, rows: the packed terms of B
+// acc = A * B^T on terms.  la, top, fa, order: as in gemm_nt_tile_terms; pack, rows: the packed terms of B
 // (launch_split2) and its rows; brow(g, c): row of B behind column c of the tile, gate g; load_a, frow: as
 // in contract_f32.  The MFMA rounds its sum down (towards minus infinity) below the last bit, the same
 // way in every row: sums over rows (bias gradients, residual norms) would collect it, with the sign of
 // the odd rows turned it alternates instead (bias gradients at 12800 rows x 1000, three bf16 terms:
 // 4.3e-7 off with the signs as they are, 2.9e-7 with fp32 MFMAs).
-template <class C, class LoadA, class FinA, class BRow, class LoadA4, class FRow>
-__device__ inline void contract_terms(TermAcc<C>& acc, int K, LoadA la, FinA fa, const void* pack,
-                                      long long rows, BRow brow, void* lds, LoadA4 load_a,
-                                      FRow frow) {
+template <class C, class LoadA, class Top, class FinA, class BRow, class LoadA4, class FRow,
+          class Order = InOrder<C>>
+__device__ inline void contract_terms(TermAcc<C>& acc, int K, LoadA la, Top top, FinA fa,
+                                      const void* pack, long long rows, BRow brow, void* lds,
+                                      LoadA4 load_a, FRow frow, Order order = InOrder<C>()) {
   typedef TermGeom<C> G;
   __shared__ __attribute__((aligned(16))) int rowexp[C::TM];
   const TermLane<C> me;
@@ -347,12 +388,8 @@ __device__ inline void contract_terms(TermAcc<C>& acc, int K, LoadA la, FinA fa,
 #pragma unroll 1
   for (int through = 0; through < 2; ++through) {
     acc.zero();
-    if (K % C::TK == 0)
-      gemm_nt_tile_terms<C, false>(acc, K, la, fa, (const char*)pack, brow, (f16x8*)lds, rowexp,
-                                   through != 0);
-    else
-      gemm_nt_tile_terms<C, true>(acc, K, la, fa, (const char*)pack, brow, (f16x8*)lds, rowexp,
-                                  through != 0);
+    gemm_nt_tile_terms<C>(acc, K, la, top, fa, order, (const char*)pack, brow, (f16x8*)lds,
+                          rowexp, through != 0);
 #pragma unroll
     for (int r = 0; r < G::RB; ++r) {
       typedef int intx4_ __attribute__((ext_vector_type(4)));

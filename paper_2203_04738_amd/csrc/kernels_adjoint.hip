@@ -259,13 +259,35 @@ __global__ __launch_bounds__(C::NT, C::MINWAVES) void adj_step_kernel_bf16(AdjAr
   auto fa = [](const KapW8& r) { return F32x8{r.k0 * r.w0, r.k1 * r.w1}; };
   if constexpr (C::NP == 3) {
     auto urow = [&](int, int c) { return (long long)min(n0 + c, H - 1); };
+    // Where gates are whole slices: the sum over k may run in any slice order, so slice i takes gate i % 3
+    // and the columns of slice i / 3 of that gate; the three slices that multiply the same columns
+    // of w follow each other, and w is loaded for the first of them only (see adj_step_kernel).
+    const bool whole = H % C::TK == 0;
+    F32x8 wkeep[C::A_CHUNKS];
+    auto ordered = [&](int s, int k) {
+      if (!whole || __builtin_amdgcn_readfirstlane(k) < H) {
+        const int kk = k >= 2 * H ? k - 2 * H : (k >= H ? k - H : k);
+        wkeep[s] = F32x8{ldg4(wrow[s] + kk), ldg4(wrow[s] + kk + 4)};
+      }
+      return KapW8{ldg4(krow[s] + k), ldg4(krow[s] + k + 4), wkeep[s].lo4, wkeep[s].hi4};
+    };
+    // Rows of a zero guess, and those that decay below the smallest number (18 of 256 tiles of the last
+    // launch at 2048 steps), often have zeros in their first slice: they are scaled by w alone.
+    // k_d w is part of the result, so what is small next to w is small next to that; products of
+    // more than 2^9 times w overflow and are read through.
+    auto top = [&](int s, bool through) {
+      if (through) return row_top<C>(s, K, [&](int k) { return fa(la(s, k)); });
+      return row_top<C>(s, H,
+                        [&](int k) { return F32x8{ldg4(wrow[s] + k), ldg4(wrow[s] + k + 4)}; });
+    };
     contract_terms<C>(
-        acc, K, la, fa, a.UT3, H, urow, lds,
+        acc, K, ordered, top, fa, a.UT3, H, urow, lds,
         [&](int tr, int k) {
           const int kk = k >= 2 * H ? k - 2 * H : (k >= H ? k - H : k);
           return ldg4(a.kap + rowtab[tr].k + k) * ldg4(a.w_in + rowtab[tr].in + kk);
         },
-        [&](int g, int c) { return (const float*)a.UT + urow(g, c) * K; });
+        [&](int g, int c) { return (const float*)a.UT + urow(g, c) * K; },
+        [&](int i) { return whole ? i % 3 * H + i / 3 * C::TK : i * C::TK; });
   } else {
     acc.zero();
     const bf16_t* brow[C::B_CHUNKS];
@@ -414,7 +436,8 @@ __global__ __launch_bounds__(C::NT, InTerms<C>::value ? C::MINWAVES : 1) void in
   if constexpr (C::NP == 3) {
     auto wrow_of = [&](int, int c) { return (long long)min(n0 + c, D - 1); };
     contract_terms<C>(
-        acc, K, la, fa, WT, D, wrow_of, lds,
+        acc, K, la, [&](int s, bool) { return row_top<C>(s, K, [&](int k) { return fa(la(s, k)); }); }, fa,
+        WT, D, wrow_of, lds,
         [&](int tr, int k) {
           const long long r = m0 + tr < R ? m0 + tr : R - 1;
           const int kk = k >= 2 * H ? k - 2 * H : (k >= H ? k - H : k);
@@ -550,10 +573,10 @@ typedef TileCfg<2, 2, 1, 1, 1> AdjMid;    //  64 x 64, 256 threads
 typedef TileCfg<1, 1, 1, 1, 1, 128, 1, 4> AdjSmall;  //  32 x 32, 4 waves splitting K
 // fp32 operands in terms (K-slices of 32)
 typedef TileCfgB<2, 2, 2, 2, 1, true, 1, 1, 2, 3, 32> AdjBigS;
-// the same tile with 8 waves of 32 x 64 each: half the accumulators per wave, so that two
-// workgroups (16 waves, 128 registers per lane) share a CU and keep twice the loads in
-// flight; the relaxation mode fits that register budget, the others use the 4-wave form
+// the same tile with 8 waves of 64 x 32 each
 typedef TileCfgB<4, 2, 1, 2, 1, true, 1, 1, 2, 3, 32> AdjBigS8;
+// 128 x 256 as eight waves of 128 x 32, one workgroup per CU: see launch_adj_step
+typedef TileCfgB<2, 4, 2, 2, 1, true, 1, 1, 1, 3, 32> AdjHugeS;
 // mid-size launches: 64 x 128 as four waves of 32 x 64, and 64 x 64 with two groups of four waves
 // splitting K (the adjoint's K is 3H: with one group the 64 x 64 tile waits on its slices)
 typedef TileCfgB<2, 2, 1, 2, 1, true, 1, 1, 2, 3, 32> AdjWideS;
@@ -670,6 +693,13 @@ hipError_t launch_adj_step(const AdjArgs& a, hipStream_t s) {
   } else if (a.bf16 == 1) {
     if (a.one_term) launch_adj_half<false>(a, s);
     else launch_adj_half<true>(a, s);
+  }
+  // terms, large launches: the products kappa * w are formed, scaled and split once per column tile, so
+  // the widest tile that fills the CUs, one workgroup each (us at 16384 rows x 512, x 1024: 128 x 128
+  // 91, 312; 64 x 256 88, 296; 128 x 256 85, 281).  Two column tiles from 384 on: below that it would be
+  // mostly padding
+  else if (a.bf16 == 2 && a.H >= 384 && tiles(AdjHugeS::TM, AdjHugeS::TN) >= 192) {
+    launch_adj_terms<AdjHugeS>(a, s);
   } else if (tiles(AdjBig::TM, AdjBig::TN) >= 384) {
     if (a.bf16 == 2 && a.mode == STEP_RELAX)
       launch_adj_terms<AdjBigS8>(a, s);
@@ -678,7 +708,8 @@ hipError_t launch_adj_step(const AdjArgs& a, hipStream_t s) {
     else
       launch_adj_f32<AdjBig>(a, s);
   }
-  // three terms, by what fills the chip (us, 64 x 64 without the split : 64 x 128 : 64 x 64 split):
+  // terms, by what fills the chip (us on three bf16 terms, 64 x 64 without the split : 64 x 128 : 64 x 64
+  // split):
   // 3200 rows x 1000 (400 wide tiles) 247 : 179 : 207, 4096 x 1024 (512) 215 : 169 : 193,
   // 4096 x 512 (256) 65 : 69 : 56, 1024 x 1024 (256 tiles of 64 x 64) 101 : 121 : 75, 800 x 1000 (208)
   // 99 with 32 x 32 tiles, 82 split

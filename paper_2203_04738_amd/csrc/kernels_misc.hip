@@ -120,10 +120,11 @@ __global__ __launch_bounds__(256) void split2_kernel(const float* __restrict__ s
   const int e = term_exponent(m, TERM_TOP_B);
   char* q = dst + pack_row(row, K);
   for (int k = lane * 8; k < K; k += 512) {
-    f16x8 t0, t1;
-    split_f16_2(F32x8{ldg4(p + k), ldg4(p + k + 4)}, exp2_int(e), t0, t1);
-    *reinterpret_cast<f16x8*>(q + (size_t)(k >> 3) * PACK_K8) = t0;
-    *reinterpret_cast<f16x8*>(q + (size_t)(k >> 3) * PACK_K8 + PACK_TERM) = t1;
+    Words8 w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) split_pair(F32x8{ldg4(p + k), ldg4(p + k + 4)}, i, exp2_int(e), w);
+    *reinterpret_cast<f16x8*>(q + (size_t)(k >> 3) * PACK_K8) = words8(w.t0);
+    *reinterpret_cast<f16x8*>(q + (size_t)(k >> 3) * PACK_K8 + PACK_TERM) = words8(w.t1);
   }
   if (lane == 0) const_cast<int*>(pack_exponents(dst, rows, K))[row] = e;
 }

@@ -11,9 +11,15 @@ pytestmark = pytest.mark.gpu
 T, CF = 6, 3
 
 
-# batch sizes and widths of the five tiles of each direction (two launch rows per batch row), K tails
-@pytest.mark.parametrize("B,H", [(2050, 136), (6145, 136), (12225, 136), (1350, 264), (4100, 264)])
-def test_rows_that_differ_from_their_first_slice(B, H):
+# batch sizes and widths of the five tiles of each direction (two launch rows per batch row), K tails, and of
+# the adjoint's widest tile, 128 x 256, with gates of whole K-slices (416 = 13 x 32) and without
+HUGE = "TileCfgB<2, 4, 2, 2, 1, true, 1, 1, 1, 3, 32"
+
+
+@pytest.mark.parametrize("B,H,adj", [(2050, 136, None), (6145, 136, None), (12225, 136, None),
+                                     (1350, 264, None), (4100, 264, None), (6100, 392, HUGE),
+                                     (6100, 416, HUGE)])
+def test_rows_that_differ_from_their_first_slice(B, H, adj):
     """Row 0: nothing but zeros; 1: zeros in the first 72 columns (both K-split groups' slice); 2: the
     rest 2^14 times the first slice, which overflows in its scale, so that its tile's rows are read
     through; 3: a first slice 2^14 times the rest; 4: all of it 2^-40.  The bar is that of the other
@@ -41,7 +47,10 @@ def test_rows_that_differ_from_their_first_slice(B, H):
     for i, b in enumerate(r):
         for t in range(T + 1):
             assert gh.rel_err(h[t, b], h_ref[t, i]) <= 1e-5 or not h_ref[t, i].any(), ("h", b, t)
-    w = run.backward_iterates(h, 1)[0][-1]
+    box = []
+    gh.expect_kernels(lambda: box.append(run.backward_iterates(h, 1)),
+                      *(f"adj_step_kernel_bf16<mg::{adj}, true, false>, {m}" for m in (0, 1) if adj))
+    w = box[0][0][-1]
     want = orc.mgrit_backward(*P, d["x"][:, r], h[:, r], d["dL_dhT"][r], z, CF, 2, 1)[0]
     for i, b in enumerate(r):
         for t in range(T + 1):
