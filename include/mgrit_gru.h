@@ -32,11 +32,10 @@
  *   results to the same accuracy; the kernels of larger launches carry each fp32
  *   operand of a contraction as a sum of 16-bit terms and multiply them on the
  *   16-bit matrix pipe with fp32 sums, which is faster than the fp32 one.  The
- *   projection and the weight gradients take three bf16 terms (3 x 8 mantissa bits,
- *   six of the nine term products); the level steps, adjoint steps and input
- *   gradients two fp16 terms (2 x 11 bits of rows scaled to fp16's range, three of
- *   the four products), which on this pipe come out closer to 64 bits than either
- *   six products or fp32 ones.  (Smaller launches, and the steps of layers of up to
+ *   projection takes three bf16 terms (3 x 8 mantissa bits, six of the nine term
+ *   products), everything else two fp16 terms (2 x 11 bits, scaled to fp16's range
+ *   by rows or columns, three of the four products), which on this pipe come out
+ *   closer to 64 bits than either six products or fp32 ones.  (Smaller launches, and the steps of layers of up to
  *   128 columns, run in the fp32 kernels, which are faster there and as accurate.)
  *   The weights' term arrays live in the workspace (it is larger for this dtype)
  *   and are rebuilt by every call; H and D must be multiples of 8.  A tile with

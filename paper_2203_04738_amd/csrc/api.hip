@@ -206,7 +206,7 @@ static bool misaligned(const void* p) { return ((uintptr_t)p & 15) != 0; }
 // operand form of a call
 // ---------------------------------------------------------------------------
 // MGRIT_F32 runs the tile kernels on the 16-bit matrix pipe, each fp32 operand as two fp16 terms (steps
-// and input gradients, gemm_terms.h) or three bf16 terms (projection and gradients, gemm_core_bf16.h),
+// and gradients, gemm_terms.h) or three bf16 terms (projection, gemm_core_bf16.h),
 // where that is faster and no less accurate than the fp32 MFMAs.
 // (MGRIT_F32_BF16X3 asks for the terms on every shape; its smallest launches and its layers of up to
 // 128 columns share the fp32 kernels of MGRIT_F32 all the same, which are no less accurate (against

@@ -1,5 +1,5 @@
 // Workgroup-tile product of fp32 VALUES on the 16-bit matrix pipe, for the step kernels and the input
-// gradients: the "NT" tile product of gemm_core.h with each operand carried as two fp16 terms,
+// gradients (the weight gradients take their terms from here too): the "NT" tile product of gemm_core.h with each operand carried as two fp16 terms,
 // a = a0 + a1 (22 mantissa bits), consumed by v_mfma_f32_16x16x32_f16 as a0*b0 + a1*b0 + a0*b1.
 //
 // Accuracy.  What the terms and the dropped a1*b1 leave out is about 6e-8 of a product, of either
@@ -8,7 +8,9 @@
 // Error against 64 bits, states against Xavier weights (two fp16 terms : three bf16 terms : fp32
 // MFMA): 512 columns 2.6e-7 : 3.5e-7 : 2.9e-7, 1024 columns 3.6 : 4.9 : 4.1, 1536 columns
 // 4.4 : 5.9 : 4.9.  (The projection keeps three bf16 terms with the lower products summed apart,
-// gemm_core_bf16.h: 1.8e-7 over 1024 columns, 2.2e-7 with fp16 terms in that form.)
+// gemm_core_bf16.h: 1.8e-7 over 1024 columns, 2.2e-7 with fp16 terms in that form.  Summed 128 columns
+// at a time two fp16 terms reach 1.6e-7 there and half the time, but the states that follow end up
+// further off, 2.07e-7 against 1.77e-7: few large errors become many small ones.)
 //
 // Range.  fp16 has five exponent bits, so every row of an operand is scaled by a power of two of its
 // own and the sums back, exactly: the rows of B, split once per call, by their largest value; a row of

@@ -1400,22 +1400,31 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_tr_kernel(GradArgs a) {
       }
 }
 
-// The same partial products for fp32 operands carried as three bf16 terms each (see gemm_core_bf16.h):
-// S and the second operand (h or x) are split on their way to LDS and six of the nine term products are
-// kept.  Staging as in grad_gemm_tr_kernel: LDS rows in memory order, fragments from the transpose read.
+// The same partial products for fp32 operands carried as two fp16 terms each (see gemm_terms.h): S and the
+// second operand (h or x) are split on their way to LDS, three products.  Staging as in
+// grad_gemm_tr_kernel: LDS rows in memory order, fragments from the transpose read.
 // NB: 32-column blocks of a wave; 4: tiles of 128 x 256, 2: of 128 x 128.  Every operand element is loaded,
 // multiplied and split once per tile that uses it; the wide tile does that a quarter less often per MFMA.
-// Two workgroups' tiles of terms (72 KB each) fit the LDS without padding only: columns are exchanged by
-// bits 0-1 of the row instead, so that the four rows of a read fall on different banks.
-// (Tiles of 128 x 128 with operands transposed in registers, half of whose LDS cycles were bank conflicts,
-// took 1.00 ms for a gradient of 65536 rows, 1536 x 768 on average, now 0.77; 12800 rows, 3000 x 1000
-// 0.53, now 0.42: 184 TFLOP/s; the wide tile spills 31 registers of 256.)
+// Columns are exchanged by bits 0-1 of the row, so that the four rows of a read fall on different banks.
+// The sums run over time, so it is the columns of both operands that are scaled, each by its largest value in
+// the last slice of the split: an adjoint decays backwards, and what is larger by more than 2^9 before
+// overflows.  (The sum runs forwards all the same, small values first: backwards it ends up 1.7-3 times
+// further from 64 bits.)  Columns of zeros there are scaled by 2^127, so that anything but values near the
+// smallest there are overflows; a tile that does reads its columns through for their largest values, and
+// if a sum is still not finite, runs in fp32.
+// What bounds it is staging (loads, products, conversions, LDS), the matrix pipe is busy for a good third:
+// 65536 rows, 1536 x 1024 0.68 ms (303 TFLOP/s; six products of three bf16 terms 1.07), 1536 x 512 0.37
+// (0.55), 3072 x 1024 1.24 (2.09), 12800 rows, 3000 x 1000 0.30 (0.42).  (Conditions for the columns and
+// rows beyond the matrix in every slice: 0.94 for the first of these.)
 constexpr int HS_TK = 32;
 template <int NB>
 __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
   constexpr int GN = 64 * NB;
-  __shared__ __attribute__((aligned(16))) bf16_t As[3][HS_TK * GT];
-  __shared__ __attribute__((aligned(16))) bf16_t Bs[3][HS_TK * GN];
+  // (the fp32 repetition takes two slices of its own)
+  constexpr int AEL = 2 * HS_TK * GT, BEL = 2 * HS_TK * GN, FEL = 2 * GTK * GLD;
+  __shared__ __attribute__((aligned(16))) bf16_t tiles_lds[AEL + BEL > 2 * FEL ? AEL + BEL : 2 * FEL];
+  __shared__ __attribute__((aligned(16))) int mexp[GT], nexp[GN];
+  bf16_t *const As = tiles_lds, *const Bs = tiles_lds + AEL;
   const int H = a.H, N = a.N, M = 3 * a.H;
   const int tiles = a.mtiles * a.ntiles;
   // an XCD gets consecutive items, split by split: its rows of S and Bm enter one L2 only
@@ -1433,13 +1442,6 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
 
   // wave: rows wm * 64 .., columns (j / 2) * 128 + wn * 64 + (j % 2) * 32 .. of block j
   floatx16 acc[2][NB];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
   // staging of S: columns m4*4..+3, slice rows k8 + 8r; of the second operand: c4*4..+3, rows kf + KS r
   constexpr int CL = GN / 4, KS = 256 / CL, NR = HS_TK / KS;
   static_assert(KS % 4 == 0, "one exchange of columns per thread");
@@ -1450,8 +1452,8 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
   const int mc = m_ok ? m : 0, nc = n_ok ? n : 0;
   const int gate = mc / H, jcol = mc - gate * H;
   const int src = gate == 2 ? a.third_off + jcol : mc;
-  bf16_t* const adst = &As[0][k8 * GT + ((m4 * 4) ^ ((k8 & 3) << 5))];
-  bf16_t* const bdst = &Bs[0][kf * GN + ((c4 * 4) ^ ((kf & 3) << 5))];
+  bf16_t* const adst = &As[k8 * GT + ((m4 * 4) ^ ((k8 & 3) << 5))];
+  bf16_t* const bdst = &Bs[kf * GN + ((c4 * 4) ^ ((kf & 3) << 5))];
   const float* const kbase = a.kap0 + rowoff * (5LL * H) + src;
   const float* const wbase = a.w + rowoff * H + jcol;
   const float* const bbase = (const float*)a.Bm + nc;
@@ -1472,27 +1474,70 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
       rb[r] = ldg4(bbase + k * N);
     }
   };
-  auto put = [](bf16_t* dst, int plane, floatx4 v) {
+  // scales of the thread's columns
+  floatx4 fm = zero4(), fn = zero4();
+  auto put = [](bf16_t* dst, int plane, floatx4 v, floatx4 f) {
     typedef unsigned uintx2_ __attribute__((ext_vector_type(2)));
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] *= SPLIT3_SCALE;
+    v *= f;
     float x[4] = {v[0], v[1], v[2], v[3]};
-#pragma unroll
-    for (int t = 0; t < 3; ++t) {
-      const uintx2_ w = {round2_bf16(x[0], x[1]), round2_bf16(x[2], x[3])};
-      *reinterpret_cast<uintx2_*>(dst + t * plane) = w;
-      if (t < 2) {
-        minus2_bf16(x[0], x[1], w[0]);
-        minus2_bf16(x[2], x[3], w[1]);
-      }
-    }
+    const uintx2_ w0 = {round2_f16(x[0], x[1]), round2_f16(x[2], x[3])};
+    minus2_f16(x[0], x[1], w0[0]);
+    minus2_f16(x[2], x[3], w0[1]);
+    const uintx2_ w1 = {round2_f16(x[0], x[1]), round2_f16(x[2], x[3])};
+    *reinterpret_cast<uintx2_*>(dst) = w0;
+    *reinterpret_cast<uintx2_*>(dst + plane) = w1;
   };
+  auto top4 = [](floatx4& m, floatx4 v) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m[e] = fmaxf(m[e], fabsf(v[e]));
+  };
+  // column maxima of the rows in registers (slice k0)
+  auto maxima = [&](long long k0, floatx4& tm, floatx4& tn) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (k0 + k8 + 8 * r < kend) top4(tm, rk[r] * rw[r]);
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+      if (k0 + kf + KS * r < kend) top4(tn, rb[r]);
+  };
+  // fm, fn, mexp, nexp from the threads' maxima of their columns
+  auto scales = [&](floatx4 tm, floatx4 tn) {
+    float* red = reinterpret_cast<float*>(tiles_lds);    // [8][GT], then [KS][GN]
+    static_assert(4 * (8 * GT + KS * GN) <= sizeof(tiles_lds), "");
+    __syncthreads();
+    *reinterpret_cast<floatx4*>(&red[k8 * GT + m4 * 4]) = tm;
+    *reinterpret_cast<floatx4*>(&red[8 * GT + kf * GN + c4 * 4]) = tn;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) top4(tm, *reinterpret_cast<const floatx4*>(&red[q * GT + m4 * 4]));
+#pragma unroll
+    for (int q = 0; q < KS; ++q)
+      top4(tn, *reinterpret_cast<const floatx4*>(&red[8 * GT + q * GN + c4 * 4]));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int em = term_exponent(tm[e], TERM_TOP_A), en = term_exponent(tn[e], TERM_TOP_A);
+      fm[e] = exp2_int(em);
+      fn[e] = exp2_int(en);
+      if (k8 == 0) mexp[m4 * 4 + e] = em;
+      if (kf == 0) nexp[c4 * 4 + e] = en;
+    }
+    __syncthreads();
+  };
+  // (columns beyond the matrix are copies of others and not stored; rows beyond the split count as zeros)
   auto stash = [&](long long k0) {
+    if (k0 + HS_TK > kend) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (k0 + k8 + 8 * r >= kend) rk[r] = rw[r] = zero4();
+#pragma unroll
+      for (int r = 0; r < NR; ++r)
+        if (k0 + kf + KS * r >= kend) rb[r] = zero4();
+    }
     floatx4 p[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      p[r] = (m_ok && k0 + k8 + 8 * r < kend) ? rk[r] * rw[r] : zero4();
-      put(adst + 8 * r * GT, HS_TK * GT, p[r]);
+      p[r] = rk[r] * rw[r];
+      put(adst + 8 * r * GT, HS_TK * GT, p[r], fm);
     }
     // a tree of eight rows: one addition per slice into the long sum (four rows: bias gradients 2-15 %
     // further from 64 bits).  The halves of the wave exchange two columns each.  Only the first column
@@ -1508,7 +1553,7 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
     }
 #pragma unroll
     for (int r = 0; r < NR; ++r)
-      put(bdst + KS * r * GN, HS_TK * GN, (n_ok && k0 + kf + KS * r < kend) ? rb[r] : zero4());
+      put(bdst + KS * r * GN, HS_TK * GN, rb[r], fn);
   };
   // transpose reads: see grad_gemm_tr_kernel
   const int i16 = lane & 15, half = (lane >> 4) & 1, rr = i16 >> 2;
@@ -1519,8 +1564,26 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
     boff[i] = (lh * 8 + rr) * GN + ((wn * 64 + i * 32 + half * 16 + 4 * (i16 & 3)) ^ (rr << 5));
   }
 
-  if (kbeg < kend) {
+  // first: the scales come from the last slice, otherwise from all rows
+  auto pass = [&](bool first) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    colsum[0] = colsum[1] = 0.f;
+    const long long klast = kbeg + (kend - 1 - kbeg) / HS_TK * HS_TK;
+    floatx4 tm = zero4(), tn = zero4();
+    if (!first)
+      for (long long k0 = kbeg; k0 < klast; k0 += HS_TK) {
+        fetch(k0);
+        maxima(k0, tm, tn);
+      }
+    fetch(klast);
+    maxima(klast, tm, tn);
     fetch(kbeg);
+    scales(tm, tn);
     stash(kbeg);
     __syncthreads();
     for (long long k0 = kbeg; k0 < kend; k0 += HS_TK) {
@@ -1530,26 +1593,26 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
       __builtin_amdgcn_s_setprio(2);
 #pragma unroll
       for (int c = 0; c < HS_TK / 16; ++c) {
-        bf16x8 fa[3][2];
+        f16x8 fa[2][2];
 #pragma unroll
-        for (int t = 0; t < 3; ++t)
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-          for (int i = 0; i < 2; ++i) fa[t][i] = lds_tr8(&As[t][aoff[i] + c * 16 * GT], GT);
+          for (int i = 0; i < 2; ++i)
+            fa[t][i] = __builtin_bit_cast(
+                f16x8, lds_tr8(&As[t * HS_TK * GT + aoff[i] + c * 16 * GT], GT));
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
-          bf16x8 fb[3];
+          f16x8 fb[2];
 #pragma unroll
-          for (int u = 0; u < 3; ++u)
-            fb[u] = lds_tr8(&Bs[u][boff[j & 1] + c * 16 * GN + (j >> 1) * 128], GN);
+          for (int u = 0; u < 2; ++u)
+            fb[u] = __builtin_bit_cast(
+                f16x8, lds_tr8(&Bs[u * HS_TK * GN + boff[j & 1] + c * 16 * GN + (j >> 1) * 128], GN));
 #pragma unroll
-          for (int t = 0; t < 3; ++t)
+          for (int u = 0; u < 3; ++u)              // a0 b0, a1 b0, a0 b1
 #pragma unroll
-            for (int u = 0; u < 3; ++u) {
-              if (t + u > 2) continue;
-#pragma unroll
-              for (int i = 0; i < 2; ++i)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[t][i], fb[u], acc[i][j], 0, 0, 0);
-            }
+            for (int i = 0; i < 2; ++i)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[u == 1][i], fb[u == 2], acc[i][j],
+                                                                 0, 0, 0);
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -1560,43 +1623,65 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
         __syncthreads();
       }
     }
-  }
-  {
-    // sums that are not finite: with fp32 operands (see gemm_core_bf16.h)
-    float t = 0.f;
+    // whether a sum is not finite
+    floatx4 t = zero4();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      typedef int intx4_ __attribute__((ext_vector_type(4)));
+      intx4_ me[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        me[q] = *reinterpret_cast<const intx4_*>(&mexp[wm * 64 + i * 32 + 8 * q + 4 * lh]);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const int ne = nexp[(j >> 1) * 128 + wn * 64 + (j & 1) * 32 + li];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          acc[i][j][e] = ldexpf(acc[i][j][e], -me[e / 4][e % 4] - ne);
+          t[e & 3] = fmaf(acc[i][j][e], 0.f, t[e & 3]);
+        }
+      }
+    }
+    const float u = (t[0] + t[1]) + (t[2] + t[3]);
+    return __syncthreads_or(u != u) != 0;
+  };
+  bool bad = false;
+  if (kbeg < kend) {
+#pragma unroll 1
+    for (int n = 0; n < 2; ++n) {
+      bad = pass(n == 0);
+      if (!bad) break;
+    }
+  } else {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < NB; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          acc[i][j][e] *= SPLIT3_UNSCALE;
-          t = fmaf(acc[i][j][e], 0.f, t);
-        }
-    if (__syncthreads_or(t != t)) {
-      static_assert(sizeof(As) >= GTK * GLD * sizeof(float), "fp32 slice must fit");
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  }
+  if (bad) {
 #pragma unroll
-      for (int hb = 0; hb < NB / 2; ++hb) {
-        if (n0 + hb * 128 >= N) break;                 // (uniform)
-        floatx16 full[2][2];
+    for (int hb = 0; hb < NB / 2; ++hb) {
+      if (n0 + hb * 128 >= N) break;                 // (uniform)
+      floatx16 full[2][2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) full[i][j][e] = 0.f;
-        floatx4 unused = zero4();
-        grad_contract_f32<float, false>(a, m0, n0 + hb * 128, kbeg, kend, (float*)&As[0][0],
-                                 (float*)&Bs[0][0], full, unused);
+          for (int e = 0; e < 16; ++e) full[i][j][e] = 0.f;
+      floatx4 unused = zero4();
+      grad_contract_f32<float, false>(a, m0, n0 + hb * 128, kbeg, kend, (float*)tiles_lds,
+                                      (float*)(tiles_lds + FEL), full, unused);
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j) acc[i][2 * hb + j] = full[i][j];
-      }
+        for (int j = 0; j < 2; ++j) acc[i][2 * hb + j] = full[i][j];
     }
   }
   // column sums of S: the four waves' sums of a column meet in LDS (the A tiles are free now)
-  float* red = reinterpret_cast<float*>(&As[0][0]);      // [4][GT] floats
+  float* red = reinterpret_cast<float*>(As);      // [4][GT] floats
   __syncthreads();
 #pragma unroll
   for (int e = 0; e < 2; ++e) red[wave * GT + m4 * 4 + 2 * lh + e] = colsum[e];
@@ -1743,18 +1828,17 @@ static int grad_splits(long long Ktot, int M, int N, int bf16) {
   return (int)best;
 }
 
-// Tile columns and row splits of the three-term kernel, at most `cap` splits (what the partials have room
+// Tile columns and row splits of the kernel on terms, at most `cap` splits (what the partials have room
 // for): the least of rounds over the 512 workgroup slots x (slices x us per slice + 10) + what the partials
-// cost.  us per slice of 32 rows, measured: a workgroup alone on its CU 2.17 (128 columns) and 3.45 (256), two
-// of them 2.9 and 5.1; partials are written and read at 6 TB/s.  Predicted : measured us of one gradient,
-// 128 / 256 columns at their best splits: 12800 rows, 1512 x 504 136 : 132 / 133 : 136; 4096, 1536 x 512
-// 58 : 54 / 65 : 59; 12800, 888 x 296 67 : 63 / 86 : 77; 8192, 3072 x 1024 331 : 319 / 296 : 292; 65536,
-// 1536 x 512 623 : 599 / 541 : 540.
+// cost.  us per slice of 32 rows, measured: a workgroup alone on its CU 1.62 (128 columns) and 2.3 (256), two
+// of them 1.97 and 3.2; partials are written and read at 6 TB/s.  Predicted : measured us of one gradient of
+// 65536 rows, 128 / 256 columns at their best splits: 1536 x 1024 820 : 805 / 687 : 680; 1536 x 512
+// 427 : 436 / 346 : 366; 3072 x 1024 1577 : 1592 / 1343 : 1235.
 struct GradX3 {
   int cols, splits;
 };
 static GradX3 grad_x3_shape(long long Ktot, int M, int N, int cap) {
-  constexpr double LONE[2] = {2.17, 3.45}, TWO[2] = {2.9, 5.1};
+  constexpr double LONE[2] = {1.62, 2.3}, TWO[2] = {1.97, 3.2};
   GradX3 best = {0, 1};
   double least = 0;
   for (int wide = 0; wide < (N > GT ? 2 : 1); ++wide) {

@@ -58,3 +58,30 @@ def test_rows_that_differ_from_their_first_slice(B, H, adj):
                 assert gh.rel_err(w[t, b], want[t, i]) <= 1e-5, ("w", b, t)
             else:
                 assert not np.asarray(w[t, b]).any(), ("w", b, t)
+
+
+@pytest.mark.parametrize("D", [72, 200])
+def test_columns_that_differ_from_their_last_slice(D):
+    """Weight gradients: the columns of both operands are scaled by what the last slice of 32 rows holds.
+    Inputs of zeros there (3), larger before by 2^14 (5) and smaller before by 2^14 (6); an adjoint column
+    (7, of all three gates) that starts at zero.  128-column tiles (D 72), both widths (D 200)."""
+    import gpu_harness as gh
+    print("fp16 terms, columns", D, flush=True)
+    steps, B, H = 64, 67, 136
+    d = random_small(12, steps, B, D, H, scale=0.3 / np.sqrt(H))
+    d["x"][-2:, :, 3] = 0
+    d["x"][-2:, :, 5] *= 2.0 ** -14
+    d["x"][:-2, :, 6] *= 2.0 ** -14
+    d["dL_dhT"][:, 7] = 0
+    P = (d["W"], d["U"], d["b_i"], d["b_h"])
+    h = orc.serial_scan(*P, d["x"], d["h0"]).astype(np.float32)
+    want = orc.serial_bptt(*P, d["x"], h, d["dL_dhT"])
+    run = gh.GpuRun(d)
+    box = []
+    gh.expect_kernels(lambda: box.append(run.serial_backward(h)), "grad_gemm_x3_kernel")
+    for name, g, r in zip(("w", "dW", "dU", "db_i", "db_h"), box[0], want):
+        assert gh.rel_err(g, r) <= 1e-5, name
+    for n in (3, 5, 6):
+        assert gh.rel_err(box[0][1][:, n], want[1][:, n]) <= 1e-5, ("dW", n)
+    for m in (7, H + 7, 2 * H + 7):
+        assert gh.rel_err(box[0][2][m], want[2][m]) <= 1e-5, ("dU", m)
