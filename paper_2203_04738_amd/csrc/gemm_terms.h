@@ -15,9 +15,12 @@
 // Range.  fp16 has five exponent bits, so every row of an operand is scaled by a power of two of its
 // own and the sums back, exactly: the rows of B, split once per call, by their largest value; a row of
 // A, split on its way to LDS, by the largest value of its first K-slice, which leaves the rest of the
-// row a factor of 2^9.  A row whose first slice is zero is read through for its largest value, and so
-// are all rows of a tile with a sum that is not finite; one that still has such a sum holds an operand
-// that is not finite itself and is contracted in fp32.  Subnormal terms keep their bits on this pipe;
+// row a factor of 2^9.  A row whose first slice is zero is scaled by 2^127: rows of zeros (H0, zero
+// guesses) and adjoints that have decayed to the smallest numbers are carried like that, anything else
+// overflows.  The rows of a tile with a sum that is not finite are read through for their largest
+// values; one that still has such a sum holds an operand that is not finite itself and is contracted
+// in fp32.  (Reading through every row that starts with zeros took 35 us in one tile of ten of an
+// adjoint over 2048 steps.)  Subnormal terms keep their bits on this pipe;
 // what is below them is 2^-31 of the row's largest value.
 //
 // Data path (16384 rows x 512, the level step: 145 us with three bf16 terms, 118 with two fp16 terms in
@@ -137,8 +140,7 @@ struct InOrder {
 };
 
 // Largest magnitude over the row behind chunk s of the calling thread: load(k), columns k..k+7 of the row, K
-// of them (the CPR lanes that share a row are neighbours).  Eight slices' loads at a time: a tile with
-// rows of zeros waits for this (H0, adjoints of a zero guess).
+// of them (the CPR lanes that share a row are neighbours).  Eight slices' loads at a time.
 template <class C>
 __device__ inline float over_row(float m) {
 #pragma unroll
@@ -159,7 +161,7 @@ __device__ inline float row_top(int s, int K, Load load) {
 }
 
 // One pass over K (a multiple of 8).  loadA, finA: as in gemm_nt_tile_bf16, called slice after slice;
-// order(i): first k of the i-th slice; top(s, through): row_top of the row behind chunk s; brow(g, c): packed row
+// order(i): first k of the i-th slice; top(s): row_top of the row behind chunk s; brow(g, c): packed row
 // (g, column c of the tile) of B; rowexp: LDS, receives the exponents the tile rows of A are scaled
 // by; through: find them from whole rows, not from first slices.
 template <class C, class LoadA, class Top, class FinA, class Order, class BRow>
@@ -197,7 +199,7 @@ __device__ inline void gemm_nt_tile_terms(TermAcc<C>& acc, int K, LoadA loadA, T
     for (int s = 0; s < C::A_CHUNKS; ++s) {
       const int q = tid + s * C::NT;
       float m = over_row<C>(top8(0.f, finA(ra[s])));
-      if (through || m == 0.f) m = top(s, through);
+      if (through) m = top(s);
       const int e = term_exponent(m, TERM_TOP_A);
       rowscale[s] = (q / C::CPR) & 1 ? -exp2_int(e) : exp2_int(e);
       if (q % C::CPR == 0) rowexp[q / C::CPR] = e;

@@ -271,17 +271,9 @@ __global__ __launch_bounds__(C::NT, C::MINWAVES) void adj_step_kernel_bf16(AdjAr
       }
       return KapW8{ldg4(krow[s] + k), ldg4(krow[s] + k + 4), wkeep[s].lo4, wkeep[s].hi4};
     };
-    // Rows of a zero guess, and those that decay below the smallest number (18 of 256 tiles of the last
-    // launch at 2048 steps), often have zeros in their first slice: they are scaled by w alone.
-    // k_d w is part of the result, so what is small next to w is small next to that; products of
-    // more than 2^9 times w overflow and are read through.
-    auto top = [&](int s, bool through) {
-      if (through) return row_top<C>(s, K, [&](int k) { return fa(la(s, k)); });
-      return row_top<C>(s, H,
-                        [&](int k) { return F32x8{ldg4(wrow[s] + k), ldg4(wrow[s] + k + 4)}; });
-    };
     contract_terms<C>(
-        acc, K, ordered, top, fa, a.UT3, H, urow, lds,
+        acc, K, ordered,
+        [&](int s) { return row_top<C>(s, K, [&](int k) { return fa(la(s, k)); }); }, fa, a.UT3, H, urow, lds,
         [&](int tr, int k) {
           const int kk = k >= 2 * H ? k - 2 * H : (k >= H ? k - H : k);
           return ldg4(a.kap + rowtab[tr].k + k) * ldg4(a.w_in + rowtab[tr].in + kk);
@@ -436,7 +428,7 @@ __global__ __launch_bounds__(C::NT, InTerms<C>::value ? C::MINWAVES : 1) void in
   if constexpr (C::NP == 3) {
     auto wrow_of = [&](int, int c) { return (long long)min(n0 + c, D - 1); };
     contract_terms<C>(
-        acc, K, la, [&](int s, bool) { return row_top<C>(s, K, [&](int k) { return fa(la(s, k)); }); }, fa,
+        acc, K, la, [&](int s) { return row_top<C>(s, K, [&](int k) { return fa(la(s, k)); }); }, fa,
         WT, D, wrow_of, lds,
         [&](int tr, int k) {
           const long long r = m0 + tr < R ? m0 + tr : R - 1;

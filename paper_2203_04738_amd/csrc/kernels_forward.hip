@@ -469,7 +469,7 @@ __global__ __launch_bounds__(C::NT, C::MINWAVES) void phi_step_kernel_bf16(PhiAr
   } else if constexpr (C::NP == 3) {
     auto urow = [&](int g, int c) { return (long long)g * H + min(n0 + c, H - 1); };
     contract_terms<C>(
-        acc, H, la, [&](int s, bool) { return row_top<C>(s, H, [&](int k) { return la(s, k); }); }, fa,
+        acc, H, la, [&](int s) { return row_top<C>(s, H, [&](int k) { return la(s, k); }); }, fa,
         a.U3, 3LL * H, urow, lds,
         [&](int tr, int k) { return ldg4(a.u_in + rowtab[tr].in + k); },
         [&](int g, int c) { return (const float*)a.U + urow(g, c) * H; });

@@ -238,7 +238,7 @@ __global__ __launch_bounds__(C::NT, 2) void lstm_step_kernel_x3(PhiArgs a) {
   auto urow = [&](int g, int c) { return (long long)g * H + min(n0 + c, H - 1); };
   auto la = [&](int s, int k) { return F32x8{ldg4(arow[s] + k), ldg4(arow[s] + k + 4)}; };
   contract_terms<C>(
-      acc, H, la, [&](int s, bool) { return row_top<C>(s, H, [&](int k) { return la(s, k); }); },
+      acc, H, la, [&](int s) { return row_top<C>(s, H, [&](int k) { return la(s, k); }); },
       [](const F32x8& v) { return v; }, a.U3, 4LL * H, urow, ldsf,
       [&](int tr, int k) { return ldg4(a.u_in + rowtab[tr].in + k); },
       [&](int g, int c) { return (const float*)a.U + urow(g, c) * H; });
