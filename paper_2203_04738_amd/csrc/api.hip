@@ -668,9 +668,11 @@ static int run_projection(const mgrit_gru_cfg* c, const Layout& lay, const Forms
   // GRU: three gates; demonstration ODE: one block; LSTM: four gates of the hidden width c->H / 2
   const int width = c->propagator == PROP_ODE_DEMO ? c->H
                     : prop_is_lstm(c->propagator) ? 2 * c->H : 3 * c->H;
-  if (f.proj == 2) CHECK_HIP(launch_split3((const float*)W, f.W3, (long long)width * c->D, s));
-  CHECK_HIP(launch_projection(x, W, f.W3, b_i, (float*)(base + lay.P), (long long)c->T * c->B,
-                              width, c->D, f.proj, s));
+  const long long rows = (long long)c->T * c->B;
+  const int form = f.proj == 2 && projection_is_wide(rows, width, c->D) ? 3 : f.proj;
+  if (form == 3) CHECK_HIP(launch_split3_pack((const float*)W, f.W3, width, c->D, s));
+  if (form == 2) CHECK_HIP(launch_split3((const float*)W, f.W3, (long long)width * c->D, s));
+  CHECK_HIP(launch_projection(x, W, f.W3, b_i, (float*)(base + lay.P), rows, width, c->D, form, s));
   return MGRIT_OK;
 }
 

@@ -139,10 +139,12 @@ hipError_t launch_adj_sweep(const AdjArgs& first, int n, int mid, int last, hipS
                             const float* coarse = nullptr);
 
 // P[M,N] = X[M,K] W[N,K]^T + bias[N]
-// X, W: float (bf16 = 0) or bf16 (bf16 = 1); bf16 = 2: X, W float, W3 the three bf16 terms
-// [3][N,K] of the weights (otherwise not read)
+// X, W: float (bf16 = 0) or bf16 (bf16 = 1); bf16 = 2, 3: X, W float, W3 the three bf16 terms of the
+// weights, [3][N,K] (launch_split3) / packed (launch_split3_pack), otherwise not read
 hipError_t launch_projection(const void* X, const void* W, const void* W3, const float* bias,
                              float* P, long long M, int N, int K, int bf16, hipStream_t s);
+// whether a projection of fp32 operands in terms takes the packed ones (128 x 256 tiles)
+bool projection_is_wide(long long M, int N, int K);
 // UT[H,3H] = U[3H,H]^T; elements are 4 bytes (bf16 = 0) or 2 bytes
 hipError_t launch_transpose(const void* U, void* UT, int rows, int cols, int bf16, hipStream_t s);
 
@@ -168,6 +170,8 @@ hipError_t launch_input_grads(const float* kap0, const float* w, const void* WT,
 // dst[t][i] (t = 0..2, bf16) = t-th term of 2^24 src[i] (exactly: see gemm_core_bf16.h); n a multiple
 // of 4
 hipError_t launch_split3(const float* src, void* dst, long long n, hipStream_t s);
+// the same terms of src[rows][K], packed (see gemm_terms.h); rows and K multiples of 8
+hipError_t launch_split3_pack(const float* src, void* dst, int rows, int K, hipStream_t s);
 // Weights src[rows][K] as the step and input-gradient kernels read them with bf16 = 2: packed fp16 terms
 // (see gemm_terms.h); rows and K multiples of 8, dst of 4 rows (K + 1) bytes.
 hipError_t launch_split2(const float* src, void* dst, int rows, int K, hipStream_t s);

@@ -52,14 +52,24 @@ __device__ inline void minus2_f16(float& a, float& b, unsigned r) {
 }
 // Terms of pair i (0..3) of eight values: t0 + t1 = v f up to 2^-22.
 struct Words8 {
-  unsigned t0[4], t1[4];           // eight values' terms, two to a word
+  unsigned t[3][4];                // eight values' terms, two to a word
 };
 __device__ inline void split_pair(const F32x8& v, int i, float f, Words8& w) {
   float a = (i < 2 ? v.lo4[2 * i] : v.hi4[2 * i - 4]) * f;
   float b = (i < 2 ? v.lo4[2 * i + 1] : v.hi4[2 * i - 3]) * f;
-  w.t0[i] = round2_f16(a, b);
-  minus2_f16(a, b, w.t0[i]);
-  w.t1[i] = round2_f16(a, b);
+  w.t[0][i] = round2_f16(a, b);
+  minus2_f16(a, b, w.t[0][i]);
+  w.t[1][i] = round2_f16(a, b);
+}
+// The same in three bf16 terms, exactly (gemm_core_bf16.h).
+__device__ inline void split_pair_bf16(const F32x8& v, int i, float f, Words8& w) {
+  float a = (i < 2 ? v.lo4[2 * i] : v.hi4[2 * i - 4]) * f;
+  float b = (i < 2 ? v.lo4[2 * i + 1] : v.hi4[2 * i - 3]) * f;
+#pragma unroll
+  for (int t = 0; t < 3; ++t) {
+    w.t[t][i] = round2_bf16(a, b);
+    if (t < 2) minus2_bf16(a, b, w.t[t][i]);
+  }
 }
 __device__ inline f16x8 words8(const unsigned (&w)[4]) {
   typedef unsigned uintx4_ __attribute__((ext_vector_type(4)));
@@ -82,10 +92,10 @@ constexpr int TERM_TOP_A = 6, TERM_TOP_B = 13;
 
 // Packed terms of B[rows][K] (rows, K multiples of 8): chunks of eight k of a row, 16 bytes, ordered
 // [row / 8][k / 8][term][row % 8], so that the 16 rows x 32 k that a wave loads at once are whole
-// 128-byte lines, its two terms side by side; behind them the rows' exponents, int[rows].
-constexpr int PACK_TERM = 128, PACK_K8 = 256;             // bytes from term to term, from k / 8 to the next
-__host__ __device__ inline size_t pack_row(long long row, int K) {
-  return (size_t)(row >> 3) * (K >> 3) * PACK_K8 + (row & 7) * 16;
+// 128-byte lines, its terms side by side; behind two terms the rows' exponents, int[rows].
+constexpr int PACK_TERM = 128;                            // bytes from term to term
+__host__ __device__ inline size_t pack_row(long long row, int K, int terms) {
+  return (size_t)(row >> 3) * (K >> 3) * (PACK_TERM * terms) + (row & 7) * 16;
 }
 __device__ inline const int* pack_exponents(const void* pack, long long rows, int K) {
   return reinterpret_cast<const int*>((const char*)pack + (size_t)rows * K * 4);
@@ -99,9 +109,12 @@ struct TermGeom {
   static constexpr int WR = NW > 4 && C::TN <= 128 ? 2 : 1, WC = NW / WR;
   static constexpr int RB = C::TM / 16 / WR, CB = C::TN / 16 / WC;
   static constexpr int NF = C::NG * CB;                   // B fragments per term and slice
-  static constexpr int GB = NF >= 3 ? 1 : 2;              // row blocks whose MFMAs alternate
+  // terms per operand: with LOSUM three bf16 terms and six products, the lower five summed apart
+  static constexpr bool X3 = C::LOSUM;
+  static constexpr int NTM = X3 ? 3 : 2;
+  static constexpr int GB = NF >= 3 || X3 ? 1 : 2;        // row blocks whose MFMAs alternate
   static constexpr int BLK = C::TM / 16;                  // row blocks of the tile
-  static constexpr int BUF = C::KS * 2 * BLK * 64;        // 16-byte chunks of one slice of A
+  static constexpr int BUF = C::KS * NTM * BLK * 64;        // 16-byte chunks of one slice of A
   static_assert(RB * WR * 16 == C::TM && CB * WC * 16 == C::TN, "waves must cover the tile");
   static_assert(C::TK == 32 * C::KS && RB % GB == 0, "");
 };
@@ -181,11 +194,11 @@ __device__ inline void gemm_nt_tile_terms(TermAcc<C>& acc, int K, LoadA loadA, T
   for (int g = 0; g < C::NG; ++g)
 #pragma unroll
     for (int c = 0; c < G::CB; ++c)
-      bo[g][c] = (unsigned)pack_row(brow(g, me.col0 + c * 16 + me.li), K);
-  f16x8 rb[2][2][C::NG][G::CB];                 // [slice % 2][term]
-  constexpr int NLB = 2 * C::NG * G::CB;        // loads of B per slice
+      bo[g][c] = (unsigned)pack_row(brow(g, me.col0 + c * 16 + me.li), K, G::NTM);
+  f16x8 rb[2][G::NTM][C::NG][G::CB];                 // [slice % 2][term]
+  constexpr int NLB = G::NTM * C::NG * G::CB, PACK_K8 = PACK_TERM * G::NTM;        // loads of B per slice
   auto fetch_b = [&](int d, int j, int k0) {
-    const int g = j / 2 / G::CB, c = j / 2 % G::CB, t = j % 2;
+    const int g = j / G::NTM / G::CB, c = j / G::NTM % G::CB, t = j % G::NTM;
     // (columns beyond K, a whole K-split group of them in the last slice: those of the last k / 8)
     const int k8 = min(k0 / 8 + me.ks * 4, K / 8 - 1);
     const unsigned lane = (unsigned)min(me.lq, K / 8 - 1 - k8) * PACK_K8;
@@ -198,6 +211,10 @@ __device__ inline void gemm_nt_tile_terms(TermAcc<C>& acc, int K, LoadA loadA, T
 #pragma unroll
     for (int s = 0; s < C::A_CHUNKS; ++s) {
       const int q = tid + s * C::NT;
+      if constexpr (G::X3) {
+        rowscale[s] = (q / C::CPR) & 1 ? -SPLIT3_SCALE : SPLIT3_SCALE;
+        continue;
+      }
       float m = over_row<C>(top8(0.f, finA(ra[s])));
       if (through) m = top(s);
       const int e = term_exponent(m, TERM_TOP_A);
@@ -211,27 +228,51 @@ __device__ inline void gemm_nt_tile_terms(TermAcc<C>& acc, int K, LoadA loadA, T
   auto convert = [&](int j, int k0) {           // pair j of the thread's 4 A_CHUNKS
     const int s = j / 4, c = (tid + s * C::NT) % C::CPR;
     // (columns beyond K: zeros, or what makes the tile one that is not finite)
-    split_pair(finA(ra[s]), j % 4, k0 + c * 8 < K ? rowscale[s] : 0.f, aw[s]);
+    const float f = k0 + c * 8 < K ? rowscale[s] : 0.f;
+    if constexpr (G::X3)
+      split_pair_bf16(finA(ra[s]), j % 4, f, aw[s]);
+    else
+      split_pair(finA(ra[s]), j % 4, f, aw[s]);
   };
   auto stash = [&](int p, int s) {
     const int q = tid + s * C::NT, row = q / C::CPR, c = q % C::CPR;
-    const int at = p * G::BUF + (c / 4) * 2 * G::BLK * 64 + (row / 16) * 64 + (c % 4) * 16 +
+    const int at = p * G::BUF + (c / 4) * G::NTM * G::BLK * 64 + (row / 16) * 64 + (c % 4) * 16 +
                    ((row & 15) ^ (2 * (c % 4)));
-    lds[at] = words8(aw[s].t0);
-    lds[at + G::BLK * 64] = words8(aw[s].t1);
+#pragma unroll
+    for (int t = 0; t < G::NTM; ++t) lds[at + t * G::BLK * 64] = words8(aw[s].t[t]);
   };
-  const int a_at = me.ks * 2 * G::BLK * 64 + (me.row0 / 16) * 64 + me.lq * 16 + (me.li ^ (2 * me.lq));
+  const int a_at = me.ks * G::NTM * G::BLK * 64 + (me.row0 / 16) * 64 + me.lq * 16 + (me.li ^ (2 * me.lq));
   auto read_a = [&](int p, int r, int t) {
     return lds[p * G::BUF + a_at + t * G::BLK * 64 + r * 64];
   };
-  typedef f16x8 Frags[2][G::GB];                // [term][row block]
+  typedef f16x8 Frags[G::NTM][G::GB];                // [term][row block]
   auto read_group = [&](int p, int r0, Frags& f) {
 #pragma unroll
     for (int i = 0; i < G::GB; ++i)
 #pragma unroll
-      for (int t = 0; t < 2; ++t) f[t][i] = read_a(p, r0 + i, t);
+      for (int t = 0; t < G::NTM; ++t) f[t][i] = read_a(p, r0 + i, t);
   };
+  TermAcc<C> lo;                                // (X3: the lower products)
+  if constexpr (G::X3) lo.zero();
   auto multiply = [&](int d, int r0, const Frags& f) {
+    if constexpr (G::X3) {
+      auto mm = [&](TermAcc<C>& sum, int t, int u) {
+#pragma unroll
+        for (int g = 0; g < C::NG; ++g)
+#pragma unroll
+          for (int c = 0; c < G::CB; ++c)
+            sum.v[r0][g][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(bf16x8, f[t][0]), __builtin_bit_cast(bf16x8, rb[d][u][g][c]),
+                sum.v[r0][g][c], 0, 0, 0);
+      };
+      mm(lo, 2, 0);
+      mm(acc, 0, 0);
+      mm(lo, 1, 0);
+      mm(lo, 0, 1);
+      mm(lo, 1, 1);
+      mm(lo, 0, 2);
+      return;
+    }
 #pragma unroll
     for (int u = 0; u < 3; ++u)                // a0 b0, a1 b0, a0 b1
 #pragma unroll
@@ -318,6 +359,18 @@ __device__ inline void gemm_nt_tile_terms(TermAcc<C>& acc, int K, LoadA loadA, T
     slice(odd, kt + 1);
   }
   if (kt < nkt) slice(even, kt);
+  if constexpr (G::X3) {
+#pragma unroll
+    for (int r = 0; r < G::RB; ++r)
+#pragma unroll
+      for (int g = 0; g < C::NG; ++g)
+#pragma unroll
+        for (int c = 0; c < G::CB; ++c) {
+          acc.v[r][g][c] += lo.v[r][g][c];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc.v[r][g][c][e] *= e & 1 ? -SPLIT3_UNSCALE : SPLIT3_UNSCALE;
+        }
+  }
 }
 
 // Whether any sum of the workgroup's tile is not finite (the same answer in every thread).  A value
@@ -434,6 +487,37 @@ __device__ inline void stage_write_terms(const TermAcc<C>& acc, int ba, float* s
         for (int e = 0; e < 4; ++e)
           stage[me.ks * E::SLAB + (g * E::ROWS + row + e) * E::LD + me.col0 + c * 16 + me.li] =
               acc.v[r][g][c][e];
+  }
+}
+
+// The same on three bf16 terms (LOSUM).
+template <class C, class LoadA, class FinA, class BRow, class LoadA4, class FRow>
+__device__ inline void contract_terms_x3(TermAcc<C>& acc, int K, LoadA la, FinA fa, const void* pack,
+                                         BRow brow, void* lds, LoadA4 load_a, FRow frow) {
+  acc.zero();
+  gemm_nt_tile_terms<C>(acc, K, la, [](int) { return 0.f; }, fa, InOrder<C>(), (const char*)pack,
+                        brow, (f16x8*)lds, nullptr, false);
+  if (tile_not_finite<C>(acc)) contract_f32<C>(acc, K, load_a, frow);
+}
+
+// Stores the tile of a plain GEMM: out[m, n] + bias[n], leading dimension N.
+template <class C>
+__device__ inline void store_tile_terms(const TermAcc<C>& acc, float* out, const float* bias,
+                                        long long m0, int n0, long long M, int N) {
+  typedef TermGeom<C> G;
+  const TermLane<C> me;
+#pragma unroll
+  for (int c = 0; c < G::CB; ++c) {
+    const int n = n0 + me.col0 + c * 16 + me.li;
+    if (n >= N) continue;
+    const float b = bias ? bias[n] : 0.f;
+#pragma unroll
+    for (int r = 0; r < G::RB; ++r) {
+      const long long m = m0 + me.row0 + r * 16 + 4 * me.lq;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (m + e < M) out[(m + e) * N + n] = acc.v[r][0][c][e] + b;
+    }
   }
 }
 

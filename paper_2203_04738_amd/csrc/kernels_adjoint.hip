@@ -335,23 +335,6 @@ __device__ inline void store_tile(const Acc<C>& acc, float* out, long long m0, i
     }
 }
 
-template <class C>
-__device__ inline void store_tile_terms(const TermAcc<C>& acc, float* out, long long m0,
-                                        int n0, long long M, int N) {
-  typedef TermGeom<C> G;
-  const TermLane<C> me;
-#pragma unroll
-  for (int r = 0; r < G::RB; ++r)
-#pragma unroll
-    for (int c = 0; c < G::CB; ++c) {
-      const int n = n0 + me.col0 + c * 16 + me.li;
-      const long long m = m0 + me.row0 + r * 16 + 4 * me.lq;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (n < N && m + e < M) out[(m + e) * N + n] = acc.v[r][0][c][e];
-    }
-}
-
 __global__ __launch_bounds__(DxCfg::NT) void input_grad_kernel(
     const float* __restrict__ kap0, const float* __restrict__ w, const float* __restrict__ WT,
     float* __restrict__ dx, long long R, int B, int H, int D) {
@@ -453,7 +436,7 @@ __global__ __launch_bounds__(C::NT, InTerms<C>::value ? C::MINWAVES : 1) void in
       gemm_nt_tile_bf16<C, true>(acc, K, la, lb, fa, lds);
   }
   if constexpr (InTerms<C>::value)
-    store_tile_terms<C>(acc, dx, m0, n0, R, D);
+    store_tile_terms<C>(acc, dx, nullptr, m0, n0, R, D);
   else
     store_tile<C>(acc, dx, m0, n0, R, D);
 }

@@ -148,10 +148,53 @@ __global__ __launch_bounds__(C::NT, C::NP == 3 ? 2 : 1) void projection_kernel_b
     }
 }
 
+// The same by the data path of gemm_terms.h, W as packed terms: tiles of 128 x 256, 8 waves.  The split of X
+// and the loads of W are paid per column tile, twice as wide here: 65536 rows, 1024 -> 1536 columns 1.12 ->
+// 0.97 ms (212 TFLOP/s), 12800 rows, 1000 -> 3000 0.52 -> 0.40.  Same products, same errors.  Launches that leave CUs empty, and widths of one and a half such
+// tiles or less, keep the 128 x 128 tiles.
+typedef TileCfgB<2, 4, 2, 2, 1, true, 1, 1, 1, 3, 32, true, true> ProjCfgW;
+
+__global__ __launch_bounds__(ProjCfgW::NT, 2) void projection_kernel_wide(
+    const float* __restrict__ X, const void* __restrict__ Wt, const float* __restrict__ W,
+    const float* __restrict__ bias, float* __restrict__ P, long long M, int N, int K) {
+  typedef ProjCfgW C;
+  __shared__ f16x8 lds[3 * TermGeom<C>::BUF];
+  long long rt;
+  int ct;
+  if (!xcd_tile(blockIdx.x, (M + C::TM - 1) / C::TM, (N + C::TN - 1) / C::TN, rt, ct)) return;
+  const long long m0 = rt * C::TM;
+  const int n0 = ct * C::TN;
+  const float* arow[C::A_CHUNKS];
+#pragma unroll
+  for (int s = 0; s < C::A_CHUNKS; ++s) {
+    const long long r = m0 + chunk_row_b<C>(s);
+    arow[s] = X + (r < M ? r : M - 1) * K;
+  }
+  TermAcc<C> acc;
+  auto wrow = [&](int, int c) { return (long long)min(n0 + c, N - 1); };
+  contract_terms_x3<C>(
+      acc, K, [&](int s, int k) { return F32x8{ldg4(arow[s] + k), ldg4(arow[s] + k + 4)}; },
+      [](const F32x8& v) { return v; }, Wt, wrow, lds,
+      [&](int r, int k) { return ldg4(X + (m0 + r < M ? m0 + r : M - 1) * K + k); },
+      [&](int g, int c) { return W + wrow(g, c) * K; });
+  store_tile_terms<C>(acc, P, bias, m0, n0, M, N);
+}
+
+bool projection_is_wide(long long M, int N, int K) {
+  typedef ProjCfgW C;
+  return N >= 384 && ((M + C::TM - 1) / C::TM) * ((N + C::TN - 1) / C::TN) >= 192 &&
+         6LL * N * K < (1LL << 32);
+}
+
 hipError_t launch_projection(const void* X, const void* W, const void* W3, const float* bias,
                              float* P, long long M, int N, int K, int bf16, hipStream_t s) {
   prof_begin(2, s);
-  if (bf16 == 2) {
+  if (bf16 == 3) {
+    typedef ProjCfgW C;
+    dim3 grid((unsigned)xcd_grid((M + C::TM - 1) / C::TM, (N + C::TN - 1) / C::TN));
+    hipLaunchKernelGGL(projection_kernel_wide, grid, dim3(C::NT), 0, s, (const float*)X, W3,
+                       (const float*)W, bias, P, M, N, K);
+  } else if (bf16 == 2) {
     typedef ProjCfgS C;
     dim3 grid((unsigned)xcd_grid((M + C::TM - 1) / C::TM, (N + C::TN - 1) / C::TN));
     hipLaunchKernelGGL(projection_kernel_bf16<C>, grid, dim3(C::NT), 0, s, X, (const bf16_t*)W3,

@@ -118,13 +118,14 @@ __global__ __launch_bounds__(256) void split2_kernel(const float* __restrict__ s
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
   const int e = term_exponent(m, TERM_TOP_B);
-  char* q = dst + pack_row(row, K);
+  char* q = dst + pack_row(row, K, 2);
   for (int k = lane * 8; k < K; k += 512) {
     Words8 w;
 #pragma unroll
     for (int i = 0; i < 4; ++i) split_pair(F32x8{ldg4(p + k), ldg4(p + k + 4)}, i, exp2_int(e), w);
-    *reinterpret_cast<f16x8*>(q + (size_t)(k >> 3) * PACK_K8) = words8(w.t0);
-    *reinterpret_cast<f16x8*>(q + (size_t)(k >> 3) * PACK_K8 + PACK_TERM) = words8(w.t1);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+      *reinterpret_cast<f16x8*>(q + (size_t)(k >> 3) * 2 * PACK_TERM + t * PACK_TERM) = words8(w.t[t]);
   }
   if (lane == 0) const_cast<int*>(pack_exponents(dst, rows, K))[row] = e;
 }
@@ -132,6 +133,31 @@ __global__ __launch_bounds__(256) void split2_kernel(const float* __restrict__ s
 hipError_t launch_split2(const float* src, void* dst, int rows, int K, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
   hipLaunchKernelGGL(split2_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, src,
+                     (char*)dst, rows, K);
+  return hipGetLastError();
+}
+
+// Packed bf16 terms (three, gemm_terms.h) of weights src[rows][K], eight values per thread.
+__global__ __launch_bounds__(256) void split3_pack_kernel(const float* __restrict__ src,
+                                                          char* __restrict__ dst, int rows, int K) {
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (long long)rows * (K >> 3)) return;
+  const long long row = i / (K >> 3);
+  const int k8 = (int)(i - row * (K >> 3));
+  const float* p = src + row * K + k8 * 8;
+  char* q = dst + pack_row(row, K, 3) + (size_t)k8 * 3 * PACK_TERM;
+  const F32x8 v{ldg4(p), ldg4(p + 4)};
+  Words8 w;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) split_pair_bf16(v, j, SPLIT3_SCALE, w);
+#pragma unroll
+  for (int t = 0; t < 3; ++t) *reinterpret_cast<f16x8*>(q + t * PACK_TERM) = words8(w.t[t]);
+}
+
+hipError_t launch_split3_pack(const float* src, void* dst, int rows, int K, hipStream_t s) {
+  const long long n = (long long)rows * (K >> 3);
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(split3_pack_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, src,
                      (char*)dst, rows, K);
   return hipGetLastError();
 }

@@ -1,8 +1,9 @@
-"""Scales of the rows in the step kernels' fp16 terms (gemm_terms.h): rows whose first K-slice says nothing
-about the rest of them, in every tile.  (The tiles themselves, their tails and their fp32 repetition:
-test_gpu_term_tiles.py.)"""
+"""Operands in terms (gemm_terms.h) beyond what test_gpu_term_tiles.py holds: scales of the fp16 terms' rows,
+whose first K-slice says nothing about the rest of them, in every tile of the steps, and of the columns of
+the weight gradients; the wide tiles of the adjoint and the projection."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import mgrit_gru_oracle as orc
 from synthetic_inputs import random_small
@@ -85,3 +86,21 @@ def test_columns_that_differ_from_their_last_slice(D):
         assert gh.rel_err(box[0][1][:, n], want[1][:, n]) <= 1e-5, ("dW", n)
     for m in (7, H + 7, 2 * H + 7):
         assert gh.rel_err(box[0][2][m], want[2][m]) <= 1e-5, ("dU", m)
+
+
+@pytest.mark.parametrize("value", [None, 3.4e38])
+def test_wide_projection(value):
+    """128 x 256 tiles on three bf16 terms, packed weights: rows, columns (600) and K (136) with tails; one
+    input beyond the terms, whose tiles are contracted again in fp32."""
+    import gpu_harness as gh
+    print("wide projection", value, flush=True)
+    B, D, H = 1363, 136, 200
+    d = random_small(13, T, B, D, H, scale=0.5 / np.sqrt(H))
+    if value:
+        d["x"][2, 5, 11] = value
+    run = gh.GpuRun(d, cf=CF, levels=2)
+    gh.expect_kernels(lambda: run.forward_iterates(1), "projection_kernel_wide")
+    got = run.ws[:T * B * 3 * H * 4].view(torch.float32).view(T * B, 3 * H).cpu().numpy()
+    want = orc.input_projection(d["W"], d["b_i"], d["x"]).reshape(T * B, 3 * H)
+    top = np.max(np.abs(want), axis=1, keepdims=True)
+    assert np.all(np.abs(got.astype(np.float64) - want) <= 1e-5 * top)
