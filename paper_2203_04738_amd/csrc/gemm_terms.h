@@ -223,7 +223,7 @@ __device__ inline void gemm_nt_tile_terms(TermAcc<C>& acc, int K, LoadA loadA, T
     }
   };
   // A in LDS: [slice % 3][K-split group][term][row block][k / 8][row % 16], the rows of a k / 8 exchanged
-  // by it, so that the eight lanes of two rows write to different banks
+  // by it and by the group, so that eight lanes (two rows, or one of both groups) write to different banks
   Words8 aw[C::A_CHUNKS];
   auto convert = [&](int j, int k0) {           // pair j of the thread's 4 A_CHUNKS
     const int s = j / 4, c = (tid + s * C::NT) % C::CPR;
@@ -237,11 +237,12 @@ __device__ inline void gemm_nt_tile_terms(TermAcc<C>& acc, int K, LoadA loadA, T
   auto stash = [&](int p, int s) {
     const int q = tid + s * C::NT, row = q / C::CPR, c = q % C::CPR;
     const int at = p * G::BUF + (c / 4) * G::NTM * G::BLK * 64 + (row / 16) * 64 + (c % 4) * 16 +
-                   ((row & 15) ^ (2 * (c % 4)));
+                   ((row & 15) ^ (2 * (c % 4)) ^ (c / 4));
 #pragma unroll
     for (int t = 0; t < G::NTM; ++t) lds[at + t * G::BLK * 64] = words8(aw[s].t[t]);
   };
-  const int a_at = me.ks * G::NTM * G::BLK * 64 + (me.row0 / 16) * 64 + me.lq * 16 + (me.li ^ (2 * me.lq));
+  const int a_at = me.ks * G::NTM * G::BLK * 64 + (me.row0 / 16) * 64 + me.lq * 16 +
+                   (me.li ^ (2 * me.lq) ^ me.ks);
   auto read_a = [&](int p, int r, int t) {
     return lds[p * G::BUF + a_at + t * G::BLK * 64 + r * 64];
   };
@@ -500,25 +501,27 @@ __device__ inline void contract_terms_x3(TermAcc<C>& acc, int K, LoadA la, FinA 
   if (tile_not_finite<C>(acc)) contract_f32<C>(acc, K, load_a, frow);
 }
 
-// Stores the tile of a plain GEMM: out[m, n] + bias[n], leading dimension N.
+// Stores the tile of a plain GEMM: out[m, n] + bias[n], leading dimension N.  A wave's two column blocks
+// exchange every other quad of rows first, so that a store covers whole 128-byte lines of two rows (lines
+// in halves: 559 MB written where 403 are the projection of 65536 x 1536).
 template <class C>
 __device__ inline void store_tile_terms(const TermAcc<C>& acc, float* out, const float* bias,
                                         long long m0, int n0, long long M, int N) {
   typedef TermGeom<C> G;
+  static_assert(G::CB == 2 && C::NG == 1, "");
   const TermLane<C> me;
+  const int n = n0 + me.col0 + (me.lq & 1) * 16 + me.li;
+  const float b = bias && n < N ? bias[n] : 0.f;
 #pragma unroll
-  for (int c = 0; c < G::CB; ++c) {
-    const int n = n0 + me.col0 + c * 16 + me.li;
-    if (n >= N) continue;
-    const float b = bias ? bias[n] : 0.f;
+  for (int r = 0; r < G::RB; ++r)
 #pragma unroll
-    for (int r = 0; r < G::RB; ++r) {
-      const long long m = m0 + me.row0 + r * 16 + 4 * me.lq;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (m + e < M) out[(m + e) * N + n] = acc.v[r][0][c][e] + b;
+    for (int e = 0; e < 4; ++e) {
+      const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc.v[r][0][0][e]),
+                                                      __float_as_uint(acc.v[r][0][1][e]), false, false);
+      const long long m = m0 + me.row0 + r * 16 + 4 * (me.lq & 2) + e;
+      if (n < N && m < M) out[m * N + n] = __uint_as_float(x[0]) + b;
+      if (n < N && m + 4 < M) out[(m + 4) * N + n] = __uint_as_float(x[1]) + b;
     }
-  }
 }
 
 // Sums of the workgroup tile of a kernel of configuration C (TileCfg or TileCfgB).

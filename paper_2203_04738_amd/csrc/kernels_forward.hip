@@ -150,7 +150,7 @@ __global__ __launch_bounds__(C::NT, C::NP == 3 ? 2 : 1) void projection_kernel_b
 
 // The same by the data path of gemm_terms.h, W as packed terms: tiles of 128 x 256, 8 waves.  The split of X
 // and the loads of W are paid per column tile, twice as wide here: 65536 rows, 1024 -> 1536 columns 1.12 ->
-// 0.97 ms (212 TFLOP/s), 12800 rows, 1000 -> 3000 0.52 -> 0.40.  Same products, same errors.  Launches that leave CUs empty, and widths of one and a half such
+// 0.93 ms (222 TFLOP/s), 12800 rows, 1000 -> 3000 0.52 -> 0.38.  Same products, same errors.  Launches that leave CUs empty, and widths of one and a half such
 // tiles or less, keep the 128 x 128 tiles.
 typedef TileCfgB<2, 4, 2, 2, 1, true, 1, 1, 1, 3, 32, true, true> ProjCfgW;
 
