@@ -24,16 +24,23 @@ if ROOT not in sys.path:
 MI355X_PEAK = {"hbm_GBps": 8000.0, "fp32_TFLOPs": 157.3, "bf16_TFLOPs": 2500.0}
 
 
-def fp32_peak(T, B, H, D, cf, levels):
+def products(kind):
+    """16-bit products per multiply-add of the kernels on terms: the projection (kind 2) contracts three
+    bf16 terms per operand, the others two fp16 terms."""
+    return 6.0 if kind == 2 else 3.0
+
+
+def fp32_peak(T, B, H, D, cf, levels, kind=0):
     """Matrix peak that bounds the algorithmic flops of an fp32 GRU / LSTM problem: problems that the
-    library contracts as three bf16 terms (six bf16 products per multiply-add) are priced against a
-    sixth of the bf16 peak, the others against the fp32 peak (the rule is MGRIT_F32's, see
+    library contracts in 16-bit terms (three products per multiply-add, six in the projection) are
+    priced against a third or a sixth of the 16-bit peak, the others against the fp32 peak (the rule is MGRIT_F32's, see
     include/mgrit_gru.h; its last condition, that the terms fit the gradient partials, holds from a few
     thousand steps x batch on; layers of 128 columns take their steps in the fp32 sweep kernel up to
     8192 rows)."""
     rows = T * B // (cf if levels > 1 else 1)
     terms = H % 8 == 0 and rows >= 1024 and (H > 128 or (H == 128 and rows > 8192))
-    return MI355X_PEAK["bf16_TFLOPs"] / 6.0 if terms else MI355X_PEAK["fp32_TFLOPs"]
+    return (MI355X_PEAK["bf16_TFLOPs"] / products(kind) if terms
+            else MI355X_PEAK["fp32_TFLOPs"])
 
 
 def parse():
@@ -67,8 +74,8 @@ def parse():
     ap.add_argument("--train-steps", type=int, default=300)
     ap.add_argument("--operands", choices=["stored", "bf16x3"], default="stored",
                     help="stored: the workload's own form (fp32 or bf16 MFMA).  bf16x3 (fp32 "
-                         "workloads): the tile kernels contract the fp32 operands as three bf16 "
-                         "terms each on the bf16 matrix pipe (same inputs, same parity bar)")
+                         "workloads): the tile kernels contract the fp32 operands in 16-bit "
+                         "terms on the 16-bit matrix pipe (same inputs, same parity bar)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-serial", action="store_true")
     ap.add_argument("--no-side-workloads", action="store_true",
@@ -89,7 +96,7 @@ def kernel_sources_sha256():
     import re
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2203_04738_amd", "csrc")
-    for f in ("common.h", "gates.h", "gemm_core.h", "gemm_core_bf16.h", "phi_elem.h",
+    for f in ("common.h", "gates.h", "gemm_core.h", "gemm_core_bf16.h", "gemm_terms.h", "phi_elem.h",
               "kernels_forward.hip"):
         text = open(os.path.join(csrc, f), "r").read()
         text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
@@ -322,7 +329,7 @@ def stack_main(args):
         "value": T * B / sec, "unit": "time-steps*batch/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": 1e3 * sec, "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None,
-        "dtype": "f32 as 3 bf16 terms (bf16 MFMA, f32 accumulate)" if x3 else "f32",
+        "dtype": "f32 in 16-bit terms (fp16 / bf16 MFMA, f32 accumulate)" if x3 else "f32",
         "data": "synthetic",
         "config": {"workload": f"{wl.name} x {L} layers: T={T} B={B} D={wl.D} H={H} cf={wl.cf} "
                                f"levels={wl.levels} fwd_iters={fwd_iters} bwd_iters={bwd_iters} per layer, "
@@ -835,7 +842,7 @@ def run_workload(args, light=False):
                                       else "cycle limit N_1/2")}
         del ws0, hs, hh
 
-    # the form timed beside the main one: fp32 workloads, three bf16 terms per operand; bf16
+    # the form timed beside the main one: fp32 workloads, operands in 16-bit terms; bf16
     # workloads, the fp32 state operand as two bf16 terms (MGRIT_BF16_STATE2)
     other = None
     if not x3 and not light:
@@ -939,11 +946,12 @@ def run_workload(args, light=False):
                 kernels[nm]["us_per_step_of_batch"] = 1e3 * ms / (fl / (6.0 * B * H * H))
             if kind in (0, 1, 2, 3):
                 kernels[nm]["frac_of_mfma_peak"] = fl / ms / 1e9 / (
-                    fp32_peak(T, B, H, wl.D, wl.cf, wl.levels) if dtype_code == 0
+                    fp32_peak(T, B, H, wl.D, wl.cf, wl.levels, kind) if dtype_code == 0
                     else MI355X_PEAK["bf16_TFLOPs"])
-                if x3:   # six bf16 MFMA products per algorithmic multiply-add
-                    kernels[nm]["issued_TFLOPs"] = 6.0 * fl / ms / 1e9
-                    kernels[nm]["issued_frac_of_mfma_peak"] = 6.0 * kernels[nm]["frac_of_mfma_peak"]
+                if x3:   # 16-bit MFMA products per algorithmic multiply-add
+                    kernels[nm]["issued_TFLOPs"] = products(kind) * fl / ms / 1e9
+                    kernels[nm]["issued_frac_of_mfma_peak"] = (products(kind) *
+                                                               kernels[nm]["frac_of_mfma_peak"])
             if kind == 7:
                 kernels[nm]["frac_of_hbm_peak"] = by / ms / 1e6 / MI355X_PEAK["hbm_GBps"]
     # whole step against the matrix-core peak: flops of all library kernels / step time
@@ -984,10 +992,10 @@ def run_workload(args, light=False):
                     "launches_per_step": dom["launches_per_step"],
                     "all_launch_shapes_TFLOPs": kernels[names[0]]["TFLOPs"]}
         if x3:
-            # the pipe runs six bf16 products per algorithmic multiply-add: frac prices the
-            # algorithmic flops against the bf16 peak, issued_frac the MFMA work actually done
-            roofline["issued_TFLOPs"] = 6.0 * dom["TFLOPs"]
-            roofline["issued_frac"] = 6.0 * dom["TFLOPs"] / peak
+            # the pipe runs three fp16 products per algorithmic multiply-add: frac prices the
+            # algorithmic flops against the 16-bit peak, issued_frac the MFMA work actually done
+            roofline["issued_TFLOPs"] = products(0) * dom["TFLOPs"]
+            roofline["issued_frac"] = products(0) * dom["TFLOPs"] / peak
             roofline["frac_of_fp32_mfma_peak"] = dom["TFLOPs"] / MI355X_PEAK["fp32_TFLOPs"]
 
     # the same step without declaring the zero initial guesses: every pass of the first cycles
@@ -999,7 +1007,7 @@ def run_workload(args, light=False):
                               "cycles also run the contractions whose result is exactly zero)",
                       "ms_per_step": 1e3 * usec, "value": T * B / usec}
 
-    # fp32 workloads: the same step with the operands contracted as three bf16 terms
+    # fp32 workloads: the same step with the operands contracted in 16-bit terms
     other_form = None
     if other is not None:
         osec = timed(lambda: mgrit_step(other), args.steps, 1)
@@ -1012,8 +1020,9 @@ def run_workload(args, light=False):
             mg.mgrit_gru_profile_read(kind)
         if other == 2:
             other_form = {"what": "same step, same inputs, dtype MGRIT_F32_BF16X3: fp32 operands of the "
-                                  "tile kernels contracted as three bf16 terms each (six bf16 MFMA "
-                                  "products per multiply-add, fp32 accumulation; same 1e-5 parity bar)",
+                                  "tile kernels contracted in 16-bit terms (three fp16 MFMA products per "
+                                  "multiply-add, in the projection six of bf16, fp32 accumulation; same "
+                                  "1e-5 parity bar)",
                           "ms_per_step": 1e3 * osec, "value": T * B / osec,
                           "speedup_over_f32_dtype": sec / osec}
         else:
@@ -1062,7 +1071,7 @@ def run_workload(args, light=False):
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": ("f32 as 3 bf16 terms (bf16 MFMA, f32 accumulate)" if x3 else
+        "dtype": ("f32 in 16-bit terms (fp16 / bf16 MFMA, f32 accumulate)" if x3 else
                   "f32" if wl.dtype == "fp32" else "bf16-in/f32-state"),
         "data": "synthetic",
         "config": {"workload": f"{wl.name}: T={T} B={B} D={D} H={H} cf={wl.cf} levels={wl.levels} "
