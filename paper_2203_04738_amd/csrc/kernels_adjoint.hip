@@ -552,6 +552,8 @@ typedef TileCfgB<2, 2, 2, 2, 1, true, 1, 1, 2, 3, 32> AdjBigS;
 typedef TileCfgB<4, 2, 1, 2, 1, true, 1, 1, 2, 3, 32> AdjBigS8;
 // 128 x 256 as eight waves of 128 x 32, one workgroup per CU: see launch_adj_step
 typedef TileCfgB<2, 4, 2, 2, 1, true, 1, 1, 1, 3, 32> AdjHugeS;
+// 64 x 128 as eight waves, two groups splitting K, one workgroup per CU
+typedef TileCfgB<2, 2, 1, 2, 1, true, 2, 1, 1, 3, 32> AdjWideKS;
 // mid-size launches: 64 x 128 as four waves of 32 x 64, and 64 x 64 with two groups of four waves
 // splitting K (the adjoint's K is 3H: with one group the 64 x 64 tile waits on its slices)
 typedef TileCfgB<2, 2, 1, 2, 1, true, 1, 1, 2, 3, 32> AdjWideS;
@@ -690,6 +692,12 @@ hipError_t launch_adj_step(const AdjArgs& a, hipStream_t s) {
   // 99 with 32 x 32 tiles, 82 split
   else if (a.bf16 == 2 && tiles(AdjWideS::TM, AdjWideS::TN) >= 384)
     launch_adj_terms<AdjWideS>(a, s);
+  // one round of 64 x 128 tiles, one per CU: eight waves splitting K (4096 rows x 512, 256 tiles: 44 us with
+  // two 64 x 64 tiles per CU, which form and split every product twice as often, 31 this way; 3200 x 1000,
+  // 400 tiles and two rounds of them, 121 : 114 with the tile above)
+  else if (a.bf16 == 2 && tiles(AdjWideS::TM, AdjWideS::TN) >= 192 &&
+           tiles(AdjWideS::TM, AdjWideS::TN) <= 256)
+    launch_adj_terms<AdjWideKS>(a, s);
   else if (a.bf16 == 2 && R > 32 && tiles(AdjMidS::TM, AdjMidS::TN) >= 192)
     launch_adj_terms<AdjMidS>(a, s);
   else if (R > 32 && tiles(AdjMid::TM, AdjMid::TN) >= 256)

@@ -768,6 +768,10 @@ typedef TileCfgB<2, 2, 1, 1, 3, true, 1, 1, 2, 3, 32> PhiMidS;
 // 64 : this, three bf16 terms): 1024 rows x 1024 (256 tiles of 64 x 64) 64 : 50, 800 x 1000 (208) 66 : 53, 4096 x 256
 // (256) 19.6 : 16.7, but 4096 x 512 (512) 50 : 58
 typedef TileCfgB<2, 1, 1, 1, 3, true, 2, 1, 2, 3, 32> PhiNarrowS;
+// 64 x 64 as eight waves, two groups splitting K, one workgroup per CU, for one round of them: 1024 rows x
+// 1024 (256 tiles) 32 us with 64 x 32 : 28, 800 x 1000 (208) 32 : 26.  From 384 columns on, where there are slices
+// to split
+typedef TileCfgB<2, 2, 1, 1, 3, true, 2, 1, 1, 3, 32> PhiMidKS;
 
 #define MG_LAUNCH_BY_MODE(KERNEL, ...)                                                   \
   switch (a.mode) {                                                                      \
@@ -933,7 +937,10 @@ hipError_t launch_phi_step(const PhiArgs& a, hipStream_t s) {
     launch_phi_cfg<PhiBig, PhiBigB, PhiBigS, PhiBigF>(a, s);
   } else if (R > 32 && tiles(PhiMid::TM, PhiMid::TN) >= 128) {
     contracted(PhiMid::TM);
-    if (a.bf16 == 2 && tiles(PhiMid::TM, PhiMid::TN) < 512)
+    const long long mid = tiles(PhiMid::TM, PhiMid::TN);
+    if (a.bf16 == 2 && a.H >= 384 && mid >= 192 && mid <= 256)
+      launch_phi_x3<PhiMidKS>(a, s);
+    else if (a.bf16 == 2 && mid < 512)
       launch_phi_x3<PhiNarrowS>(a, s);
     else if (a.bf16 == 1 && a.one_term && tiles(PhiMid::TM, PhiMid::TN) <= 256)
       launch_phi_cfg<PhiMid, PhiMidB, PhiMidS, PhiMidFK>(a, s);

@@ -13,14 +13,19 @@ T, CF = 6, 3
 
 
 # batch sizes and widths of the five tiles of each direction (two launch rows per batch row), K tails, and of
-# the adjoint's widest tile, 128 x 256, with gates of whole K-slices (416 = 13 x 32) and without
+# the tiles for one workgroup per CU: the adjoint's 128 x 256 and 64 x 128 and the forward 64 x 64 with split
+# K, with gates of whole K-slices (416 = 13 x 32, 448 = 7 x 64) and without
 HUGE = "TileCfgB<2, 4, 2, 2, 1, true, 1, 1, 1, 3, 32"
+WIDE_KS, MID_KS = "TileCfgB<2, 2, 1, 2, 1, true, 2, 1, 1, 3, 32", "TileCfgB<2, 2, 1, 1, 3, true, 2, 1, 1, 3, 32"
 
 
-@pytest.mark.parametrize("B,H,adj", [(2050, 136, None), (6145, 136, None), (12225, 136, None),
-                                     (1350, 264, None), (4100, 264, None), (6100, 392, HUGE),
-                                     (6100, 416, HUGE)])
-def test_rows_that_differ_from_their_first_slice(B, H, adj):
+@pytest.mark.parametrize("B,H,phi,adj", [(2050, 136, None, None), (6145, 136, None, None),
+                                         (12225, 136, None, None), (1350, 264, None, None),
+                                         (4100, 264, None, None), (6100, 392, None, HUGE),
+                                         (6100, 416, None, HUGE), (1000, 392, MID_KS, None),
+                                         (1000, 448, MID_KS, None), (1801, 392, None, WIDE_KS),
+                                         (1801, 448, None, WIDE_KS)])
+def test_rows_that_differ_from_their_first_slice(B, H, phi, adj):
     """Row 0: nothing but zeros; 1: zeros in the first 72 columns (both K-split groups' slice); 2: the
     rest 2^14 times the first slice, which overflows in its scale, so that its tile's rows are read
     through; 3: a first slice 2^14 times the rest; 4: all of it 2^-40.  The bar is that of the other
@@ -44,7 +49,10 @@ def test_rows_that_differ_from_their_first_slice(B, H, adj):
     P, z = (d["W"], d["U"], d["b_i"], d["b_h"]), np.zeros((T + 1, len(r), H))
     h_ref, _ = orc.mgrit_forward(*P, d["x"][:, r], d["h0"][r], z, CF, 2, 1)
     run = gh.GpuRun(d, cf=CF, levels=2)
-    h = run.forward_iterates(1)[0][-1]
+    box = []
+    gh.expect_kernels(lambda: box.append(run.forward_iterates(1)),
+                      *(f"phi_step_kernel_bf16<mg::{phi}, true, false>, {m}" for m in (0, 1) if phi))
+    h = box[0][0][-1]
     for i, b in enumerate(r):
         for t in range(T + 1):
             assert gh.rel_err(h[t, b], h_ref[t, i]) <= 1e-5 or not h_ref[t, i].any(), ("h", b, t)
