@@ -106,7 +106,7 @@ __device__ inline void gemm_nt_tile(Acc<C>& acc, int K, LoadA loadA, LoadB loadB
   constexpr int NC = C::TK / 8 / C::KS;  // k-groups of eight per slice and K-split group
   constexpr int NB = C::NG * C::BN;      // B fragments per k-group
   // A wave with one block sums every second k apart: half the additions into each sum.  Adjoint
-  // of 320 rows x 1024, error of w against 64 bits: 5.7e-8 with one sum, 5.2e-8 with two (three-term
+  // of 320 rows x 1024, error of w against 64 bits: 5.7e-8 with one sum, 5.2e-8 with two (three bf16-term
   // tiles: 5.4e-8), in the same time.
   constexpr bool LONE = NB * C::BM == 1;
   floatx16 odd;

@@ -702,7 +702,7 @@ hipError_t launch_adj_step(const AdjArgs& a, hipStream_t s) {
     launch_adj_terms<AdjMidS>(a, s);
   else if (R > 32 && tiles(AdjMid::TM, AdjMid::TN) >= 256)
     launch_adj_f32<AdjMid>(a, s);
-  else   // (three terms included: 32 x 32 tiles are faster in fp32, see launch_phi_cfg, and no less
+  else   // (operands in terms included: 32 x 32 tiles are faster in fp32, see launch_phi_cfg, and no less
          // accurate, see gemm_nt_tile)
     launch_adj_f32<AdjSmall>(a, s);
   prof_end(kind, 6.0 * (double)R * a.H * a.H, 28.0 * (double)R * a.H, s);
