@@ -2,6 +2,7 @@
 // host-side level drivers that enqueue the kernels of one MGRIT cycle
 // (Alg. 2 of the paper, recursive per Remark 2) for the forward recurrence and
 // for its adjoint in reversed time.
+#include <algorithm>
 #include <cstdint>
 #include <cstring>
 #include <mutex>
@@ -10,6 +11,7 @@
 
 #include "common.h"
 #include "scan.h"
+#include "term_pack.h"
 
 // Workspace of mgrit_gru_forward_static: one array per GPU, held from the moment the library's
 // code object is loaded on that GPU until the process ends.  In host code this name is only a
@@ -278,10 +280,12 @@ static Forms make_forms(const mgrit_gru_cfg& c, const Layout& lay, char* base) {
     return f;
   const size_t u3 = align_up((size_t)6 * gates * H * H);
   const size_t w3 = align_up((size_t)6 * gates * H * c.D);
+  const size_t wt = align_up(pack2_bytes(c.D, gates * H));       // (few features: more than w3)
+  const size_t second = std::max(u3, std::max(w3, wt));
   const size_t room = lay.total_part - CTL_BYTES;
-  if (u3 + (u3 > w3 ? u3 : w3) > room) return f;
+  if (u3 + second > room) return f;
   f.rec = 2;
-  f.part_bytes = u3 + (u3 > w3 ? u3 : w3);
+  f.part_bytes = u3 + second;
   f.U3 = base + lay.part + CTL_BYTES;
   f.UT3 = f.U3 + u3;                      // W3 and UT3 take turns: the projection comes first, the
   f.W3 = f.UT3;                           // input gradients after the last adjoint step

@@ -170,10 +170,10 @@ hipError_t launch_input_grads(const float* kap0, const float* w, const void* WT,
 // dst[t][i] (t = 0..2, bf16) = t-th term of 2^24 src[i] (exactly: see gemm_core_bf16.h); n a multiple
 // of 4
 hipError_t launch_split3(const float* src, void* dst, long long n, hipStream_t s);
-// the same terms of src[rows][K], packed (see gemm_terms.h); rows and K multiples of 8
+// the same terms of src[rows][K], packed (see term_pack.h); rows and K multiples of 8
 hipError_t launch_split3_pack(const float* src, void* dst, int rows, int K, hipStream_t s);
 // Weights src[rows][K] as the step and input-gradient kernels read them with bf16 = 2: packed fp16 terms
-// (see gemm_terms.h); rows and K multiples of 8, dst of 4 rows (K + 1) bytes.
+// and exponents (see term_pack.h); K a multiple of 8, dst of pack2_bytes(rows, K).
 hipError_t launch_split2(const float* src, void* dst, int rows, int K, hipStream_t s);
 
 hipError_t launch_fill_f64(double* p, long long n, double v, hipStream_t s);

@@ -27,12 +27,13 @@
 // the loop of gemm_core_bf16.h, 100 this way; 16384 LSTM rows 243, 157, 126).  With half the MFMAs the K loop is bound by what feeds them, LDS above all: 32x32 blocks
 // of A and B fragments read by every wave cost 105 of the LDS's 128 bytes per clock at full matrix
 // rate for the 128 x 64 (x3) tile.  So B does not pass through LDS: the split leaves it in the order in
-// which lanes take it (pack below), a wave owns its columns alone (the waves of a tile lie side by
+// which lanes take it (term_pack.h), a wave owns its columns alone (the waves of a tile lie side by
 // side) and loads its fragments straight into registers, one slice ahead.  A goes to LDS in fragment
 // order too, in three slices taking turns, so that a slice costs one barrier, its conversion and writes
 // go between the MFMAs of an earlier one, and its first fragments are read before the barrier.
 #pragma once
 #include "gemm_core_bf16.h"
+#include "term_pack.h"
 
 namespace mg {
 
@@ -90,15 +91,8 @@ __device__ inline int term_exponent(float m, int top) {
 __device__ inline float exp2_int(int e) { return __uint_as_float((unsigned)(e + 127) << 23); }
 constexpr int TERM_TOP_A = 6, TERM_TOP_B = 13;
 
-// Packed terms of B[rows][K] (rows, K multiples of 8): chunks of eight k of a row, 16 bytes, ordered
-// [row / 8][k / 8][term][row % 8], so that the 16 rows x 32 k that a wave loads at once are whole
-// 128-byte lines, its terms side by side; behind two terms the rows' exponents, int[rows].
-constexpr int PACK_TERM = 128;                            // bytes from term to term
-__host__ __device__ inline size_t pack_row(long long row, int K, int terms) {
-  return (size_t)(row >> 3) * (K >> 3) * (PACK_TERM * terms) + (row & 7) * 16;
-}
 __device__ inline const int* pack_exponents(const void* pack, long long rows, int K) {
-  return reinterpret_cast<const int*>((const char*)pack + (size_t)rows * K * 4);
+  return reinterpret_cast<const int*>((const char*)pack + pack_exponents_at(rows, K));
 }
 
 // How the waves of configuration C (NP = 3) share a tile: WR x WC waves per K-split group, each RB x CB

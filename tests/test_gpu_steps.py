@@ -155,6 +155,26 @@ def test_bf16_backward_with_source_and_dx(gh, form):
         assert e <= TOL_BF16 and e <= TIGHT_BF16, (name, e)
 
 
+@pytest.mark.parametrize("D", [4, 12, 20, 300])
+def test_input_gradients_on_terms_of_widths_that_are_no_multiple_of_eight(gh, D):
+    """W^T is packed with its D rows in groups of eight: each column of dx, the last group's too."""
+    T, B, H, cf, levels = 64, 67, 136, 4, 2
+    print("input gradients on terms", D, flush=True)
+    d = random_small(83, T, B, D, H, scale=0.5 / np.sqrt(H))
+    src = _source(17, T, B, H)
+    h = orc.serial_scan(*_P(d), d["x"], d["h0"]).astype(np.float32)
+    run = gh.GpuRun(d, cf=cf, levels=levels)
+    box = []
+    gh.expect_kernels(lambda: box.append(run.serial_backward_steps(h, src)), "input_grad_kernel_bf16")
+    want = orc.serial_bptt_steps(*_P(d), d["x"], h, src)[5]
+    _, _, grads = run.backward_steps_iterates(h, src, 1)
+    want_mgrit = orc.mgrit_backward(*_P(d), d["x"], h, None, np.zeros_like(h), cf, levels, 1,
+                                    dL_dh=src)[6]
+    for n in range(D):
+        assert gh.rel_err(box[0][5][..., n], want[..., n]) <= TOL, ("serial", n)
+        assert gh.rel_err(grads[4][..., n], want_mgrit[..., n]) <= TOL, ("mgrit", n)
+
+
 def test_two_layer_stack_forward_and_backward(gh):
     """Layer 2 reads the states of layer 1; the loss sits on every state of layer 2;
     dL/dx of layer 2 is the source term of layer 1.  2 forward cycles, 1 backward
