@@ -1389,25 +1389,139 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_tr_kernel(GradArgs a) {
 // NB: 32-column blocks of a wave; 4: tiles of 128 x 256, 2: of 128 x 128.  Every operand element is loaded,
 // multiplied and split once per tile that uses it; the wide tile does that a quarter less often per MFMA.
 // Columns are exchanged by bits 0-1 of the row, so that the four rows of a read fall on different banks.
-// The sums run over time, so it is the columns of both operands that are scaled, each by its largest value in
-// the last slice of the split: an adjoint decays backwards, and what is larger by more than 2^9 before
-// overflows.  (The sum runs forwards all the same, small values first: backwards it ends up 1.7-3 times
-// further from 64 bits.)  Columns of zeros there are scaled by 2^127, so that anything but values near the
-// smallest there are overflows; a tile that does reads its columns through for their largest values, and
-// if a sum is still not finite, runs in fp32.
-// What bounds it is staging (loads, products, conversions, LDS), the matrix pipe is busy for a good third:
-// 65536 rows, 1536 x 1024 0.68 ms (303 TFLOP/s; six products of three bf16 terms 1.07), 1536 x 512 0.37
-// (0.55), 3072 x 1024 1.24 (2.09), 12800 rows, 3000 x 1000 0.30 (0.42).  (Conditions for the columns and
-// rows beyond the matrix in every slice: 0.94 for the first of these.)
+// The sums run over time, so it is the columns of both operands that are scaled, and since an adjoint decays backwards
+// (2^-0.3 to 2^-1 a step) while inputs begin and end anywhere, the scales move along: a slice whose values leave
+// the range of a scale renews the scales from its own largest values, and the sums follow by the same powers of
+// two, exactly.  (Scales of a whole split, 128 to 6500 rows: gradients of inputs that end 32 steps before the
+// sequence does were 3e-3 off, 64 steps 1.)  In a slice that no scales fit, because rows of it (batch rows, steps) lie
+// further apart than fp16 reaches, and in the GRAD_THREES - 1 after it, the operands are three bf16 terms, six
+// products.  What two terms leave out of a value is thus at most 2^-20 of the largest of its row and of its
+// column in the slice (2^-22 of the value where it is within 2^10 of the column's largest); values that
+// are denormal beside normal ones count as zeros.  (The sum runs forwards: backwards it ends up 1.7-3
+// times further from 64 bits.)
+// What bounds it is issue: per slice and wave 48 MFMAs (1536 clocks of 3700), 230 VALU instructions of staging and 100
+// that look whether the scales fit; renewing them takes 3 us.  65536 rows, 1536 x 1024 0.79 ms (261 TFLOP/s; six
+// products of three bf16 terms 1.07, two terms with scales of a whole split 0.69), 1536 x 512 0.45 (0.55,
+// 0.37), 3072 x 1024 1.53 (2.09, 1.25), 12800 rows, 3000 x 1000 0.31 (0.42, 0.30).  By the data, 65536 rows x
+// 1536 x (1024 + 512): dense 1.31, inputs that end early 1.29, one-hot 1.37, 2 % dense 1.51, rectified 1.48, a loss
+// that differs by 10^3 between batch rows 1.52, by 10^6 3.3 (three terms throughout; with fp32 slices 6.2).
+// Branches that are rarely taken are marked as such: without that the compiler spills sums around the products.
 constexpr int HS_TK = 32;
+// A column's largest value of a slice is brought into [2^GRAD_TOP, 2^(GRAD_TOP + 1)) when the scales are renewed, and
+// they stay as long as it and the rows' largest values are within [2^GRAD_LOW, 2^GRAD_HIGH).  (GRAD_TOP 6 to
+// 10: the same time.)  A scale rises by up to 2^GRAD_RISE above the least one of its column: no sum overflows.
+constexpr int GRAD_TOP = 8, GRAD_LOW = -5, GRAD_HIGH = 15, GRAD_RISE = 30, GRAD_THREES = 8;
+constexpr int EXP2_MAX = 127;              // of a column that has held nothing but zeros
+
+__device__ inline int exponent_of(float x) { return (int)(__float_as_uint(x) >> 23) - 127; }
+__device__ inline void top4(floatx4& m, floatx4 v) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) m[e] = fmaxf(m[e], fabsf(v[e]));
+}
+template <int CTRL>
+__device__ inline unsigned dpp(unsigned x) {
+  return __builtin_amdgcn_mov_dpp((int)x, CTRL, 0xf, 0xf, false);
+}
+constexpr int DPP_XOR1 = 0xb1, DPP_XOR2 = 0x4e, DPP_HALF_MIRROR = 0x141, DPP_ROR8 = 0x128;
+// Largest of the lanes' values of each of four columns that Q neighbouring lanes take of a row, the other lanes of the
+// wave of other rows: lane i receives it for column i / 16 of its four.
+template <int Q>
+__device__ inline float column_top(const floatx4& m) {
+  auto top2 = [](auto x) { return fmaxf(__uint_as_float(x[0]), __uint_as_float(x[1])); };
+  const float a = top2(__builtin_amdgcn_permlane32_swap(__float_as_uint(m[0]), __float_as_uint(m[2]), false, false));
+  const float b = top2(__builtin_amdgcn_permlane32_swap(__float_as_uint(m[1]), __float_as_uint(m[3]), false, false));
+  const float c = top2(__builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false));
+  return Q == 16 ? c : fmaxf(c, __uint_as_float(dpp<DPP_ROR8>(__float_as_uint(c))));
+}
+// The lanes' bits of a row that Q neighbouring lanes take.
+template <int Q>
+__device__ inline unsigned row_or(unsigned x) {
+  x |= dpp<DPP_XOR1>(x);
+  x |= dpp<DPP_XOR2>(x);
+  x |= dpp<DPP_HALF_MIRROR>(x);
+  return Q == 16 ? x | dpp<DPP_ROR8>(x) : x;
+}
+// Whether two fp16 terms plainly carry a slice's values in the scales of their columns: every column and every row has
+// a value of at least 2, and none is 2^GRAD_HIGH or more.  From the terms as a wave stages them, row after row (Q
+// neighbouring lanes to a row, R rows to a lane): "at least 2" is one bit of a first term, so that
+// bits are collected instead of largest values.  Zeros do not fit here (all zeros of S do: an adjoint that
+// has decayed to nothing).
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+template <int R, int Q>
+struct GradFit {
+  static constexpr unsigned TWO = 0x40004000u;
+  unsigned c0 = 0, c1 = 0, rows = 0;
+  float top = 0.f;
+  // v: the lane's values of row r, t: their first terms
+  __device__ inline void add(int r, const floatx4& v, uintx2 t) {
+    c0 |= t[0];
+    c1 |= t[1];
+    rows |= ((t[0] | t[1]) >> r) & (TWO >> r);
+    top = fmaxf(fmaxf(fmaxf(top, fabsf(v[0])), fmaxf(fabsf(v[1]), fabsf(v[2]))), fabsf(v[3]));
+  }
+  // f: the scales of the lane's columns
+  __device__ inline unsigned long long off(const floatx4& f) const {
+    const auto h = __builtin_amdgcn_permlane32_swap(c0, c1, false, false);
+    const unsigned x = h[0] | h[1];
+    const auto q = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    unsigned c = q[0] | q[1];
+    if (Q == 8) c |= dpp<DPP_ROR8>(c);
+    unsigned g = row_or<Q>(rows);
+    g |= g >> 16;
+    constexpr unsigned FULL = 0x7fffu & (0x7fffu << (15 - R));
+    const bool low = ((c & TWO) != TWO) | ((g & FULL) != FULL);
+    const unsigned long long b = __ballot(low | (top >= (float)(1 << GRAD_HIGH)));
+    const float least = fminf(fminf(f[0], f[1]), fminf(f[2], f[3])) * 0x1p-126f;
+    return Q == 8 && __ballot(top > least) == 0 ? 0 : b;
+  }
+};
+// Whether they do not: a value of 2^GRAD_LOW is enough, zeros fit, and what was denormal before it was scaled.
+// value(r): row r, scaled by f; scale: that of the lane's column after column_top.
+template <int R, int Q, class Value>
+__device__ inline bool grad_misfit(const floatx4& f, float scale, Value value) {
+  constexpr float low = 1.f / (1 << -GRAD_LOW), high = 1 << GRAD_HIGH;
+  floatx4 cm = zero4();
+  unsigned in = 0, any = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const floatx4 v = value(r);
+    top4(cm, v);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      in |= fabsf(v[e]) >= low ? 1u << r : 0;
+      any |= fabsf(v[e]) > f[e] * 0x1p-126f ? 1u << r : 0;
+    }
+    __builtin_amdgcn_sched_barrier(0);     // (rows one by one: registers are short)
+  }
+  const float m = column_top<Q>(cm);
+  return (m >= high) | ((m < low) & (m > scale * 0x1p-126f)) | ((row_or<Q>(any) & ~row_or<Q>(in)) != 0);
+}
+// Renews the scale f of a column whose largest value in the slice is m (all: of the wave's columns), returns by how
+// much its exponent changes.  least: the least exponent it has been scaled by.
+__device__ inline int grad_renew(float& f, float m, float all, int& least) {
+  auto usable = [](float x) { return x >= 0x1p-126f && x <= 3.4028235e38f; };
+  const int old = exponent_of(f), t = exponent_of(m) + old;
+  int e = old;
+  if (usable(m)) {
+    if (t > GRAD_TOP || t < 0) e = GRAD_TOP - exponent_of(m);
+  } else if (old == EXP2_MAX && usable(all)) {
+    e = GRAD_TOP - exponent_of(all);       // (what it will hold is most likely of that size)
+  }
+  e = max(min(min(e, EXP2_MAX), least + GRAD_RISE), -100);
+  f = exp2_int(e);
+  least = min(least, e);
+  return e - old;
+}
+
 template <int NB>
 __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
   constexpr int GN = 64 * NB;
-  // (the fp32 repetition takes two slices of its own)
-  constexpr int AEL = 2 * HS_TK * GT, BEL = 2 * HS_TK * GN, FEL = 2 * GTK * GLD;
-  __shared__ __attribute__((aligned(16))) bf16_t tiles_lds[AEL + BEL > 2 * FEL ? AEL + BEL : 2 * FEL];
-  __shared__ __attribute__((aligned(16))) int mexp[GT], nexp[GN];
-  bf16_t *const As = tiles_lds, *const Bs = tiles_lds + AEL;
+  constexpr int APL = HS_TK * GT, BPL = HS_TK * GN;        // elements of a term
+  __shared__ __attribute__((aligned(16))) bf16_t tiles_lds[3 * (APL + BPL)];
+  __shared__ __attribute__((aligned(16))) float mscale[GT], nscale[GN];
+  __shared__ __attribute__((aligned(16))) int change[GT + GN];
+  __shared__ int mleast[GT], nleast[GN], refused, renewed;
+  bf16_t *const As = tiles_lds, *const Bs = tiles_lds + 3 * APL;
   const int H = a.H, N = a.N, M = 3 * a.H;
   const int tiles = a.mtiles * a.ntiles;
   // an XCD gets consecutive items, split by split: its rows of S and Bm enter one L2 only
@@ -1419,124 +1533,193 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
   const long long kbeg = (long long)z * a.Kper;
   long long kend = kbeg + a.Kper;
   if (kend > a.Ktot) kend = a.Ktot;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1, li = lane & 31, lh = lane >> 5;
-  const long long rowoff = a.B;           // kap0 / w rows are one time point ahead
 
   // wave: rows wm * 64 .., columns (j / 2) * 128 + wn * 64 + (j % 2) * 32 .. of block j
   floatx16 acc[2][NB];
-  // staging of S: columns m4*4..+3, slice rows k8 + 8r; of the second operand: c4*4..+3, rows kf + KS r
-  constexpr int CL = GN / 4, KS = 256 / CL, NR = HS_TK / KS;
-  static_assert(KS % 4 == 0, "one exchange of columns per thread");
-  const int m4 = tid & 31, k8 = tid >> 5;
-  const int c4 = tid % CL, kf = tid / CL;
-  const int m = m0 + m4 * 4, n = n0 + c4 * 4;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  // Staging: a wave takes 32 columns of S and GN / 4 of the second operand, all rows of the slice, so that it finds
+  // its columns' largest values by itself.  A thread takes four columns of rows srow(r) and xrow(r), whose
+  // bits 0-1 (the exchange of columns) do not depend on r; those of half a wave fall on different banks.
+  constexpr unsigned XQ = GN / 16;
+  constexpr int XG = 64 / XQ, NR = HS_TK / XG;       // lanes to a row, rows at a time
+  auto srow = [](unsigned lane, int r) { return (int)(lane / 8) + 8 * r; };
+  auto xrow = [](unsigned lane, int r) {
+    const int g = lane / XQ;
+    return XG * r + (XG == 4 ? (g & 1) * 2 + (g >> 1) : g);
+  };
+  auto scol = [&](unsigned lane) { return wave * 32 + (int)(lane % 8 * 4); };
+  auto xcol = [&](unsigned lane) { return wave * (GN / 4) + (int)(lane % XQ * 4); };
+  const int m = m0 + scol(lane), n = n0 + xcol(lane);
   const bool m_ok = m < M, n_ok = n < N;
   const int mc = m_ok ? m : 0, nc = n_ok ? n : 0;
   const int gate = mc / H, jcol = mc - gate * H;
   const int src = gate == 2 ? a.third_off + jcol : mc;
-  bf16_t* const adst = &As[k8 * GT + ((m4 * 4) ^ ((k8 & 3) << 5))];
-  bf16_t* const bdst = &Bs[kf * GN + ((c4 * 4) ^ ((kf & 3) << 5))];
-  const float* const kbase = a.kap0 + rowoff * (5LL * H) + src;
-  const float* const wbase = a.w + rowoff * H + jcol;
-  const float* const bbase = (const float*)a.Bm + nc;
   floatx4 rk[4], rw[4], rb[NR];
-  float colsum[2] = {0.f, 0.f};           // of columns m4*4 + 2 lh, + 1: both row groups of the wave
+  float colsum[2] = {0.f, 0.f};           // of columns scol + 2 lh, + 1: rows of both halves of the wave
+  // Slice k0 into registers (rows beyond the split: its last one).  Uniform bases and 32-bit offsets.  (What follows
+  // from the thread's position is formed anew for each slice: kept, it would spill, and a reload in front of
+  // the products waits for every load in flight.)
+  const unsigned koff = 4 * src, woff = 4 * jcol, noff = 4 * nc;
+  auto at = [](const float* base, unsigned offset) {
+    return ldg4(reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + offset));
+  };
   auto fetch = [&](long long k0) {
+    if (k0 >= kend) k0 = kend - 1;
+    const int last = (int)min(kend - k0, (long long)HS_TK) - 1;
+    unsigned t = lane;
+    asm volatile("" : "+v"(t));
+    const float* const kbase = a.kap0 + (k0 + a.B) * (5LL * H);
+    const float* const wbase = a.w + (k0 + a.B) * H;       // kap0 / w rows are one time point ahead
+    const float* const bbase = (const float*)a.Bm + k0 * N;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      long long k = k0 + k8 + 8 * r;
-      if (k >= kend) k = kend - 1;
-      rk[r] = ldg4(kbase + k * (5LL * H));
-      rw[r] = ldg4(wbase + k * H);
+      const unsigned k = min(srow(t, r), last);
+      rk[r] = at(kbase, __umul24(k, 20 * H) + koff);
+      rw[r] = at(wbase, __umul24(k, 4 * H) + woff);
     }
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+      rb[r] = at(bbase, min(xrow(t, r), last) * (4u * N) + noff);
+  };
+  // (the scales stay in LDS: registers are short)
+  if (tid < GT) {
+    mscale[tid] = exp2_int(EXP2_MAX);
+    mleast[tid] = EXP2_MAX;
+  }
+  if (tid < GN) {
+    nscale[tid] = exp2_int(EXP2_MAX);
+    nleast[tid] = EXP2_MAX;
+  }
+  if (tid == 0) refused = renewed = 0;
+  __syncthreads();
+  auto scale4 = [](const float* p) { return *reinterpret_cast<const floatx4*>(p); };
+  auto put = [](bf16_t* dst, int plane, floatx4 v) {
+    const uintx2 w0 = uintx2{round2_f16(v[0], v[1]), round2_f16(v[2], v[3])};
+    float rest[4];                         // (v[e] minus its half of w0: as minus2_f16, v is used again)
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(rest[0]) : "v"(w0[0]), "v"(v[0]));
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(rest[1]) : "v"(w0[0]), "v"(v[1]));
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(rest[2]) : "v"(w0[1]), "v"(v[2]));
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(rest[3]) : "v"(w0[1]), "v"(v[3]));
+    const uintx2 w1 = uintx2{round2_f16(rest[0], rest[1]), round2_f16(rest[2], rest[3])};
+    *reinterpret_cast<uintx2*>(dst) = w0;
+    *reinterpret_cast<uintx2*>(dst + plane) = w1;
+    return w0;
+  };
+  // the rows in registers to LDS, in terms; whether they do not fit
+  auto stash = [&]() {
+    unsigned t = lane;
+    asm volatile("" : "+v"(t));
+    const floatx4 fm = scale4(&mscale[scol(t)]), fn = scale4(&nscale[xcol(t)]);
+    GradFit<4, 8> fit;
+    bf16_t* const ad = &As[srow(t, 0) * GT + (scol(t) ^ ((srow(t, 0) & 3) << 5))];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const floatx4 v = rk[r] * rw[r] * fm;
+      fit.add(r, v, put(ad + 8 * r * GT, APL, v));
+      if (r & 1) __builtin_amdgcn_sched_barrier(0);        // (more rows at a time: sums spill)
+    }
+    GradFit<NR, XQ> fitb;
+    bf16_t* const bd = &Bs[xrow(t, 0) * GN + (xcol(t) ^ ((xrow(t, 0) & 3) << 5))];
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      long long k = k0 + kf + KS * r;
-      if (k >= kend) k = kend - 1;
-      rb[r] = ldg4(bbase + k * N);
+      const floatx4 v = rb[r] * fn;
+      fitb.add(r, v, put(bd + XG * r * GN, BPL, v));
+      if (r & 1) __builtin_amdgcn_sched_barrier(0);
     }
-  };
-  // scales of the thread's columns
-  floatx4 fm = zero4(), fn = zero4();
-  auto put = [](bf16_t* dst, int plane, floatx4 v, floatx4 f) {
-    typedef unsigned uintx2_ __attribute__((ext_vector_type(2)));
-    v *= f;
-    float x[4] = {v[0], v[1], v[2], v[3]};
-    const uintx2_ w0 = {round2_f16(x[0], x[1]), round2_f16(x[2], x[3])};
-    minus2_f16(x[0], x[1], w0[0]);
-    minus2_f16(x[2], x[3], w0[1]);
-    const uintx2_ w1 = {round2_f16(x[0], x[1]), round2_f16(x[2], x[3])};
-    *reinterpret_cast<uintx2_*>(dst) = w0;
-    *reinterpret_cast<uintx2_*>(dst + plane) = w1;
-  };
-  auto top4 = [](floatx4& m, floatx4 v) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) m[e] = fmaxf(m[e], fabsf(v[e]));
-  };
-  // column maxima of the rows in registers (slice k0)
-  auto maxima = [&](long long k0, floatx4& tm, floatx4& tn) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (k0 + k8 + 8 * r < kend) top4(tm, rk[r] * rw[r]);
-#pragma unroll
-    for (int r = 0; r < NR; ++r)
-      if (k0 + kf + KS * r < kend) top4(tn, rb[r]);
-  };
-  // fm, fn, mexp, nexp from the threads' maxima of their columns
-  auto scales = [&](floatx4 tm, floatx4 tn) {
-    float* red = reinterpret_cast<float*>(tiles_lds);    // [8][GT], then [KS][GN]
-    static_assert(4 * (8 * GT + KS * GN) <= sizeof(tiles_lds), "");
-    __syncthreads();
-    *reinterpret_cast<floatx4*>(&red[k8 * GT + m4 * 4]) = tm;
-    *reinterpret_cast<floatx4*>(&red[8 * GT + kf * GN + c4 * 4]) = tn;
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 8; ++q) top4(tm, *reinterpret_cast<const floatx4*>(&red[q * GT + m4 * 4]));
-#pragma unroll
-    for (int q = 0; q < KS; ++q)
-      top4(tn, *reinterpret_cast<const floatx4*>(&red[8 * GT + q * GN + c4 * 4]));
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int em = term_exponent(tm[e], TERM_TOP_A), en = term_exponent(tn[e], TERM_TOP_A);
-      fm[e] = exp2_int(em);
-      fn[e] = exp2_int(en);
-      if (k8 == 0) mexp[m4 * 4 + e] = em;
-      if (kf == 0) nexp[c4 * 4 + e] = en;
-    }
-    __syncthreads();
+    if (__builtin_expect((fit.off(fm) | fitb.off(fn)) == 0, 1)) return false;
+    asm volatile("" : "+v"(t));            // (the scaled values are formed anew, and in a branch)
+    const floatx4 gm = scale4(&mscale[scol(t)]), gn = scale4(&nscale[xcol(t)]);
+    const bool bad = grad_misfit<4, 8>(gm, mscale[scol(t) + t / 16], [&](int r) { return rk[r] * rw[r] * gm; });
+    return __ballot(bad | grad_misfit<NR, XQ>(gn, nscale[xcol(t) + t / 16],
+                                              [&](int r) { return rb[r] * gn; })) != 0;
   };
   // (columns beyond the matrix are copies of others and not stored; rows beyond the split count as zeros)
-  auto stash = [&](long long k0) {
-    if (k0 + HS_TK > kend) {
+  auto clear = [&](long long k0) {
+    if (__builtin_expect(k0 + HS_TK > kend, 0)) {
+      const int rows = (int)(kend - k0);
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        if (k0 + k8 + 8 * r >= kend) rk[r] = rw[r] = zero4();
+        if (srow(lane, r) >= rows) rk[r] = rw[r] = zero4();
 #pragma unroll
       for (int r = 0; r < NR; ++r)
-        if (k0 + kf + KS * r >= kend) rb[r] = zero4();
+        if (xrow(lane, r) >= rows) rb[r] = zero4();
     }
-    floatx4 p[4];
+  };
+  // sums times 2^(sign (exps[row] + exps[GT + column]))
+  auto add_exponents = [&](const int* exps, int sign) {
+    typedef int intx4_ __attribute__((ext_vector_type(4)));
+    unsigned t = tid;
+    asm volatile("" : "+v"(t));            // (addresses are formed here, not kept through the loop)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      p[r] = rk[r] * rw[r];
-      put(adst + 8 * r * GT, HS_TK * GT, p[r], fm);
-    }
-    // a tree of eight rows: one addition per slice into the long sum (four rows: bias gradients 2-15 %
-    // further from 64 bits).  The halves of the wave exchange two columns each.  Only the first column
-    // tile reports it.
-    if (nt == 0) {
-      const floatx4 t = (p[0] + p[1]) + (p[2] + p[3]);
+    for (int i = 0; i < 2; ++i) {
+      intx4_ me[4];
 #pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(t[e]), __float_as_uint(t[2 + e]),
-                                                        false, false);
-        colsum[e] += __uint_as_float(x[0]) + __uint_as_float(x[1]);
+      for (int q = 0; q < 4; ++q)
+        me[q] = *reinterpret_cast<const intx4_*>(&exps[t / 128 * 64 + i * 32 + 8 * q + (t / 32 & 1) * 4]);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const int ne = exps[GT + (j >> 1) * 128 + (t / 64 & 1) * 64 + (j & 1) * 32 + t % 32];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = ldexpf(acc[i][j][e], sign * (me[e / 4][e % 4] + ne));
       }
     }
+  };
+  // new scales from the rows in registers, the sums are brought to them; whether there are any
+  auto rescale = [&](int turn) {
+    unsigned t = lane;
+    asm volatile("" : "+v"(t));
+    floatx4 tm = zero4(), tn = zero4();
 #pragma unroll
-    for (int r = 0; r < NR; ++r)
-      put(bdst + KS * r * GN, HS_TK * GN, rb[r], fn);
+    for (int r = 0; r < 4; ++r) top4(tm, rk[r] * rw[r]);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) top4(tn, rb[r]);
+    const float m = column_top<8>(tm), n = column_top<XQ>(tn);
+    float allm = m, alln = n;              // (of the wave's columns)
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      allm = fmaxf(allm, __shfl_xor(allm, o, 64));
+      alln = fmaxf(alln, __shfl_xor(alln, o, 64));
+    }
+    const int cm = scol(t) + t / 16, cn = xcol(t) + t / 16;
+    int d = 0;
+    if (t % 16 < 8) d |= change[cm] = grad_renew(mscale[cm], m, allm, mleast[cm]);
+    if (t % 16 < XQ) d |= change[GT + cn] = grad_renew(nscale[cn], n, alln, nleast[cn]);
+    if (d != 0) renewed = turn;
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(renewed) != turn) return false;
+    add_exponents(change, 1);
+    return true;
+  };
+  // the rows in registers to LDS, in three bf16 terms (scaled too: the sums are)
+  auto stash3 = [&]() {
+    unsigned t = lane;
+    asm volatile("" : "+v"(t));
+    const floatx4 fm = scale4(&mscale[scol(t)]), fn = scale4(&nscale[xcol(t)]);
+    auto put3 = [](bf16_t* dst, int plane, floatx4 v) {
+      float x[4] = {v[0], v[1], v[2], v[3]};
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const uintx2 w = {round2_bf16(x[0], x[1]), round2_bf16(x[2], x[3])};
+        *reinterpret_cast<uintx2*>(dst + i * plane) = w;
+        if (i < 2) {
+          minus2_bf16(x[0], x[1], w[0]);
+          minus2_bf16(x[2], x[3], w[1]);
+        }
+      }
+    };
+    bf16_t* const ad = &As[srow(t, 0) * GT + (scol(t) ^ ((srow(t, 0) & 3) << 5))];
+    bf16_t* const bd = &Bs[xrow(t, 0) * GN + (xcol(t) ^ ((xrow(t, 0) & 3) << 5))];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) put3(ad + 8 * r * GT, APL, rk[r] * rw[r] * fm);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) put3(bd + XG * r * GN, BPL, rb[r] * fn);
   };
   // transpose reads: see grad_gemm_tr_kernel
   const int i16 = lane & 15, half = (lane >> 4) & 1, rr = i16 >> 2;
@@ -1546,128 +1729,148 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_x3_kernel(GradArgs a) {
     aoff[i] = (lh * 8 + rr) * GT + ((wm * 64 + i * 32 + half * 16 + 4 * (i16 & 3)) ^ (rr << 5));
     boff[i] = (lh * 8 + rr) * GN + ((wn * 64 + i * 32 + half * 16 + 4 * (i16 & 3)) ^ (rr << 5));
   }
-
-  // first: the scales come from the last slice, otherwise from all rows
-  auto pass = [&](bool first) {
+  auto multiply = [&]() {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int c = 0; c < HS_TK / 16; ++c) {
+      f16x8 fa[2][2];
 #pragma unroll
-      for (int j = 0; j < NB; ++j)
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    colsum[0] = colsum[1] = 0.f;
-    const long long klast = kbeg + (kend - 1 - kbeg) / HS_TK * HS_TK;
-    floatx4 tm = zero4(), tn = zero4();
-    if (!first)
-      for (long long k0 = kbeg; k0 < klast; k0 += HS_TK) {
-        fetch(k0);
-        maxima(k0, tm, tn);
-      }
-    fetch(klast);
-    maxima(klast, tm, tn);
-    fetch(kbeg);
-    scales(tm, tn);
-    stash(kbeg);
-    __syncthreads();
-    for (long long k0 = kbeg; k0 < kend; k0 += HS_TK) {
-      const bool more = k0 + HS_TK < kend;
-      if (more) fetch(k0 + HS_TK);
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_setprio(2);
-#pragma unroll
-      for (int c = 0; c < HS_TK / 16; ++c) {
-        f16x8 fa[2][2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-            fa[t][i] = __builtin_bit_cast(
-                f16x8, lds_tr8(&As[t * HS_TK * GT + aoff[i] + c * 16 * GT], GT));
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-          f16x8 fb[2];
-#pragma unroll
-          for (int u = 0; u < 2; ++u)
-            fb[u] = __builtin_bit_cast(
-                f16x8, lds_tr8(&Bs[u * HS_TK * GN + boff[j & 1] + c * 16 * GN + (j >> 1) * 128], GN));
-#pragma unroll
-          for (int u = 0; u < 3; ++u)              // a0 b0, a1 b0, a0 b1
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[u == 1][i], fb[u == 2], acc[i][j],
-                                                                 0, 0, 0);
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_setprio(0);
-      __syncthreads();
-      if (more) {
-        stash(k0 + HS_TK);
-        __syncthreads();
-      }
-    }
-    // whether a sum is not finite
-    floatx4 t = zero4();
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      typedef int intx4_ __attribute__((ext_vector_type(4)));
-      intx4_ me[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        me[q] = *reinterpret_cast<const intx4_*>(&mexp[wm * 64 + i * 32 + 8 * q + 4 * lh]);
+        for (int i = 0; i < 2; ++i)
+          fa[t][i] = __builtin_bit_cast(
+              f16x8, lds_tr8(&As[t * APL + aoff[i] + c * 16 * GT], GT));
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
-        const int ne = nexp[(j >> 1) * 128 + wn * 64 + (j & 1) * 32 + li];
+        f16x8 fb[2];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          acc[i][j][e] = ldexpf(acc[i][j][e], -me[e / 4][e % 4] - ne);
-          t[e & 3] = fmaf(acc[i][j][e], 0.f, t[e & 3]);
-        }
+        for (int u = 0; u < 2; ++u)
+          fb[u] = __builtin_bit_cast(
+              f16x8, lds_tr8(&Bs[u * BPL + boff[j & 1] + c * 16 * GN + (j >> 1) * 128], GN));
+#pragma unroll
+        for (int u = 0; u < 3; ++u)              // a0 b0, a1 b0, a0 b1
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[u == 1][i], fb[u == 2], acc[i][j], 0, 0, 0);
       }
     }
-    const float u = (t[0] + t[1]) + (t[2] + t[3]);
-    return __syncthreads_or(u != u) != 0;
   };
-  bool bad = false;
-  if (kbeg < kend) {
+  // Six products of three terms.  (Sums of their own, added to the others: accumulating where they are, the compiler
+  // keeps two sets of them.)
+  auto multiply3 = [&]() {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      floatx16 sum[2];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sum[0][e] = sum[1][e] = 0.f;
 #pragma unroll 1
-    for (int n = 0; n < 2; ++n) {
-      bad = pass(n == 0);
-      if (!bad) break;
+      for (int c = 0; c < HS_TK / 16; ++c) {
+        bf16x8 fa[3][2], fb[3];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+          fb[t] = lds_tr8(&Bs[t * BPL + boff[j & 1] + c * 16 * GN + (j >> 1) * 128], GN);
+#pragma unroll
+          for (int i = 0; i < 2; ++i) fa[t][i] = lds_tr8(&As[t * APL + aoff[i] + c * 16 * GT], GT);
+        }
+#pragma unroll
+        for (int s = 2; s >= 0; --s)
+#pragma unroll
+          for (int t = s; t >= 0; --t)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+              sum[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[t][i], fb[s - t], sum[i], 0, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) acc[i][j] += sum[i];
     }
-  } else {
+  };
+
+  if (kbeg < kend) fetch(kbeg);
+  // refused: 2 t if slice t (1, 2, ..) does not fit the scales as they are, 2 t + 1 if no renewed ones either
+  int turn = 2, threes = 0;                // slices that three terms take from here on
+  for (long long k0 = kbeg; k0 < kend; k0 += HS_TK, turn += 2) {
+    clear(k0);
+    // a tree of eight rows: one addition per slice into the long sum (four rows: bias gradients 2-15 %
+    // further from 64 bits).  The halves of the wave exchange two columns each.  Only the first column
+    // tile reports it.
+    if (nt == 0) {
+      const floatx4 t = (rk[0] * rw[0] + rk[1] * rw[1]) + (rk[2] * rw[2] + rk[3] * rw[3]);
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(t[e]), __float_as_uint(t[2 + e]),
+                                                        false, false);
+        colsum[e] += __uint_as_float(x[0]) + __uint_as_float(x[1]);
+      }
+    }
+    if (__builtin_expect(threes == 0, 1)) {
+      if (stash()) refused = turn;
+      __syncthreads();
+      if (__builtin_expect(__builtin_amdgcn_readfirstlane(refused) == turn, 0)) {
+        bool plain = rescale(turn);
+        if (plain) {
+          if (stash()) refused = turn + 1;
+          __syncthreads();
+          plain = __builtin_amdgcn_readfirstlane(refused) != turn + 1;
+        }
+        if (!plain) threes = GRAD_THREES;
+      }
+    }
+    const bool three = threes > 0;
+    if (__builtin_expect(three, 0)) {
+      --threes;
+      stash3();
+      __syncthreads();
+      multiply3();
+    }
+    fetch(k0 + HS_TK);                     // (beyond the split: its last row, not used)
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(2);
+    if (__builtin_expect(!three, 1)) multiply();
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(0);
+    __syncthreads();
+  }
+  // the sums as they are
+  if (tid < GT) change[tid] = exponent_of(mscale[tid]);
+  if (tid < GN) change[GT + tid] = exponent_of(nscale[tid]);
+  __syncthreads();
+  add_exponents(change, -1);
+  {
+    // sums that are not finite: with fp32 operands (terms of an infinity make sums of infinities not a number)
+    floatx4 s = zero4();
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < NB; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  }
-  if (bad) {
+        for (int e = 0; e < 16; ++e) s[e & 3] = fmaf(acc[i][j][e], 0.f, s[e & 3]);
+    const float u = (s[0] + s[1]) + (s[2] + s[3]);
+    if (__builtin_expect(__syncthreads_or(u != u), 0)) {
+      static_assert(sizeof(tiles_lds) >= 2 * GTK * GLD * sizeof(float), "fp32 slices must fit");
 #pragma unroll
-    for (int hb = 0; hb < NB / 2; ++hb) {
-      if (n0 + hb * 128 >= N) break;                 // (uniform)
-      floatx16 full[2][2];
+      for (int hb = 0; hb < NB / 2; ++hb) {
+        if (n0 + hb * 128 >= N) break;               // (uniform)
+        floatx16 full[2][2];
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+          for (int j = 0; j < 2; ++j)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) full[i][j][e] = 0.f;
-      floatx4 unused = zero4();
-      grad_contract_f32<float, false>(a, m0, n0 + hb * 128, kbeg, kend, (float*)tiles_lds,
-                                      (float*)(tiles_lds + FEL), full, unused);
+            for (int e = 0; e < 16; ++e) full[i][j][e] = 0.f;
+        floatx4 unused = zero4();
+        grad_contract_f32<float, false>(a, m0, n0 + hb * 128, kbeg, kend, (float*)tiles_lds,
+                                        (float*)tiles_lds + GTK * GLD, full, unused);
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][2 * hb + j] = full[i][j];
+          for (int j = 0; j < 2; ++j) acc[i][2 * hb + j] = full[i][j];
+      }
     }
   }
-  // column sums of S: the four waves' sums of a column meet in LDS (the A tiles are free now)
+  // column sums of S: those of the rows of a wave meet in LDS (the A tiles are free now)
   float* red = reinterpret_cast<float*>(As);      // [4][GT] floats
   __syncthreads();
 #pragma unroll
-  for (int e = 0; e < 2; ++e) red[wave * GT + m4 * 4 + 2 * lh + e] = colsum[e];
+  for (int e = 0; e < 2; ++e) red[(lane / 8 & 3) * GT + scol(lane) + 2 * lh + e] = colsum[e];
   __syncthreads();
   if (nt == 0 && tid < GT && m0 + tid < M) {
     float sum = 0.f;
@@ -1813,15 +2016,15 @@ static int grad_splits(long long Ktot, int M, int N, int bf16) {
 
 // Tile columns and row splits of the kernel on terms, at most `cap` splits (what the partials have room
 // for): the least of rounds over the 512 workgroup slots x (slices x us per slice + 10) + what the partials
-// cost.  us per slice of 32 rows, measured: a workgroup alone on its CU 1.62 (128 columns) and 2.3 (256), two
-// of them 1.97 and 3.2; partials are written and read at 6 TB/s.  Predicted : measured us of one gradient of
-// 65536 rows, 128 / 256 columns at their best splits: 1536 x 1024 820 : 805 / 687 : 680; 1536 x 512
-// 427 : 436 / 346 : 366; 3072 x 1024 1577 : 1592 / 1343 : 1235.
+// cost.  us per slice of 32 rows, measured: a workgroup alone on its CU 1.9 (128 columns) and 2.9 (256), two
+// of them 2.3 and 3.8; partials are written and read at 6 TB/s.  Predicted : measured us of one gradient of
+// 65536 rows, 128 / 256 columns at their best splits: 1536 x 1024 963 : 947 / 810 : 793; 1536 x 512 789 : 822 (5
+// splits) / 404 : 459; 3072 x 1024 in 256 columns 1589 : 1536.
 struct GradX3 {
   int cols, splits;
 };
 static GradX3 grad_x3_shape(long long Ktot, int M, int N, int cap) {
-  constexpr double LONE[2] = {1.62, 2.3}, TWO[2] = {1.97, 3.2};
+  constexpr double LONE[2] = {1.9, 2.9}, TWO[2] = {2.3, 3.8};
   GradX3 best = {0, 1};
   double least = 0;
   for (int wide = 0; wide < (N > GT ? 2 : 1); ++wide) {

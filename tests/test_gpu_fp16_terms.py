@@ -1,6 +1,7 @@
 """Operands in terms (gemm_terms.h) beyond what test_gpu_term_tiles.py holds: scales of the fp16 terms' rows,
 whose first K-slice says nothing about the rest of them, in every tile of the steps, and of the columns of
-the weight gradients; the wide tiles of the adjoint and the projection."""
+the weight gradients, whose sums may consist of the smallest values of a column alone; the wide tiles of
+the adjoint and the projection."""
 import numpy as np
 import pytest
 import torch
@@ -71,8 +72,8 @@ def test_rows_that_differ_from_their_first_slice(B, H, phi, adj):
 
 @pytest.mark.parametrize("D", [72, 200])
 def test_columns_that_differ_from_their_last_slice(D):
-    """Weight gradients: the columns of both operands are scaled by what the last slice of 32 rows holds.
-    Inputs of zeros there (3), larger before by 2^14 (5) and smaller before by 2^14 (6); an adjoint column
+    """Weight gradients: the columns of both operands are scaled, by scales that move along the rows.  Inputs
+    that become zeros (3), smaller by 2^14 (5) and larger by 2^14 (6) in the last steps; an adjoint column
     (7, of all three gates) that starts at zero.  128-column tiles (D 72), both widths (D 200)."""
     import gpu_harness as gh
     print("fp16 terms, columns", D, flush=True)
@@ -94,6 +95,66 @@ def test_columns_that_differ_from_their_last_slice(D):
         assert gh.rel_err(box[0][1][:, n], want[1][:, n]) <= 1e-5, ("dW", n)
     for m in (7, H + 7, 2 * H + 7):
         assert gh.rel_err(box[0][2][m], want[2][m]) <= 1e-5, ("dU", m)
+
+
+def graded(kind, d):
+    """Inputs whose weight gradients, or single columns of them, are sums of numbers far below others of the
+    same column of an operand.  (The adjoint decays backwards, by 2^-0.3 to 2^-1 a step; with one batch row
+    a row split holds 128 steps.)  Returns the columns of dW to look at."""
+    T, B, D = d["x"].shape
+    if kind.startswith("ends"):              # no inputs in the last steps (end-padded sequences)
+        d["x"][T - int(kind[4:]):] = 0
+    elif kind.startswith("event"):           # one input that is there in one step only
+        d["x"][:, :, 3] = 0
+        d["x"][T - int(kind[5:]), :, 3] = 1
+    elif kind == "decaying":                 # inputs that fade while the adjoint grows
+        d["x"] *= 2.0 ** -np.maximum(0, np.arange(T) - T + 100)[:, None, None]
+    elif kind == "impulse":                  # states that fade: one input step, no biases
+        d["x"][:] = 0
+        d["x"][T - 100] = 1
+        d["h0"][:] = d["b_i"][:] = d["b_h"][:] = 0
+    elif kind == "sample":                   # an input of a batch row that the loss hardly depends on
+        d["dL_dhT"][5] *= 2.0 ** -40
+        d["x"][:, :, 3] = 0
+        d["x"][:, 5, 3] = 1
+    elif kind == "masked":                   # a batch row with large inputs that the loss does not depend on
+        d["x"][:, 5] *= 2.0 ** 24
+        d["dL_dhT"][5] = 0
+    elif kind == "small":                    # the loss depends on the batch row with the smallest inputs only
+        d["x"][:, 5] *= 2.0 ** -40
+        d["dL_dhT"][:5] = d["dL_dhT"][6:] = 0
+    d.update({k: np.ascontiguousarray(v, dtype=np.float32) for k, v in d.items()})
+
+
+@pytest.mark.parametrize("prop", [orc.IMPLICIT, orc.CLASSIC])
+@pytest.mark.parametrize("kind,T,B", [("ends32", 1024, 1), ("ends64", 1024, 1), ("ends96", 1024, 1),
+                                      ("ends16", 256, 4), ("event50", 1024, 1), ("event20", 512, 2),
+                                      ("event100", 1024, 1), ("decaying", 1024, 1), ("impulse", 1024, 1),
+                                      ("sample", 65, 33), ("masked", 64, 33), ("small", 64, 33)])
+@pytest.mark.parametrize("D", [72, 200])
+def test_gradients_of_graded_sums(D, kind, T, B, prop):
+    """Every column of dW and dU to 1e-5 of its own largest value, however small beside the others: a
+    32-bit sum gives that, whatever the largest value is that the same column of an operand holds at
+    another step or in another batch row.  (65 x 33 rows: the last slice is a row long.)"""
+    import gpu_harness as gh
+    print("graded sums", D, kind, T, B, prop, flush=True)
+    H = 136
+    d = random_small(14, T, B, D, H, scale=0.3 / np.sqrt(H))
+    graded(kind, d)
+    P = (d["W"], d["U"], d["b_i"], d["b_h"])
+    h = orc.serial_scan(*P, d["x"], d["h0"], prop).astype(np.float32)
+    want = orc.serial_bptt(*P, d["x"], h, d["dL_dhT"], prop)
+    run = gh.GpuRun(d, propagator=prop)
+    box = []
+    gh.expect_kernels(lambda: box.append(run.serial_backward(h)), "grad_gemm_x3_kernel")
+    worst = {}
+    for name, g, r in (("dW", box[0][1], want[1]), ("dU", box[0][2], want[2])):
+        for n in range(r.shape[1]):
+            top = np.max(np.abs(r[:, n]))
+            if top > 2.0 ** -90:
+                worst[name] = max(worst.get(name, (0, 0)), (gh.rel_err(g[:, n], r[:, n]), n))
+    print(worst, flush=True)
+    assert worst and all(e <= 1e-5 for e, _ in worst.values()), worst
 
 
 @pytest.mark.parametrize("value", [None, 3.4e38])
