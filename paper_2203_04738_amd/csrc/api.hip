@@ -260,10 +260,20 @@ static float* scan_ring(const mgrit_gru_cfg& c, const Layout& lay, const Forms& 
   return need <= lay.part - lay.WT ? (float*)(base + lay.WT) : nullptr;
 }
 
+// Packed terms, and the rows of a slice in the gradients, are addressed with 32 bits: GRU layers of up to 18912
+// columns, LSTM layers of up to 16376; beyond that the steps and gradients run on the fp32 MFMAs (the projection does not).
+static bool packs_fit(int gates, int H, int D) {
+  constexpr size_t FOUR_GB = (size_t)1 << 32;
+  return pack2_bytes((long long)gates * H, H) < FOUR_GB && pack2_bytes(D, gates * H) < FOUR_GB &&
+         (size_t)128 * D < FOUR_GB;
+}
+
 static Forms make_forms(const mgrit_gru_cfg& c, const Layout& lay, char* base) {
   Forms f{kform(c.dtype), kform(c.dtype), nullptr, nullptr, nullptr, 0};
-  // (packed terms are addressed with 32 bits: widths from about 18000 on, the fp32 MFMAs)
-  const bool packs = 16LL * c.H * (c.H > c.D ? c.H : c.D) < (1LL << 32);
+  const bool gru = c.propagator == MGRIT_PROP_IMPLICIT || c.propagator == MGRIT_PROP_CLASSIC;
+  const bool lstm = prop_is_lstm(c.propagator);        // (c.H is the state width 2 H then)
+  const int H = lstm ? c.H / 2 : c.H, gates = lstm ? 4 : 3;
+  const bool packs = packs_fit(gates, H, c.D);
   if (c.dtype == MGRIT_F32_BF16X3) {
     f.U3 = base + lay.U3;
     f.UT3 = base + lay.UT3;
@@ -271,11 +281,8 @@ static Forms make_forms(const mgrit_gru_cfg& c, const Layout& lay, char* base) {
     if (!packs) f.rec = 0;
     return f;
   }
-  const bool gru = c.propagator == MGRIT_PROP_IMPLICIT || c.propagator == MGRIT_PROP_CLASSIC;
-  const bool lstm = prop_is_lstm(c.propagator);        // (c.H is the state width 2 H then)
-  const int H = lstm ? c.H / 2 : c.H, gates = lstm ? 4 : 3;
   const long long rows = (long long)c.T * c.B / (c.levels > 1 ? c.cf : 1);
-  if (!packs || c.dtype != MGRIT_F32 || (!gru && !lstm) || H % 8 != 0 || H < TERMS_MIN_H ||
+  if (c.dtype != MGRIT_F32 || (!gru && !lstm) || H % 8 != 0 || H < TERMS_MIN_H ||
       rows < TERMS_MIN_ROWS)
     return f;
   const size_t u3 = align_up((size_t)6 * gates * H * H);
@@ -284,7 +291,7 @@ static Forms make_forms(const mgrit_gru_cfg& c, const Layout& lay, char* base) {
   const size_t second = std::max(u3, std::max(w3, wt));
   const size_t room = lay.total_part - CTL_BYTES;
   if (u3 + second > room) return f;
-  f.rec = 2;
+  if (packs) f.rec = 2;
   f.part_bytes = u3 + second;
   f.U3 = base + lay.part + CTL_BYTES;
   f.UT3 = f.U3 + u3;                      // W3 and UT3 take turns: the projection comes first, the

@@ -76,3 +76,15 @@ def test_a_solve_that_cannot_be_launched_is_reported(runtime, entry, kernel):
     assert rc == 0 and any(kernel in name for _, name in got), got
     rc, _ = call(runtime, entry, *c, FAKE_HIP_FAIL=kernel)
     assert rc == MGRIT_E_LAUNCH
+
+
+@pytest.mark.parametrize("H,D,terms", [(16384, 64, True), (18912, 64, True), (18920, 64, False),
+                                       (1024, 262144, True), (1024, 349600, False)])
+def test_widths_up_to_which_packed_terms_are_addressed(runtime, H, D, terms):
+    # (32-bit offsets into 12 H^2 and 12 H D bytes; the projection's terms have a bound of their own)
+    rc, got = call(runtime, "forward", *cfg(64, 32, D, H, cf=4, levels=2, dtype=2))
+    names = " ".join(name for _, name in got)
+    assert rc == 0
+    assert ("split2_kernel" in names) == terms
+    assert ("phi_step_kernel_bf16" in names) == terms
+    assert "split3" in names and "projection_kernel(" not in names
