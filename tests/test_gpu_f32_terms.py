@@ -1,6 +1,6 @@
-"""MGRIT_F32 on the bf16 matrix pipe (three terms per fp32 operand): whole solves around the line of its
-rule, operands that the terms cannot carry, and operands far below one.  (The step kernels tile by
-tile: test_gpu_term_tiles.py.)"""
+"""MGRIT_F32 on the 16-bit matrix pipe (two fp16 terms per operand, three bf16 terms in the projection):
+whole solves around the line of its rule, operands that the terms cannot carry, and operands far below
+one.  (The step kernels tile by tile: test_gpu_term_tiles.py.)"""
 import numpy as np
 import pytest
 import torch
@@ -119,7 +119,7 @@ def test_infinite_adjoints_reach_the_gradients():
 
 
 def test_gradients_of_adjoints_beyond_the_terms(gh):
-    # sums that overflow in the scale of the terms but not in fp32: every tile is summed again in fp32
+    # one adjoint element 1e35 times the others: its column is scaled by itself, its row is not like the rest
     T, B, D, H = 64, 70, 72, 136
     d = random_small(6, T, B, D, H, scale=0.3 / np.sqrt(H))
     d["dL_dhT"][2, 9] = 1e35
@@ -136,7 +136,7 @@ def test_gradients_of_adjoints_beyond_the_terms(gh):
 @pytest.mark.parametrize("loss", [1.0, 1e35])
 def test_gradients_on_wide_and_narrow_tiles(gh, loss):
     """1320 = 41 x 32 + 8 rows; dW, 3096 x 1000, on tiles of 256 columns and dU, 3096 x 1032, on tiles of
-    128, neither a whole number of them.  1e35: sums beyond the terms, taken again in fp32."""
+    128, neither a whole number of them.  1e35: scales of 2^-108."""
     T, B, D, H = 40, 33, 1000, 1032
     print("wide and narrow gradient tiles", loss, flush=True)
     d = random_small(7, T, B, D, H, scale=0.3 / np.sqrt(H))

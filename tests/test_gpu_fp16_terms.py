@@ -15,18 +15,25 @@ T, CF = 6, 3
 
 # batch sizes and widths of the five tiles of each direction (two launch rows per batch row), K tails, and of
 # the tiles for one workgroup per CU: the adjoint's 128 x 256 and 64 x 128 and the forward 64 x 64 with split
-# K, with gates of whole K-slices (416 = 13 x 32, 448 = 7 x 64) and without
-HUGE = "TileCfgB<2, 4, 2, 2, 1, true, 1, 1, 1, 3, 32"
-WIDE_KS, MID_KS = "TileCfgB<2, 2, 1, 2, 1, true, 2, 1, 1, 3, 32", "TileCfgB<2, 2, 1, 1, 3, true, 2, 1, 1, 3, 32"
+# K, with gates of whole K-slices (416 = 13 x 32, 448 = 7 x 64) and without.  Per case the forward tile, the
+# adjoint's of relaxation and of the residual (None: one that another case is for).
+NARROW, MID, BIG = "2, 1, 1, 1, 3, true, 2, 1, 2", "2, 2, 1, 1, 3, true, 1, 1, 2", "2, 2, 2, 1, 3, true, 1, 1, 2"
+A_MID, A_WIDE = "2, 2, 1, 1, 1, true, 2, 1, 2", "2, 2, 1, 2, 1, true, 1, 1, 2"
+A_BIG8, A_BIG = "4, 2, 1, 2, 1, true, 1, 1, 2", "2, 2, 2, 2, 1, true, 1, 1, 2"
+HUGE, WIDE_KS, MID_KS = "2, 4, 2, 2, 1, true, 1, 1, 1", "2, 2, 1, 2, 1, true, 2, 1, 1", "2, 2, 1, 1, 3, true, 2, 1, 1"
+TILES = [(2050, 136, NARROW, A_MID, A_MID), (6145, 136, MID, A_WIDE, A_WIDE), (12225, 136, BIG, A_BIG8, A_BIG),
+         (1350, 264, NARROW, A_MID, A_MID), (4100, 264, MID, A_WIDE, A_WIDE), (6100, 392, None, HUGE, HUGE),
+         (6100, 416, None, HUGE, HUGE), (1000, 392, MID_KS, None, None), (1000, 448, MID_KS, None, None),
+         (1801, 392, None, WIDE_KS, WIDE_KS), (1801, 448, None, WIDE_KS, WIDE_KS)]
 
 
-@pytest.mark.parametrize("B,H,phi,adj", [(2050, 136, None, None), (6145, 136, None, None),
-                                         (12225, 136, None, None), (1350, 264, None, None),
-                                         (4100, 264, None, None), (6100, 392, None, HUGE),
-                                         (6100, 416, None, HUGE), (1000, 392, MID_KS, None),
-                                         (1000, 448, MID_KS, None), (1801, 392, None, WIDE_KS),
-                                         (1801, 448, None, WIDE_KS)])
-def test_rows_that_differ_from_their_first_slice(B, H, phi, adj):
+def kernels(step, *tiles):
+    """Name parts of the kernels of the modes relaxation (0) and residual (1) on these tiles."""
+    return [f"{step}_step_kernel_bf16<mg::TileCfgB<{c}, 3, 32, true, false>, {m}" for m, c in enumerate(tiles) if c]
+
+
+@pytest.mark.parametrize("B,H,phi,adj,adj_resid", TILES, ids=[f"{c[0]}-{c[1]}" for c in TILES])
+def test_rows_that_differ_from_their_first_slice(B, H, phi, adj, adj_resid):
     """Row 0: nothing but zeros; 1: zeros in the first 72 columns (both K-split groups' slice); 2: the
     rest 2^14 times the first slice, which overflows in its scale, so that its tile's rows are read
     through; 3: a first slice 2^14 times the rest; 4: all of it 2^-40.  The bar is that of the other
@@ -52,14 +59,14 @@ def test_rows_that_differ_from_their_first_slice(B, H, phi, adj):
     run = gh.GpuRun(d, cf=CF, levels=2)
     box = []
     gh.expect_kernels(lambda: box.append(run.forward_iterates(1)),
-                      *(f"phi_step_kernel_bf16<mg::{phi}, true, false>, {m}" for m in (0, 1) if phi))
+                      *kernels("phi", phi, phi))
     h = box[0][0][-1]
     for i, b in enumerate(r):
         for t in range(T + 1):
             assert gh.rel_err(h[t, b], h_ref[t, i]) <= 1e-5 or not h_ref[t, i].any(), ("h", b, t)
     box = []
     gh.expect_kernels(lambda: box.append(run.backward_iterates(h, 1)),
-                      *(f"adj_step_kernel_bf16<mg::{adj}, true, false>, {m}" for m in (0, 1) if adj))
+                      *kernels("adj", adj, adj_resid))
     w = box[0][0][-1]
     want = orc.mgrit_backward(*P, d["x"][:, r], h[:, r], d["dL_dhT"][r], z, CF, 2, 1)[0]
     for i, b in enumerate(r):
@@ -68,6 +75,34 @@ def test_rows_that_differ_from_their_first_slice(B, H, phi, adj):
                 assert gh.rel_err(w[t, b], want[t, i]) <= 1e-5, ("w", b, t)
             else:
                 assert not np.asarray(w[t, b]).any(), ("w", b, t)
+
+
+@pytest.mark.parametrize("B,H,phi,adj,adj_resid", TILES, ids=[f"{c[0]}-{c[1]}" for c in TILES])
+def test_rows_beside_one_that_is_not_finite(B, H, phi, adj, adj_resid):
+    """An infinity in a batch row of the first tile: the tiles that hold it are read through, then contracted
+    in fp32 operand by operand, and the other rows come out as if it were not there."""
+    import gpu_harness as gh
+    print("fp16 terms, beside an infinity", B, H, flush=True)
+    d, bad, r = random_small(15, T, B, 8, H, scale=0.5 / np.sqrt(H)), 2, [0, 1, 3, 31, 33, 62, B - 1]
+    P, z = (d["W"], d["U"], d["b_i"], d["b_h"]), np.zeros((T + 1, len(r), H))
+    h_ref, _ = orc.mgrit_forward(*P, d["x"][:, r], d["h0"][r], z, CF, 2, 1)
+    want = orc.mgrit_backward(*P, d["x"][:, r], h_ref.astype(np.float32), d["dL_dhT"][r], z, CF, 2, 1)[0]
+    run = gh.GpuRun(d, cf=CF, levels=2)
+    h_fin = run.forward_iterates(1)[0][-1]
+    run.t["h0"][bad, 7] = float("inf")
+    box = []
+    gh.expect_kernels(lambda: box.append(run.forward_iterates(1)), *kernels("phi", phi, phi))
+    h = box[0][0][-1]
+    assert not np.isfinite(h[:, bad]).all()
+    for i, b in enumerate(r):
+        assert gh.rel_err(h[:, b], h_ref[:, i]) <= 1e-5, ("h", b)
+    run.t["dL_dhT"][bad, 7] = float("inf")
+    box = []
+    gh.expect_kernels(lambda: box.append(run.backward_iterates(h_fin, 1)), *kernels("adj", adj, adj_resid))
+    w = box[0][0][-1]
+    assert not np.isfinite(w[:, bad]).all()
+    for i, b in enumerate(r):
+        assert gh.rel_err(w[:, b], want[:, i]) <= 1e-5, ("w", b)
 
 
 @pytest.mark.parametrize("D", [72, 200])

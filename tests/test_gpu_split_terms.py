@@ -1,5 +1,5 @@
 """Parity of the third operand form (MGRIT_F32_BF16X3: fp32 inputs and weights, the tile
-kernels contract them as three bf16 terms each on the bf16 matrix pipe) with the CPU oracle,
+kernels contract them as 16-bit terms on the 16-bit matrix pipe) with the CPU oracle,
 element by element, through the C ABI.  It is an fp32 path: same inputs, same oracle and
 the same bar as the fp32 form, max|gpu - oracle| / max|oracle| <= 1e-5 per tensor.  Projection,
 coefficient pass and gradients run on terms at every shape; the steps do in launches of 128 tiles
@@ -81,7 +81,7 @@ def test_mgrit_hierarchies_every_iterate(gh, cf, levels, fcf):
 
 
 def test_mgrit_hierarchy_of_a_wide_layer(gh):
-    """4224 rows on level 0 (three-term tiles, forward and adjoint), 1056 on level 1 (fp32 tiles), 44 on
+    """4224 rows on level 0 (tiles on terms, forward and adjoint), 1056 on level 1 (fp32 tiles), 44 on
     the coarsest level (one-launch solves): every form in one solve."""
     d = random_small(92, 384, 44, 72, 136, scale=0.5 / np.sqrt(136))
     run = gh.GpuRun(d, cf=4, levels=3, dtype=FORM)
@@ -101,7 +101,7 @@ def test_mgrit_reduced_twins(gh, name):
 
 @pytest.mark.parametrize("T,B,D,H", [(32, 70, 16, 40), (16, 1030, 16, 136)])
 def test_terms_of_small_and_large_magnitudes(gh, T, B, D, H):
-    """The three-term split keeps the exponent range of fp32: a tiny loss gradient (1e-20)
+    """Terms, scaled by rows or columns, keep the exponent range of fp32: a tiny loss gradient (1e-20)
     and large inputs change nothing about the relative error.  (40 columns: steps in the sweep
     kernels; 4120 rows x 136: all steps of level 0 on terms.)"""
     d = dict(random_small(17, T, B, D, H, scale=0.3 if H < 100 else 0.5 / np.sqrt(H)))

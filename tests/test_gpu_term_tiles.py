@@ -1,7 +1,8 @@
-"""The step kernels with fp32 operands as three bf16 terms (gemm_core_bf16.h), tile by tile: each tile
-of the dispatch with row, column and K tails, and its fp32 repetition of tiles with sums that are not
-finite.  Every case checks by the names of the launched kernels that the tile it names has run.  Batch
-rows are independent, so the oracle (fp64) follows some of them only.  Bar: 1e-5 of the largest value."""
+"""The step kernels with fp32 operands as two fp16 terms (gemm_terms.h), tile by tile: each tile of the
+dispatch with row, column and K tails, and a row that holds a value near the largest there is (rows
+beside one that is not finite: test_gpu_fp16_terms.py).  Every case checks by the names of the launched
+kernels that the tile it names has run.  Batch rows are independent, so the oracle (fp64) follows some of
+them only.  Bar: 1e-5 of the largest value."""
 import numpy as np
 import pytest
 import torch
@@ -24,7 +25,7 @@ CASES = [(2050, 136, NARROW, A_MID, A_MID), (6145, 136, MID, A_WIDE, A_WIDE),
          (12225, 136, BIG, A_BIG8, A_BIG), (1350, 264, NARROW, A_MID, A_MID),
          (4100, 264, MID, A_WIDE, A_WIDE)]
 T, CF = 6, 3
-BIG_VALUE = 3.4e38                  # finite, but not in three bf16 terms
+BIG_VALUE = 3.4e38                  # finite; its row is scaled by 2^-121
 
 
 @pytest.fixture(scope="module")
@@ -65,8 +66,8 @@ def _close(got, want, what):
 @pytest.mark.parametrize("value", [None, BIG_VALUE])
 @pytest.mark.parametrize("B,H,phi,adj,adj_resid", CASES, ids=[f"{c[0]}-{c[1]}" for c in CASES])
 def test_gru_tiles(gh, B, H, phi, adj, adj_resid, value):
-    """One batch row in the first tile starts at a value the terms cannot carry: its tiles are
-    contracted again in fp32 and give what fp32 gives, in every row of the tile."""
+    """One batch row in the first tile starts at a value that only its row's scale brings into fp16, and all
+    rows of its tiles come out as in fp32."""
     print("term tiles", B, H, value, flush=True)
     d, r, bad, col = _problem(B, H), _rows(B), 2, 7
     if value:
@@ -130,7 +131,8 @@ def test_adjoint_tiles_on_bf16_weights(gh, B, H, adj, form, tol):
 @pytest.mark.parametrize("value", [None, BIG_VALUE])
 def test_projection_and_input_gradients(gh, value):
     """Projection (its only user of D as the contracted width) and input gradients, D and 3 H with
-    tails; the input row and the adjoint row of one batch element beyond the terms."""
+    tails; an input row beyond three bf16 terms, contracted again in fp32, and an adjoint row near the largest
+    values there are."""
     B, D, H, bad, col = 520, 136, 200, 5, 11
     print("term tiles projection, dx", value, flush=True)
     rng = np.random.default_rng(8)
