@@ -131,9 +131,9 @@ struct TileCfgB {
   static constexpr int CPR = TK / 8;            // 16-byte chunks per tile row
   static constexpr int A_CHUNKS = (TM * CPR) / NT;
   static constexpr int B_CHUNKS = (BROWS * CPR) / NT;
-  // (NP = 3 without LOSUM: three slices of A in two terms, gemm_terms.h)
   // waves per SIMD that the register budget is planned for
   static constexpr int MINWAVES = NP == 3 && !LOSUM ? NT * MINWG / 256 : MINWG;
+  // (NP = 3 without LOSUM: three slices of A in two terms, gemm_terms.h)
   static constexpr int LDS_ELEMS =
       NP == 3 && !LOSUM ? 3 * 2 * TM * TK : (NA * TM + NBP * BROWS) * LD;
   static_assert(SPLIT_A || NP == 1, "three-term operands are fp32 in memory");
@@ -156,6 +156,7 @@ __device__ inline int swz_chunk(int row, int chunk) {
 template <class C, bool KTAIL, class LoadA, class LoadB, class FinA>
 __device__ inline void gemm_nt_tile_bf16(Acc<C>& acc, int K, LoadA loadA, LoadB loadB, FinA finA,
                                          bf16_t* lds) {
+  static_assert(C::NP == 1 || (C::LOSUM && C::KS == 1), "other operands in terms: gemm_terms.h");
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = (tid >> 6) % (C::WM * C::WN);
@@ -297,7 +298,7 @@ __device__ inline void gemm_nt_tile_bf16(Acc<C>& acc, int K, LoadA loadA, LoadB 
           // lane reads are 32 apart: one exchange pattern, bits 2-3 of li)
           const int a_row = ((wm * C::BM) * 32 + li) * C::LD;
           const int b_row = ((wn * C::BN) * 32 + li) * C::LD;
-          auto kpos = [&](int c) { return swz_chunk<C>(li, ks * NC * 2 + 2 * c + lh) * 8; };
+          auto kpos = [&](int c) { return swz_chunk<C>(li, 2 * c + lh) * 8; };
           auto rdA = [&](int c, int t, bf16x8 (&f)[C::BM]) {
 #pragma unroll
             for (int a = 0; a < C::BM; ++a)
@@ -322,12 +323,7 @@ __device__ inline void gemm_nt_tile_bf16(Acc<C>& acc, int K, LoadA loadA, LoadB 
                   sum.v[g][a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                       f[a], h[g * C::BN + b], sum.v[g][a][b], 0, 0, 0);
           };
-          auto mm = [&](const bf16x8 (&f)[C::BM], const bf16x8 (&h)[NB]) {
-            if constexpr (C::LOSUM)
-              mm_into(lo, f, h);
-            else
-              mm_into(acc, f, h);
-          };
+          auto mm = [&](const bf16x8 (&f)[C::BM], const bf16x8 (&h)[NB]) { mm_into(lo, f, h); };
           constexpr int UM = C::BM * NB;            // MFMAs of one (A term, B term) pair
           rdA(0, 0, a0[0]);
           rdB(0, 0, bt[0]);

@@ -146,14 +146,15 @@ struct InOrder {
   __device__ inline int operator()(int i) const { return i * C::TK; }
 };
 
-// Largest magnitude over the row behind chunk s of the calling thread: load(k), columns k..k+7 of the row, K
-// of them (the CPR lanes that share a row are neighbours).  Eight slices' loads at a time.
+// Largest m of the CPR lanes that share a row (neighbours).
 template <class C>
 __device__ inline float over_row(float m) {
 #pragma unroll
   for (int o = 1; o < C::CPR; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
   return m;
 }
+// Largest magnitude over the row behind chunk s of the calling thread: load(k), columns k..k+7 of the row, K of
+// them.  Eight slices' loads at a time.
 template <class C, class Load>
 __device__ inline float row_top(int s, int K, Load load) {
   float m = 0.f;
