@@ -32,11 +32,18 @@
  *   results to the same accuracy; the kernels of larger launches carry each fp32
  *   operand of a contraction as a sum of 16-bit terms and multiply them on the
  *   16-bit matrix pipe with fp32 sums, which is faster than the fp32 one.  The
- *   projection takes three bf16 terms (3 x 8 mantissa bits, six of the nine term
- *   products), everything else two fp16 terms (2 x 11 bits, scaled to fp16's range
- *   by rows or columns, three of the four products), which on this pipe come out
- *   closer to 64 bits than either six products or fp32 ones.  (Smaller launches, and the steps of layers of up to
- *   128 columns, run in the fp32 kernels, which are faster there and as accurate.)
+ *   projection takes three bf16 terms (3 x 8 mantissa bits at every magnitude, six
+ *   of the nine term products; the dtype has its name from them), everything else two
+ *   fp16 terms (2 x 11 bits, scaled to fp16's range by powers of two per row or
+ *   column, three of the four products).  On dense operands those come out closer to
+ *   64 bits than six products or fp32 ones.  The bound is relative to a row or column:
+ *   in the steps and input gradients what is left out of a state or adjoint value is
+ *   2^-22 of it, or, where it is 2^9 or more below the largest of its row, 2^-31 of that
+ *   largest (weights: 2^15, 2^-38).  In the weight gradients it is 2^-22 of a value, and
+ *   at most 2^-20 of the largest of its row and of its column within 32 rows
+ *   (steps x batch); rows that lie further apart take three bf16 terms.  (Smaller
+ *   launches, and the steps of layers of up to 128 columns, run in the fp32 kernels,
+ *   which are faster there and as accurate.)
  *   The weights' term arrays live in the workspace (it is larger for this dtype)
  *   and are rebuilt by every call; H and D must be multiples of 8.  A tile with
  *   a sum that is not finite (an operand the terms cannot carry, like an

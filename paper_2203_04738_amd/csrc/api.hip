@@ -216,14 +216,14 @@ static bool misaligned(const void* p) { return ((uintptr_t)p & 15) != 0; }
 // adjoint errors at 72, 104 and 128 columns 1.2-1.7e-7 and 6.5e-8 against 1.5-2.0e-7 and 7.1e-8 with
 // terms, at 520 to 1024 columns 1.3-1.9e-7 and 7.0-7.9e-8 against 1.6-2.1e-7 and 7.7-8.9e-8.)  The line:
 //  - widths are multiples of 8 (16-byte rows of terms), of at least 128 (64 for the projection).
-//    Error of a contraction against 64 bits: 1.35e-7 against 1.44e-7 of the fp32 MFMAs over 64
-//    columns, 2.5 : 2.9 over 256, 5.0 : 5.8 over 1024 (fewer additions into the sum), but 0.83 :
-//    0.73 over 16.  Below 128 columns nothing is gained in time;
+//    Error of a contraction against 64 bits, two fp16 terms : fp32 MFMAs 1.2e-7 : 1.1e-7 over 64
+//    columns, 2.6 : 2.9 over 512, 3.6 : 4.1 over 1024 (fewer additions into the sum); of the projection's three
+//    bf16 terms 1.35 : 1.44 over 64, 5.0 : 5.8 over 1024.  Below 128 columns nothing is gained in time;
 //  - GRU and LSTM (the ODE kernels have no such form);
 //  - 1024 rows or more in a level-0 launch (serial propagation: steps x batch; projection,
-//    coefficients and gradients take all steps in one launch there).  Training step of two levels, fp32 MFMAs : terms:
-//    256 rows x 1000 1.44 : 1.52 ms, 512 x 512 0.88 : 0.88, 1024 x 512 1.66 : 1.52, 4096 x 1000
-//    12.8 : 10.7;
+//    coefficients and gradients take all steps in one launch there).  Training step of two levels, fp32
+//    MFMAs : terms: 1024 rows x 136 0.47 : 0.47 ms, 1024 x 512 1.32 : 0.79, 4096 x 1000 9.4 : 4.9.  The line
+//    was drawn on three bf16 terms; below it 512 x 512 0.73 : 0.71, 256 x 1000 1.28 : 1.23, 512 x 1000 2.7 : 1.7;
 //  - the terms fit the space of the gradient partials, which nothing else uses until the last
 //    solve of a call is done: the workspace is no larger than without them.
 struct Forms {

@@ -23,8 +23,13 @@
 // adjoint over 2048 steps.)  Subnormal terms keep their bits on this pipe;
 // what is below them is 2^-31 of the row's largest value.
 //
+// What is left out is thus bounded by 2^-22 of a value where it is within 2^9 of its row's largest and by 2^-31 of
+// that largest below: an element of a product whose row of B is zero wherever the row of A is not small (two
+// nets of different scale side by side in one layer) has fewer digits than in fp32.  Every row of a dense
+// B sees the large elements too.
+//
 // Data path (16384 rows x 512, the level step: 145 us with three bf16 terms, 118 with two fp16 terms in
-// the loop of gemm_core_bf16.h, 100 this way; 16384 LSTM rows 243, 157, 126).  With half the MFMAs the K loop is bound by what feeds them, LDS above all: 32x32 blocks
+// the loop of gemm_core_bf16.h, 91 this way; 16384 LSTM rows 243, 157, 126).  With half the MFMAs the K loop is bound by what feeds them, LDS above all: 32x32 blocks
 // of A and B fragments read by every wave cost 105 of the LDS's 128 bytes per clock at full matrix
 // rate for the 128 x 64 (x3) tile.  So B does not pass through LDS: the split leaves it in the order in
 // which lanes take it (term_pack.h), a wave owns its columns alone (the waves of a tile lie side by

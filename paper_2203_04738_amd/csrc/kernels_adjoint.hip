@@ -673,7 +673,7 @@ hipError_t launch_adj_step(const AdjArgs& a, hipStream_t s) {
   }
   // terms, large launches: the products kappa * w are formed, scaled and split once per column tile, so
   // the widest tile that fills the CUs, one workgroup each (us at 16384 rows x 512, x 1024: 128 x 128
-  // 91, 312; 64 x 256 88, 296; 128 x 256 85, 281).  Two column tiles from 384 on: below that it would be
+  // 92, 322; 64 x 256 88, 296; 128 x 256 86, 291).  Two column tiles from 384 on: below that it would be
   // mostly padding
   else if (a.bf16 == 2 && a.H >= 384 && tiles(AdjHugeS::TM, AdjHugeS::TN) >= 192) {
     launch_adj_terms<AdjHugeS>(a, s);
@@ -685,16 +685,15 @@ hipError_t launch_adj_step(const AdjArgs& a, hipStream_t s) {
     else
       launch_adj_f32<AdjBig>(a, s);
   }
-  // terms, by what fills the chip (us on three bf16 terms, 64 x 64 without the split : 64 x 128 : 64 x 64
-  // split):
-  // 3200 rows x 1000 (400 wide tiles) 247 : 179 : 207, 4096 x 1024 (512) 215 : 169 : 193,
-  // 4096 x 512 (256) 65 : 69 : 56, 1024 x 1024 (256 tiles of 64 x 64) 101 : 121 : 75, 800 x 1000 (208)
-  // 99 with 32 x 32 tiles, 82 split
+  // terms, by what fills the chip (us, 64 x 128 : the same with K split : 64 x 64 with K split):
+  // 4096 rows x 1024 (512 wide tiles) 101 : 103 : 137, 3200 x 1000 (400) 113 : 108 : 153, 2048 x 512 (128;
+  // 256 of 64 x 64) 34 : 24 : 23, 1024 x 1024 (128; 256) 62 : 41 : 40.  The lines of 384 and 192 tiles
+  // were drawn on three bf16 terms, where such steps took twice as long; below them fp32 tiles are the
+  // slower ones now (1024 x 520, 144 tiles of 64 x 64: 22, with the 32 x 32 fp32 tiles it takes 42)
   else if (a.bf16 == 2 && tiles(AdjWideS::TM, AdjWideS::TN) >= 384)
     launch_adj_terms<AdjWideS>(a, s);
-  // one round of 64 x 128 tiles, one per CU: eight waves splitting K (4096 rows x 512, 256 tiles: 44 us with
-  // two 64 x 64 tiles per CU, which form and split every product twice as often, 31 this way; 3200 x 1000,
-  // 400 tiles and two rounds of them, 121 : 114 with the tile above)
+  // one round of 64 x 128 tiles, one per CU: eight waves splitting K (4096 rows x 512, 256 tiles: 43 us with
+  // two 64 x 64 tiles per CU, which form and split every product twice as often, 30 this way)
   else if (a.bf16 == 2 && tiles(AdjWideS::TM, AdjWideS::TN) >= 192 &&
            tiles(AdjWideS::TM, AdjWideS::TN) <= 256)
     launch_adj_terms<AdjWideKS>(a, s);

@@ -764,13 +764,14 @@ typedef TileCfgB<2, 2, 1, 1, 3, true, 2, 1, 1, 1, 64, false> PhiMidFK;
 // fp32 operands in terms: K-slices of 32 keep two workgroups' tiles in a CU's LDS
 typedef TileCfgB<2, 2, 2, 1, 3, true, 1, 1, 2, 3, 32> PhiBigS;
 typedef TileCfgB<2, 2, 1, 1, 3, true, 1, 1, 2, 3, 32> PhiMidS;
-// 64 x 32 with two groups of two waves splitting K, where 64 x 64 tiles leave CUs half empty (us, 64 x
-// 64 : this, three bf16 terms): 1024 rows x 1024 (256 tiles of 64 x 64) 64 : 50, 800 x 1000 (208) 66 : 53, 4096 x 256
-// (256) 19.6 : 16.7, but 4096 x 512 (512) 50 : 58
+// 64 x 32 with two groups of two waves splitting K, for few tiles of 64 x 64 (us, 64 x 64 : this): 1024 rows
+// x 264 (80 tiles) 10.8 : 9.0, 2048 x 264 (160) 11.6 : 12.7, 1024 x 520 (144) 16.3 : 16.4, 2048 x 512 (256) 17.8 :
+// 17.6, 1600 x 776 (325) 31 : 40, 4096 x 512 (512) 26 : 32.  (Up to 511 tiles by a line drawn on three bf16
+// terms: 64 : 50 at 1024 x 1024.)
 typedef TileCfgB<2, 1, 1, 1, 3, true, 2, 1, 2, 3, 32> PhiNarrowS;
 // 64 x 64 as eight waves, two groups splitting K, one workgroup per CU, for one round of them: 1024 rows x
-// 1024 (256 tiles) 32 us with 64 x 32 : 28, 800 x 1000 (208) 32 : 26.  From 384 columns on, where there are slices
-// to split
+// 1024 (256 tiles) 25 us, 28 without the split and 29 with 64 x 32; 2048 x 512 (256) 16, 18 and 18.  From 384
+// columns on, where there are slices to split
 typedef TileCfgB<2, 2, 1, 1, 3, true, 2, 1, 1, 3, 32> PhiMidKS;
 
 #define MG_LAUNCH_BY_MODE(KERNEL, ...)                                                   \

@@ -169,10 +169,17 @@ def test_results_do_not_depend_on_who_computes_them(form, B, H, monkeypatch):
     print("scan case bits", form, B, H, flush=True)
     want, left = solve()
     monkeypatch.setenv("MGRIT_SCAN_WAIT_TICKS", "0")
-    got, left0 = solve()
-    assert all(torch.equal(a, b) for a, b in zip(got, want))
-    # (the control words are the only part of the workspace that tells the two apart)
-    assert 0 < int((left0 != left).sum()) <= 16
+    # (the control words are the only part of the workspace that tells the two apart.  A few workgroups may
+    # all have arrived when the first one looks, one time in ten at 3 x 136: then none leaves)
+    differ = 0
+    for _ in range(12):
+        got, left0 = solve()
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+        differ = int((left0 != left).sum())
+        assert differ <= 16
+        if differ:
+            break
+    assert differ > 0
 
 
 @pytest.mark.parametrize("B,H", [(8, 512), (64, 256), (12, 1024)])
