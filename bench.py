@@ -96,8 +96,8 @@ def kernel_sources_sha256():
     import re
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2203_04738_amd", "csrc")
-    for f in ("common.h", "gates.h", "gemm_core.h", "gemm_core_bf16.h", "gemm_terms.h", "phi_elem.h",
-              "kernels_forward.hip"):
+    for f in ("common.h", "gates.h", "gemm_core.h", "gemm_core_bf16.h", "gemm_terms.h", "term_pack.h",
+              "phi_elem.h", "kernels_forward.hip"):
         text = open(os.path.join(csrc, f), "r").read()
         text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
         text = re.sub(r"//[^\n]*", " ", text)

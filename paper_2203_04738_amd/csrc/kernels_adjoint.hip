@@ -1403,7 +1403,8 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_tr_kernel(GradArgs a) {
 // products of three bf16 terms 1.07, two terms with scales of a whole split 0.69), 1536 x 512 0.45 (0.55,
 // 0.37), 3072 x 1024 1.53 (2.09, 1.25), 12800 rows, 3000 x 1000 0.31 (0.42, 0.30).  By the data, 65536 rows x
 // 1536 x (1024 + 512): dense 1.31, inputs that end early 1.29, one-hot 1.37, 2 % dense 1.51, rectified 1.48, a loss
-// that differs by 10^3 between batch rows 1.52, by 10^6 3.3 (three terms throughout; with fp32 slices 6.2).
+// that differs by 10^3 between batch rows 1.52, by 10^6 3.3 (three terms throughout; with fp32 slices 6.2),
+// columns of the inputs by 10^6 3.5; six products throughout without a look at scales 1.6.
 // Branches that are rarely taken are marked as such: without that the compiler spills sums around the products.
 constexpr int HS_TK = 32;
 // A column's largest value of a slice is brought into [2^GRAD_TOP, 2^(GRAD_TOP + 1)) when the scales are renewed, and
